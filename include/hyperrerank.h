@@ -394,6 +394,10 @@ int hr_doc_prefill(hr_model* model, hr_pool* pool, int32_t n_docs, const int32_t
  * pointers or sizes out of range. */
 int hr_rerank_topk(const float* scores_dev, const int32_t* seg_dev, int32_t n_queries, int32_t max_cands, int32_t k,
                    int32_t* topk_idx_dev, float* topk_scores_dev, void* stream);
+/* The same with the offsets in host memory: they travel as kernel arguments, so there is no copy to wait for and the array
+ * may be reused as soon as the call returns. */
+int hr_rerank_topk_host(const float* scores_dev, const int32_t* seg_offsets, int32_t n_queries, int32_t max_cands, int32_t k,
+                        int32_t* topk_idx_dev, float* topk_scores_dev, void* stream);
 
 /* ---- introspection for benchmarks ---- */
 

@@ -69,7 +69,7 @@ EXPORTS = [
     "hr_rerank_score_static", "hr_rerank_plan_create", "hr_rerank_plan_set_inputs", "hr_rerank_plan_run",
     "hr_rerank_plan_destroy", "hr_model_set_precise_layers", "hr_model_precise_layers", "hr_rerank_set_streams", "hr_rerank_parts", "hr_rerank_validate",
     "hr_rerank_full_workspace_bytes", "hr_rerank_score_full", "hr_doc_prefill_workspace_bytes", "hr_doc_prefill", "hr_attention_path", "hr_gemm_path",
-    "hr_rerank_topk", "hr_model_range_report", "hr_kv_pool_range_report", "hr_probe_read_bandwidth", "hr_profile_enable", "hr_profile_select", "hr_profile_count", "hr_profile_name", "hr_profile_read",
+    "hr_rerank_topk", "hr_rerank_topk_host", "hr_model_range_report", "hr_kv_pool_range_report", "hr_probe_read_bandwidth", "hr_profile_enable", "hr_profile_select", "hr_profile_count", "hr_profile_name", "hr_profile_read",
 ]
 
 
@@ -130,6 +130,7 @@ def _load() -> C.CDLL:
         "hr_doc_prefill": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, i32p, i32p, i32p, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]),
         "hr_attention_path": (C.c_char_p, [C.c_void_p, C.c_void_p]),
         "hr_gemm_path": (C.c_char_p, [C.c_void_p]),
+        "hr_rerank_topk_host": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
         "hr_rerank_topk": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
         "hr_model_range_report": (C.c_int, [C.c_void_p, C.POINTER(hr_range_report)]),
         "hr_kv_pool_range_report": (C.c_int, [C.c_void_p, C.POINTER(hr_range_report)]),
@@ -216,13 +217,11 @@ def rerank_topk(scores, seg_offsets, k: int, with_scores: bool = False, stream=N
     seg = _i32(seg_offsets)
     n_q = len(seg) - 1
     max_c = max(int((seg[1:] - seg[:-1]).max()) if n_q > 0 else 1, k, 1)      # an upper bound is all the library needs
-    seg_dev = torch.from_numpy(seg).to(scores.device)
     idx = torch.empty((max(n_q, 0), k), dtype=torch.int32, device=scores.device)
     sc = torch.empty((max(n_q, 0), k), dtype=torch.float32, device=scores.device) if with_scores else None
-    check(lib.hr_rerank_topk(C.c_void_p(scores.data_ptr()), C.c_void_p(seg_dev.data_ptr()), n_q, max_c, k,
-                             C.c_void_p(idx.data_ptr()), C.c_void_p(sc.data_ptr()) if with_scores else None, _stream_ptr(stream)),
+    check(lib.hr_rerank_topk_host(C.c_void_p(scores.data_ptr()), _i32p(seg), n_q, max_c, k,
+                                  C.c_void_p(idx.data_ptr()), C.c_void_p(sc.data_ptr()) if with_scores else None, _stream_ptr(stream)),
           "hr_rerank_topk")
-    idx._hr_seg = seg_dev          # keep the offsets alive until the result is dropped (the kernel may still be queued)
     return (idx, sc) if with_scores else idx
 
 

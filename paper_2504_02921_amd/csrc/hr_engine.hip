@@ -191,6 +191,68 @@ struct PrefillTarget {
     int n_pages;
 };
 
+// Metadata that the pass's first kernel fetches itself: `host` is the pinned block as the device addresses it (nullptr: an
+// upload has been enqueued already), read_ev (if set) is recorded behind that kernel.
+struct MetaSource {
+    const int32_t* host = nullptr;
+    size_t ints = 0;
+    hipEvent_t read_ev = nullptr;
+};
+
+// Calls with little metadata let the first kernel read it over the bus (one launch less, and no copy engine or blit
+// kernel in front of it); every token's row needs two words from there, so only where tokens are few.
+constexpr size_t kMetaByKernelInts = 16384;
+constexpr int64_t kMetaByKernelTokens = 1024;
+bool meta_by_kernel(size_t ints, int64_t T) { return ints <= kMetaByKernelInts && T <= kMetaByKernelTokens; }
+
+int pinned_device_view(const int32_t* p, const int32_t** out) {
+    void* d = nullptr;
+    HR_HIP(hipHostGetDevicePointer(&d, const_cast<int32_t*>(p), 0));
+    *out = (const int32_t*)d;
+    return HR_OK;
+}
+
+// The layers of an fp32 pass: per layer five launches (norm + QKV + RoPE, attention, O + residual, norm + gate/up + SwiGLU,
+// down + residual).  In the last layer of a scoring pass only each sequence's last token goes through attention and
+// behind it.
+int run_layers_f32(hr_model* m, const PoolView& pv, const MetaView& mv, const Workspace& ws, char* wsb, int max_new_len, float* scores,
+                   hipStream_t st) {
+    const hr_model_cfg& c = m->cfg;
+    const int H = c.hidden, d = c.head_dim, F = c.ffn, nq = c.n_q_heads * d, nqkv = nq + 2 * c.n_kv_heads * d;
+    float *x = (float*)(wsb + ws.off_x), *q = (float*)(wsb + ws.off_q), *k = (float*)(wsb + ws.off_k), *v = (float*)(wsb + ws.off_v),
+          *o = (float*)(wsb + ws.off_o), *mm = (float*)(wsb + ws.off_m);
+    const float2* rope = (const float2*)(wsb + ws.off_rope);
+    MetaView head = mv;
+    int64_t T = mv.T;
+    for (int l = 0; l < c.n_layers; ++l) {
+        F32GemmArgs a{};
+        a.A = x; a.W = layer_w(m, l, m->pack.wqkv); a.M = T; a.N = nqkv; a.K = H; a.gain = m->norm1[l]; a.eps = c.rms_eps;
+        a.rope = rope; a.q = q; a.k = k; a.v = v; a.n_q = c.n_q_heads; a.n_kv = c.n_kv_heads; a.d = d;
+        HR_TIMED(PC_GEMM_QKV, launch_gemm_f32(F32_ROPE, HR_F32, a, st));
+        const bool last = l + 1 == c.n_layers && !m->no_last_short && mv.n_out == mv.n_seq;
+        HR_TIMED(PC_ATTENTION, launch_attn_f32(q, k, v, o, mv, pv, l, c.n_q_heads, max_new_len, last, st));
+        F32GemmArgs b{};
+        b.A = o; b.W = layer_w(m, l, m->pack.wo); b.N = H; b.K = nq; b.C = x;
+        if (last) {
+            T = mv.n_seq;
+            b.add = x; b.add_rows = mv.out_row;
+            x = b.C = (float*)(wsb + ws.off_y);             // [n_seq][H]; the norms are fused, nothing else uses y
+            head.out_row = nullptr;
+        }
+        b.M = T;
+        HR_TIMED(PC_GEMM_O, launch_gemm_f32(F32_ADD, HR_F32, b, st));
+        F32GemmArgs gu{};
+        gu.A = x; gu.W = layer_w(m, l, m->pack.wgu); gu.M = T; gu.N = 2 * F; gu.K = H; gu.gain = m->norm2[l]; gu.eps = c.rms_eps;
+        gu.C = mm; gu.ib = m->pack.gu_interleave;
+        HR_TIMED(PC_GEMM_GATE_UP, launch_gemm_f32(F32_SWIGLU, HR_F32, gu, st));
+        F32GemmArgs dn{};
+        dn.A = mm; dn.W = layer_w(m, l, m->pack.wd); dn.M = T; dn.N = H; dn.K = F; dn.C = x;
+        HR_TIMED(PC_GEMM_DOWN, launch_gemm_f32(F32_ADD, HR_F32, dn, st));
+    }
+    HR_TIMED(PC_SCORE_HEAD, launch_score_head(HR_F32, x, m->final_norm, m->embedding, head, scores, H, c.rms_eps, c.yes_id, c.no_id, st));
+    return HR_OK;
+}
+
 // One pass of all layers over the T new tokens described by `mv`.
 //   pool         cached-document pool (scoring pass), or nullptr
 //   self_prefix  the sequences are chunks of longer sequences whose earlier tokens are found as pages of this call's
@@ -199,9 +261,10 @@ struct PrefillTarget {
 //                layer's K/V (no scores)
 //   groups       if set, the attention work items are these groups of sequences with one shared document
 //   after_qkv0   if set, recorded on `st` behind the first layer's QKV projection
+//   src          where the metadata still has to come from, if it has not been uploaded
 int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaView& mv, const Workspace& ws, char* wsb,
                int max_keys, int max_new_len, float* scores, hipStream_t st, const PrefillTarget* fill = nullptr,
-               const GroupView* groups = nullptr, hipEvent_t after_qkv0 = nullptr, int n_precise = 0) {
+               const GroupView* groups = nullptr, hipEvent_t after_qkv0 = nullptr, int n_precise = 0, const MetaSource& src = {}) {
     const hr_model_cfg& c = m->cfg;
     const int dt = c.dtype;
     const int H = c.hidden, d = c.head_dim, F = c.ffn;
@@ -234,6 +297,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
     }
     const bool mfma_attn = use_mfma_attn(m, pv.kv_dtype, max_new_len, groups && groups->n_groups > 0);
     if (self_prefix && !mfma_attn) return HR_ERR_UNSUPPORTED_SHAPE;
+    const bool fused_f32 = !m->force_generic && f32_fused_supported(c);
     if (!mfma_attn && max_keys > kGenericMaxKeys) return HR_ERR_UNSUPPORTED_SHAPE;     // the generic attention keeps a row's scores in LDS
     // the shortened last layer needs one output row per sequence, the MFMA kernels, something to save (T > P), and
     // room for P fp32 rows in the q buffer
@@ -252,9 +316,15 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
     // with the MFMA attention the new tokens' K/V are written straight into 16-slot pages (k and v regions together);
     // slots past a sequence's end are never written by any layer, so one clear per call keeps them finite
     const size_t kv_region = ws.off_o - ws.off_k;
-    if (mfma_attn) HR_TIMED(PC_EMBED, launch_fill_zero(k, kv_region, st));
-    HR_TIMED(PC_EMBED, launch_embed(dt, m->embedding, mv, x, H, st));
-    HR_TIMED(PC_EMBED, launch_rope_table(mv, rope, d, c.rope_base, st));
+    HR_TIMED(PC_EMBED, launch_prologue(dt, m->embedding, mv, x, H, rope, d, c.rope_base, k, mfma_attn ? kv_region : 0, src.host,
+                                       (int32_t*)(wsb + ws.off_meta), src.ints, st));
+    if (src.read_ev) HR_HIP(hipEventRecord(src.read_ev, st));
+    if (fused_f32) return run_layers_f32(m, pv, mv, ws, wsb, max_new_len, scores, st);
+    auto gemm_plain = [&](F32Epilogue epi, const void* A, const void* W, float* C, int N, int K) {
+        F32GemmArgs a{};
+        a.A = A; a.W = W; a.M = T; a.N = N; a.K = K; a.C = C;
+        return launch_gemm_f32(epi, dt, a, st);
+    };
     for (int l = 0; l < c.n_layers; ++l) {
         // First layer, several sequences with the same token string (one query against its candidates): the normalised
         // rows and the pre-RoPE q / k / v of equal strings are equal, so they are computed on the distinct rows only and
@@ -300,7 +370,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             if (mfma_attn) { a.kv_pages = k; a.new_slot = mv.new_slot; }
             HR_TIMED(PC_GEMM_QKV, launch_gemm_mfma(EPI_QKV_ROPE, a, st));
         } else {
-            HR_TIMED(PC_GEMM_QKV, launch_gemm_generic(dt, y, layer_w(m, l, m->pack.wqkv), f32, T, nqkv, H, false, st));
+            HR_TIMED(PC_GEMM_QKV, gemm_plain(F32_STORE, y, layer_w(m, l, m->pack.wqkv), f32, nqkv, H));
             HR_TIMED(PC_ELEMENTWISE, launch_rope_split(dt, f32, rope, q, k, v, T, c.n_q_heads, c.n_kv_heads, d, st));
         }
         if (l == 0 && after_qkv0) HR_HIP(hipEventRecord(after_qkv0, st));
@@ -353,7 +423,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             a.A = o; a.W = layer_w(m, l, m->pack.wo); a.M = T; a.N = H; a.K = nq; a.x = x;
             HR_TIMED(PC_GEMM_O, launch_gemm_mfma(EPI_RESID_ADD, a, st));
         } else {
-            HR_TIMED(PC_GEMM_O, launch_gemm_generic(dt, o, layer_w(m, l, m->pack.wo), x, T, H, nq, true, st));
+            HR_TIMED(PC_GEMM_O, gemm_plain(F32_ADD, o, layer_w(m, l, m->pack.wo), x, H, nq));
         }
         HR_TIMED(PC_RMSNORM, launch_rmsnorm(dt, x, m->norm2[l], y, T, H, c.rms_eps, st));
         if (m->mfma_gemm) {
@@ -364,9 +434,9 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             b.A = mm; b.W = layer_w(m, l, m->pack.wd); b.M = T; b.N = H; b.K = F; b.x = x;
             HR_TIMED(PC_GEMM_DOWN, launch_gemm_mfma(EPI_RESID_ADD, b, st));
         } else {
-            HR_TIMED(PC_GEMM_GATE_UP, launch_gemm_generic(dt, y, layer_w(m, l, m->pack.wgu), f32, T, 2 * F, H, false, st));
+            HR_TIMED(PC_GEMM_GATE_UP, gemm_plain(F32_STORE, y, layer_w(m, l, m->pack.wgu), f32, 2 * F, H));
             HR_TIMED(PC_ELEMENTWISE, launch_swiglu(dt, f32, mm, T, F, m->pack.gu_interleave, st));
-            HR_TIMED(PC_GEMM_DOWN, launch_gemm_generic(dt, mm, layer_w(m, l, m->pack.wd), x, T, H, F, true, st));
+            HR_TIMED(PC_GEMM_DOWN, gemm_plain(F32_ADD, mm, layer_w(m, l, m->pack.wd), x, H, F));
         }
     }
     HR_TIMED(PC_SCORE_HEAD, launch_score_head(dt, x, m->final_norm, m->embedding, mv, scores, H, c.rms_eps, c.yes_id, c.no_id, st));
@@ -692,18 +762,23 @@ static void build_score_part(hr_model* m, int32_t n_pairs, const int32_t* page_t
 
 static int prepare_score_part(hr_model* m, int32_t n_pairs, const int32_t* page_table, int32_t pt_stride, const int32_t* doc_lens,
                               const int32_t* query_tokens, const int32_t* query_lens, int64_t T, bool mfma_attn, const hr::Workspace& ws,
-                              const hr::MetaLayout& ml, int64_t grp_ints, int32_t* stage, char* wsb, hipStream_t st, ScorePart* out) {
+                              const hr::MetaLayout& ml, int64_t grp_ints, int32_t* stage, char* wsb, hipStream_t st, ScorePart* out,
+                              MetaSource* src = nullptr) {
     size_t upload_ints = 0;
     build_score_part(m, n_pairs, page_table, pt_stride, doc_lens, query_tokens, query_lens, T, mfma_attn, ws, ml, grp_ints, stage, wsb, true,
                      out, &upload_ints);
+    if (src && meta_by_kernel(upload_ints, T)) {
+        src->ints = upload_ints;
+        return pinned_device_view(stage, &src->host);
+    }
     HR_HIP(hipMemcpyAsync(wsb + ws.off_meta, stage, upload_ints * sizeof(int32_t), hipMemcpyHostToDevice, st));
     return HR_OK;
 }
 
 static int run_score_part(hr_model* m, const hr_pool* pool, const ScorePart& part, const hr::Workspace& ws, char* wsb, int max_q,
-                          float* scores_dev, hipStream_t st, hipEvent_t after_qkv0 = nullptr) {
+                          float* scores_dev, hipStream_t st, hipEvent_t after_qkv0 = nullptr, const MetaSource& src = {}) {
     return run_layers(m, pool, false, part.mv, ws, wsb, part.max_keys, max_q, scores_dev, st, nullptr,
-                      part.gv.n_groups > 0 ? &part.gv : nullptr, after_qkv0, m->n_precise);
+                      part.gv.n_groups > 0 ? &part.gv : nullptr, after_qkv0, m->n_precise, src);
 }
 
 // A scoring call (already validated) in one piece on `st`, with the workspace at `wsb`.
@@ -715,12 +790,15 @@ static int score_one_piece(hr_model* m, const hr_pool* pool, int32_t n_pairs, co
     int rc = stage_reserve(m, ml.total, staging_may_grow);
     if (rc != HR_OK) return rc;
     ScorePart part;
+    MetaSource src;
     rc = prepare_score_part(m, n_pairs, page_table, pt_stride, doc_lens, query_tokens, query_lens, T, mfma_attn, ws, ml, grp_ints,
-                            m->stage, wsb, st, &part);
-    HR_HIP(hipEventRecord(m->stage_ev, st));
-    m->stage_pending = true;
+                            m->stage, wsb, st, &part, &src);
     if (rc != HR_OK) return rc;
-    return run_score_part(m, pool, part, ws, wsb, max_q, scores_dev, st);
+    src.read_ev = m->stage_ev;                  // recorded behind the kernel that reads the block (or the upload in front of it)
+    m->stage_pending = true;
+    rc = run_score_part(m, pool, part, ws, wsb, max_q, scores_dev, st, nullptr, src);
+    if (rc != HR_OK) (void)hipEventRecord(m->stage_ev, st);      // it may have ended in front of that kernel
+    return rc;
 }
 
 int hr_rerank_score(hr_model* m, const hr_pool* pool, int32_t n_pairs, const int32_t* page_table, int32_t pt_stride,
@@ -860,6 +938,7 @@ struct hr_plan {
     hr::MetaLayout ml;
     char* wsb = nullptr;
     int32_t* stage = nullptr;                        // pinned, ml.total ints, owned by the plan
+    const int32_t* stage_dev = nullptr;              // ... as the device addresses it
     size_t upload_ints = 0;
     ScorePart part;
 };
@@ -905,6 +984,10 @@ int hr_rerank_plan_create(hr_model* m, const hr_pool* pool, int32_t n_pairs, con
         return HR_ERR_DEVICE;
     }
     std::memset(pl->stage, 0, pl->ml.total * sizeof(int32_t));
+    if (int rc = pinned_device_view(pl->stage, &pl->stage_dev); rc != HR_OK) {
+        hr_rerank_plan_destroy(pl);
+        return rc;
+    }
     *out = pl;
     return HR_OK;
 }
@@ -929,13 +1012,19 @@ int hr_rerank_plan_run(hr_plan* pl, float* scores_dev, void* stream) {
     }
     hr_model* m = pl->m;
     hipStream_t st = (hipStream_t)stream;
-    // everything below is stream work only: one copy from the plan's own pinned block and the kernels.  No host wait, no
-    // allocation, no event, no second stream, no timing.
-    HR_HIP(hipMemcpyAsync(pl->wsb + pl->ws.off_meta, pl->stage, pl->upload_ints * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    // everything below is stream work only: the kernels, the first of which fetches the plan's own pinned block (or a
+    // copy in front of them).  No host wait, no allocation, no event, no second stream, no timing.
+    MetaSource src;
+    if (meta_by_kernel(pl->upload_ints, pl->T)) {
+        src.host = pl->stage_dev;
+        src.ints = pl->upload_ints;
+    } else {
+        HR_HIP(hipMemcpyAsync(pl->wsb + pl->ws.off_meta, pl->stage, pl->upload_ints * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    }
     const bool prof = m->prof_on;
     m->prof_on = false;
     const int rc = run_layers(m, pl->pool, false, pl->part.mv, pl->ws, pl->wsb, pl->part.max_keys, pl->max_q, scores_dev, st, nullptr,
-                              pl->part.gv.n_groups > 0 ? &pl->part.gv : nullptr, nullptr, pl->n_precise);
+                              pl->part.gv.n_groups > 0 ? &pl->part.gv : nullptr, nullptr, pl->n_precise, src);
     m->prof_on = prof;
     return rc;
 }
@@ -1140,6 +1229,17 @@ int hr_rerank_topk(const float* scores_dev, const int32_t* seg_dev, int32_t n_qu
         return HR_ERR_INVALID_ARG;
     }
     HR_HIP(launch_segment_topk(scores_dev, seg_dev, n_queries, max_cands, k, topk_idx_dev, topk_scores_dev, (hipStream_t)stream));
+    return HR_OK;
+}
+
+int hr_rerank_topk_host(const float* scores_dev, const int32_t* seg_offsets, int32_t n_queries, int32_t max_cands, int32_t k,
+                        int32_t* topk_idx_dev, float* topk_scores_dev, void* stream) {
+    if (n_queries == 0) return HR_OK;
+    if (!scores_dev || !seg_offsets || !topk_idx_dev || n_queries < 0 || max_cands < 1 || max_cands > 4096 || k < 1 || k > max_cands) {
+        snprintf(g_last_error, sizeof(g_last_error), "hr_rerank_topk_host: null pointer, or n_queries / max_cands (1..4096) / k (1..max_cands) out of range");
+        return HR_ERR_INVALID_ARG;
+    }
+    HR_HIP(launch_segment_topk_host(scores_dev, seg_offsets, n_queries, max_cands, k, topk_idx_dev, topk_scores_dev, (hipStream_t)stream));
     return HR_OK;
 }
 

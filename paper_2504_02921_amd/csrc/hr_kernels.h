@@ -39,8 +39,11 @@ struct MetaView {
 };
 
 // ---- generic (any shape, VALU arithmetic in fp32) ----
-hipError_t launch_embed(int dtype, const void* E, const MetaView& mv, float* x, int H, hipStream_t st);
-hipError_t launch_rope_table(const MetaView& mv, float2* tab, int head_dim, float base, hipStream_t st);
+// Everything in front of the first layer as one launch: the embedding rows -> x, the RoPE table, `zero_bytes` (a multiple of
+// 16) cleared at `zero`, and, with meta_host (pinned host memory as the device addresses it), the metadata block copied to
+// meta_dev, which the pointers of `mv` lie in.
+hipError_t launch_prologue(int dtype, const void* E, const MetaView& mv, float* x, int H, float2* tab, int head_dim, float base,
+                           void* zero, size_t zero_bytes, const int32_t* meta_host, int32_t* meta_dev, size_t meta_ints, hipStream_t st);
 // rows: optional gather (device array of T row indices into x): y row t <- x row rows[t]
 hipError_t launch_rmsnorm(int dtype, const float* x, const float* gain, void* y, int64_t T, int H, float eps, hipStream_t st,
                           const int32_t* rows = nullptr);
@@ -51,9 +54,29 @@ hipError_t launch_rmsnorm_split(const float* x, const float* gain, void* y, int6
 // the rounding residue of K/V in kv_lo).  tok_src != nullptr: token t reads qkv row tok_src[t] instead of row t.
 hipError_t launch_rope_pages(const float* qkv, const float2* tab, void* q, void* kv_hi, void* kv_lo, const int32_t* new_slot,
                              const int32_t* tok_src, int64_t T, int n_q, int n_kv, int d, hipStream_t st);
-// C[M][N] (+)= A[M][K] * W[N][K]^T, C fp32
-hipError_t launch_gemm_generic(int dtype, const void* A, const void* W, float* C, int64_t M, int N, int K,
-                               bool accumulate, hipStream_t st);
+// ---- fp32 arithmetic (hr_f32.hip): every projection of fp32 models, and (STORE / ADD) of 16-bit models whose shapes the
+// half MFMA family does not cover.  C = A W^T; gain set: the rows of A are RMS-normalised with it first (fp32 only).
+enum F32Epilogue { F32_STORE = 0, F32_ADD = 1, F32_ROPE = 2, F32_SWIGLU = 3 };
+struct F32GemmArgs {
+    const void* A;             // [M][K] in the model's activation type
+    const void* W;             // [N][K]
+    int64_t M;
+    int N, K;
+    const float* gain;         // [K] or nullptr
+    float eps;
+    float* C;                  // STORE: [M][N]; ADD: C += A W^T; SWIGLU: [M][N / 2]
+    const float* add;          // ADD with add_rows: C[m] = add[add_rows[m]] + A W^T
+    const int32_t* add_rows;
+    int ib;                    // SWIGLU: gate and up columns alternate in blocks of this many (1 or 32)
+    const float2* rope;        // ROPE: [M][d / 2]; q and k columns are rotated, all three written as [M][heads][d]
+    float *q, *k, *v;
+    int n_q, n_kv, d;
+};
+hipError_t launch_gemm_f32(F32Epilogue epi, int dtype, const F32GemmArgs& a, hipStream_t st);
+bool f32_fused_supported(const hr_model_cfg& c);     // fp32 models whose head size the fused epilogue and the attention take
+// last_only: the rows of each sequence's last token only, written as [n_seq][n_q][d]
+hipError_t launch_attn_f32(const float* q, const float* k_new, const float* v_new, float* o, const MetaView& mv, const PoolView& pv,
+                           int layer, int n_q, int max_q_len, bool last_only, hipStream_t st);
 hipError_t launch_rope_split(int dtype, const float* qkv, const float2* tab, void* q, void* k, void* v, int64_t T,
                              int n_q, int n_kv, int d, hipStream_t st);
 hipError_t launch_swiglu(int dtype, const float* gu, void* m, int64_t T, int F, int interleave, hipStream_t st);
@@ -133,6 +156,9 @@ hipError_t launch_gather_rows_f32(const float* src, const int32_t* rows, float* 
 // per-segment top-k by rank counting: idx [n_seg][k] (-1 padded), optional scores [n_seg][k]
 hipError_t launch_segment_topk(const float* scores, const int32_t* seg, int n_seg, int max_cands, int k, int32_t* idx, float* out_scores,
                                hipStream_t st);
+// the same with the offsets in host memory (they travel as kernel arguments)
+hipError_t launch_segment_topk_host(const float* scores, const int32_t* seg_host, int n_seg, int max_cands, int k, int32_t* idx,
+                                    float* out_scores, hipStream_t st);
 // copy whole pages (all kv heads) from the new-KV page buffer to pool pages of one layer:
 // pool page dst_table[i] <- new page src_first[doc(i)] + i  (16-bit pools: same arrangement on both sides)
 hipError_t launch_pages_to_pool(const char* kv_new, char* pool_layer_base, const int32_t* src_page, const int32_t* dst_page,

@@ -13,30 +13,51 @@
 namespace hr {
 
 // ------------------------------------------------------------------------------------------------
-// embedding gather: x[t][:] = E[token[t]][:]   (fp32 residual stream)
+// What a pass needs before its first layer, as one launch (each part alone is bound by launch latency at the sizes of a
+// single request):
+//   blocks [0, T)        x[t][:] = E[token[t]][:] (fp32 residual stream), and the token's row of the RoPE table:
+//                        tab[t][j] = (cos, sin)(pos[t] * base^(-2j/d)), angles in fp64
+//   then zero_blocks     clear the new tokens' K/V pages (slots past a sequence's end are never written by any layer)
+//   then meta blocks     copy the call's metadata from pinned host memory (calls with little of it; tok_id / tok_pos point
+//                        there then, too)
 // ------------------------------------------------------------------------------------------------
 template <typename T>
-__global__ void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok_id, float* __restrict__ x, int H) {
-    size_t t = blockIdx.x;
-    const T* src = E + (size_t)tok_id[t] * H;
-    float* dst = x + t * H;
-    for (int c = threadIdx.x; c < H; c += blockDim.x) dst[c] = to_float(src[c]);
-}
-
-// ------------------------------------------------------------------------------------------------
-// RoPE table: tab[t][j] = (cos, sin)(pos[t] * base^(-2j/d)), angles in fp64, once per call
-// ------------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(const int32_t* __restrict__ tok_pos, float2* __restrict__ tab, int64_t T, int half,
-                                  double base) {
-    int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= T * half) return;
-    int64_t t = idx / half;
-    int j = (int)(idx - t * half);
-    double inv_freq = pow(base, -(double)j / (double)half);
-    double ang = (double)tok_pos[t] * inv_freq;
-    double s, c;
-    sincos(ang, &s, &c);
-    tab[idx] = make_float2((float)c, (float)s);
+__global__ void __launch_bounds__(256) prologue_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok_id,
+                                                       const int32_t* __restrict__ tok_pos, float* __restrict__ x, int H,
+                                                       float2* __restrict__ tab, int half, double base, unsigned n_tok,
+                                                       uint4* __restrict__ zero, size_t zero_n16, unsigned zero_blocks,
+                                                       const int32_t* __restrict__ meta_src, int32_t* __restrict__ meta_dst, int meta_ints) {
+    const unsigned b = blockIdx.x;
+    if (b >= n_tok) {
+        if (b - n_tok < zero_blocks) {
+            for (size_t i = (size_t)(b - n_tok) * 256 + threadIdx.x; i < zero_n16; i += (size_t)zero_blocks * 256)
+                zero[i] = make_uint4(0u, 0u, 0u, 0u);
+        } else {
+            const int i = (int)(b - n_tok - zero_blocks) * 1024 + (int)threadIdx.x * 4;      // blocks of 4 KiB
+            if (i + 3 < meta_ints) *(int4*)(meta_dst + i) = *(const int4*)(meta_src + i);
+            else
+                for (int e = i; e < meta_ints; ++e) meta_dst[e] = meta_src[e];
+        }
+        return;
+    }
+    const T* src = E + (size_t)tok_id[b] * H;
+    float* dst = x + (size_t)b * H;
+    if (H % 4 == 0) {
+        typedef __attribute__((ext_vector_type(4))) T tx4;
+        for (int c = threadIdx.x; c < H / 4; c += 256) {
+            const tx4 e = ((const tx4*)src)[c];
+            ((float4*)dst)[c] = make_float4(to_float<T>(e[0]), to_float<T>(e[1]), to_float<T>(e[2]), to_float<T>(e[3]));
+        }
+    } else {
+        for (int c = threadIdx.x; c < H; c += 256) dst[c] = to_float(src[c]);
+    }
+    for (int j = threadIdx.x; j < half; j += 256) {
+        const double inv_freq = pow(base, -(double)j / (double)half);
+        const double ang = (double)tok_pos[b] * inv_freq;
+        double s, c;
+        sincos(ang, &s, &c);
+        tab[(size_t)b * half + j] = make_float2((float)c, (float)s);
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -130,54 +151,6 @@ __global__ void __launch_bounds__(256) rmsnorm_split_kernel(const float* __restr
         const half_t hi = from_float<half_t>(v);
         yr[c] = hi;
         yr[H + c] = from_float<half_t>(v - (float)hi);
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// generic GEMM: C[M][N] (+)= A[M][K] W[N][K]^T, 64x64 tile, 256 threads x (4x4), fp32 FMA
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) gemm_generic_kernel(const T* __restrict__ A, const T* __restrict__ W,
-                                                           float* __restrict__ C, int64_t M, int N, int K, int accumulate) {
-    constexpr int BM = 64, BN = 64, BK = 16;
-    __shared__ float sA[BK][BM + 4];
-    __shared__ float sW[BK][BN + 4];
-    int64_t m0 = (int64_t)blockIdx.x * BM;
-    int n0 = blockIdx.y * BN;
-    int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4] = {};
-    int lr = threadIdx.x >> 2;         // 0..63 tile row loaded by this thread
-    int lc = (threadIdx.x & 3) * 4;    // 0,4,8,12 first of 4 k's
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        for (int u = 0; u < 4; ++u) {
-            int kk = k0 + lc + u;
-            int64_t am = m0 + lr;
-            int wn = n0 + lr;
-            sA[lc + u][lr] = (am < M && kk < K) ? to_float(A[am * K + kk]) : 0.f;
-            sW[lc + u][lr] = (wn < N && kk < K) ? to_float(W[(size_t)wn * K + kk]) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < BK; ++kk) {
-            float a[4], w[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = sA[kk][ty * 4 + i]; w[i] = sW[kk][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    for (int i = 0; i < 4; ++i) {
-        int64_t m = m0 + ty * 4 + i;
-        if (m >= M) continue;
-        for (int j = 0; j < 4; ++j) {
-            int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float* c = C + m * N + n;
-            *c = accumulate ? (*c + acc[i][j]) : acc[i][j];
-        }
     }
 }
 
@@ -608,17 +581,16 @@ hipError_t launch_fill_zero(void* dst, size_t bytes, hipStream_t st) {     // by
         else { using AT = bf16_t; __VA_ARGS__; }                      \
     } while (0)
 
-hipError_t launch_embed(int dtype, const void* E, const MetaView& mv, float* x, int H, hipStream_t st) {
+hipError_t launch_prologue(int dtype, const void* E, const MetaView& mv, float* x, int H, float2* tab, int head_dim, float base,
+                           void* zero, size_t zero_bytes, const int32_t* meta_host, int32_t* meta_dev, size_t meta_ints, hipStream_t st) {
     if (mv.T == 0) return hipSuccess;
-    HR_DISPATCH_EMB(dtype, embed_kernel<AT><<<dim3((unsigned)mv.T), 256, 0, st>>>((const AT*)E, mv.tok_id, x, H));
-    return hipGetLastError();
-}
-
-hipError_t launch_rope_table(const MetaView& mv, float2* tab, int head_dim, float base, hipStream_t st) {
-    if (mv.T == 0) return hipSuccess;
-    int half = head_dim / 2;
-    int64_t n = mv.T * half;
-    rope_table_kernel<<<dim3((unsigned)((n + 255) / 256)), 256, 0, st>>>(mv.tok_pos, tab, mv.T, half, (double)base);
+    const unsigned zb = (unsigned)std::min<size_t>((zero_bytes / 16 + 255) / 256, 4096);
+    const unsigned mb = meta_host ? (unsigned)((meta_ints + 1023) / 1024) : 0;
+    const int32_t* ids = meta_host ? meta_host + (mv.tok_id - meta_dev) : mv.tok_id;
+    const int32_t* pos = meta_host ? meta_host + (mv.tok_pos - meta_dev) : mv.tok_pos;
+    HR_DISPATCH_EMB(dtype, prologue_kernel<AT><<<dim3((unsigned)mv.T + zb + mb), 256, 0, st>>>(
+                               (const AT*)E, ids, pos, x, H, tab, head_dim / 2, (double)base, (unsigned)mv.T, (uint4*)zero, zero_bytes / 16, zb,
+                               meta_host, meta_dev, (int)meta_ints));
     return hipGetLastError();
 }
 
@@ -707,14 +679,6 @@ hipError_t launch_rope_pages(const float* qkv, const float2* tab, void* q, void*
     else
         rope_pages_kernel<false><<<dim3((unsigned)T), 256, 0, st>>>(qkv, tab, (half_t*)q, (half_t*)kv_hi, nullptr, new_slot, tok_src, n_q,
                                                                     n_kv, d);
-    return hipGetLastError();
-}
-
-hipError_t launch_gemm_generic(int dtype, const void* A, const void* W, float* C, int64_t M, int N, int K, bool accumulate,
-                               hipStream_t st) {
-    if (M == 0) return hipSuccess;
-    dim3 grid((unsigned)((M + 63) / 64), (unsigned)((N + 63) / 64));
-    HR_DISPATCH_ACT(dtype, gemm_generic_kernel<AT><<<grid, 256, 0, st>>>((const AT*)A, (const AT*)W, C, M, N, K, accumulate ? 1 : 0));
     return hipGetLastError();
 }
 
@@ -1018,13 +982,16 @@ namespace {
 constexpr int kTopkThreads = 256;
 constexpr int kTopkMaxCands = 4096;
 
+struct SegChunk { int32_t off[257]; };      // offsets of up to 256 segments as a kernel argument
+
+// seg: offsets in device memory, or nullptr: in `chunk`
 __global__ void __launch_bounds__(kTopkThreads) segment_topk_kernel(const float* __restrict__ scores, const int32_t* __restrict__ seg,
-                                                                     int max_cands, int k, int32_t* __restrict__ idx,
+                                                                     SegChunk chunk, int max_cands, int k, int32_t* __restrict__ idx,
                                                                      float* __restrict__ out_scores) {
     __shared__ float key[kTopkMaxCands];
     const int q = blockIdx.x;
-    const int begin = seg[q];
-    int n = seg[q + 1] - begin;
+    const int begin = seg ? seg[q] : chunk.off[q];
+    int n = (seg ? seg[q + 1] : chunk.off[q + 1]) - begin;
     n = n < 0 ? 0 : (n > max_cands ? max_cands : n);
     for (int i = threadIdx.x; i < k; i += kTopkThreads) {
         idx[(size_t)q * k + i] = -1;
@@ -1054,8 +1021,22 @@ hipError_t launch_segment_topk(const float* scores, const int32_t* seg, int n_se
                                hipStream_t st) {
     if (n_seg == 0) return hipSuccess;
     if (max_cands < 1 || max_cands > kTopkMaxCands || k < 1 || k > max_cands) return hipErrorInvalidValue;
-    segment_topk_kernel<<<dim3((unsigned)n_seg), kTopkThreads, 0, st>>>(scores, seg, max_cands, k, idx, out_scores);
+    segment_topk_kernel<<<dim3((unsigned)n_seg), kTopkThreads, 0, st>>>(scores, seg, SegChunk{}, max_cands, k, idx, out_scores);
     return hipGetLastError();
+}
+
+hipError_t launch_segment_topk_host(const float* scores, const int32_t* seg_host, int n_seg, int max_cands, int k, int32_t* idx,
+                                    float* out_scores, hipStream_t st) {
+    if (max_cands < 1 || max_cands > kTopkMaxCands || k < 1 || k > max_cands) return hipErrorInvalidValue;
+    for (int s0 = 0; s0 < n_seg; s0 += 256) {
+        const int n = std::min(256, n_seg - s0);
+        SegChunk chunk;
+        for (int i = 0; i <= n; ++i) chunk.off[i] = seg_host[s0 + i];
+        segment_topk_kernel<<<dim3((unsigned)n), kTopkThreads, 0, st>>>(scores, nullptr, chunk, max_cands, k, idx + (size_t)s0 * k,
+                                                                        out_scores ? out_scores + (size_t)s0 * k : nullptr);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace hr

@@ -56,6 +56,20 @@ def test_fp32_ragged_lengths_and_group_sizes(n_q, n_kv, d):
     case.close()
 
 
+@pytest.mark.parametrize("n_q,n_kv,d,hidden,ffn,n_queries", [(4, 4, 64, 256, 688, 9), (4, 2, 16, 72, 56, 3), (2, 1, 32, 40, 24, 3)])
+def test_fp32_projection_tiles_give_a_pair_the_same_bits_alone_and_in_a_batch(n_q, n_kv, d, hidden, ffn, n_queries):
+    """Every dispatch of the fp32 projections (large and small tiles, row lengths that are no multiple of 16) against
+    the oracle; an output element is summed in one order whatever the tile, so a pair alone scores bit for bit the same."""
+    model = small_model(n_q=n_q, n_kv=n_kv, d=d, hidden=hidden, ffn=ffn)
+    cfg = wlmod.WorkloadCfg("f32_tiles", model, n_queries, 5, (1, 40), (29, 33) if n_queries > 3 else (1, 19), "f32", seed=d)
+    w = wlmod.SeededWeights(model, seed=4, std=0.08, gain_jitter=0.1)
+    case, got, want = run_case(cfg, w, H.TOL["f32"])
+    assert np.abs(want).max() > 1e-2
+    for i in (0, len(got) // 2, len(got) - 1):
+        assert np.array_equal(case.gpu_scores(case.wl.subset([i])), got[i:i + 1])
+    case.close()
+
+
 def test_fp32_page_aligned_and_single_token_edges():
     model = small_model()
     w = wlmod.SeededWeights(model, seed=2, std=0.08, gain_jitter=0.1)
