@@ -62,12 +62,26 @@ __device__ __forceinline__ TileCoord map_tile(int pid, int tiles_m, int tiles_n)
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
 
+// A thread's 16-byte chunks of the tile's part of x, for tiles whose fp32 form fits the two stages (one slab below).
+template <int BN, int NT, int CHUNKS>
+__device__ __forceinline__ void x_prefetch(float4 (&xv)[CHUNKS], const GemmArgs& a, int64_t tile_m0, int tile_n0) {
+    constexpr int CPRW = BN / 4;
+#pragma unroll
+    for (int it = 0; it < CHUNKS; ++it) {
+        const int L = it * NT + threadIdx.x, row = L / CPRW, pch = L % CPRW;
+        const int64_t grow = min(tile_m0 + row, a.M - 1);
+        const int col = min(tile_n0 + ((pch ^ (row & 15)) << 2), a.N - 4);
+        xv[it] = *(const float4*)(a.x + grow * a.N + col);
+    }
+}
+
 // Epilogues on transposed accumulators: a lane owns output row (lane & 31) of each 32 x 32 block, register r holds
 // column 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3).  `smem` is the kernel's LDS (two stages of A, then two of W), free
-// behind the main loop's last barrier except that, in a persistent launch, stage 0 may be receiving the next tile.
+// behind the main loop's last barrier except that, in a persistent launch, stage 0 may be receiving the next tile.  x_pre: what
+// x_prefetch read (nullptr: x is read here).
 template <int EPI, int BM, int BN, int WM, int WN, int HB>
 __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN / WN / 32], const GemmArgs& a, char* smem,
-                                              int64_t tile_m0, int tile_n0) {
+                                              int64_t tile_m0, int tile_n0, const float4* x_pre = nullptr) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 32, NI = TN / 32;
@@ -131,7 +145,12 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
                     *(float4*)(a.x + grow * a.N + col) = v;
                 }
             };
-            load_x(0);
+            if (PASSES == 1 && x_pre) {
+#pragma unroll
+                for (int it = 0; it < G; ++it) xv[it] = x_pre[it];
+            } else {
+                load_x(0);
+            }
             if (p > 0) __syncthreads();                 // the previous slab has been read
             if ((wn * TN) / CW == p) {
                 const int c_off = wn * TN - p * CW + 4 * fh;
@@ -156,7 +175,12 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
             update_x(0);
 #pragma unroll
             for (int g = 1; g < NG; ++g) {
-                load_x(g * G);
+                if (PASSES == 1 && x_pre) {
+#pragma unroll
+                    for (int it = 0; it < G; ++it) xv[it] = x_pre[g * G + it];
+                } else {
+                    load_x(g * G);
+                }
                 update_x(g * G);
             }
         }
@@ -306,8 +330,9 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
                 }
         }
         __syncthreads();                                            // every lane is done with the table
-        constexpr int CPT = BN / 8;                                 // 16-byte chunks per tile row (16 or 32)
-        static_assert(EPI != EPI_QKV_ROPE || (CPT % 16 == 0 && (BM * CPT) % NT == 0), "output tile shape");
+        constexpr int CPT = BN / 8;                                 // 16-byte chunks per tile row (8, 16 or 32)
+        static_assert(EPI != EPI_QKV_ROPE || ((CPT == 8 || CPT % 16 == 0) && (BM * CPT) % NT == 0), "output tile shape");
+        auto swz = [](int r) { return CPT == 8 ? ((r >> 1) & 7) : (r & 15); };
         half_t* stage = (half_t*)smem;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
@@ -317,7 +342,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     const int ch = (wn * TN + j * 32) / 8 + r4;
-                    *(halfx4*)(stage + lr * BN + ((ch ^ (lr & 15)) << 3) + 4 * fh) = res[i][j][r4];
+                    *(halfx4*)(stage + lr * BN + ((ch ^ swz(lr)) << 3) + 4 * fh) = res[i][j][r4];
                 }
         }
         __syncthreads();
@@ -325,7 +350,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
         for (int it = 0; it < BM * CPT / NT; ++it) {
             const int L = it * NT + tid;
             const int row = L / CPT, pch = L % CPT;
-            const int col = tile_n0 + ((pch ^ (row & 15)) << 3);
+            const int col = tile_n0 + ((pch ^ swz(row)) << 3);
             const int64_t grow = tile_m0 + row;
             if (grow >= a.M || col >= nq + nkv) continue;           // past the matrix, or V (stored above)
             const uint4v w = *(const uint4v*)(stage + row * BN + (pch << 3));
@@ -500,15 +525,19 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_mfma_kernel(GemmArgs a) {
     }
 }
 
-// Small-M variant: the same tile arithmetic with a ring of NS LDS stages.  With fewer tiles than CUs a tile has its
-// CU to itself and the two-stage loop above is bound by latency (one load round trip, ~1 us, per k-tile: the down
-// projection's 76 k-tiles alone are 77 us for 640 rows); with NS - 1 k-tiles in flight the loop runs at the rate the
-// direct-to-LDS path delivers.  Vector memory operations complete in order, so "k-tile kt has landed" is a wait
-// until at most the loads of the NS - 2 younger k-tiles are outstanding; the one barrier per k-tile also tells that
-// every wave is done with the stage of k-tile kt - 1, which is where k-tile kt + NS - 1 goes.  Same operand order and
-// same k order as the kernel above: an output element gets the same bits from either.
+// Small-M variant: the same tile arithmetic (operand and k order as above: an output element gets the same bits from
+// either) with a ring of NS LDS stages, for launches whose tiles fit the chip in about one round.  A tile then has its CU to
+// itself, one wavefront per SIMD, and what counts is the serial length of a k-tile:
+//   * NS k-tiles are requested ahead; vector memory operations complete in order, so "k-tile kt has landed" is a counted wait;
+//   * the fragments of k-tile kt + 1 are read from LDS into a second register set before the MFMAs of k-tile kt issue, so
+//     a k-tile costs one barrier, and neither LDS latency nor the loads sit in front of the matrix pipe.  The barrier that
+//     says k-tile kt + 1 has landed also says that every wave holds k-tile kt in registers: its stage is free for kt + NS.
+// What is left is the delivery to the CU: about 60 bytes per cycle from L2 (measured with a bare direct-to-LDS loop: 272
+// cycles for the 16 KiB of a 64 x 64 k-tile, 544 for 128 x 128).  The previous loop (fragments read behind the barrier,
+// one k-step ahead) took ~750 cycles per 64 x 64 k-tile whatever the number of workgroups: the down projection of 65 or
+// 640 rows (K = 4864) 27 / 28 us.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
-__global__ void __launch_bounds__(WM * WN * 64) gemm_ring_kernel(GemmArgs a) {
+__global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 32, NI = TN / 32;
@@ -516,10 +545,8 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_ring_kernel(GemmArgs a) {
     constexpr int PA = BM / RPP, PB = BN / RPP;
     constexpr int KS = BK / 16;
     constexpr int LPT = PA + PB;                    // loads per thread and k-tile
-    constexpr int AHEAD = (NS - 2) * LPT;           // loads that may still be outstanding when a k-tile is consumed
     static_assert(RPP % 16 == 0 && BM % RPP == 0 && BN % RPP == 0, "loader shape");
-    static_assert(NS >= 3 && AHEAD < 64, "the load counter has six bits");
-    constexpr int kWaitAhead = (AHEAD & 15) | ((AHEAD >> 4) << 14) | 0x0F70;     // s_waitcnt vmcnt(AHEAD) only
+    static_assert(NS >= 2 && NS <= 10 && (NS - 1) * LPT < 64, "the load counter has six bits");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     half_t* sA = (half_t*)smem;                         // [NS][BM][BK]
     half_t* sB = sA + NS * BM * BK;                     // [NS][BN][BK]
@@ -534,38 +561,36 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_ring_kernel(GemmArgs a) {
     const int wm = wave / WN, wn = wave % WN;
     const int K = a.K;
     const int Kw = a.Kw > 0 ? a.Kw : K;
-    const int nkw = Kw / BK;
-    const half_t* A = (const half_t*)a.A;
-    const half_t* W = (const half_t*)a.W;
+    const int nkw = Kw / BK, nk = K / BK;
 
+    // x of a residual add: requested first, so that it has arrived long before the epilogue
+    constexpr bool XPRE = EPI == EPI_RESID_ADD;
+    float4 xv[XPRE ? BM * BN / 4 / NT : 1];
+    if constexpr (XPRE) x_prefetch<BN, NT>(xv, a, m0, n0);
+
+    // loader: a wave-uniform tile base and a 32-bit byte offset per lane and pass
+    const char* baseA = (const char*)((const half_t*)a.A + m0 * K);
+    const char* baseB = (const char*)((const half_t*)a.W + (size_t)n0 * Kw);
     const int lrow = tid >> 3;
     const int lchunk = (tid & 7) ^ ((lrow >> 1) & 7);
-    const half_t* pa[PA];
-    const half_t* pb[PB];
+    const int rows_a = (int)min((int64_t)BM, a.M - m0), rows_b = min(BN, a.N - n0);
+    unsigned oa[PA], ob[PB];
 #pragma unroll
-    for (int p = 0; p < PA; ++p) {
-        int64_t r = m0 + p * RPP + lrow;
-        r = r < a.M ? r : a.M - 1;
-        pa[p] = A + r * K + lchunk * 8;
-    }
+    for (int p = 0; p < PA; ++p) oa[p] = (unsigned)(min(p * RPP + lrow, rows_a - 1) * K + lchunk * 8) * 2u;
 #pragma unroll
-    for (int p = 0; p < PB; ++p) {
-        int r = n0 + p * RPP + lrow;
-        r = r < a.N ? r : a.N - 1;
-        pb[p] = W + (size_t)r * Kw + lchunk * 8;
-    }
+    for (int p = 0; p < PB; ++p) ob[p] = (unsigned)(min(p * RPP + lrow, rows_b - 1) * Kw + lchunk * 8) * 2u;
     auto dma = [&](int kt, int buf) {
         half_t* da = sA + buf * BM * BK + wave * 64 * 8;
         half_t* db = sB + buf * BN * BK + wave * 64 * 8;
-        const int ktw = kt < nkw ? kt : kt - nkw;
+        const char* ka = baseA + (size_t)kt * (BK * 2);
+        const char* kb = baseB + (size_t)(kt < nkw ? kt : kt - nkw) * (BK * 2);
 #pragma unroll
         for (int p = 0; p < PA; ++p)
-            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(pa[p] + kt * BK), (lds_ptr_t)(da + p * NT * 8), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(ka + oa[p]), (lds_ptr_t)(da + p * NT * 8), 16, 0, 0);
 #pragma unroll
         for (int p = 0; p < PB; ++p)
-            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(pb[p] + ktw * BK), (lds_ptr_t)(db + p * NT * 8), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(kb + ob[p]), (lds_ptr_t)(db + p * NT * 8), 16, 0, 0);
     };
-
     floatx16 acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -577,48 +602,84 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_ring_kernel(GemmArgs a) {
     const int a_row0 = wm * TM + frow;
     const int b_row0 = wn * TN + frow;
     const int sw = (frow >> 1) & 7;
-    halfx8 af[2][MI], bfr[2][NI];
-    auto fload = [&](int slot, const half_t* cA, const half_t* cB, int kk) {
-        const int pch = ((kk * 2 + fh) ^ sw) * 8;
-#pragma unroll
-        for (int i = 0; i < MI; ++i) af[slot][i] = *(const halfx8*)(cA + (a_row0 + i * 32) * BK + pch);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) bfr[slot][j] = *(const halfx8*)(cB + (b_row0 + j * 32) * BK + pch);
-    };
-    auto mfmas = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bfr[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
-    };
-
-    const int nk = K / BK;
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
-        if (s < nk) dma(s, s);
-    int cur = 0;                                   // stage of k-tile kt
-    for (int kt = 0; kt < nk; ++kt) {
-        // own loads of k-tile kt have landed: in the steady state the NS - 2 younger k-tiles may be outstanding; once no
-        // new loads are issued everything is simply waited for
-        if (kt + NS - 2 < nk) __builtin_amdgcn_s_waitcnt(kWaitAhead);
-        else __builtin_amdgcn_s_waitcnt(0x0F70);
-        // LDS-only barrier (a __syncthreads() would wait for the loads in flight as well)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const int nxt = kt + NS - 1;
-        if (nxt < nk) dma(nxt, cur == 0 ? NS - 1 : cur - 1);       // the stage k-tile kt - 1 was read from
-        const half_t* cA = sA + cur * BM * BK;
-        const half_t* cB = sB + cur * BN * BK;
-        fload(0, cA, cB, 0);
+    halfx8 af[2][KS][MI], bfr[2][KS][NI];           // fragments of a whole k-tile, double buffered
+    auto fload = [&](int set, int buf) {
+        const half_t* cA = sA + buf * BM * BK;
+        const half_t* cB = sB + buf * BN * BK;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            if (kk + 1 < KS) fload((kk + 1) & 1, cA, cB, kk + 1);
-            mfmas(kk & 1);
+            const int pch = ((kk * 2 + fh) ^ sw) * 8;
+#pragma unroll
+            for (int i = 0; i < MI; ++i) af[set][kk][i] = *(const halfx8*)(cA + (a_row0 + i * 32) * BK + pch);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) bfr[set][kk][j] = *(const halfx8*)(cB + (b_row0 + j * 32) * BK + pch);
         }
-        cur = cur + 1 == NS ? 0 : cur + 1;
+    };
+
+    // One k-tile, its fragments in (or on their way to) set SET, stage `slot`.  YOUNGER: how many of the k-tiles requested so
+    // far come after the next one (their loads may still be outstanding), -1: there is no next one.
+    int slot = 0;
+    auto step = [&](auto set_c, auto younger_c, bool request, int kt) {
+        constexpr int SET = decltype(set_c)::value, YOUNGER = decltype(younger_c)::value;
+        const int next = slot + 1 == NS ? 0 : slot + 1;
+        if constexpr (YOUNGER >= 0) {
+            // the wait is the compiler's to see (its own waits in front of the MFMAs then leave the reads below alone);
+            // a __syncthreads() would wait for the loads in flight as well
+            constexpr int V = YOUNGER * LPT;
+            __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0070);       // vmcnt(V) lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            fload(SET ^ 1, next);
+            if (request) dma(kt + NS, slot);
+        }
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bfr[SET][kk][j], af[SET][kk][i], acc[i][j], 0, 0, 0);
+        if constexpr (YOUNGER >= 0) {
+            // all fragment reads first, then the requests spread over the MFMAs
+            __builtin_amdgcn_sched_group_barrier(0x100, KS * (MI + NI), 0);
+            constexpr int PER = KS * MI * NI / LPT > 0 ? KS * MI * NI / LPT : 1;
+#pragma unroll
+            for (int n = 0; n < LPT; ++n) {
+                __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
+                __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+            }
+            asm volatile("" ::: "memory");
+        }
+        slot = next;
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, (NS - 1) & 1> set_p{};         // sets alternate, counted from the last k-tile (set 0)
+    constexpr integral_constant<int, NS & 1> set_q{};
+    constexpr integral_constant<int, NS - 2> steady{};
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (s < nk) dma(s, s);
+    if (nk >= NS) __builtin_amdgcn_s_waitcnt((((NS - 1) * LPT) & 15) | ((((NS - 1) * LPT) >> 4) << 14) | 0x0F70);
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if ((nk - 1) & 1) fload(1, 0);
+    else fload(0, 0);
+    int kt = 0;
+    if (nk > NS && ((nk - NS) & 1)) step(set_q, steady, true, kt++);
+    for (; kt + NS < nk; kt += 2) {
+        step(set_p, steady, true, kt);
+        step(set_q, steady, true, kt + 1);
     }
+    // the last NS k-tiles (all requested): k-tile nk - 1 - R has R - 1 requested ones behind the next
+    auto tail = [&](auto self, auto r_c) -> void {
+        constexpr int R = decltype(r_c)::value;
+        if (R < nk) step(integral_constant<int, R & 1>{}, integral_constant<int, R - 1>{}, false, 0);
+        if constexpr (R > 0) self(self, integral_constant<int, R - 1>{});
+    };
+    tail(tail, integral_constant<int, NS - 1>{});
     __syncthreads();                               // every wave is done reading the stages before the epilogue reuses them
-    gemm_epilogue<EPI, BM, BN, WM, WN, HB>(acc, a, smem, m0, n0);
+    gemm_epilogue<EPI, BM, BN, WM, WN, HB>(acc, a, smem, m0, n0, XPRE ? xv : nullptr);
 }
 
 int cu_count();
@@ -702,28 +763,31 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
     if (a.K % BK != 0) return hipErrorInvalidValue;
     if (a.Kw > 0 && (a.Kw % BK != 0 || (a.K != a.Kw && a.K != 2 * a.Kw))) return hipErrorInvalidValue;
     const bool wide_head = epi == EPI_QKV_ROPE && a.d == 128;       // a wave must span a whole 128-wide head
-    // Few rows: when even 128 x 128 tiles do not give every CU one, the ring variants take over.  64-row tiles double
-    // the tile count; they pay when that still fits one round of the chip (a ring workgroup has its CU to itself),
-    // otherwise 128-row tiles with fewer, larger k-steps do (modelled as rounds x bytes per k-tile).
-    const int64_t tiles128 = ((a.M + 127) / 128) * ((a.N + (wide_head ? 255 : 127)) / (wide_head ? 256 : 128));
-    if (tiles128 < cu_count()) {
-        const int64_t cus = cu_count();
-        const int64_t t64 = ((a.M + 63) / 64) * ((a.N + (wide_head ? 255 : 127)) / (wide_head ? 256 : 128));
-        if (wide_head) return launch_ring<EPI_QKV_ROPE, 64, 256, 2, 2, 2, 3>(a, st);
-        const int64_t cost64 = ((t64 + cus - 1) / cus) * (64 + 128), cost128 = ((tiles128 + cus - 1) / cus) * (128 + 128);
-        const bool r64 = cost64 <= cost128;
-        // residual-add launches with so few rows that even 64 x 64 tiles fit one round: four times the workgroups of the
-        // 128 x 128 shape, each with eight k-tiles in flight (nine stages of 16 KiB)
-        const int64_t t6464 = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-        if (epi == EPI_RESID_ADD && t6464 <= cus) return launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(a, st);
-        switch (epi) {
-            case EPI_QKV_ROPE:
-                return r64 ? launch_ring<EPI_QKV_ROPE, 64, 128, 2, 2, 1, 5>(a, st) : launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(a, st);
-            case EPI_RESID_ADD:
-                return r64 ? launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 5>(a, st) : launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(a, st);
-            case EPI_SWIGLU:
-                return r64 ? launch_ring<EPI_SWIGLU, 64, 128, 2, 2, 1, 5>(a, st) : launch_ring<EPI_SWIGLU, 128, 128, 2, 2, 1, 4>(a, st);
-        }
+    // Few rows: the ring variants, while one of their shapes takes the launch in one round of the chip (a ring workgroup has
+    // its CU to itself).  Among those the one with the fewest operand bytes per k-tile, i.e. the smallest that fits: the
+    // loop is bound by the delivery of BM + BN rows per k-tile to the CU.
+    const int64_t cus = cu_count();
+    auto fits = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) <= cus; };
+    switch (epi) {
+        case EPI_QKV_ROPE:
+            if (wide_head) {
+                if (fits(64, 128)) return launch_ring<EPI_QKV_ROPE, 64, 128, 2, 1, 2, 5>(a, st);
+                if (fits(128, 128)) return launch_ring<EPI_QKV_ROPE, 128, 128, 4, 1, 2, 4>(a, st);
+            } else {
+                if (fits(64, 64)) return launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(a, st);
+                if (fits(128, 128)) return launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(a, st);
+            }
+            break;
+        case EPI_RESID_ADD:
+            if (fits(64, 64)) return launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(a, st);
+            if (fits(64, 128)) return launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(a, st);
+            if (fits(128, 128)) return launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(a, st);
+            break;
+        case EPI_SWIGLU:
+            if (fits(64, 128)) return launch_ring<EPI_SWIGLU, 64, 128, 2, 2, 1, 6>(a, st);
+            if (fits(128, 128)) return launch_ring<EPI_SWIGLU, 128, 128, 2, 2, 1, 4>(a, st);
+            if (fits(128, 256)) return launch_ring<EPI_SWIGLU, 128, 256, 2, 2, 1, 3>(a, st);
+            break;
     }
     // the tall tile: residual-add launches, and gate/up launches with a long k loop (not persistent: at K = 896 the
     // start-up round trip per tile costs more than the shape saves: 8.8 against 8.0 ms per step at the 0.5B shape)
