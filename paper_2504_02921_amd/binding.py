@@ -85,7 +85,7 @@ def _load() -> C.CDLL:
     if os.path.exists(bundled):
         C.CDLL(bundled, mode=C.RTLD_GLOBAL)
     lib = C.CDLL(LIB_PATH)
-    i32p = C.POINTER(C.c_int32)
+    i32p = C.c_void_p                  # int32 arrays of the host: an address, or anything ctypes takes as a pointer
     sig = {
         "hr_status_str": (C.c_char_p, [C.c_int]),
         "hr_last_error": (C.c_char_p, []),
@@ -130,7 +130,7 @@ def _load() -> C.CDLL:
         "hr_doc_prefill": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, i32p, i32p, i32p, C.c_int32, C.c_void_p, C.c_size_t, C.c_void_p]),
         "hr_attention_path": (C.c_char_p, [C.c_void_p, C.c_void_p]),
         "hr_gemm_path": (C.c_char_p, [C.c_void_p]),
-        "hr_rerank_topk_host": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
+        "hr_rerank_topk_host": (C.c_int, [C.c_void_p, i32p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
         "hr_rerank_topk": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]),
         "hr_model_range_report": (C.c_int, [C.c_void_p, C.POINTER(hr_range_report)]),
         "hr_kv_pool_range_report": (C.c_int, [C.c_void_p, C.POINTER(hr_range_report)]),
@@ -164,19 +164,19 @@ def check(status: int, where: str) -> None:
 
 
 def _i32(a) -> np.ndarray:
-    return np.ascontiguousarray(np.asarray(a), dtype=np.int32)
+    return np.ascontiguousarray(a, np.int32)
 
 
 def _i32p(a: Optional[np.ndarray]):
-    if a is None:
-        return None
-    return a.ctypes.data_as(C.POINTER(C.c_int32))
+    """Address of an int32 array (a plain integer: a typed ctypes pointer costs 3 us, as much as a launch)."""
+    return None if a is None else a.ctypes.data
 
 
-def _stream_ptr(stream=None) -> C.c_void_p:
+def _stream_ptr(stream=None) -> int:
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 # ----------------------------------------------------------------------------------------------
@@ -219,15 +219,15 @@ def rerank_topk(scores, seg_offsets, k: int, with_scores: bool = False, stream=N
     max_c = max(int((seg[1:] - seg[:-1]).max()) if n_q > 0 else 1, k, 1)      # an upper bound is all the library needs
     idx = torch.empty((max(n_q, 0), k), dtype=torch.int32, device=scores.device)
     sc = torch.empty((max(n_q, 0), k), dtype=torch.float32, device=scores.device) if with_scores else None
-    check(lib.hr_rerank_topk_host(C.c_void_p(scores.data_ptr()), _i32p(seg), n_q, max_c, k,
-                                  C.c_void_p(idx.data_ptr()), C.c_void_p(sc.data_ptr()) if with_scores else None, _stream_ptr(stream)),
+    check(lib.hr_rerank_topk_host(scores.data_ptr(), _i32p(seg), n_q, max_c, k,
+                                  idx.data_ptr(), sc.data_ptr() if with_scores else None, _stream_ptr(stream)),
           "hr_rerank_topk")
     return (idx, sc) if with_scores else idx
 
 
 def probe_read_bandwidth(src, sink, to_lds: bool = False, stream=None) -> None:
     """One read-only pass of the library's streaming yardstick kernel over the device tensor `src`."""
-    check(lib.hr_probe_read_bandwidth(C.c_void_p(src.data_ptr()), src.numel() * src.element_size(), C.c_void_p(sink.data_ptr()),
+    check(lib.hr_probe_read_bandwidth(src.data_ptr(), src.numel() * src.element_size(), sink.data_ptr(),
                                       sink.numel() * sink.element_size(), 1 if to_lds else 0, _stream_ptr(stream)),
           "hr_probe_read_bandwidth")
 
@@ -243,6 +243,9 @@ class KVPool:
         if nbytes == 0:
             raise HrError(HR_ERR_INVALID_ARG, "hr_kv_pool_bytes")
         self.mem = torch.zeros(nbytes, dtype=torch.uint8, device=device)
+        self._dims = (n_layers, n_kv_heads, head_dim)
+        self.kv_fp8 = self.cfg.kv_dtype == HR_FP8_E4M3
+        self._read_dtype = {HR_F32: torch.float32, HR_BF16: torch.float16, HR_FP8_E4M3: torch.uint8}[self.cfg.kv_dtype]
         st, self.handle = hr_kv_pool_create(self.cfg, self.mem.data_ptr(), nbytes)
         check(st, "hr_kv_pool_create")
 
@@ -250,9 +253,9 @@ class KVPool:
         """k, v: device tensors [L][doc_len][n_kv][d] in the pool dtype (uint8 codes for fp8)."""
         ids = _i32(page_ids)
         assert k.is_contiguous() and v.is_contiguous() and k.is_cuda and v.is_cuda
-        ks = C.c_void_p(k_scale.data_ptr()) if k_scale is not None else None
-        vs = C.c_void_p(v_scale.data_ptr()) if v_scale is not None else None
-        st = lib.hr_doc_kv_write(self.handle, int(doc_len), _i32p(ids), C.c_void_p(k.data_ptr()), C.c_void_p(v.data_ptr()),
+        ks = k_scale.data_ptr() if k_scale is not None else None
+        vs = v_scale.data_ptr() if v_scale is not None else None
+        st = lib.hr_doc_kv_write(self.handle, int(doc_len), _i32p(ids), k.data_ptr(), v.data_ptr(),
                                  ks, vs, _stream_ptr(stream))
         check(st, "hr_doc_kv_write")
 
@@ -261,18 +264,18 @@ class KVPool:
         (float32, float16 for 16-bit pools, uint8 codes for fp8), plus K / V scales [L][n_pages][n_kv] for fp8."""
         import torch
         ids = _i32(page_ids)
-        L, n_kv, d = self.cfg.n_layers, self.cfg.n_kv_heads, self.cfg.head_dim
-        dt = {HR_F32: torch.float32, HR_BF16: torch.float16, HR_FP8_E4M3: torch.uint8}[self.cfg.kv_dtype]
-        k = torch.empty((L, int(doc_len), n_kv, d), dtype=dt, device=self.mem.device)
+        L, n_kv, d = self._dims
+        k = self.mem.new_empty((L, int(doc_len), n_kv, d), dtype=self._read_dtype)
         v = torch.empty_like(k)
-        ks = vs = None
-        if self.cfg.kv_dtype == HR_FP8_E4M3:
-            ks = torch.empty((L, len(ids), n_kv), dtype=torch.float32, device=self.mem.device)
+        if self.kv_fp8:
+            ks = self.mem.new_empty((L, len(ids), n_kv), dtype=torch.float32)
             vs = torch.empty_like(ks)
-        check(lib.hr_doc_kv_read(self.handle, int(doc_len), _i32p(ids), C.c_void_p(k.data_ptr()), C.c_void_p(v.data_ptr()),
-                                 C.c_void_p(ks.data_ptr()) if ks is not None else None,
-                                 C.c_void_p(vs.data_ptr()) if vs is not None else None, _stream_ptr(stream)), "hr_doc_kv_read")
-        return (k, v, ks, vs) if ks is not None else (k, v)
+            check(lib.hr_doc_kv_read(self.handle, int(doc_len), _i32p(ids), k.data_ptr(), v.data_ptr(), ks.data_ptr(), vs.data_ptr(),
+                                     _stream_ptr(stream)), "hr_doc_kv_read")
+            return k, v, ks, vs
+        check(lib.hr_doc_kv_read(self.handle, int(doc_len), _i32p(ids), k.data_ptr(), v.data_ptr(), None, None, _stream_ptr(stream)),
+              "hr_doc_kv_read")
+        return k, v
 
     def free(self, page_ids) -> None:
         ids = _i32(page_ids)
@@ -295,26 +298,26 @@ class KVPool:
         """4-bit records (16-bit pools): quantised as the pages leave."""
         ids = _i32(page_ids)
         assert records.numel() * records.element_size() >= len(ids) * self.page_record4_bytes
-        check(lib.hr_kv_pages_out4(self.handle, len(ids), _i32p(ids), C.c_void_p(records.data_ptr()), _stream_ptr(stream)),
+        check(lib.hr_kv_pages_out4(self.handle, len(ids), _i32p(ids), records.data_ptr(), _stream_ptr(stream)),
               "hr_kv_pages_out4")
 
     def pages_in4(self, page_ids, records, stream=None) -> None:
         ids = _i32(page_ids)
         assert records.numel() * records.element_size() >= len(ids) * self.page_record4_bytes
-        check(lib.hr_kv_pages_in4(self.handle, len(ids), _i32p(ids), C.c_void_p(records.data_ptr()), _stream_ptr(stream)),
+        check(lib.hr_kv_pages_in4(self.handle, len(ids), _i32p(ids), records.data_ptr(), _stream_ptr(stream)),
               "hr_kv_pages_in4")
 
     def pages_out(self, page_ids, records, stream=None) -> None:
         """records: uint8 tensor of len(page_ids) * page_record_bytes, on the device or in pinned host memory."""
         ids = _i32(page_ids)
         assert records.numel() * records.element_size() >= len(ids) * self.page_record_bytes
-        check(lib.hr_kv_pages_out(self.handle, len(ids), _i32p(ids), C.c_void_p(records.data_ptr()), _stream_ptr(stream)),
+        check(lib.hr_kv_pages_out(self.handle, len(ids), _i32p(ids), records.data_ptr(), _stream_ptr(stream)),
               "hr_kv_pages_out")
 
     def pages_in(self, page_ids, records, stream=None) -> None:
         ids = _i32(page_ids)
         assert records.numel() * records.element_size() >= len(ids) * self.page_record_bytes
-        check(lib.hr_kv_pages_in(self.handle, len(ids), _i32p(ids), C.c_void_p(records.data_ptr()), _stream_ptr(stream)),
+        check(lib.hr_kv_pages_in(self.handle, len(ids), _i32p(ids), records.data_ptr(), _stream_ptr(stream)),
               "hr_kv_pages_in")
 
     def alloc(self, n: int) -> np.ndarray:
@@ -353,7 +356,7 @@ class Plan:
         self.ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=model.device)
         out = C.c_void_p()
         check(lib.hr_rerank_plan_create(model.handle, pool.handle, self.n_pairs, _i32p(dl), _i32p(ql), self.pt_stride,
-                                        C.c_void_p(self.ws.data_ptr()), self.ws.numel(), C.byref(out)), "hr_rerank_plan_create")
+                                        self.ws.data_ptr(), self.ws.numel(), C.byref(out)), "hr_rerank_plan_create")
         self.handle = out
 
     def set_inputs(self, page_table, query_tokens) -> None:
@@ -361,7 +364,7 @@ class Plan:
         check(lib.hr_rerank_plan_set_inputs(self.handle, _i32p(pt), _i32p(qt)), "hr_rerank_plan_set_inputs")
 
     def run(self, out, stream=None):
-        check(lib.hr_rerank_plan_run(self.handle, C.c_void_p(out.data_ptr()), _stream_ptr(stream)), "hr_rerank_plan_run")
+        check(lib.hr_rerank_plan_run(self.handle, out.data_ptr(), _stream_ptr(stream)), "hr_rerank_plan_run")
         return out[:self.n_pairs]
 
     def close(self):
@@ -405,7 +408,7 @@ class Model:
             raise HrError(HR_ERR_INVALID_ARG, "hr_weights_pack_bytes")
         self.pack = torch.empty(nbytes, dtype=torch.uint8, device=device)
         out = C.c_void_p()
-        st = lib.hr_weights_load(C.byref(self.cfg), C.byref(ptrs), C.c_void_p(self.pack.data_ptr()), nbytes,
+        st = lib.hr_weights_load(C.byref(self.cfg), C.byref(ptrs), self.pack.data_ptr(), nbytes,
                                  _stream_ptr(), C.byref(out))
         check(st, "hr_weights_load")
         self.handle = out
@@ -460,7 +463,7 @@ class Model:
         ws = self._workspace(max(nbytes, 256))
         scores = out if out is not None else torch.empty(max(P, 1), dtype=torch.float32, device=self.device)
         st = lib.hr_rerank_score(self.handle, pool.handle, P, _i32p(pt), stride, _i32p(dl), _i32p(qt), _i32p(ql),
-                                 C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(scores.data_ptr()), _stream_ptr(stream))
+                                 ws.data_ptr(), ws.numel(), scores.data_ptr(), _stream_ptr(stream))
         check(st, "hr_rerank_score")
         return scores[:P]
 
@@ -474,7 +477,7 @@ class Model:
         P = len(dl)
         stride = pt.shape[1] if pt.ndim == 2 else 0
         st = lib.hr_rerank_score_static(self.handle, pool.handle, P, _i32p(pt), stride, _i32p(dl), _i32p(qt), _i32p(ql),
-                                        C.c_void_p(out.data_ptr()), _stream_ptr(stream))
+                                        out.data_ptr(), _stream_ptr(stream))
         check(st, "hr_rerank_score_static")
         return out[:P]
 
@@ -502,7 +505,7 @@ class Model:
         ws = self._workspace(max(nbytes, 256))
         scores = out if out is not None else torch.empty(max(P, 1), dtype=torch.float32, device=self.device)
         st = lib.hr_rerank_score_full(self.handle, P, _i32p(dt), _i32p(dl), _i32p(qt), _i32p(ql),
-                                      C.c_void_p(ws.data_ptr()), ws.numel(), C.c_void_p(scores.data_ptr()), _stream_ptr(stream))
+                                      ws.data_ptr(), ws.numel(), scores.data_ptr(), _stream_ptr(stream))
         check(st, "hr_rerank_score_full")
         return scores[:P]
 
@@ -520,7 +523,7 @@ class Model:
             raise HrError(HR_ERR_UNSUPPORTED_SHAPE, "hr_doc_prefill_workspace_bytes")
         ws = self._workspace(nbytes)
         st = lib.hr_doc_prefill(self.handle, pool.handle, n, _i32p(toks), _i32p(dl), _i32p(pt), stride,
-                                C.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr(stream))
+                                ws.data_ptr(), ws.numel(), _stream_ptr(stream))
         check(st, "hr_doc_prefill")
 
     def close(self):

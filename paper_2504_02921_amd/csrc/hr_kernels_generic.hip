@@ -353,13 +353,43 @@ __global__ void __launch_bounds__(256) score_head_kernel(const float* __restrict
 // ------------------------------------------------------------------------------------------------
 struct PageIdChunk { int32_t ids[256]; };   // page ids travel as kernel arguments: no device staging
 
-// pool write: logical [L][D][n_kv][d] -> pages in the private arrangement (see hr_layout.h), tail zeroed
-// grid: (n_pages, n_layers * n_kv); 256 threads
+// Pool write and read-back: logical [L][D][n_kv][d] <-> pages in the private arrangement (see hr_layout.h).  One workgroup
+// per (page, layer, 128 of the n_kv * d columns): every thread moves one word of eight elements of K and one of V.  K rows
+// stay rows, so the word is only placed elsewhere; V is turned through LDS (a page holds eight keys of a channel side by
+// side).  One document is one launch, and a short one: with one element per load and store the write of a 544-token
+// document (24 layers, 128 columns, 13 MB) took 9.5 us, the read 8 us.
+// grid: (n_pages, n_layers * slabs); 256 threads
 // ------------------------------------------------------------------------------------------------
-template <typename SRC, typename DST> __device__ __forceinline__ DST kv_convert(SRC v) { return (DST)v; }
-// 16-bit pools: the caller's bf16 values are stored as half (exact for |x| in [2^-14, 65504]; smaller
-// magnitudes keep an absolute error below 2^-25, larger ones become infinity; both are counted)
-template <> __device__ __forceinline__ half_t kv_convert<bf16_t, half_t>(bf16_t v) { return from_float<half_t>((float)v); }
+constexpr int kSlab = 128, kSlabLd = kSlab + 8;
+template <typename T> using Word8 = T __attribute__((ext_vector_type(8)));
+// 16-bit pools: the caller's bf16 values are stored as half (exact for |x| in [2^-14, 65504]; smaller magnitudes keep an
+// absolute error below 2^-25, larger ones become infinity; both are counted).  Where all eight values are zero or in that
+// range, which is the ordinary case, the conversion is exact in any rounding mode and nothing has to be counted.
+__device__ __forceinline__ void convert_half8(const Word8<bf16_t>& src, Word8<half_t>& dst, int& over, int& under, int& nonfinite) {
+    typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+    const u32x4 w = __builtin_bit_cast(u32x4, src);
+    bool odd = false;
+    float f[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned lo = w[i] & 0x7FFFu, hi = (w[i] >> 16) & 0x7FFFu;
+        odd |= (lo - 0x3880u > 0x477Fu - 0x3880u && lo != 0u) || (hi - 0x3880u > 0x477Fu - 0x3880u && hi != 0u);      // bf16 2^-14 .. 65280
+        f[2 * i] = __uint_as_float(w[i] << 16);
+        f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+    }
+    if (odd) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            dst[e] = from_float<half_t>(f[e]);
+            count_half_range(f[e], over, under, nonfinite);
+        }
+    } else {
+        u32x4 out;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(f[2 * i], f[2 * i + 1]));
+        dst = __builtin_bit_cast(Word8<half_t>, out);
+    }
+}
 
 __device__ __forceinline__ void flush_range_counts(long long* counters, int over, int under, int nonfinite, int nan_code, int bad_scale) {
     if (!counters) return;
@@ -375,43 +405,64 @@ __global__ void __launch_bounds__(256) kv_scatter_kernel(KVT* __restrict__ pool,
                                                          PageIdChunk page_ids, int pg0, int doc_len, int n_pages,
                                                          const KVS* __restrict__ k, const KVS* __restrict__ v,
                                                          const float* __restrict__ ks, const float* __restrict__ vs,
-                                                         int num_pages, int n_kv, int d, long long* __restrict__ counters) {
-    int pg = pg0 + blockIdx.x;
-    int layer = blockIdx.y / n_kv, h = blockIdx.y % n_kv;
-    int page = page_ids.ids[blockIdx.x];
-    size_t blk = (size_t)kPageTokens * d;
-    size_t bi = (((size_t)layer * num_pages + page) * n_kv + h) * 2;
-    KVT* kb = pool + bi * blk;
-    KVT* vb = kb + blk;
+                                                         int num_pages, int n_kv, int d, int slabs, long long* __restrict__ counters) {
+    __shared__ Word8<KVT> turn[kPageTokens * kSlabLd / 8];
+    const int pg = pg0 + blockIdx.x, page = page_ids.ids[blockIdx.x];
+    const int layer = blockIdx.y / slabs, slab = blockIdx.y - layer * slabs;
+    const int cols = n_kv * d, blk = kPageTokens * d, tid = threadIdx.x;
+    KVT* dst = pool + ((size_t)layer * num_pages + page) * n_kv * 2 * blk;
     int over = 0, under = 0, nonfinite = 0, nan_code = 0, bad_scale = 0;
-    for (int e = threadIdx.x; e < (int)blk; e += 256) {
-        int tk = e / d, c = e - tk * d;
-        int tok = pg * kPageTokens + tk;
-        KVT kvl = KVT(0.0f), vvl = KVT(0.0f);
-        if (tok < doc_len) {
-            size_t src = (((size_t)layer * doc_len + tok) * n_kv + h) * d + c;
-            kvl = kv_convert<KVS, KVT>(k[src]);
-            vvl = kv_convert<KVS, KVT>(v[src]);
-            if constexpr (sizeof(KVT) == 2) {
-                count_half_range((float)k[src], over, under, nonfinite);
-                count_half_range((float)v[src], over, under, nonfinite);
-            } else if constexpr (sizeof(KVT) == 1) {          // E4M3 has two NaN codes and no infinity
-                nan_code += ((unsigned)k[src] & 0x7Fu) == 0x7Fu;
-                nan_code += ((unsigned)v[src] & 0x7Fu) == 0x7Fu;
+    {
+        const int t = tid >> 4, col = slab * kSlab + (tid & 15) * 8, tok = pg * kPageTokens + t;
+        Word8<KVT> kw, vw;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) kw[e] = vw[e] = KVT(0.0f);
+        if (col < cols) {
+            if (tok < doc_len) {
+                const size_t src = ((size_t)layer * doc_len + tok) * cols + col;
+                const Word8<KVS> ks8 = *(const Word8<KVS>*)(k + src), vs8 = *(const Word8<KVS>*)(v + src);
+                if constexpr (sizeof(KVT) == 2) {
+                    convert_half8(ks8, kw, over, under, nonfinite);
+                    convert_half8(vs8, vw, over, under, nonfinite);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        kw[e] = ks8[e];
+                        vw[e] = vs8[e];
+                        if constexpr (sizeof(KVT) == 1) {             // E4M3 has two NaN codes and no infinity
+                            nan_code += ((unsigned)ks8[e] & 0x7Fu) == 0x7Fu;
+                            nan_code += ((unsigned)vs8[e] & 0x7Fu) == 0x7Fu;
+                        }
+                    }
+                }
             }
+            const int h = col / d, c = col - h * d;
+            *(Word8<KVT>*)(dst + (size_t)h * 2 * blk + k_elem(t, c, d, (int)sizeof(KVT))) = kw;
         }
-        kb[k_elem(tk, c, d, (int)sizeof(KVT))] = kvl;
-        vb[v_elem(tk, c, d)] = vvl;
+        turn[t * (kSlabLd / 8) + (tid & 15)] = vw;
     }
-    if (scales && threadIdx.x == 0) {
-        size_t si = ((size_t)layer * n_pages + pg) * n_kv + h;
-        const float sk = ks[si], sv = vs[si];
-        scales[bi] = sk;
-        scales[bi + 1] = sv;
-        // a scale must be positive and finite; the V scale's power of two is applied while the codes are expanded to
-        // half, which covers 2^-22 <= scale < 2^8
-        bad_scale += !(sk > 0.0f && sk <= 3.0e38f);
-        bad_scale += !(sv >= 2.384185791015625e-07f && sv < 256.0f);
+    __syncthreads();
+    {
+        const int tg = tid >> 7, cl = tid & 127, col = slab * kSlab + cl;      // keys 4 tg .. + 3 and 8 + 4 tg .. + 3 of a channel
+        if (col < cols) {
+            Word8<KVT> w;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) w[e] = ((const KVT*)turn)[(4 * tg + (e & 3) + ((e & 4) << 1)) * kSlabLd + cl];
+            const int h = col / d, c = col - h * d;
+            *(Word8<KVT>*)(dst + (size_t)h * 2 * blk + blk + v_elem(4 * tg, c, d)) = w;
+        }
+    }
+    if (scales && slab == 0) {
+        for (int h = tid; h < n_kv; h += 256) {
+            const size_t si = ((size_t)layer * n_pages + pg) * n_kv + h, bi = (((size_t)layer * num_pages + page) * n_kv + h) * 2;
+            const float sk = ks[si], sv = vs[si];
+            scales[bi] = sk;
+            scales[bi + 1] = sv;
+            // a scale must be positive and finite; the V scale's power of two is applied while the codes are expanded to
+            // half, which covers 2^-22 <= scale < 2^8
+            bad_scale += !(sk > 0.0f && sk <= 3.0e38f);
+            bad_scale += !(sv >= 2.384185791015625e-07f && sv < 256.0f);
+        }
     }
     flush_range_counts(counters, over, under, nonfinite, nan_code, bad_scale);
 }
@@ -490,31 +541,44 @@ __global__ void __launch_bounds__(256) pages_to_pool_fp8_kernel(const half_t* __
     }
 }
 
-// pool read-back: pages in the private arrangement -> logical [L][D][n_kv][d] in the pool's own element type
-// grid: (n_pages, n_layers * n_kv); 256 threads
 template <typename KVT>
 __global__ void __launch_bounds__(256) kv_gather_kernel(const KVT* __restrict__ pool, const float* __restrict__ scales, PageIdChunk page_ids,
                                                         int pg0, int doc_len, int n_pages, KVT* __restrict__ k, KVT* __restrict__ v,
-                                                        float* __restrict__ ks, float* __restrict__ vs, int num_pages, int n_kv, int d) {
-    const int pg = pg0 + blockIdx.x;
-    const int layer = blockIdx.y / n_kv, h = blockIdx.y % n_kv;
-    const int page = page_ids.ids[blockIdx.x];
-    const size_t blk = (size_t)kPageTokens * d;
-    const size_t bi = (((size_t)layer * num_pages + page) * n_kv + h) * 2;
-    const KVT* kb = pool + bi * blk;
-    const KVT* vb = kb + blk;
-    for (int e = threadIdx.x; e < (int)blk; e += 256) {
-        const int tk = e / d, c = e - tk * d;
-        const int tok = pg * kPageTokens + tk;
-        if (tok >= doc_len) continue;
-        const size_t o = (((size_t)layer * doc_len + tok) * n_kv + h) * d + c;
-        k[o] = kb[k_elem(tk, c, d, (int)sizeof(KVT))];
-        v[o] = vb[v_elem(tk, c, d)];
+                                                        float* __restrict__ ks, float* __restrict__ vs, int num_pages, int n_kv, int d,
+                                                        int slabs) {
+    __shared__ Word8<KVT> turn[kPageTokens * kSlabLd / 8];
+    const int pg = pg0 + blockIdx.x, page = page_ids.ids[blockIdx.x];
+    const int layer = blockIdx.y / slabs, slab = blockIdx.y - layer * slabs;
+    const int cols = n_kv * d, blk = kPageTokens * d, tid = threadIdx.x;
+    const KVT* src = pool + ((size_t)layer * num_pages + page) * n_kv * 2 * blk;
+    const int t = tid >> 4, col = slab * kSlab + (tid & 15) * 8, tok = pg * kPageTokens + t;
+    const bool mine = col < cols && tok < doc_len;
+    Word8<KVT> kw;
+    if (mine) {
+        const int h = col / d, c = col - h * d;
+        kw = *(const Word8<KVT>*)(src + (size_t)h * 2 * blk + k_elem(t, c, d, (int)sizeof(KVT)));
     }
-    if (scales && threadIdx.x == 0) {
-        const size_t si = ((size_t)layer * n_pages + pg) * n_kv + h;
-        ks[si] = scales[bi];
-        vs[si] = scales[bi + 1];
+    {
+        const int tg = tid >> 7, cl = tid & 127, vcol = slab * kSlab + cl;
+        if (vcol < cols) {
+            const int h = vcol / d, c = vcol - h * d;
+            const Word8<KVT> w = *(const Word8<KVT>*)(src + (size_t)h * 2 * blk + blk + v_elem(4 * tg, c, d));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ((KVT*)turn)[(4 * tg + (e & 3) + ((e & 4) << 1)) * kSlabLd + cl] = w[e];
+        }
+    }
+    __syncthreads();
+    if (mine) {
+        const size_t o = ((size_t)layer * doc_len + tok) * cols + col;
+        *(Word8<KVT>*)(k + o) = kw;
+        *(Word8<KVT>*)(v + o) = turn[t * (kSlabLd / 8) + (tid & 15)];
+    }
+    if (scales && slab == 0) {
+        for (int h = tid; h < n_kv; h += 256) {
+            const size_t si = ((size_t)layer * n_pages + pg) * n_kv + h, bi = (((size_t)layer * num_pages + page) * n_kv + h) * 2;
+            ks[si] = scales[bi];
+            vs[si] = scales[bi + 1];
+        }
     }
 }
 
@@ -537,16 +601,17 @@ hipError_t launch_kv_gather(const PoolLayout& lay, const char* pool_base, const 
         const int n = n_pages - pg0 < 256 ? n_pages - pg0 : 256;
         PageIdChunk ids;
         for (int i = 0; i < 256; ++i) ids.ids[i] = i < n ? page_ids_host[pg0 + i] : 0;
-        const dim3 grid((unsigned)n, (unsigned)(lay.n_layers * lay.n_kv));
+        const int slabs = (lay.n_kv * lay.d + kSlab - 1) / kSlab;
+        const dim3 grid((unsigned)n, (unsigned)(lay.n_layers * slabs));
         if (lay.kv_dtype == HR_F32)
             kv_gather_kernel<float><<<grid, 256, 0, st>>>((const float*)pool_base, nullptr, ids, pg0, doc_len, n_pages, (float*)k, (float*)v,
-                                                          nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d);
+                                                          nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d, slabs);
         else if (lay.kv_dtype == HR_BF16)
             kv_gather_kernel<half_t><<<grid, 256, 0, st>>>((const half_t*)pool_base, nullptr, ids, pg0, doc_len, n_pages, (half_t*)k,
-                                                           (half_t*)v, nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d);
+                                                           (half_t*)v, nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d, slabs);
         else
             kv_gather_kernel<uint8_t><<<grid, 256, 0, st>>>((const uint8_t*)pool_base, scales, ids, pg0, doc_len, n_pages, (uint8_t*)k,
-                                                            (uint8_t*)v, ks, vs, lay.num_pages, lay.n_kv, lay.d);
+                                                            (uint8_t*)v, ks, vs, lay.num_pages, lay.n_kv, lay.d, slabs);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -729,19 +794,20 @@ hipError_t launch_kv_scatter(const PoolLayout& lay, char* pool_base, const int32
         int n = n_pages - pg0 < 256 ? n_pages - pg0 : 256;
         PageIdChunk ids;
         for (int i = 0; i < 256; ++i) ids.ids[i] = i < n ? page_ids_host[pg0 + i] : 0;
-        dim3 grid((unsigned)n, (unsigned)(lay.n_layers * lay.n_kv));
+        const int slabs = (lay.n_kv * lay.d + kSlab - 1) / kSlab;
+        const dim3 grid((unsigned)n, (unsigned)(lay.n_layers * slabs));
         if (lay.kv_dtype == HR_F32)
             kv_scatter_kernel<float, float><<<grid, 256, 0, st>>>((float*)pool_base, nullptr, ids, pg0, doc_len, n_pages,
                                                            (const float*)k, (const float*)v, nullptr, nullptr, lay.num_pages,
-                                                           lay.n_kv, lay.d, counters);
+                                                           lay.n_kv, lay.d, slabs, counters);
         else if (lay.kv_dtype == HR_BF16)
             kv_scatter_kernel<half_t, bf16_t><<<grid, 256, 0, st>>>((half_t*)pool_base, nullptr, ids, pg0, doc_len, n_pages,
                                                               (const bf16_t*)k, (const bf16_t*)v, nullptr, nullptr,
-                                                              lay.num_pages, lay.n_kv, lay.d, counters);
+                                                              lay.num_pages, lay.n_kv, lay.d, slabs, counters);
         else
             kv_scatter_kernel<uint8_t, uint8_t><<<grid, 256, 0, st>>>((uint8_t*)pool_base, scales, ids, pg0, doc_len, n_pages,
                                                              (const uint8_t*)k, (const uint8_t*)v, ks, vs, lay.num_pages,
-                                                             lay.n_kv, lay.d, counters);
+                                                             lay.n_kv, lay.d, slabs, counters);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -752,7 +818,7 @@ hipError_t launch_pack_rows(int dtype, const void* src, void* dst, int rows, int
                             long long* counters, hipStream_t st) {
     if (dtype == HR_F32)
         pack_rows_kernel<float, float><<<dim3((unsigned)rows), 256, 0, st>>>((const float*)src, (float*)dst, rows, cols, ib, mul, sel, counters);
-    else   // the caller's bf16 weights become half operands (same rule as kv_convert)
+    else   // the caller's bf16 weights become half operands (same rule as the pool write)
         pack_rows_kernel<bf16_t, half_t><<<dim3((unsigned)rows), 256, 0, st>>>((const bf16_t*)src, (half_t*)dst, rows, cols, ib,
                                                                               mul, sel, counters);
     return hipGetLastError();
