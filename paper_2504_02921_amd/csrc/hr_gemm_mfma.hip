@@ -20,6 +20,7 @@
 // measured the same).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <type_traits>
@@ -33,7 +34,7 @@ namespace hr {
 
 typedef __attribute__((ext_vector_type(8))) _Float16 halfx8;
 typedef __attribute__((ext_vector_type(4))) _Float16 halfx4;
-typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(4))) unsigned uint4v;
 
 namespace {
@@ -62,6 +63,31 @@ __device__ __forceinline__ TileCoord map_tile(int pid, int tiles_m, int tiles_n)
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
 
+// Tile loader.  The rows of a tile lie K halves apart in memory, so a lane's offset inside a pass is one 32-bit vector offset
+// for all passes and k-tiles, and the rest a scalar: buffer loads straight to LDS take exactly that (no vector registers or
+// additions per pass).  Rows past the end of the matrix fail the descriptor's range check; a pass without any row left
+// starts at row 0 instead (its rows feed outputs that are not stored), so a scalar offset never exceeds the range.
+template <int PASSES, int RPP>
+struct TileSrc {
+    int pass[PASSES];               // byte offset of each pass's first row
+#ifdef __HIP_DEVICE_COMPILE__       // the host pass does not know the descriptor type
+    __amdgpu_buffer_rsrc_t rsrc;
+#endif
+    __device__ __forceinline__ void set(const half_t* base, int rows, int ld) {
+#ifdef __HIP_DEVICE_COMPILE__
+        rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, rows * ld * 2, 0x00020000);
+#endif
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) pass[p] = p * RPP < rows ? p * RPP * ld * 2 : 0;
+    }
+    __device__ __forceinline__ void load(int p, half_t* lds, int voff, int koff) const {
+#ifdef __HIP_DEVICE_COMPILE__
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 16, voff, pass[p] + koff, 0, 0);
+#endif
+    }
+};
+constexpr int kNoLoad = 0x7FF00000;      // a vector offset past every range: nothing is fetched
+
 // A thread's 16-byte chunks of the tile's part of x, for tiles whose fp32 form fits the two stages (one slab below).
 template <int BN, int NT, int CHUNKS>
 __device__ __forceinline__ void x_prefetch(float4 (&xv)[CHUNKS], const GemmArgs& a, int64_t tile_m0, int tile_n0) {
@@ -75,24 +101,24 @@ __device__ __forceinline__ void x_prefetch(float4 (&xv)[CHUNKS], const GemmArgs&
     }
 }
 
-// Epilogues on transposed accumulators: a lane owns output row (lane & 31) of each 32 x 32 block, register r holds
-// column 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3).  `smem` is the kernel's LDS (two stages of A, then two of W), free
+// Epilogues on transposed accumulators: a lane owns output row (lane & 15) of each 16 x 16 block and columns
+// 4 * (lane >> 4) + {0..3}.  `smem` is the kernel's LDS (SA stages of A, then of W), free
 // behind the main loop's last barrier except that, in a persistent launch, stage 0 may be receiving the next tile.  x_pre: what
 // x_prefetch read (nullptr: x is read here).
-template <int EPI, int BM, int BN, int WM, int WN, int HB>
-__device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN / WN / 32], const GemmArgs& a, char* smem,
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
+__device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / WN / 16], const GemmArgs& a, char* smem,
                                               int64_t tile_m0, int tile_n0, const float4* x_pre = nullptr) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
-    constexpr int MI = TM / 32, NI = TN / 32;
+    constexpr int MI = TM / 16, NI = TN / 16;
     half_t* sA = (half_t*)smem;
-    half_t* sB = sA + 2 * BM * BK;
+    half_t* sB = sA + SA * BM * BK;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int frow = lane & 31, fh = lane >> 5;
+    const int frow = lane & 15, fq = lane >> 4;
     const int64_t row_base = tile_m0 + wm * TM + frow;
-    const int col_base = tile_n0 + wn * TN + 4 * fh;
+    const int col_base = tile_n0 + wn * TN + 4 * fq;
     (void)sA; (void)sB; (void)row_base; (void)col_base; (void)NT; (void)MI; (void)NI;
     if constexpr (EPI == EPI_RESID_ADD) {
         // x += C through LDS.  In the accumulator layout a lane holds 16 bytes of one row, so a direct update touches
@@ -153,22 +179,15 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
             }
             if (p > 0) __syncthreads();                 // the previous slab has been read
             if ((wn * TN) / CW == p) {
-                const int c_off = wn * TN - p * CW + 4 * fh;
+                const int c_off = wn * TN - p * CW + 4 * fq;
 #pragma unroll
                 for (int i = 0; i < MI; ++i) {
-                    const int lr = wm * TM + i * 32 + frow;
+                    const int lr = wm * TM + i * 16 + frow;
 #pragma unroll
-                    for (int j = 0; j < NI; ++j)
-#pragma unroll
-                        for (int r4 = 0; r4 < 4; ++r4) {
-                            const int ch = (c_off + j * 32 + 8 * r4) >> 2;
-                            float4 v;
-                            v.x = acc[i][j][r4 * 4 + 0];
-                            v.y = acc[i][j][r4 * 4 + 1];
-                            v.z = acc[i][j][r4 * 4 + 2];
-                            v.w = acc[i][j][r4 * 4 + 3];
-                            *(float4*)(stage + lr * CW + ((ch ^ (lr & 15)) << 2)) = v;
-                        }
+                    for (int j = 0; j < NI; ++j) {
+                        const int ch = (c_off + j * 16) >> 2;
+                        *(floatx4*)(stage + lr * CW + ((ch ^ (lr & 15)) << 2)) = acc[i][j];
+                    }
                 }
             }
             __syncthreads();
@@ -185,7 +204,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
             }
         }
     } else if constexpr (EPI == EPI_SWIGLU) {
-        static_assert(EPI != EPI_SWIGLU || NI % 2 == 0, "gate/up block pairs");
+        static_assert(EPI != EPI_SWIGLU || NI % 4 == 0, "gate/up block pairs");
         // m = silu(g) * u goes through LDS as a half [BM][BN / 2] tile (16-byte chunks XOR-swizzled by the row) and
         // leaves in whole row segments, like the residual update above.
         constexpr int OW = BN / 2;                      // output columns of the tile
@@ -213,22 +232,22 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
             if (part) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the hi tile has been read out of the stage
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
-                const int lr = wm * TM + i * 32 + frow;
+                const int lr = wm * TM + i * 16 + frow;
 #pragma unroll
-                for (int j = 0; j < NI; j += 2)
+                for (int j = 0; j < NI; j += 4)                 // 32 gate columns, then the 32 up columns that belong to them
 #pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        const int ch = ((wn * TN) / 2 + (j / 2) * 32) / 8 + r4;
+                    for (int b = 0; b < 2; ++b) {
+                        const int ch = ((wn * TN) / 2 + j * 8 + b * 16) / 8 + (fq >> 1);
                         halfx4 w;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const float g = acc[i][j][r4 * 4 + e], u = acc[i][j + 1][r4 * 4 + e];
+                            const float g = acc[i][j + b][e], u = acc[i][j + 2 + b][e];
                             const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
                             const float v = g * sg * u;
                             const half_t hi = from_float<half_t>(v);
                             w[e] = part ? from_float<half_t>(v - (float)hi) : hi;
                         }
-                        *(halfx4*)(stage_row(lr) + ((ch ^ swz(lr)) << 3) + 4 * fh) = w;
+                        *(halfx4*)(stage_row(lr) + ((ch ^ swz(lr)) << 3) + 4 * (fq & 1)) = w;
                     }
             }
             // LDS-only barrier: __syncthreads() would also wait for the next tile's loads, which were just requested
@@ -244,8 +263,8 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
             }
         }
     } else {   // EPI_QKV_ROPE
-        constexpr int hb = HB;                                  // 32-wide blocks per half head: head_dim = 64 * HB
-        static_assert(EPI != EPI_QKV_ROPE || NI % (2 * HB) == 0, "a wave must hold whole heads");
+        constexpr int hb = 2 * HB;                              // 16-wide blocks per half head: head_dim = 64 * HB
+        static_assert(EPI != EPI_QKV_ROPE || NI % (2 * hb) == 0, "a wave must hold whole heads");
         constexpr int d = 64 * HB, half = d / 2;
         const int nq = a.n_q * d, nkv = a.n_kv * d;
         // The (cos, sin) rows of this tile's tokens go to LDS first (the stages are free: nobody reads them behind
@@ -270,15 +289,15 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
         int slot_i[MI];
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            const int64_t row = row_base + i * 32;
+            const int64_t row = row_base + i * 16;
             slot_i[i] = (a.kv_pages && row < a.M) ? a.new_slot[row] : 0;
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
         // q and K quads are kept (rotated and rounded) until the table is no longer needed, then staged in LDS as a
-        // half [BM][BN] tile and stored in whole row segments; V quads go straight to their pages: a lane's 32 tokens
-        // fall into two pages, where each channel's keys are adjacent, which is as coalesced as V gets.
-        halfx4 res[MI][NI][4];
+        // half [BM][BN] tile and stored in whole row segments; V quads go straight to their pages: a wave's 16 tokens
+        // fall into one or two pages, where each channel's keys are adjacent, which is as coalesced as V gets.
+        halfx4 res[MI][NI];
         auto store_v_quad = [&](int i, int64_t row, int col, halfx4 w) {
             const int c_all = col - nq - nkv;
             if (!a.kv_pages) {
@@ -295,39 +314,37 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
         };
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            const int64_t row = row_base + i * 32;
+            const int64_t row = row_base + i * 16;
             const bool row_ok = row < a.M;
-            const int lrow = wm * TM + i * 32 + frow;              // row inside the tile
+            const int lrow = wm * TM + i * 16 + frow;              // row inside the tile
             const char* trow = smem + (size_t)lrow * (CPR * 16);
 #pragma unroll
-            for (int hbi = 0; hbi < hb; ++hbi)
+            for (int hbi = 0; hbi < hb; ++hbi) {
+                // rotary indices hbi * 16 + 4 * fq + {0..3}: two chunks of two (cos, sin) pairs
+                const int c0 = hbi * 8 + 2 * fq;
+                const float4 cs01 = *(const float4*)(trow + ((c0 ^ (lrow & 15)) << 4));
+                const float4 cs23 = *(const float4*)(trow + (((c0 + 1) ^ (lrow & 15)) << 4));
+                const float cs_c[4] = {cs01.x, cs01.z, cs23.x, cs23.z}, cs_s[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    // rotary indices hbi * 32 + 8 * r4 + 4 * fh + {0..3}: two chunks of two (cos, sin) pairs
-                    const int c0 = hbi * 16 + 4 * r4 + 2 * fh;
-                    const float4 cs01 = *(const float4*)(trow + ((c0 ^ (lrow & 15)) << 4));
-                    const float4 cs23 = *(const float4*)(trow + (((c0 + 1) ^ (lrow & 15)) << 4));
-                    const float cs_c[4] = {cs01.x, cs01.z, cs23.x, cs23.z}, cs_s[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
+                for (int hd = 0; hd < NI / (2 * hb); ++hd) {
+                    const int jl = hd * 2 * hb + hbi, jh = jl + hb;       // low / high half of the head: same lane, same register
+                    const int col_l = col_base + jl * 16, col_h = col_base + jh * 16;
+                    const bool rot = col_l < nq + nkv;                      // q and k rotate, v does not
+                    halfx4 wl, wh;
 #pragma unroll
-                    for (int hd = 0; hd < NI / (2 * hb); ++hd) {
-                        const int jl = hd * 2 * hb + hbi, jh = jl + hb;       // low / high half of the head: same lane, same register
-                        const int col_l = col_base + jl * 32 + 8 * r4, col_h = col_base + jh * 32 + 8 * r4;
-                        const bool rot = col_l < nq + nkv;                      // q and k rotate, v does not
-                        halfx4 wl, wh;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float lo = acc[i][jl][r4 * 4 + e], hi = acc[i][jh][r4 * 4 + e];
-                            wl[e] = from_float<half_t>(rot ? rope_lo(lo, hi, cs_c[e], cs_s[e]) : lo);
-                            wh[e] = from_float<half_t>(rot ? rope_hi(lo, hi, cs_c[e], cs_s[e]) : hi);
-                        }
-                        res[i][jl][r4] = wl;
-                        res[i][jh][r4] = wh;
-                        if (!rot && row_ok && col_l < a.N) {                  // N is a multiple of the head size
-                            store_v_quad(i, row, col_l, wl);
-                            store_v_quad(i, row, col_h, wh);
-                        }
+                    for (int e = 0; e < 4; ++e) {
+                        const float lo = acc[i][jl][e], hi = acc[i][jh][e];
+                        wl[e] = from_float<half_t>(rot ? rope_lo(lo, hi, cs_c[e], cs_s[e]) : lo);
+                        wh[e] = from_float<half_t>(rot ? rope_hi(lo, hi, cs_c[e], cs_s[e]) : hi);
+                    }
+                    res[i][jl] = wl;
+                    res[i][jh] = wh;
+                    if (!rot && row_ok && col_l < a.N) {                  // N is a multiple of the head size
+                        store_v_quad(i, row, col_l, wl);
+                        store_v_quad(i, row, col_h, wh);
                     }
                 }
+            }
         }
         __syncthreads();                                            // every lane is done with the table
         constexpr int CPT = BN / 8;                                 // 16-byte chunks per tile row (8, 16 or 32)
@@ -336,14 +353,12 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
         half_t* stage = (half_t*)smem;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            const int lr = wm * TM + i * 32 + frow;
+            const int lr = wm * TM + i * 16 + frow;
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const int ch = (wn * TN + j * 32) / 8 + r4;
-                    *(halfx4*)(stage + lr * BN + ((ch ^ swz(lr)) << 3) + 4 * fh) = res[i][j][r4];
-                }
+            for (int j = 0; j < NI; ++j) {
+                const int ch = (wn * TN + j * 16) / 8 + (fq >> 1);
+                *(halfx4*)(stage + lr * BN + ((ch ^ swz(lr)) << 3) + 4 * (fq & 1)) = res[i][j];
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -368,28 +383,34 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[BM / WM / 32][BN /
     }
 }
 
-// BM x BN x 64 macro tile, WM x WN wavefronts, each wave (BM/WM) x (BN/WN) = MI x NI blocks of 32 x 32.
+// BM x BN x 64 macro tile, WM x WN wavefronts, each wave (BM/WM) x (BN/WN) = MI x NI blocks of 16 x 16.
 //
-// Data path: global_load_lds_dwordx4 (HBM/L2 -> LDS without passing through VGPRs; lane l of a wave
-// writes LDS bytes [base + 16 l, base + 16 l + 16)), two LDS stages.  The loads of k-tile kt + 1 are
-// issued at the top of iteration kt and waited for just before the last k-step of the iteration,
-// where the only workgroup barrier of the iteration sits; the fragments of the next k-step are read
-// one step ahead and the scheduler is pinned to alternate one ds_read with one MFMA.
-// Accumulation is transposed (D = W_frag * A_frag^T): a lane owns ONE output row (lane & 31) and
-// 4 consecutive columns per register quad, so the epilogues address one row pointer per block and
-// store 8 / 16 bytes at a time.
-template <int EPI, int BM, int BN, int WM, int WN, int HB>
-__global__ void __launch_bounds__(WM * WN * 64) gemm_mfma_kernel(GemmArgs a) {
+// What bounds it at large M is power: with operands of full mantissas the chip holds 1.65-1.85 GHz under this kernel (2.2
+// with zeros), and every variant of the schedule that spends the same energy per product ends at the same rate.  A
+// register-only loop reaches 1.94 PFLOP/s with v_mfma_f32_16x16x32_f16 and 1.71 with v_mfma_f32_32x32x16_f16 (twice the
+// accumulator traffic per product), 1.57 / 1.43 with the fragments read from LDS as here: hence the 16 x 16 x 32 form.
+//
+// Data path: global_load_lds_dwordx4 (HBM/L2 -> LDS without passing through VGPRs; lane l of a wave writes LDS bytes
+// [base + 16 l, base + 16 l + 16)); SA stages of A and two of W.  A k-tile is two k-steps of 32.  A fragment of A is
+// replaced by the next k-step's right behind its last MFMA, W fragments are double buffered; the k-tile's one barrier sits a
+// quarter into its second k-step, when every fragment of the k-tile has been read.  Behind it the W loads of k-tile
+// kt + 2 go out (their stage is free), the A loads of kt + 2 with a third stage a k-step later (a whole k-tile ahead of
+// their barrier, which does not wait for them), with two stages together with W.  Requests and reads are spread over the
+// MFMAs (a wave issues in order, and the CU takes 60 bytes per cycle).
+// Accumulation is transposed (D = W_frag * A_frag^T): a lane owns ONE output row (lane & 15) and 4 consecutive columns
+// per block, so the epilogues address one row pointer per block and store 8 / 16 bytes at a time.
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
+__global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) gemm_mfma_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;      // wave tile
-    constexpr int MI = TM / 32, NI = TN / 32;
+    constexpr int MI = TM / 16, NI = TN / 16;
     constexpr int RPP = NT / 8;                     // rows per loader pass (8 lanes cover one 128-byte k row)
     constexpr int PA = BM / RPP, PB = BN / RPP;
-    constexpr int KS = BK / 16;
     static_assert(RPP % 16 == 0 && BM % RPP == 0 && BN % RPP == 0, "loader shape");
+    static_assert(BK == 64 && (SA == 2 || SA == 3), "two k-steps per k-tile");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    half_t* sA = (half_t*)smem;                         // [2][BM][BK]
-    half_t* sB = sA + 2 * BM * BK;                      // [2][BN][BK]
+    half_t* sA = (half_t*)smem;                         // [SA][BM][BK]
+    half_t* sB = sA + SA * BM * BK;                     // [2][BN][BK]
 
     // The gate/up launch is persistent: a workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ... (the same
     // XCD-chunked order) and requests the first k-tile of its next tile before it starts the epilogue of the current
@@ -407,107 +428,145 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_mfma_kernel(GemmArgs a) {
     const int wm = wave / WN, wn = wave % WN;
     const int K = a.K;
     const int Kw = a.Kw > 0 ? a.Kw : K;         // columns of W: K, or K / 2 when A carries [hi | lo] halves of a split operand
-    const int nkw = Kw / BK;
-    const half_t* A = (const half_t*)a.A;
-    const half_t* W = (const half_t*)a.W;
+    const int nkw = Kw / BK, nk = K / BK;
 
     // loader: lane -> LDS chunk (row lrow of the pass, physical 16-byte chunk tid & 7); it fetches the logical
     // chunk that the row-pair swizzle maps there
     const int lrow = tid >> 3;
     const int lchunk = (tid & 7) ^ ((lrow >> 1) & 7);
-    const half_t* pa[PA];
-    const half_t* pb[PB];
+    const int va = (lrow * K + lchunk * 8) * 2, vb = (lrow * Kw + lchunk * 8) * 2;
+    TileSrc<PA, RPP> srcA;
+    TileSrc<PB, RPP> srcB;
     auto set_tile = [&](const TileCoord& t) {
         m0 = (int64_t)t.tm * BM;
         n0 = t.tn * BN;
-#pragma unroll
-        for (int p = 0; p < PA; ++p) {
-            int64_t r = m0 + p * RPP + lrow;
-            r = r < a.M ? r : a.M - 1;
-            pa[p] = A + r * K + lchunk * 8;
-        }
-#pragma unroll
-        for (int p = 0; p < PB; ++p) {
-            int r = n0 + p * RPP + lrow;
-            r = r < a.N ? r : a.N - 1;
-            pb[p] = W + (size_t)r * Kw + lchunk * 8;
-        }
+        srcA.set((const half_t*)a.A + m0 * K, (int)min((int64_t)BM, a.M - m0), K);
+        srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
     };
     set_tile(tc);
-    auto dma = [&](int kt, int buf) {
-        half_t* da = sA + buf * BM * BK + wave * 64 * 8;      // wave-uniform: the hardware adds 16 bytes per lane
-        half_t* db = sB + buf * BN * BK + wave * 64 * 8;
+    // load p of the PA of A's k-tile kt / of the PB of W's (the LDS address is wave-uniform: the hardware adds 16 bytes per
+    // lane); a k-tile past the end fetches nothing
+    auto dma_a = [&](int p, int kt, int slot) {
+        srcA.load(p, sA + slot * BM * BK + wave * 64 * 8 + p * NT * 8, kt < nk ? va : kNoLoad, kt < nk ? kt * (BK * 2) : 0);
+    };
+    auto dma_b = [&](int p, int kt, int slot) {
         const int ktw = kt < nkw ? kt : kt - nkw;             // the lo half of a split A meets the same W columns again
+        srcB.load(p, sB + slot * BN * BK + wave * 64 * 8 + p * NT * 8, kt < nk ? vb : kNoLoad, kt < nk ? ktw * (BK * 2) : 0);
+    };
+    auto dma_first = [&]() {                                  // k-tile 0 of a tile, into stages 0
 #pragma unroll
-        for (int p = 0; p < PA; ++p)
-            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(pa[p] + kt * BK), (lds_ptr_t)(da + p * NT * 8), 16, 0, 0);
+        for (int p = 0; p < PA; ++p) dma_a(p, 0, 0);
 #pragma unroll
-        for (int p = 0; p < PB; ++p)
-            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(pb[p] + ktw * BK), (lds_ptr_t)(db + p * NT * 8), 16, 0, 0);
+        for (int p = 0; p < PB; ++p) dma_b(p, 0, 0);
     };
 
-    floatx16 acc[MI][NI];
-
-    const int frow = lane & 31, fh = lane >> 5;
-    const int a_row0 = wm * TM + frow;
-    const int b_row0 = wn * TN + frow;
+    floatx4 acc[MI][NI];
+    const int frow = lane & 15, fq = lane >> 4;
     const int sw = (frow >> 1) & 7;           // row pair index: rows are 128 bytes, the bank window 256
-
-    halfx8 af[2][MI], bfr[2][NI];             // fragment double buffer
-    auto fload = [&](int slot, const half_t* cA, const half_t* cB, int kk) {
-        const int pch = ((kk * 2 + fh) ^ sw) * 8;
+    halfx8 af[MI], bfr[2][NI];
+    auto read_a = [&](int i, const half_t* cA, int ks) { af[i] = *(const halfx8*)(cA + (wm * TM + i * 16 + frow) * BK + (((ks * 4 + fq) ^ sw) * 8)); };
+    auto read_b = [&](int j, const half_t* cB, int ks) { bfr[ks][j] = *(const halfx8*)(cB + (wn * TN + j * 16 + frow) * BK + (((ks * 4 + fq) ^ sw) * 8)); };
+    auto mfma_row = [&](int i, int ks) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i) af[slot][i] = *(const halfx8*)(cA + (a_row0 + i * 32) * BK + pch);
-#pragma unroll
-        for (int j = 0; j < NI; ++j) bfr[slot][j] = *(const halfx8*)(cB + (b_row0 + j * 32) * BK + pch);
-    };
-    auto mfmas = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bfr[slot][j], af[slot][i], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bfr[ks][j], af[i], acc[i][j], 0, 0, 0);
     };
 
-    const int nk = K / BK;
-    dma(0, 0);
+    using std::integral_constant;
+    // how `n` operations are spread over the rows r0 .. MI - 1 of a k-step: operation q goes behind row r0 + q * (MI - r0) / n
+    auto spread = [&](auto r0_c, auto n_c, int row, auto op) {
+        constexpr int R0 = decltype(r0_c)::value, N = decltype(n_c)::value;
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if (R0 + q * (MI - R0) / N == row) op(q);
+    };
+    constexpr int XR = MI / 4;                 // the barrier sits behind this many rows of the second k-step
+    constexpr integral_constant<int, 0> c0{};
+    constexpr integral_constant<int, XR> cx{};
+    constexpr integral_constant<int, PA> cpa{};
+    constexpr integral_constant<int, PB> cpb{};
+    constexpr integral_constant<int, NI> cni{};
+    int slot_a = 0;                            // A stage of k-tile kt
+    // A k-tile is a head (first k-step, the rows of the second in front of the barrier) and a tail (the barrier and the
+    // rest); the loop's edge lies at the barrier, where no LDS read is outstanding.  No branch inside either; the
+    // scheduling barriers keep a fragment's replacement behind the MFMAs that use it (the same registers) and the
+    // memory operations spread.
+    auto head = [&](int kt) {
+        const half_t *cA = sA + slot_a * BM * BK, *cB = sB + (kt & 1) * BN * BK;
+        const int sa2 = slot_a == 0 ? SA - 1 : slot_a - 1;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            mfma_row(i, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            read_a(i, cA, 1);
+            spread(c0, cni, i, [&](int j) { read_b(j, cB, 1); });
+            if constexpr (SA == 3) spread(c0, cpa, i, [&](int p) { dma_a(p, kt + 2, sa2); });
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < XR; ++i) mfma_row(i, 1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto tail = [&](auto last_c, int kt) {
+        constexpr bool LAST = decltype(last_c)::value;
+        if constexpr (!LAST) {
+            // the next k-tile has landed (own loads; A of the one after may be outstanding) and every wave has read this one
+            constexpr int V = SA == 3 ? PA : 0;
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0070);       // vmcnt(V) lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        const int cur = kt & 1, sa_old = slot_a;
+        slot_a = slot_a + 1 == SA ? 0 : slot_a + 1;
+        const half_t *nA = sA + slot_a * BM * BK, *nB = sB + (cur ^ 1) * BN * BK;
+        if constexpr (!LAST) {
+#pragma unroll
+            for (int r = 0; r < XR; ++r) read_a(r, nA, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = XR; i < MI; ++i) {
+            mfma_row(i, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!LAST) {
+                read_a(i, nA, 0);
+                spread(cx, cni, i, [&](int j) { read_b(j, nB, 0); });
+                spread(cx, cpb, i, [&](int p) { dma_b(p, kt + 2, cur); });
+                if constexpr (SA == 2) spread(cx, cpa, i, [&](int p) { dma_a(p, kt + 2, sa_old); });
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+
+    dma_first();
     for (;;) {                                // one tile per pass; a single pass unless PERSIST
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    // k-tile 0 has landed; every wave is done with the previous tile's staging reads (PERSIST)
+        for (int j = 0; j < NI; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // k-tile 0 has landed; every wave is done with the previous tile's staging reads (PERSIST), which used the other stages
     __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
     __syncthreads();
-    fload(0, sA, sB, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nk;
-        if (more) dma(kt + 1, cur ^ 1);
-        const half_t* cA = sA + cur * BM * BK;
-        const half_t* cB = sB + cur * BN * BK;
 #pragma unroll
-        for (int kk = 0; kk < KS - 1; ++kk) {
-            fload((kk + 1) & 1, cA, cB, kk + 1);
-            mfmas(kk & 1);
+    for (int p = 0; p < PB; ++p) dma_b(p, 1, 1);
 #pragma unroll
-            for (int n = 0; n < MI + NI; ++n) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - (MI + NI), 0);
-        }
-        // the next k-tile has landed (own loads) and every wave is past its last read of the other stage
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();
-        if (more) fload(KS & 1, sA + (cur ^ 1) * BM * BK, sB + (cur ^ 1) * BN * BK, 0);
-        mfmas((KS - 1) & 1);
-        static_assert(KS % 2 == 0, "slot parity of the first fragment of a tile");
+    for (int p = 0; p < PA; ++p) dma_a(p, 1, 1);
+    slot_a = 0;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) read_a(i, sA, 0);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) read_b(j, sB, 0);
+    head(0);
+    for (int kt = 0; kt + 1 < nk; ++kt) {
+        tail(std::false_type{}, kt);
+        head(kt + 1);
     }
+    tail(std::true_type{}, nk - 1);
+    // nobody reads the stages any more, and nothing is on its way into them
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
 
-    // ---- epilogue: lane owns output row (lane & 31) of each block; register r holds column 8*(r>>2) + 4*(lane>>5) + (r&3)
+    // ---- epilogue
     const int64_t tile_m0 = m0;               // the epilogue's tile; m0 / n0 move on to the next one below
     const int tile_n0 = n0;
     bool has_next = false;
@@ -517,11 +576,29 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_mfma_kernel(GemmArgs a) {
         has_next = nx.valid;
         if (has_next) {
             set_tile(nx);
-            dma(0, 0);                        // stage 0 of A and W: nobody reads LDS behind the loop's last barrier
+            dma_first();                      // stages 0: nobody reads LDS behind the loop's last barrier
         }
     }
-    gemm_epilogue<EPI, BM, BN, WM, WN, HB>(acc, a, smem, tile_m0, tile_n0);
+    gemm_epilogue<EPI, BM, BN, WM, WN, HB, SA>(acc, a, smem, tile_m0, tile_n0);
     if (!has_next) break;
+    }
+}
+
+// Reads the weights of a launch further down the stream (a.warm) and drops them: they are then in the memory-side cache when
+// that launch asks for them.  Done by workgroups of a small launch that would leave their CUs idle.  A ring workgroup
+// of 64 x 64 tiles has 128 KiB in flight; at the ~2.3 us that a first touch of HBM takes that is one k-tile per 590 cycles, and
+// 400 from the memory-side cache (down projection of 640 rows: 24 -> 17 us).
+template <int NT>
+__device__ __forceinline__ void warm_weights(const GemmArgs& a, int wg, int n_wgs) {
+    constexpr int U = 8;
+    const size_t n16 = a.warm_bytes / 16, stride = (size_t)n_wgs * NT;
+    const uint4v* src = (const uint4v*)a.warm;
+    for (size_t i = (size_t)wg * NT + threadIdx.x; i < n16; i += U * stride) {
+        uint4v v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = src[min(i + u * stride, n16 - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) asm volatile("" ::"v"(v[u]));
     }
 }
 
@@ -540,10 +617,10 @@ template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
-    constexpr int MI = TM / 32, NI = TN / 32;
+    constexpr int MI = TM / 16, NI = TN / 16;
     constexpr int RPP = NT / 8;
     constexpr int PA = BM / RPP, PB = BN / RPP;
-    constexpr int KS = BK / 16;
+    constexpr int KS = BK / 32;
     constexpr int LPT = PA + PB;                    // loads per thread and k-tile
     static_assert(RPP % 16 == 0 && BM % RPP == 0 && BN % RPP == 0, "loader shape");
     static_assert(NS >= 2 && NS <= 10 && (NS - 1) * LPT < 64, "the load counter has six bits");
@@ -552,11 +629,16 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
     half_t* sB = sA + NS * BM * BK;                     // [NS][BN][BK]
 
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int tile_wgs = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
+    if ((int)blockIdx.x >= tile_wgs) {
+        warm_weights<NT>(a, blockIdx.x - tile_wgs, gridDim.x - tile_wgs);
+        return;
+    }
     const TileCoord tc = map_tile(blockIdx.x, tiles_m, tiles_n);
     if (!tc.valid) return;
     const int64_t m0 = (int64_t)tc.tm * BM;
     const int n0 = tc.tn * BN;
-    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int K = a.K;
@@ -568,37 +650,28 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
     float4 xv[XPRE ? BM * BN / 4 / NT : 1];
     if constexpr (XPRE) x_prefetch<BN, NT>(xv, a, m0, n0);
 
-    // loader: a wave-uniform tile base and a 32-bit byte offset per lane and pass
-    const char* baseA = (const char*)((const half_t*)a.A + m0 * K);
-    const char* baseB = (const char*)((const half_t*)a.W + (size_t)n0 * Kw);
     const int lrow = tid >> 3;
     const int lchunk = (tid & 7) ^ ((lrow >> 1) & 7);
-    const int rows_a = (int)min((int64_t)BM, a.M - m0), rows_b = min(BN, a.N - n0);
-    unsigned oa[PA], ob[PB];
-#pragma unroll
-    for (int p = 0; p < PA; ++p) oa[p] = (unsigned)(min(p * RPP + lrow, rows_a - 1) * K + lchunk * 8) * 2u;
-#pragma unroll
-    for (int p = 0; p < PB; ++p) ob[p] = (unsigned)(min(p * RPP + lrow, rows_b - 1) * Kw + lchunk * 8) * 2u;
+    TileSrc<PA, RPP> srcA;
+    TileSrc<PB, RPP> srcB;
+    srcA.set((const half_t*)a.A + m0 * K, (int)min((int64_t)BM, a.M - m0), K);
+    srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
+    const int va = (lrow * K + lchunk * 8) * 2, vb = (lrow * Kw + lchunk * 8) * 2;
     auto dma = [&](int kt, int buf) {
         half_t* da = sA + buf * BM * BK + wave * 64 * 8;
         half_t* db = sB + buf * BN * BK + wave * 64 * 8;
-        const char* ka = baseA + (size_t)kt * (BK * 2);
-        const char* kb = baseB + (size_t)(kt < nkw ? kt : kt - nkw) * (BK * 2);
+        const int ktw = kt < nkw ? kt : kt - nkw;
 #pragma unroll
-        for (int p = 0; p < PA; ++p)
-            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(ka + oa[p]), (lds_ptr_t)(da + p * NT * 8), 16, 0, 0);
+        for (int p = 0; p < PA; ++p) srcA.load(p, da + p * NT * 8, va, kt * (BK * 2));
 #pragma unroll
-        for (int p = 0; p < PB; ++p)
-            __builtin_amdgcn_global_load_lds((gbl_ptr_t)(kb + ob[p]), (lds_ptr_t)(db + p * NT * 8), 16, 0, 0);
+        for (int p = 0; p < PB; ++p) srcB.load(p, db + p * NT * 8, vb, ktw * (BK * 2));
     };
-    floatx16 acc[MI][NI];
+    floatx4 acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    const int frow = lane & 31, fh = lane >> 5;
+        for (int j = 0; j < NI; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int frow = lane & 15, fq = lane >> 4;
     const int a_row0 = wm * TM + frow;
     const int b_row0 = wn * TN + frow;
     const int sw = (frow >> 1) & 7;
@@ -608,11 +681,11 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
         const half_t* cB = sB + buf * BN * BK;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            const int pch = ((kk * 2 + fh) ^ sw) * 8;
+            const int pch = ((kk * 4 + fq) ^ sw) * 8;
 #pragma unroll
-            for (int i = 0; i < MI; ++i) af[set][kk][i] = *(const halfx8*)(cA + (a_row0 + i * 32) * BK + pch);
+            for (int i = 0; i < MI; ++i) af[set][kk][i] = *(const halfx8*)(cA + (a_row0 + i * 16) * BK + pch);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) bfr[set][kk][j] = *(const halfx8*)(cB + (b_row0 + j * 32) * BK + pch);
+            for (int j = 0; j < NI; ++j) bfr[set][kk][j] = *(const halfx8*)(cB + (b_row0 + j * 16) * BK + pch);
         }
     };
 
@@ -638,15 +711,17 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
             for (int i = 0; i < MI; ++i)
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bfr[SET][kk][j], af[SET][kk][i], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bfr[SET][kk][j], af[SET][kk][i], acc[i][j], 0, 0, 0);
         if constexpr (YOUNGER >= 0) {
-            // all fragment reads first, then the requests spread over the MFMAs
-            __builtin_amdgcn_sched_group_barrier(0x100, KS * (MI + NI), 0);
-            constexpr int PER = KS * MI * NI / LPT > 0 ? KS * MI * NI / LPT : 1;
+            // a wave issues in order, one LDS read or one MFMA per ~16 cycles: reads (early), then requests between the MFMAs
+            constexpr int NM = KS * MI * NI, ND = KS * (MI + NI), DPM = (ND + NM - 1) / NM;
+            constexpr int MD = (ND + DPM - 1) / DPM;                       // MFMAs with reads behind them
+            constexpr int VPM = (LPT + NM - 1) / NM, MV = (LPT + VPM - 1) / VPM;
 #pragma unroll
-            for (int n = 0; n < LPT; ++n) {
-                __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
-                __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+            for (int n = 0; n < NM; ++n) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (n < MD) __builtin_amdgcn_sched_group_barrier(0x100, DPM, 0);
+                if (n >= NM - MV) __builtin_amdgcn_sched_group_barrier(0x010, VPM, 0);
             }
             asm volatile("" ::: "memory");
         }
@@ -679,10 +754,11 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
     };
     tail(tail, integral_constant<int, NS - 1>{});
     __syncthreads();                               // every wave is done reading the stages before the epilogue reuses them
-    gemm_epilogue<EPI, BM, BN, WM, WN, HB>(acc, a, smem, m0, n0, XPRE ? xv : nullptr);
+    gemm_epilogue<EPI, BM, BN, WM, WN, HB, NS>(acc, a, smem, m0, n0, XPRE ? xv : nullptr);
 }
 
 int cu_count();
+constexpr int kWarmWgs = 64;
 
 // Per-device "done once" flags and cached values: a host thread may drive any device, and different model handles may
 // be used from different threads.
@@ -702,7 +778,7 @@ hipError_t allow_dynamic_lds(K kernel, size_t lds, std::atomic<uint64_t>& done) 
     return e;
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int HB>
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
 hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int n_tiles = tiles_m * tiles_n;
@@ -714,17 +790,19 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
         const int resident = cu_count() * (BM >= 256 ? 1 : 2) / kXcds * kXcds;
         if (resident >= kXcds && grid > resident) grid = resident;
     }
-    const size_t lds = (size_t)2 * (BM + BN) * BK * sizeof(half_t);
+    const size_t lds = (size_t)(SA * BM + 2 * BN) * BK * sizeof(half_t);
     static std::atomic<uint64_t> attr_done{0};
-    if (hipError_t e = allow_dynamic_lds(gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB>, lds, attr_done); e != hipSuccess) return e;
-    gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(a);
+    if (hipError_t e = allow_dynamic_lds(gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA>, lds, attr_done); e != hipSuccess) return e;
+    gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(a);
     return hipGetLastError();
 }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
-    const int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
+    int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
+    // what the tiles leave of the chip, at most kWarmWgs workgroups, may fetch weights ahead
+    if (a.warm_bytes > 0) grid += std::max(0, std::min(kWarmWgs, (cu_count() - grid) / kXcds * kXcds));
     const size_t lds = (size_t)NS * (BM + BN) * BK * sizeof(half_t);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS>, lds, attr_done); e != hipSuccess) return e;
@@ -794,18 +872,18 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
     const bool tall_ok = epi == EPI_RESID_ADD || (epi == EPI_SWIGLU && a.K >= 2048);
     const TileChoice tile = choose_gemm_tile(a.M, a.N, wide_head ? 256 : 128, tall_ok, cu_count());
     if (tile == TILE_TALL)
-        return epi == EPI_RESID_ADD ? launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1>(a, st) : launch_tile<EPI_SWIGLU, 320, 256, 2, 4, 1>(a, st);
+        return epi == EPI_RESID_ADD ? launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1, 2>(a, st) : launch_tile<EPI_SWIGLU, 320, 256, 2, 4, 1, 2>(a, st);
     const bool big = tile == TILE_BIG;
     switch (epi) {
         case EPI_QKV_ROPE:
             if (!wide_head) {
-                return big ? launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1>(a, st) : launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1>(a, st);
+                return big ? launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1, 3>(a, st) : launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 2>(a, st);
             }
-            return big ? launch_tile<EPI_QKV_ROPE, 256, 256, 4, 2, 2>(a, st) : launch_tile<EPI_QKV_ROPE, 128, 256, 2, 2, 2>(a, st);
+            return big ? launch_tile<EPI_QKV_ROPE, 256, 256, 4, 2, 2, 3>(a, st) : launch_tile<EPI_QKV_ROPE, 128, 256, 2, 2, 2, 2>(a, st);
         case EPI_RESID_ADD:
-            return big ? launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1>(a, st) : launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1>(a, st);
+            return big ? launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(a, st) : launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 2>(a, st);
         case EPI_SWIGLU:
-            return big ? launch_tile<EPI_SWIGLU, 256, 256, 2, 4, 1>(a, st) : launch_tile<EPI_SWIGLU, 128, 128, 2, 2, 1>(a, st);
+            return big ? launch_tile<EPI_SWIGLU, 256, 256, 2, 4, 1, 3>(a, st) : launch_tile<EPI_SWIGLU, 128, 128, 2, 2, 1, 2>(a, st);
     }
     return hipErrorInvalidValue;
 }
