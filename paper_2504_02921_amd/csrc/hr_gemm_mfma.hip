@@ -124,7 +124,8 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
         // x += C through LDS.  In the accumulator layout a lane holds 16 bytes of one row, so a direct update touches
         // 32 rows per instruction; staged as an fp32 [BM][CW] tile (16-byte chunks XOR-swizzled by the row against
         // bank conflicts of the column-wise writes) the update reads and writes whole 512-byte row segments.  The
-        // stages hold BM x CW floats, so the tile goes in PASSES column slabs; each wave tile lies in one slab.
+        // stages hold BM x CW floats, so the tile goes in PASSES column slabs; a wave tile lies in one slab or is cut into
+        // whole slabs.
         constexpr int LDS_BYTES = 2 * (BM + BN) * BK * (int)sizeof(half_t);
         constexpr int PASSES_MIN = (BM * BN * 4 + LDS_BYTES - 1) / LDS_BYTES;
         constexpr int PASSES = PASSES_MIN <= 2 ? PASSES_MIN : (PASSES_MIN <= 4 ? 4 : 8);     // a divisor of BN
@@ -132,7 +133,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
         constexpr int CPRW = CW / 4;                    // 16-byte chunks per slab row
         constexpr int ITER = BM * CPRW / NT;
         constexpr int NG = ITER % 4 == 0 ? 4 : 5;       // register groups of the x update (320-row tiles: 10 = 5 x 2)
-        static_assert(EPI != EPI_RESID_ADD || (CW % TN == 0 && CPRW % 16 == 0 && (BM * CPRW) % (NG * NT) == 0 && BM * CW * 4 <= LDS_BYTES),
+        static_assert(EPI != EPI_RESID_ADD || ((CW % TN == 0 || TN % CW == 0) && CPRW % 16 == 0 && (BM * CPRW) % (NG * NT) == 0 && BM * CW * 4 <= LDS_BYTES),
                       "slab shape");
         float* stage = (float*)smem;
 #pragma unroll
@@ -178,15 +179,17 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
                 load_x(0);
             }
             if (p > 0) __syncthreads();                 // the previous slab has been read
-            if ((wn * TN) / CW == p) {
-                const int c_off = wn * TN - p * CW + 4 * fq;
+            constexpr int NJ = CW < TN ? CW / 16 : NI;           // blocks of a wave tile in a slab, from block j0 on
+            const int j0 = CW < TN ? (p * CW % TN) / 16 : 0;
+            if (CW < TN ? (p * CW) / TN == wn : (wn * TN) / CW == p) {
+                const int c_off = (CW < TN ? 0 : wn * TN - p * CW) + 4 * fq;
 #pragma unroll
                 for (int i = 0; i < MI; ++i) {
                     const int lr = wm * TM + i * 16 + frow;
 #pragma unroll
-                    for (int j = 0; j < NI; ++j) {
+                    for (int j = 0; j < NJ; ++j) {
                         const int ch = (c_off + j * 16) >> 2;
-                        *(floatx4*)(stage + lr * CW + ((ch ^ (lr & 15)) << 2)) = acc[i][j];
+                        *(floatx4*)(stage + lr * CW + ((ch ^ (lr & 15)) << 2)) = acc[i][j0 + j];
                     }
                 }
             }
@@ -400,7 +403,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
 // Accumulation is transposed (D = W_frag * A_frag^T): a lane owns ONE output row (lane & 15) and 4 consecutive columns
 // per block, so the epilogues address one row pointer per block and store 8 / 16 bytes at a time.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
-__global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) gemm_mfma_kernel(GemmArgs a) {
+__global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 1) gemm_mfma_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;      // wave tile
     constexpr int MI = TM / 16, NI = TN / 16;
@@ -464,8 +467,17 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 ? 2 : 1) gemm_mfma_
     const int frow = lane & 15, fq = lane >> 4;
     const int sw = (frow >> 1) & 7;           // row pair index: rows are 128 bytes, the bank window 256
     halfx8 af[MI], bfr[2][NI];
-    auto read_a = [&](int i, const half_t* cA, int ks) { af[i] = *(const halfx8*)(cA + (wm * TM + i * 16 + frow) * BK + (((ks * 4 + fq) ^ sw) * 8)); };
-    auto read_b = [&](int j, const half_t* cB, int ks) { bfr[ks][j] = *(const halfx8*)(cB + (wn * TN + j * 16 + frow) * BK + (((ks * 4 + fq) ^ sw) * 8)); };
+    // a lane's place in the first 16 rows of its wave's part of a stage, per k-step; opaque, so that the rows below fold into
+    // the instruction's offset instead of a register each
+    int at_a[2], at_b[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        at_a[ks] = (wm * TM + frow) * BK + (((ks * 4 + fq) ^ sw) * 8);
+        at_b[ks] = (wn * TN + frow) * BK + (((ks * 4 + fq) ^ sw) * 8);
+        asm("" : "+v"(at_a[ks]), "+v"(at_b[ks]));
+    }
+    auto read_a = [&](int i, const half_t* cA, int ks) { af[i] = *(const halfx8*)(cA + at_a[ks] + i * 16 * BK); };
+    auto read_b = [&](int j, const half_t* cB, int ks) { bfr[ks][j] = *(const halfx8*)(cB + at_b[ks] + j * 16 * BK); };
     auto mfma_row = [&](int i, int ks) {
 #pragma unroll
         for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bfr[ks][j], af[i], acc[i][j], 0, 0, 0);
@@ -676,16 +688,22 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
     const int b_row0 = wn * TN + frow;
     const int sw = (frow >> 1) & 7;
     halfx8 af[2][KS][MI], bfr[2][KS][NI];           // fragments of a whole k-tile, double buffered
+    int at_a[KS], at_b[KS];                         // as in the kernel above
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+        at_a[kk] = a_row0 * BK + (((kk * 4 + fq) ^ sw) * 8);
+        at_b[kk] = b_row0 * BK + (((kk * 4 + fq) ^ sw) * 8);
+        asm("" : "+v"(at_a[kk]), "+v"(at_b[kk]));
+    }
     auto fload = [&](int set, int buf) {
         const half_t* cA = sA + buf * BM * BK;
         const half_t* cB = sB + buf * BN * BK;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            const int pch = ((kk * 4 + fq) ^ sw) * 8;
 #pragma unroll
-            for (int i = 0; i < MI; ++i) af[set][kk][i] = *(const halfx8*)(cA + (a_row0 + i * 16) * BK + pch);
+            for (int i = 0; i < MI; ++i) af[set][kk][i] = *(const halfx8*)(cA + at_a[kk] + i * 16 * BK);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) bfr[set][kk][j] = *(const halfx8*)(cB + (b_row0 + j * 16) * BK + pch);
+            for (int j = 0; j < NI; ++j) bfr[set][kk][j] = *(const halfx8*)(cB + at_b[kk] + j * 16 * BK);
         }
     };
 
@@ -836,56 +854,82 @@ bool gemm_mfma_supported(const hr_model_cfg& c) {
     return true;
 }
 
+// the same launch for the rows behind the first `rows`
+static void advance_rows(GemmEpilogue epi, GemmArgs& r, int64_t rows) {
+    auto halves = [&](void* p, int64_t per_row) { return p ? (void*)((half_t*)p + rows * per_row) : nullptr; };
+    r.A = (const half_t*)r.A + rows * r.K;
+    if (epi == EPI_RESID_ADD) r.x += rows * r.N;
+    if (epi == EPI_SWIGLU) r.out0 = halves(r.out0, (r.split_out ? 2 : 1) * (int64_t)(r.N / 2));
+    if (epi == EPI_QKV_ROPE) {
+        r.out0 = halves(r.out0, (int64_t)r.n_q * r.d);
+        if (!r.kv_pages) {                      // with pages the slots say where K and V go
+            r.out1 = halves(r.out1, (int64_t)r.n_kv * r.d);
+            r.out2 = halves(r.out2, (int64_t)r.n_kv * r.d);
+        }
+        r.rope += rows * (r.d / 2);
+        if (r.new_slot) r.new_slot += rows;
+    }
+}
+
 hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st) {
     if (a.M == 0) return hipSuccess;
     if (a.K % BK != 0) return hipErrorInvalidValue;
     if (a.Kw > 0 && (a.Kw % BK != 0 || (a.K != a.Kw && a.K != 2 * a.Kw))) return hipErrorInvalidValue;
     const bool wide_head = epi == EPI_QKV_ROPE && a.d == 128;       // a wave must span a whole 128-wide head
-    // Few rows: the ring variants, while one of their shapes takes the launch in one round of the chip (a ring workgroup has
-    // its CU to itself).  Among those the one with the fewest operand bytes per k-tile, i.e. the smallest that fits: the
-    // loop is bound by the delivery of BM + BN rows per k-tile to the CU.
-    const int64_t cus = cu_count();
-    auto fits = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) <= cus; };
-    switch (epi) {
-        case EPI_QKV_ROPE:
-            if (wide_head) {
-                if (fits(64, 128)) return launch_ring<EPI_QKV_ROPE, 64, 128, 2, 1, 2, 5>(a, st);
-                if (fits(128, 128)) return launch_ring<EPI_QKV_ROPE, 128, 128, 4, 1, 2, 4>(a, st);
-            } else {
-                if (fits(64, 64)) return launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(a, st);
-                if (fits(128, 128)) return launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(a, st);
-            }
-            break;
-        case EPI_RESID_ADD:
-            if (fits(64, 64)) return launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(a, st);
-            if (fits(64, 128)) return launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(a, st);
-            if (fits(128, 128)) return launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(a, st);
-            break;
-        case EPI_SWIGLU:
-            if (fits(64, 128)) return launch_ring<EPI_SWIGLU, 64, 128, 2, 2, 1, 6>(a, st);
-            if (fits(128, 128)) return launch_ring<EPI_SWIGLU, 128, 128, 2, 2, 1, 4>(a, st);
-            if (fits(128, 256)) return launch_ring<EPI_SWIGLU, 128, 256, 2, 2, 1, 3>(a, st);
-            break;
+    const GemmKind kind = epi == EPI_RESID_ADD ? GEMM_RESID : epi == EPI_SWIGLU ? GEMM_SWIGLU : wide_head ? GEMM_QKV128 : GEMM_QKV64;
+    const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count());
+    GemmArgs r = a;
+    for (int i = 0; i < g.n; ++i) {
+        r.M = g.part[i].rows;
+        hipError_t e = hipErrorInvalidValue;
+        switch (kind) {
+            case GEMM_QKV64:
+                switch (g.part[i].tile) {
+                    case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1, 3>(r, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 2>(r, st); break;
+                    case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(r, st); break;
+                    case GT_RING64: e = launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(r, st); break;
+                    default: break;
+                }
+                break;
+            case GEMM_QKV128:
+                switch (g.part[i].tile) {
+                    case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 4, 2, 2, 3>(r, st); break;
+                    case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 4, 1, 2, 4>(r, st); break;
+                    case GT_RING64_128: e = launch_ring<EPI_QKV_ROPE, 64, 128, 2, 1, 2, 5>(r, st); break;
+                    default: break;
+                }
+                break;
+            case GEMM_RESID:
+                switch (g.part[i].tile) {
+                    case GT_BIG: e = launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(r, st); break;
+                    case GT_TALL: e = launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1, 2>(r, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 2>(r, st); break;
+                    case GT_RING128: e = launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(r, st); break;
+                    case GT_RING64_128: e = launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(r, st); break;
+                    case GT_RING64: e = launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(r, st); break;
+                    default: break;
+                }
+                break;
+            case GEMM_SWIGLU:
+                switch (g.part[i].tile) {
+                    case GT_BIG: e = launch_tile<EPI_SWIGLU, 256, 256, 2, 4, 1, 3>(r, st); break;
+                    case GT_TALL: e = launch_tile<EPI_SWIGLU, 320, 256, 2, 4, 1, 2>(r, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_SWIGLU, 128, 128, 2, 2, 1, 2>(r, st); break;
+                    case GT_RING128_256: e = launch_ring<EPI_SWIGLU, 128, 256, 2, 2, 1, 3>(r, st); break;
+                    case GT_RING128: e = launch_ring<EPI_SWIGLU, 128, 128, 2, 2, 1, 4>(r, st); break;
+                    case GT_RING64_128: e = launch_ring<EPI_SWIGLU, 64, 128, 2, 2, 1, 6>(r, st); break;
+                    default: break;
+                }
+                break;
+        }
+        if (e != hipSuccess) return e;
+        if (i + 1 < g.n) {
+            advance_rows(epi, r, g.part[i].rows);
+            r.warm_bytes = 0;
+        }
     }
-    // the tall tile: residual-add launches, and gate/up launches with a long k loop (not persistent: at K = 896 the
-    // start-up round trip per tile costs more than the shape saves: 8.8 against 8.0 ms per step at the 0.5B shape)
-    const bool tall_ok = epi == EPI_RESID_ADD || (epi == EPI_SWIGLU && a.K >= 2048);
-    const TileChoice tile = choose_gemm_tile(a.M, a.N, wide_head ? 256 : 128, tall_ok, cu_count());
-    if (tile == TILE_TALL)
-        return epi == EPI_RESID_ADD ? launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1, 2>(a, st) : launch_tile<EPI_SWIGLU, 320, 256, 2, 4, 1, 2>(a, st);
-    const bool big = tile == TILE_BIG;
-    switch (epi) {
-        case EPI_QKV_ROPE:
-            if (!wide_head) {
-                return big ? launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1, 3>(a, st) : launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 2>(a, st);
-            }
-            return big ? launch_tile<EPI_QKV_ROPE, 256, 256, 4, 2, 2, 3>(a, st) : launch_tile<EPI_QKV_ROPE, 128, 256, 2, 2, 2, 2>(a, st);
-        case EPI_RESID_ADD:
-            return big ? launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(a, st) : launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 2>(a, st);
-        case EPI_SWIGLU:
-            return big ? launch_tile<EPI_SWIGLU, 256, 256, 2, 4, 1, 3>(a, st) : launch_tile<EPI_SWIGLU, 128, 128, 2, 2, 1, 2>(a, st);
-    }
-    return hipErrorInvalidValue;
+    return hipSuccess;
 }
 
 }  // namespace hr

@@ -440,6 +440,80 @@ void store_group_plan(const GroupPlan& gp, int32_t* dst) {
     }
 }
 
+namespace {
+struct GemmShape {
+    GemmTile tile;
+    int bm, bn, per_cu;
+    float c0, c1;          // microseconds of a full round on 256 CUs: c0 + c1 K
+    int k_min;
+};
+// Measured (MI355X, full rounds, weights from HBM).  256 x 256 is the most efficient per output; 320 x 256 equals it per output
+// and takes other row counts in whole rounds (not for short k loops behind gate / up, whose 256-row form is
+// persistent); the two-per-CU tile costs 1.2-1.4 times as much per output but comes in quarter steps; the ring shapes
+// run one workgroup per CU and are what short launches take.
+const GemmShape kResidShapes[] = {{GT_BIG, 256, 256, 1, 21.3f, 0.0245f, 0},      {GT_TALL, 320, 256, 1, 19.0f, 0.0309f, 0},
+                                  {GT_SMALL, 128, 128, 2, 6.0f, 0.0175f, 0},     {GT_RING128, 128, 128, 1, 8.6f, 0.0098f, 0},
+                                  {GT_RING64_128, 64, 128, 1, 5.3f, 0.0064f, 0}, {GT_RING64, 64, 64, 1, 3.5f, 0.0042f, 0}};
+const GemmShape kSwigluShapes[] = {{GT_BIG, 256, 256, 1, 4.9f, 0.0239f, 0},          {GT_TALL, 320, 256, 1, 5.0f, 0.0295f, 2048},
+                                   {GT_SMALL, 128, 128, 2, 0.5f, 0.0177f, 0},         {GT_RING128_256, 128, 256, 1, 4.0f, 0.0170f, 0},
+                                   {GT_RING128, 128, 128, 1, 3.5f, 0.0092f, 0},       {GT_RING64_128, 64, 128, 1, 3.5f, 0.0064f, 0}};
+const GemmShape kQkv64Shapes[] = {{GT_BIG, 256, 256, 1, 12.0f, 0.0235f, 0},
+                                  {GT_SMALL, 128, 128, 2, 3.5f, 0.0175f, 0},
+                                  {GT_RING128, 128, 128, 1, 9.0f, 0.0098f, 0},
+                                  {GT_RING64, 64, 64, 1, 4.0f, 0.0046f, 0}};
+const GemmShape kQkv128Shapes[] = {{GT_BIG, 256, 256, 1, 12.0f, 0.0232f, 0},
+                                   {GT_RING128, 128, 128, 1, 5.0f, 0.0088f, 0},
+                                   {GT_RING64_128, 64, 128, 1, 4.5f, 0.0061f, 0}};
+}  // namespace
+
+GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) {
+    const int64_t cus = cus_ > 0 ? cus_ : 1;
+    const GemmShape* shapes = kResidShapes;
+    int n_shapes = (int)(sizeof(kResidShapes) / sizeof(GemmShape));
+    if (kind == GEMM_SWIGLU) { shapes = kSwigluShapes; n_shapes = (int)(sizeof(kSwigluShapes) / sizeof(GemmShape)); }
+    if (kind == GEMM_QKV64) { shapes = kQkv64Shapes; n_shapes = (int)(sizeof(kQkv64Shapes) / sizeof(GemmShape)); }
+    if (kind == GEMM_QKV128) { shapes = kQkv128Shapes; n_shapes = (int)(sizeof(kQkv128Shapes) / sizeof(GemmShape)); }
+    // a round that fills little of the chip still takes three quarters of a full one: a tile's k loop has its length, and only
+    // the shared memory system and the clock give way
+    auto cost = [&](const GemmShape& s, int64_t rows) {
+        const int64_t tiles = ((rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), slots = cus * s.per_cu;
+        const double full = (double)(tiles / slots), part = (double)(tiles % slots) / (double)slots;
+        return (full + (part > 0.0 ? 0.75 + 0.25 * part : 0.0)) * ((double)s.c0 + (double)s.c1 * K);
+    };
+    auto best_single = [&](int64_t rows, double* t) {
+        int best = -1;
+        for (int i = 0; i < n_shapes; ++i) {
+            if (K < shapes[i].k_min) continue;
+            const double c = cost(shapes[i], rows);
+            if (best < 0 || c < *t) { best = i; *t = c; }
+        }
+        return shapes[best].tile;
+    };
+    GemmLaunch g;
+    double t1 = 0.0;
+    g.n = 1;
+    g.part[0] = GemmPart{best_single(M, &t1), M};
+    for (int i = 0; i < n_shapes; ++i) {
+        const GemmShape& s = shapes[i];
+        if (s.bm < 256 || K < s.k_min) continue;
+        const int64_t tn = (N + s.bn - 1) / s.bn;
+        const int64_t rounds = ((M + s.bm - 1) / s.bm) * tn / cus;        // whole rounds that M fills
+        if (rounds < 1) continue;
+        const int64_t rows = rounds * cus / tn * s.bm;
+        if (rows <= 0 || rows >= M) continue;
+        double t2 = 0.0;
+        const GemmTile rest = best_single(M - rows, &t2);
+        const double t = cost(s, rows) + t2 + 2.0;                         // one launch more
+        if (t < t1) {
+            t1 = t;
+            g.n = 2;
+            g.part[0] = GemmPart{s.tile, rows};
+            g.part[1] = GemmPart{rest, M - rows};
+        }
+    }
+    return g;
+}
+
 TileChoice choose_gemm_tile(int64_t M, int N, int small_bn, bool tall_ok, int cus_) {
     const int64_t cus = cus_ > 0 ? cus_ : 1;
     const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);

@@ -159,13 +159,20 @@ GroupPlan make_group_plan(int64_t n_seq, const int32_t* prefix_lens, const int32
                           int64_t pt_stride, int g, int cap_blocks, bool cut_long = false);
 size_t group_plan_ints_bound(int64_t n_seq, int64_t T, int g);
 
-// ---- tile shape of an M x N MFMA GEMM launch on a device of `cus` compute units.  "big" = 256 x 256 with 8 waves (one
-// workgroup per CU, the highest rate per output), "tall" = 320 x 256 with 8 waves (where the caller allows it: 12.5 % more
-// operand bytes per k-tile for 25 % more rows, and 20 % fewer tiles) and "small" = 128 x small_bn with 4 waves (two
-// workgroups per CU, ~14 % more time per output but four times finer tiles).  With M x N outputs spread over the CUs the
-// last round of tiles is what decides (e.g. M = 20480, N = 896 on 256 CUs: 320 big tiles are two rounds, 256 tall tiles
-// one), so the cost of a shape is modelled as rounds x resident workgroups x tile area x relative cost per output,
-// from measured rates.
+// ---- how an M x N x K MFMA GEMM is launched on a device of `cus` compute units: as one or two launches over consecutive row
+// ranges, each with a tile shape of the epilogue's list.  With M x N outputs spread over the CUs the last round of tiles is what
+// decides (8B down projection of 12800 rows: 3.1 rounds of 256 x 256 tiles, a fourth round for 512 rows), so the cost of
+// a shape is rounds x measured time of a round (c0 + c1 K), and full rounds of a large tile may be followed by the best
+// shape for the rows that are left.
+enum GemmKind { GEMM_QKV64, GEMM_QKV128, GEMM_RESID, GEMM_SWIGLU };
+enum GemmTile { GT_BIG, GT_TALL, GT_SMALL, GT_RING128, GT_RING128_256, GT_RING64_128, GT_RING64 };
+struct GemmPart { GemmTile tile; int64_t rows; };
+struct GemmLaunch { int n = 0; GemmPart part[2]; };
+GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus);
+
+// ---- the measure by which a scoring call is cut in two halves: "big" = 256 x 256 tiles, "tall" = 320 x 256 (where the caller
+// allows it), "small" = 128 x small_bn, two workgroups per CU; cost = rounds x resident workgroups x tile area x relative
+// cost per output.
 enum TileChoice { TILE_SMALL, TILE_BIG, TILE_TALL };
 TileChoice choose_gemm_tile(int64_t M, int N, int small_bn, bool tall_ok, int cus);
 // Share of the workgroup slots that the tiles of an M x N residual GEMM fill in the rounds they take, in the shape
