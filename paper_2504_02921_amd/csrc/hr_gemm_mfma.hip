@@ -41,8 +41,9 @@ namespace {
 
 constexpr int BK = 64;
 constexpr int kXcds = 8, kGroupM = 8;
+constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
 
-struct TileCoord { int tm, tn; bool valid; };
+struct TileCoord { int tm, tn, share, shares; bool valid; };     // tile; its number among the `shares` that follow each other in one tile column
 
 __device__ __forceinline__ TileCoord map_tile(int pid, int tiles_m, int tiles_n) {
     int n_tiles = tiles_m * tiles_n;
@@ -55,7 +56,9 @@ __device__ __forceinline__ TileCoord map_tile(int pid, int tiles_m, int tiles_n)
     int first_m = group * kGroupM;
     int gsz = min(tiles_m - first_m, kGroupM);
     int in = tile - group * width;
-    c.tm = first_m + in % gsz;
+    c.share = in % gsz;
+    c.shares = gsz;
+    c.tm = first_m + c.share;
     c.tn = in / gsz;
     return c;
 }
@@ -83,6 +86,12 @@ struct TileSrc {
     __device__ __forceinline__ void load(int p, half_t* lds, int voff, int koff) const {
 #ifdef __HIP_DEVICE_COMPILE__
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 16, voff, pass[p] + koff, 0, 0);
+#endif
+    }
+    // four bytes a lane into 256 bytes nobody reads: what counts is that their lines are in the L2 afterwards
+    __device__ __forceinline__ void touch(half_t* lds, int voff, int koff) const {
+#ifdef __HIP_DEVICE_COMPILE__
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 4, voff, koff, 0, 0);
 #endif
     }
 };
@@ -596,24 +605,6 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
     }
 }
 
-// Reads the weights of a launch further down the stream (a.warm) and drops them: they are then in the memory-side cache when
-// that launch asks for them.  Done by workgroups of a small launch that would leave their CUs idle.  A ring workgroup
-// of 64 x 64 tiles has 128 KiB in flight; at the ~2.3 us that a first touch of HBM takes that is one k-tile per 590 cycles, and
-// 400 from the memory-side cache (down projection of 640 rows: 24 -> 17 us).
-template <int NT>
-__device__ __forceinline__ void warm_weights(const GemmArgs& a, int wg, int n_wgs) {
-    constexpr int U = 8;
-    const size_t n16 = a.warm_bytes / 16, stride = (size_t)n_wgs * NT;
-    const uint4v* src = (const uint4v*)a.warm;
-    for (size_t i = (size_t)wg * NT + threadIdx.x; i < n16; i += U * stride) {
-        uint4v v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = src[min(i + u * stride, n16 - 1)];
-#pragma unroll
-        for (int u = 0; u < U; ++u) asm volatile("" ::"v"(v[u]));
-    }
-}
-
 // Small-M variant: the same tile arithmetic (operand and k order as above: an output element gets the same bits from
 // either) with a ring of NS LDS stages, for launches whose tiles fit the chip in about one round.  A tile then has its CU to
 // itself, one wavefront per SIMD, and what counts is the serial length of a k-tile:
@@ -625,8 +616,13 @@ __device__ __forceinline__ void warm_weights(const GemmArgs& a, int wg, int n_wg
 // cycles for the 16 KiB of a 64 x 64 k-tile, 544 for 128 x 128).  The previous loop (fragments read behind the barrier,
 // one k-step ahead) took ~750 cycles per 64 x 64 k-tile whatever the number of workgroups: the down projection of 65 or
 // 640 rows (K = 4864) 27 / 28 us.
+//
+// A residual-add launch may bring one wavefront more (use_ahead below), which reads W kAhead k-tiles ahead of the ring and drops
+// it: the tiles of one column, neighbours on one XCD, take turns, so a k-tile's lines are in their L2 when the ring asks.
+// The ring alone has 128 KiB in flight, one 64 x 64 k-tile per ~590 cycles at the ~2.3 us that a first touch of HBM takes.
+// Down projection, 640 rows: 0.5B shape 23.1 -> 19.9 us, 8B shape 142 -> 117 us.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
-__global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) {
+__global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 16, NI = TN / 16;
@@ -642,11 +638,6 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
 
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int tile_wgs = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
-    if ((int)blockIdx.x >= tile_wgs) {
-        warm_weights<NT>(a, blockIdx.x - tile_wgs, gridDim.x - tile_wgs);
-        return;
-    }
     const TileCoord tc = map_tile(blockIdx.x, tiles_m, tiles_n);
     if (!tc.valid) return;
     const int64_t m0 = (int64_t)tc.tm * BM;
@@ -656,6 +647,36 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
     const int K = a.K;
     const int Kw = a.Kw > 0 ? a.Kw : K;
     const int nkw = Kw / BK, nk = K / BK;
+    TileSrc<PA, RPP> srcA;
+    TileSrc<PB, RPP> srcB;
+    srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
+    if constexpr (EPI == EPI_RESID_ADD) {
+        if (wave == WM * WN) {
+            // touches one 4-byte word of every 64 bytes: 32 rows of a k-tile per request.  Every row offset sits in the vector
+            // offset, so rows past the end fail the range check
+            int vt[BN / 32];
+#pragma unroll
+            for (int p = 0; p < BN / 32; ++p) vt[p] = (p * 32 + (lane >> 1)) * Kw * 2 + (lane & 1) * 64;
+            int turn = NS % tc.shares;                // k-tile mod shares: whose turn it is
+            auto touch = [&](int kt) {
+                if (turn == tc.share && kt < nkw) {
+#pragma unroll
+                    for (int p = 0; p < BN / 32; ++p) srcB.touch((half_t*)(smem + (size_t)NS * (BM + BN) * BK * sizeof(half_t)), vt[p], kt * (BK * 2));
+                }
+                turn = turn + 1 == tc.shares ? 0 : turn + 1;
+            };
+#pragma unroll 1
+            for (int kt = NS; kt < NS + kAhead; ++kt) touch(kt);
+            __builtin_amdgcn_s_barrier();
+#pragma unroll 1
+            for (int kt = 0; kt + 1 < nk; ++kt) {     // one barrier per k-tile but the last, as below
+                __builtin_amdgcn_s_barrier();
+                touch(kt + NS + kAhead);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);       // nothing is on its way into LDS when the wave ends; barriers go on without it
+            return;
+        }
+    }
 
     // x of a residual add: requested first, so that it has arrived long before the epilogue
     constexpr bool XPRE = EPI == EPI_RESID_ADD;
@@ -664,10 +685,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
 
     const int lrow = tid >> 3;
     const int lchunk = (tid & 7) ^ ((lrow >> 1) & 7);
-    TileSrc<PA, RPP> srcA;
-    TileSrc<PB, RPP> srcB;
     srcA.set((const half_t*)a.A + m0 * K, (int)min((int64_t)BM, a.M - m0), K);
-    srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
     const int va = (lrow * K + lchunk * 8) * 2, vb = (lrow * Kw + lchunk * 8) * 2;
     auto dma = [&](int kt, int buf) {
         half_t* da = sA + buf * BM * BK + wave * 64 * 8;
@@ -776,7 +794,6 @@ __global__ void __launch_bounds__(WM * WN * 64, 1) gemm_ring_kernel(GemmArgs a) 
 }
 
 int cu_count();
-constexpr int kWarmWgs = 64;
 
 // Per-device "done once" flags and cached values: a host thread may drive any device, and different model handles may
 // be used from different threads.
@@ -815,16 +832,19 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+// The reading-ahead wavefront pays where several tiles share a column of W and the k loop is long: with two row tiles it
+// cannot keep up (65 rows, K = 4864: 17.1 us without, 22.2 with), at K = 4096 it is worth -3 to +5 %, from K = 4864 on -14 to -18 %.
+inline bool use_ahead(const GemmArgs& a, int tiles_m) { return tiles_m >= 4 && a.K > 4096; }
+
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
-    int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
-    // what the tiles leave of the chip, at most kWarmWgs workgroups, may fetch weights ahead
-    if (a.warm_bytes > 0) grid += std::max(0, std::min(kWarmWgs, (cu_count() - grid) / kXcds * kXcds));
-    const size_t lds = (size_t)NS * (BM + BN) * BK * sizeof(half_t);
+    const int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
+    const bool ahead = EPI == EPI_RESID_ADD && use_ahead(a, tiles_m);
+    constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (EPI == EPI_RESID_ADD ? kAheadLds : 0);
     static std::atomic<uint64_t> attr_done{0};
-    if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS>, lds, attr_done); e != hipSuccess) return e;
-    gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(a);
+    if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS>, lds_most, attr_done); e != hipSuccess) return e;
+    gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS><<<dim3((unsigned)grid), (WM * WN + ahead) * 64, ahead ? lds_most : ring, st>>>(a);
     return hipGetLastError();
 }
 
@@ -924,10 +944,7 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                 break;
         }
         if (e != hipSuccess) return e;
-        if (i + 1 < g.n) {
-            advance_rows(epi, r, g.part[i].rows);
-            r.warm_bytes = 0;
-        }
+        if (i + 1 < g.n) advance_rows(epi, r, g.part[i].rows);
     }
     return hipSuccess;
 }

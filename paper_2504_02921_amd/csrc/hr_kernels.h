@@ -119,10 +119,6 @@ struct GemmArgs {
     // token t at slot new_slot[t]; out1 / out2 are ignored then
     void* kv_pages;
     const int32_t* new_slot;
-    // optional: weights of a later launch (16-byte words) that a launch of few tiles may fetch into the memory-side cache
-    // with the CUs it leaves idle; no effect on any result
-    const void* warm;
-    size_t warm_bytes;
 };
 hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st);
 
