@@ -106,7 +106,7 @@ struct GemmArgs {
     // Split A operand: 0 (or K) = plain; K / 2 = A is [M][K] holding [hi | lo] halves of a K/2-wide activation (the value
     // is hi + lo, 22 significant bits) and W has K / 2 columns, met by both halves: C = hi W^T + lo W^T
     int Kw;
-    // EPI_SWIGLU: m is written as [M][2 * N/2] = [hi | lo]; EPI_QKV_ROPE: q is written as [M][2 * n_q * d] = [hi | lo]
+    // EPI_SWIGLU: m is written as [M][2 * N/2] = [hi | lo]
     int split_out;
     // epilogue operands
     float* x;           // EPI_RESID_ADD: fp32 [M][N], x += acc

@@ -222,6 +222,45 @@ int main() {
         CHECK(f8b > 0.83 && f8b < 0.84);                                               // 640 of 768 slots
         CHECK(hr::gemm_tile_fill(25600, 4096, 256) == 1.0);                            // 1280 tall tiles = 5 full rounds
     }
+    {   // GEMM launches: the parts cover the rows, in order, with shapes the epilogue has; a cut leaves whole rounds in front
+        std::srand(11);
+        const hr::GemmKind kinds[] = {hr::GEMM_QKV64, hr::GEMM_QKV128, hr::GEMM_RESID, hr::GEMM_SWIGLU};
+        int cuts[4] = {0, 0, 0, 0};
+        for (int it = 0; it < 8000; ++it) {
+            const hr::GemmKind kind = kinds[it % 4];
+            const int64_t M = it % 8 < 4 ? 1 + std::rand() % 3000 : 1 + std::rand() % 120000;
+            const int N = 64 * (1 + std::rand() % 480), K = 64 * (1 + std::rand() % 230), cus = 8 * (1 + std::rand() % 40);
+            const hr::GemmLaunch g = hr::choose_gemm_launch(kind, M, N, K, cus);
+            CHECK(g.n == 1 || g.n == 2);
+            int64_t rows = 0;
+            for (int i = 0; i < g.n; ++i) {
+                const hr::GemmTile t = g.part[i].tile;
+                CHECK(g.part[i].rows > 0);
+                rows += g.part[i].rows;
+                switch (kind) {
+                    case hr::GEMM_QKV64: CHECK(t == hr::GT_BIG || t == hr::GT_SMALL || t == hr::GT_RING128 || t == hr::GT_RING64); break;
+                    case hr::GEMM_QKV128: CHECK(t == hr::GT_BIG || t == hr::GT_RING128 || t == hr::GT_RING64_128); break;
+                    case hr::GEMM_RESID: CHECK(t != hr::GT_RING128_256); break;
+                    case hr::GEMM_SWIGLU: CHECK(t != hr::GT_RING64 && (t != hr::GT_TALL || K >= 2048)); break;
+                }
+            }
+            CHECK(rows == M);
+            if (g.n == 2) {
+                ++cuts[it % 4];
+                const hr::GemmTile t = g.part[0].tile;
+                CHECK(t == hr::GT_BIG || t == hr::GT_TALL);
+                const int64_t bm = t == hr::GT_TALL ? 320 : 256, tn = (N + 255) / 256;
+                CHECK(g.part[0].rows % bm == 0);
+                const int64_t tiles = g.part[0].rows / bm * tn, part = tiles % cus;
+                CHECK(tiles > cus - tn && (part == 0 || part > cus - tn));       // the cut lies at the last whole row of tiles
+            }
+        }
+        for (int c : cuts) CHECK(c > 0);
+        // the launches that the GPU tests of cut projections rely on
+        CHECK(hr::choose_gemm_launch(hr::GEMM_SWIGLU, 1980, 2 * 4864, 896, 256).n == 2);
+        CHECK(hr::choose_gemm_launch(hr::GEMM_QKV64, 6600, 2560, 512, 256).n == 2);
+        CHECK(hr::choose_gemm_launch(hr::GEMM_QKV128, 12000, 1536, 256, 256).n == 2);
+    }
     {   // sequences with the same token string share first-layer rows: tables written into a layout of exactly the computed size
         // strings: A = {5, 6, 7}, B = {5, 6}, C = {9}; sequences A B A C B A C
         const std::vector<int32_t> lens = {3, 2, 3, 1, 2, 3, 1};

@@ -185,6 +185,35 @@ def test_more_query_rows_than_a_work_item_holds(d, n_q, n_kv, kv, q_len, monkeyp
             case.close()
 
 
+@pytest.mark.parametrize("d,n_q,n_kv,hidden,ffn,n_queries,qlen", [
+    (64, 14, 2, 896, 4864, 12, (33, 33)),       # gate / up: full rounds of large tiles and a rest; down: W read ahead of the ring
+    (64, 8, 2, 256, 4864, 1, (41, 41)),         # down, K = 4864: four row tiles, the last one with 13 rows
+    (128, 8, 2, 320, 4160, 2, (33, 37)),        # down, K = 4160: 65 k-tiles, a column tile of 64
+    (64, 32, 4, 512, 320, 40, (33, 33)),        # QKV of 64-wide heads in two launches
+    (128, 8, 2, 256, 320, 60, (40, 40)),        # QKV of 128-wide heads in two launches
+])
+def test_projections_cut_by_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen):
+    """A projection may be launched as two row ranges with tile shapes of their own, and the ring kernel may bring a
+    wavefront that reads W ahead: neither changes the order in which an output element is summed."""
+    model = small_model(dtype="bf16", n_layers=2, hidden=hidden, n_q=n_q, n_kv=n_kv, d=d, ffn=ffn, vocab=500)
+    cfg = wlmod.WorkloadCfg("row_ranges", model, n_queries, 5, (5, 60), qlen, "bf16", pool_docs=9, zipf_a=0.3, seed=ffn + d)
+    w = wlmod.SeededWeights(model, seed=18, std=0.05, gain_jitter=0.1)
+    wl = wlmod.make_workload(cfg, spare_pages=2)
+    case = H.Case(wl, w)
+    try:
+        case.fill_from_prefill()
+        case.model.set_streams(1)
+        got = case.gpu_scores()
+        idx = np.unique(np.linspace(0, wl.n_pairs - 1, 9).astype(int))
+        sub = wl.subset(idx)
+        H.assert_scores_close(got[idx], case.oracle_scores(sub), H.TOL["bf16"], "row ranges")
+        np.testing.assert_array_equal(case.gpu_scores(sub), got[idx])
+        for i in (0, wl.n_pairs - 1):
+            np.testing.assert_array_equal(case.gpu_scores(wl.subset(np.array([i]))), got[i:i + 1])
+    finally:
+        case.close()
+
+
 @pytest.mark.parametrize("hidden,ffn", [(256, 688), (200, 320)])
 def test_bf16_wide_heads_with_projection_shapes_outside_the_mfma_family(hidden, ffn):
     """head_dim 64 suits the MFMA attention, but hidden / ffn are not multiples of 64, so the projections run on the
