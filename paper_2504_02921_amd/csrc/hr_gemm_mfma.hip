@@ -7,10 +7,10 @@
 // Both operands are K-contiguous, which is exactly the MFMA operand order (a lane holds 8
 // consecutive k of one row / column), so tiles go global -> LDS -> registers without transposes.
 //
-// Tiling: BM x BN x 64 macro tiles of 32 x 32 blocks of v_mfma_f32_32x32x16_f16: 256 x 256 with 8 wavefronts
+// Tiling: BM x BN x 64 macro tiles of 16 x 16 blocks of v_mfma_f32_16x16x32_f16: 256 x 256 with 8 wavefronts
 // (one workgroup per CU), 320 x 256 with 8 for residual-add and long-K gate/up launches where it saves rounds of the chip,
-// 128 x 128 with 4 (two per CU), wider-than-tall shapes for 128-wide heads, and ring variants with 3-5 LDS stages for
-// launches of few rows; the launcher picks per call.  LDS rows are 64 k
+// 128 x 128 with 4 (two per CU), wider-than-tall shapes for 128-wide heads, and ring variants with 3-18 LDS stages for
+// launches of few rows; choose_gemm_launch picks per call.  LDS rows are 64 k
 // (128 B) with the 16-byte chunk index XOR-swizzled by the row pair ((row >> 1) & 7): LDS serves
 // 256 bytes per cycle to 16 lanes of a ds_read_b128, i.e. two 128-byte rows side by side, so 16
 // consecutive rows must use 8 different chunk positions per row parity (measured: 217 B/clk/CU with
@@ -105,7 +105,7 @@ __device__ __forceinline__ void x_prefetch(float4 (&xv)[CHUNKS], const GemmArgs&
     for (int it = 0; it < CHUNKS; ++it) {
         const int L = it * NT + threadIdx.x, row = L / CPRW, pch = L % CPRW;
         const int64_t grow = min(tile_m0 + row, a.M - 1);
-        const int col = min(tile_n0 + ((pch ^ (row & 15)) << 2), a.N - 4);
+        const int col = min(tile_n0 + ((pch ^ (row & (min(CPRW, 16) - 1))) << 2), a.N - 4);
         xv[it] = *(const float4*)(a.x + grow * a.N + col);
     }
 }
@@ -141,8 +141,9 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
         constexpr int CW = BN / PASSES;                 // slab width in columns
         constexpr int CPRW = CW / 4;                    // 16-byte chunks per slab row
         constexpr int ITER = BM * CPRW / NT;
-        constexpr int NG = ITER % 4 == 0 ? 4 : 5;       // register groups of the x update (320-row tiles: 10 = 5 x 2)
-        static_assert(EPI != EPI_RESID_ADD || ((CW % TN == 0 || TN % CW == 0) && CPRW % 16 == 0 && (BM * CPRW) % (NG * NT) == 0 && BM * CW * 4 <= LDS_BYTES),
+        constexpr int NG = ITER == 1 ? 1 : ITER % 4 == 0 ? 4 : 5;       // register groups of the x update (320-row tiles: 10 = 5 x 2)
+        constexpr int SWZ = CPRW < 16 ? CPRW - 1 : 15;
+        static_assert(EPI != EPI_RESID_ADD || ((CW % TN == 0 || TN % CW == 0) && (CPRW == 8 || CPRW % 16 == 0) && (BM * CPRW) % (NG * NT) == 0 && BM * CW * 4 <= LDS_BYTES),
                       "slab shape");
         float* stage = (float*)smem;
 #pragma unroll
@@ -157,7 +158,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
                 for (int it = 0; it < G; ++it) {
                     const int L = (first + it) * NT + tid;
                     const int row = L / CPRW, pch = L % CPRW;
-                    int col = tile_n0 + p * CW + ((pch ^ (row & 15)) << 2);
+                    int col = tile_n0 + p * CW + ((pch ^ (row & SWZ)) << 2);
                     int64_t grow = tile_m0 + row;
                     grow = grow < a.M ? grow : a.M - 1;
                     col = col < a.N ? col : a.N - 4;
@@ -169,7 +170,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
                 for (int it = 0; it < G; ++it) {
                     const int L = (first + it) * NT + tid;
                     const int row = L / CPRW, pch = L % CPRW;
-                    const int col = tile_n0 + p * CW + ((pch ^ (row & 15)) << 2);
+                    const int col = tile_n0 + p * CW + ((pch ^ (row & SWZ)) << 2);
                     const int64_t grow = tile_m0 + row;
                     if (grow >= a.M || col >= a.N) continue;        // N is a multiple of 8: whole chunks
                     const float4 c = *(const float4*)(stage + row * CW + (pch << 2));
@@ -198,7 +199,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) {
                         const int ch = (c_off + j * 16) >> 2;
-                        *(floatx4*)(stage + lr * CW + ((ch ^ (lr & 15)) << 2)) = acc[i][j0 + j];
+                        *(floatx4*)(stage + lr * CW + ((ch ^ (lr & SWZ)) << 2)) = acc[i][j0 + j];
                     }
                 }
             }
@@ -621,6 +622,11 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 // it: the tiles of one column, neighbours on one XCD, take turns, so a k-tile's lines are in their L2 when the ring asks.
 // The ring alone has 128 KiB in flight, one 64 x 64 k-tile per ~590 cycles at the ~2.3 us that a first touch of HBM takes.
 // Down projection, 640 rows: 0.5B shape 23.1 -> 19.9 us, 8B shape 142 -> 117 us.
+//
+// 32 x 32 tiles, 18 stages, take residual-add launches that fit one round with them: twice the k-tiles in flight, half the bytes
+// to deliver per k-tile and four times the workgroups.  Down projection, 0.5B shape (K = 4864, times with two event records
+// around the launch): 65 rows 20.0 -> 12.9 us, 288 rows 22.3 -> 15.5; 8B shape (K = 14336), 40 rows 59.7 -> 33.1.  More rows than a
+// round holds pay for A and W read twice as often: 350 rows 21.7 -> 22.5, 640 rows 21.9 -> 31.2 us.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
@@ -631,7 +637,7 @@ __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) ge
     constexpr int KS = BK / 32;
     constexpr int LPT = PA + PB;                    // loads per thread and k-tile
     static_assert(RPP % 16 == 0 && BM % RPP == 0 && BN % RPP == 0, "loader shape");
-    static_assert(NS >= 2 && NS <= 10 && (NS - 1) * LPT < 64, "the load counter has six bits");
+    static_assert(NS >= 2 && (NS - 1) * LPT < 64, "the load counter has six bits");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     half_t* sA = (half_t*)smem;                         // [NS][BM][BK]
     half_t* sB = sA + NS * BM * BK;                     // [NS][BN][BK]
@@ -770,8 +776,12 @@ __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) ge
 #pragma unroll
     for (int s = 0; s < NS; ++s)
         if (s < nk) dma(s, s);
-    if (nk >= NS) __builtin_amdgcn_s_waitcnt((((NS - 1) * LPT) & 15) | ((((NS - 1) * LPT) >> 4) << 14) | 0x0F70);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    auto first_landed = [&](auto self, auto r_c) -> void {          // R k-tiles requested behind the first
+        constexpr int R = decltype(r_c)::value;
+        if (R == 0 || nk > R) __builtin_amdgcn_s_waitcnt(((R * LPT) & 15) | (((R * LPT) >> 4) << 14) | 0x0F70);
+        else if constexpr (R > 0) self(self, integral_constant<int, R - 1>{});
+    };
+    first_landed(first_landed, integral_constant<int, NS - 1>{});
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if ((nk - 1) & 1) fload(1, 0);
@@ -834,13 +844,14 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
 
 // The reading-ahead wavefront pays where several tiles share a column of W and the k loop is long: with two row tiles it
 // cannot keep up (65 rows, K = 4864: 17.1 us without, 22.2 with), at K = 4096 it is worth -3 to +5 %, from K = 4864 on -14 to -18 %.
-inline bool use_ahead(const GemmArgs& a, int tiles_m) { return tiles_m >= 4 && a.K > 4096; }
+// The 32-row tiles are for fewer rows than that.
+inline bool use_ahead(const GemmArgs& a, int bm, int tiles_m) { return bm >= 64 && tiles_m >= 4 && a.K > 4096; }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
-    const bool ahead = EPI == EPI_RESID_ADD && use_ahead(a, tiles_m);
+    const bool ahead = EPI == EPI_RESID_ADD && use_ahead(a, BM, tiles_m);
     constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (EPI == EPI_RESID_ADD ? kAheadLds : 0);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS>, lds_most, attr_done); e != hipSuccess) return e;
@@ -928,6 +939,7 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                     case GT_RING128: e = launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(r, st); break;
                     case GT_RING64_128: e = launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(r, st); break;
                     case GT_RING64: e = launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(r, st); break;
+                    case GT_RING32: e = launch_ring<EPI_RESID_ADD, 32, 32, 2, 2, 1, 18>(r, st); break;
                     default: break;
                 }
                 break;

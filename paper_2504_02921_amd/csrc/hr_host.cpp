@@ -450,10 +450,11 @@ struct GemmShape {
 // Measured (MI355X, full rounds, weights from HBM).  256 x 256 is the most efficient per output; 320 x 256 equals it per output
 // and takes other row counts in whole rounds (not for short k loops behind gate / up, whose 256-row form is
 // persistent); the two-per-CU tile costs 1.2-1.4 times as much per output but comes in quarter steps; the ring shapes
-// run one workgroup per CU and are what short launches take.
+// run one workgroup per CU and are what short launches take (32 x 32 where all tiles fit one round).
 const GemmShape kResidShapes[] = {{GT_BIG, 256, 256, 1, 21.3f, 0.0245f, 0},      {GT_TALL, 320, 256, 1, 19.0f, 0.0309f, 0},
                                   {GT_SMALL, 128, 128, 2, 6.0f, 0.0175f, 0},     {GT_RING128, 128, 128, 1, 8.6f, 0.0098f, 0},
-                                  {GT_RING64_128, 64, 128, 1, 5.3f, 0.0064f, 0}, {GT_RING64, 64, 64, 1, 3.5f, 0.0042f, 0}};
+                                  {GT_RING64_128, 64, 128, 1, 5.3f, 0.0064f, 0}, {GT_RING64, 64, 64, 1, 3.5f, 0.0042f, 0},
+                                  {GT_RING32, 32, 32, 1, 3.3f, 0.0024f, 0}};
 const GemmShape kSwigluShapes[] = {{GT_BIG, 256, 256, 1, 4.9f, 0.0239f, 0},          {GT_TALL, 320, 256, 1, 5.0f, 0.0295f, 2048},
                                    {GT_SMALL, 128, 128, 2, 0.5f, 0.0177f, 0},         {GT_RING128_256, 128, 256, 1, 4.0f, 0.0170f, 0},
                                    {GT_RING128, 128, 128, 1, 3.5f, 0.0092f, 0},       {GT_RING64_128, 64, 128, 1, 3.5f, 0.0064f, 0}};
