@@ -362,6 +362,8 @@ struct PageIdChunk { int32_t ids[256]; };   // page ids travel as kernel argumen
 // ------------------------------------------------------------------------------------------------
 constexpr int kSlab = 128, kSlabLd = kSlab + 8;
 template <typename T> using Word8 = T __attribute__((ext_vector_type(8)));
+// eight elements of a caller's tensor: such a tensor may be a view that starts at any element
+template <typename T> struct __attribute__((packed, aligned(sizeof(T)))) Loose8 { Word8<T> w; };
 // 16-bit pools: the caller's bf16 values are stored as half (exact for |x| in [2^-14, 65504]; smaller magnitudes keep an
 // absolute error below 2^-25, larger ones become infinity; both are counted).  Where all eight values are zero or in that
 // range, which is the ordinary case, the conversion is exact in any rounding mode and nothing has to be counted.
@@ -420,7 +422,7 @@ __global__ void __launch_bounds__(256) kv_scatter_kernel(KVT* __restrict__ pool,
         if (col < cols) {
             if (tok < doc_len) {
                 const size_t src = ((size_t)layer * doc_len + tok) * cols + col;
-                const Word8<KVS> ks8 = *(const Word8<KVS>*)(k + src), vs8 = *(const Word8<KVS>*)(v + src);
+                const Word8<KVS> ks8 = ((const Loose8<KVS>*)(k + src))->w, vs8 = ((const Loose8<KVS>*)(v + src))->w;
                 if constexpr (sizeof(KVT) == 2) {
                     convert_half8(ks8, kw, over, under, nonfinite);
                     convert_half8(vs8, vw, over, under, nonfinite);
@@ -570,8 +572,8 @@ __global__ void __launch_bounds__(256) kv_gather_kernel(const KVT* __restrict__ 
     __syncthreads();
     if (mine) {
         const size_t o = ((size_t)layer * doc_len + tok) * cols + col;
-        *(Word8<KVT>*)(k + o) = kw;
-        *(Word8<KVT>*)(v + o) = turn[t * (kSlabLd / 8) + (tid & 15)];
+        ((Loose8<KVT>*)(k + o))->w = kw;
+        ((Loose8<KVT>*)(v + o))->w = turn[t * (kSlabLd / 8) + (tid & 15)];
     }
     if (scales && slab == 0) {
         for (int h = tid; h < n_kv; h += 256) {

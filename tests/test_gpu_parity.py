@@ -988,3 +988,29 @@ def test_two_model_handles_driven_from_two_host_threads_score_independently():
         if other is not None:
             other.close()
         case.close()
+
+
+@pytest.mark.parametrize("kv", ["f32", "bf16", "fp8"])
+def test_pool_write_takes_views_that_start_at_any_element(kv):
+    """The sources of a pool write need no alignment beyond their element's: a contiguous view one element into a buffer
+    writes the same pages as an aligned copy of it."""
+    import torch
+    from paper_2504_02921_amd import binding as hb
+    L, n_kv, d, n_tok = 2, 3, 16, 37
+    shape, n = (L, n_tok, n_kv, d), L * n_tok * n_kv * d
+    gen = torch.Generator().manual_seed(5)
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "fp8": torch.uint8}[kv]
+    draw = lambda: (torch.randint(0, 120, (n + 1,), generator=gen, dtype=torch.uint8) if kv == "fp8"  # noqa: E731
+                    else torch.randn(n + 1, generator=gen).to(dt)).to("cuda:0")
+    k, v = draw()[1:].view(shape), draw()[1:].view(shape)
+    scales = [torch.full((L, 3, n_kv), 0.5, device="cuda:0") for _ in range(2)] if kv == "fp8" else [None, None]
+    pages = np.array([4, 0, 2], np.int32)
+    got = []
+    for ks, vs in ((k, v), (k.clone(), v.clone())):
+        pool = hb.KVPool(L, n_kv, d, 5, kv, "cuda:0")
+        pool.write(n_tok, pages, ks, vs, *scales)
+        got.append([t.cpu() for t in pool.read(n_tok, pages) if t is not None])
+        pool.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    want = k.cpu() if kv != "bf16" else k.cpu().to(torch.float16)
+    assert torch.equal(got[0][0], want)
