@@ -242,6 +242,14 @@ __global__ void __launch_bounds__(NW * 64) attn_f32_kernel(const float* __restri
             for (int c = 0; c < CB; ++c) kv[c] = *(const floatx4*)(kb + k_elem(r, c * 16 + 4 * kg, D, 4));
 #pragma unroll
             for (int c = 0; c < CB; ++c) vv[c] = *(const floatx4*)(vb + v_elem(4 * kg, c * 16 + r, D));     // keys 4 kg .. + 3
+            if (lim < kPageTokens - 1) {                       // the document ends inside this page: what lies behind may be infinite
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (4 * kg + e > lim) {
+#pragma unroll
+                        for (int c = 0; c < CB; ++c) vv[c][e] = 0.f;
+                    }
+            }
         } else {
             const int j0 = (tile - n_pages) * 16;
             lim = tok - j0;

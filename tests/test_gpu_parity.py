@@ -79,6 +79,39 @@ def test_fp32_page_aligned_and_single_token_edges():
         case.close()
 
 
+@pytest.mark.parametrize("n_q,n_kv,d", [(4, 2, 16), (4, 2, 32), (4, 1, 64)])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_fp32_keys_behind_a_documents_end_are_not_read(n_q, n_kv, d, bad):
+    """A document may be scored at less than its written length: what its last page holds behind that, infinities and NaN
+    included, does not reach the score (a masked key's probability is 0, but 0 times an infinite value is not)."""
+    import torch
+    from paper_2504_02921_amd import binding as hb
+    model = small_model(n_q=n_q, n_kv=n_kv, d=d)
+    w = wlmod.SeededWeights(model, seed=2, std=0.08, gain_jitter=0.1)
+    m = hb.Model(model, w, "cuda:0")
+    gen = torch.Generator().manual_seed(d)
+    written, used = 48, np.array([33, 40, 46, 47, 48], np.int32)
+    shape = (model.n_layers, written, n_kv, d)
+    docs = [(torch.randn(shape, generator=gen), torch.randn(shape, generator=gen)) for _ in used]
+    rng = np.random.default_rng(d)
+    q_lens = rng.integers(1, 9, len(used)).astype(np.int32)
+    toks = rng.integers(0, model.vocab, int(q_lens.sum())).astype(np.int32)
+    table = np.arange(3 * len(used), dtype=np.int32).reshape(len(used), 3)
+    got = []
+    for fill in (0.0, bad):
+        pool = hb.KVPool(model.n_layers, n_kv, d, 3 * len(used), "f32", "cuda:0")
+        for i, (k, v) in enumerate(docs):
+            k, v = k.clone(), v.clone()
+            k[:, used[i]:] = fill
+            v[:, used[i]:] = fill
+            pool.write(written, table[i], k.cuda(), v.cuda())
+        got.append(m.score(pool, table, used, toks, q_lens).cpu().numpy())
+        pool.close()
+    m.close()
+    assert np.all(np.isfinite(got[0]))
+    np.testing.assert_array_equal(got[0], got[1])
+
+
 def test_bf16_small_model_real_document_kv():
     model = small_model(dtype="bf16", n_layers=3, hidden=256, n_q=8, n_kv=2, d=32, ffn=352)
     cfg = wlmod.WorkloadCfg("bf16_small", model, 3, 4, (20, 90), (3, 12), "bf16", seed=3)
