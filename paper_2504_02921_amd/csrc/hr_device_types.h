@@ -11,6 +11,11 @@ namespace hr {
 typedef __bf16 bf16_t;      // storage type of the caller's 16-bit weights, embedding and KV
 typedef _Float16 half_t;    // the library's 16-bit compute / activation type (MFMA operand type)
 
+// N elements of memory the caller owns (weights, K/V): such an array may be a view that starts at any element.  Vector loads
+// of the hardware take element alignment too, so nothing is lost by saying so.
+template <typename T, int N> using VecN = T __attribute__((ext_vector_type(N)));
+template <typename T, int N> struct __attribute__((packed, aligned(sizeof(T)))) Loose { VecN<T, N> w; };
+
 template <typename T> __device__ __forceinline__ float to_float(T v);
 template <> __device__ __forceinline__ float to_float<float>(float v) { return v; }
 template <> __device__ __forceinline__ float to_float<bf16_t>(bf16_t v) { return (float)v; }

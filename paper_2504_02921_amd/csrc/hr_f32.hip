@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(F32GemmArgs a) {
             for (int i = 0; i < MI; ++i) av[s][i] = load4(pa[i], k, K);
 #pragma unroll
             for (int j = 0; j < NI; ++j) wv[s][j] = load4(pw[j], k, K);
-            if constexpr (NORM) gv[s] = load4(a.gain, k, K);
+            if constexpr (NORM) gv[s] = ((const Loose<float, 4>*)(a.gain + min(k, K - 4)))->w;
         }
 #pragma unroll
         for (int s = 0; s < UN; ++s) {

@@ -42,14 +42,9 @@ __global__ void __launch_bounds__(256) prologue_kernel(const T* __restrict__ E, 
     }
     const T* src = E + (size_t)tok_id[b] * H;
     float* dst = x + (size_t)b * H;
-    if (H % 4 == 0) {
-        typedef __attribute__((ext_vector_type(4))) T tx4;
-        for (int c = threadIdx.x; c < H / 4; c += 256) {
-            const tx4 e = ((const tx4*)src)[c];
-            ((float4*)dst)[c] = make_float4(to_float<T>(e[0]), to_float<T>(e[1]), to_float<T>(e[2]), to_float<T>(e[3]));
-        }
-    } else {
-        for (int c = threadIdx.x; c < H; c += 256) dst[c] = to_float(src[c]);
+    for (int c = threadIdx.x; c < H / 4; c += 256) {               // H is a multiple of 8
+        const VecN<T, 4> e = ((const Loose<T, 4>*)src)[c].w;
+        ((float4*)dst)[c] = make_float4(to_float<T>(e[0]), to_float<T>(e[1]), to_float<T>(e[2]), to_float<T>(e[3]));
     }
     for (int j = threadIdx.x; j < half; j += 256) {
         const double inv_freq = pow(base, -(double)j / (double)half);
@@ -106,7 +101,7 @@ __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const float* __restric
     __shared__ float red[4];
     const size_t t = blockIdx.x;
     const float4* xr = (const float4*)(x + (rows ? (size_t)rows[t] : t) * H);
-    const float4* gr = (const float4*)gain;
+    const Loose<float, 4>* gr = (const Loose<float, 4>*)gain;
     const int n4 = H >> 2;
     float4 v[VPT];
     float ss = 0.f;
@@ -114,7 +109,8 @@ __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const float* __restric
     for (int i = 0; i < VPT; ++i) {
         const int c = threadIdx.x + i * 256;
         v[i] = c < n4 ? xr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
-        ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+        // the order is written out: which product of a plain sum is rounded first is the compiler's choice
+        ss += __fmaf_rn(v[i].w, v[i].w, __fmaf_rn(v[i].z, v[i].z, __fmaf_rn(v[i].x, v[i].x, __fmul_rn(v[i].y, v[i].y))));
     }
     ss = block_sum_256(ss, red);
     const float rs = 1.0f / sqrtf(ss / (float)H + eps);
@@ -124,12 +120,12 @@ __global__ void __launch_bounds__(256) rmsnorm_vec_kernel(const float* __restric
     for (int i = 0; i < VPT; ++i) {
         const int c = threadIdx.x + i * 256;
         if (c < n4) {
-            const float4 g = gr[c];
+            const VecN<float, 4> g = gr[c].w;
             h4 o;
-            o[0] = from_float<half_t>(v[i].x * rs * g.x);
-            o[1] = from_float<half_t>(v[i].y * rs * g.y);
-            o[2] = from_float<half_t>(v[i].z * rs * g.z);
-            o[3] = from_float<half_t>(v[i].w * rs * g.w);
+            o[0] = from_float<half_t>(v[i].x * rs * g[0]);
+            o[1] = from_float<half_t>(v[i].y * rs * g[1]);
+            o[2] = from_float<half_t>(v[i].z * rs * g[2]);
+            o[3] = from_float<half_t>(v[i].w * rs * g[3]);
             yr[c] = o;
         }
     }
@@ -361,9 +357,8 @@ struct PageIdChunk { int32_t ids[256]; };   // page ids travel as kernel argumen
 // grid: (n_pages, n_layers * slabs); 256 threads
 // ------------------------------------------------------------------------------------------------
 constexpr int kSlab = 128, kSlabLd = kSlab + 8;
-template <typename T> using Word8 = T __attribute__((ext_vector_type(8)));
-// eight elements of a caller's tensor: such a tensor may be a view that starts at any element
-template <typename T> struct __attribute__((packed, aligned(sizeof(T)))) Loose8 { Word8<T> w; };
+template <typename T> using Word8 = VecN<T, 8>;
+template <typename T> using Loose8 = Loose<T, 8>;
 // 16-bit pools: the caller's bf16 values are stored as half (exact for |x| in [2^-14, 65504]; smaller magnitudes keep an
 // absolute error below 2^-25, larger ones become infinity; both are counted).  Where all eight values are zero or in that
 // range, which is the ordinary case, the conversion is exact in any rounding mode and nothing has to be counted.

@@ -1047,3 +1047,38 @@ def test_pool_write_takes_views_that_start_at_any_element(kv):
     assert all(torch.equal(a, b) for a, b in zip(*got))
     want = k.cpu() if kv != "bf16" else k.cpu().to(torch.float16)
     assert torch.equal(got[0][0], want)
+
+
+@pytest.mark.parametrize("dtype,hidden,ffn,d", [("f32", 128, 176, 32), ("bf16", 256, 320, 64), ("bf16", 200, 320, 64)])
+def test_borrowed_weights_may_start_at_any_element(dtype, hidden, ffn, d, monkeypatch):
+    """The embedding and the norm gains stay in the caller's arrays, which may be views one element into a buffer: same
+    score bits as with aligned copies (fp32 pass, MFMA pass, 16-bit projections outside the MFMA family)."""
+    import torch
+    model = small_model(dtype=dtype, hidden=hidden, n_q=4, n_kv=2, d=d, ffn=ffn)
+    cfg = wlmod.WorkloadCfg("views", model, 2, 3, (5, 60), (1, 20), dtype, seed=3)
+    w = wlmod.SeededWeights(model, seed=4, std=0.05, gain_jitter=0.1)
+    wl = wlmod.make_workload(cfg)
+
+    class View:
+        def __init__(self, a):
+            self.a = a
+
+        def to(self, device, dtype):
+            v = torch.empty(self.a.size + 1, dtype=dtype, device=device)[1:].view(self.a.shape)
+            v.copy_(torch.as_tensor(self.a))
+            return v
+
+    got = []
+    for views in (False, True):
+        with monkeypatch.context() as mp:
+            if views:
+                mp.setattr(torch, "from_numpy", View)
+            case = H.Case(wl, w)
+        try:
+            assert (case.model.embedding.data_ptr() % 16 == 0 and case.model.norm1[0].data_ptr() % 16 == 0) != views
+            case.fill_from_prefill()
+            got.append(case.gpu_scores())
+        finally:
+            case.close()
+    H.assert_scores_close(got[0], case.oracle_scores(), H.TOL[dtype], "views")
+    np.testing.assert_array_equal(got[0], got[1])
