@@ -205,7 +205,7 @@ hipError_t launch_f32_shape(const F32GemmArgs& a, hipStream_t st) {
 template <int D, int NW>
 __global__ void __launch_bounds__(NW * 64) attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_new,
                                                            const float* __restrict__ v_new, float* __restrict__ o, MetaView mv,
-                                                           PoolView pv, int layer, int n_q, int last_only) {
+                                                           PoolView pv, int layer, int n_q, int last_only, int block0) {
     constexpr int CB = D / 16, LD = D + 4;
     __shared__ __attribute__((aligned(16))) float so[NW][16 * LD];
     __shared__ float sml[2][NW][16];
@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(NW * 64) attn_f32_kernel(const float* __restri
     const int p = blockIdx.x, h = blockIdx.y, n_kv = pv.n_kv, g = n_q / n_kv;
     const int t0 = mv.cu[p], q_len = mv.cu[p + 1] - t0, Dl = mv.prefix_len[p];
     const int row_first = last_only ? (q_len - 1) * g : 0, rows = last_only ? g : q_len * g;
-    const int row0 = blockIdx.z * 16;
+    const int row0 = (block0 + (int)blockIdx.z) * 16;
     if (row0 >= rows) return;
     const int row = row_first + min(row0 + r, rows - 1);       // this lane's query row
     const int tok = row / g;
@@ -349,14 +349,19 @@ hipError_t launch_attn_f32(const float* q, const float* k_new, const float* v_ne
     if (mv.T == 0) return hipSuccess;
     const int g = n_q / pv.n_kv;
     const int64_t rows = last_only ? g : (int64_t)g * max_q_len;
-    const dim3 grid((unsigned)mv.n_seq, (unsigned)pv.n_kv, (unsigned)((rows + 15) / 16));
-    switch (pv.d) {
-        case 16: attn_f32_kernel<16, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only); break;
-        case 32: attn_f32_kernel<32, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only); break;
-        case 64: attn_f32_kernel<64, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only); break;
-        default: return hipErrorInvalidValue;
+    // one launch as a rule: a grid holds 65535 row blocks in its third dimension
+    const int64_t blocks = (rows + 15) / 16;
+    for (int64_t b0 = 0; b0 < blocks; b0 += 65535) {
+        const dim3 grid((unsigned)mv.n_seq, (unsigned)pv.n_kv, (unsigned)std::min<int64_t>(blocks - b0, 65535));
+        switch (pv.d) {
+            case 16: attn_f32_kernel<16, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only, (int)b0); break;
+            case 32: attn_f32_kernel<32, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only, (int)b0); break;
+            case 64: attn_f32_kernel<64, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only, (int)b0); break;
+            default: return hipErrorInvalidValue;
+        }
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace hr

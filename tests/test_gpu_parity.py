@@ -79,6 +79,30 @@ def test_fp32_page_aligned_and_single_token_edges():
         case.close()
 
 
+def test_fp32_query_of_more_row_blocks_than_a_grid_dimension_holds(monkeypatch):
+    """8200 query tokens x 128 heads on one kv head are 65600 blocks of 16 attention rows; the same score comes from the
+    generic kernels, which run one workgroup per (token, head)."""
+    import torch
+    from paper_2504_02921_amd import binding as hb
+    n_tok, doc = 8200, 40
+    model = small_model(hidden=64, n_q=128, n_kv=1, d=16, ffn=64)
+    w = wlmod.SeededWeights(model, seed=2, std=0.08, gain_jitter=0.1)
+    gen = torch.Generator().manual_seed(3)
+    k, v = (torch.randn((model.n_layers, doc, 1, 16), generator=gen).cuda() for _ in range(2))
+    toks = np.random.default_rng(4).integers(0, model.vocab, n_tok).astype(np.int32)
+    got = []
+    for generic in ("0", "1"):
+        monkeypatch.setenv("HR_FORCE_GENERIC", generic)
+        m = hb.Model(model, w, "cuda:0")
+        pool = hb.KVPool(model.n_layers, 1, 16, 3, "f32", "cuda:0")
+        pool.write(doc, np.arange(3, dtype=np.int32), k, v)
+        s = m.score(pool, np.arange(3, dtype=np.int32)[None], np.array([doc]), toks, np.array([n_tok]))
+        got.append(float(s.cpu()[0]))
+        m.close()
+        pool.close()
+    assert abs(got[0]) > 1e-2 and abs(got[0] - got[1]) <= H.TOL["f32"], got
+
+
 @pytest.mark.parametrize("n_q,n_kv,d", [(4, 2, 16), (4, 2, 32), (4, 1, 64)])
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
 def test_fp32_keys_behind_a_documents_end_are_not_read(n_q, n_kv, d, bad):
