@@ -261,7 +261,7 @@ size_t hr_rerank_workspace_bytes(const hr_model* model, int32_t n_pairs, int64_t
  * Pairs of one call with identical query token strings (the same query against several candidates) share the first
  * layer's normalised rows and pre-RoPE q / k / v projections, which are equal for equal strings; each pair's rotation for
  * its own positions doc_lens[p] + i is applied afterwards.  Same bits again.
- * A call with at least 8192 query tokens on the MFMA path whose O / down projection tiles would leave more than 15 % of
+ * A call with at least 8192 query tokens on the MFMA path whose O / down projection tiles would leave more than 20 % of
  * the device's workgroup slots empty in the rounds they take runs as two halves of the pairs, the first on `stream`,
  * the second on a stream of the library's own that starts behind the work already enqueued on `stream` and that
  * `stream` waits for before anything enqueued after the call (see hr_rerank_set_streams); to the caller the call

@@ -60,7 +60,7 @@ constexpr int64_t kMfmaMaxKeys = 1 << 20;
 constexpr int64_t kChunkedMaxKeys = 1 << 15;   // longest sequence of the chunked passes (no-reuse pass, document prefill): bounds
                                                // the self page table, which has one row per 32- or 64-token chunk
 constexpr int64_t kSplitMinTokens = 8192;      // query tokens from which a scoring call is cut in two halves
-constexpr double kSplitMaxFill = 0.85;         // ... when the N = hidden GEMMs' tiles fill less than this share of their rounds
+constexpr double kSplitMaxFill = 0.8;          // ... when the N = hidden GEMMs' tiles fill less than this share of their rounds
 constexpr size_t kSplitSlackBytes = (size_t)1 << 20;   // what two carvings of a workspace may need beyond one (alignment gaps,
                                                        // the larger group-plan room of calls with few pairs)
 
@@ -673,9 +673,12 @@ size_t hr_rerank_workspace_bytes(const hr_model* m, int32_t n_pairs, int64_t tot
 }
 
 // Whether a scoring call of T query tokens is cut in two halves (given the MFMA attention and at least two pairs): when
-// the tiles of the N = hidden GEMMs would leave more than 15 % of the workgroup slots of their rounds empty.
+// the tiles of the N = hidden GEMMs, as they are launched, would leave more than 20 % of the workgroup slots of their
+// rounds empty.
 static bool split_wanted(const hr_model* m, int64_t T) {
-    return m->n_streams >= 2 && m->mfma_gemm && T >= kSplitMinTokens && hr::gemm_resid_fill(T, m->cfg.hidden) < kSplitMaxFill;
+    const hr_model_cfg& c = m->cfg;
+    return m->n_streams >= 2 && m->mfma_gemm && T >= kSplitMinTokens &&
+           hr::gemm_resid_fill(T, c.hidden, c.n_q_heads * c.head_dim, c.ffn, hr::device_cu_count()) < kSplitMaxFill;
 }
 
 // One contiguous part of a scoring call.  prepare: its metadata (already validated) is built at `stage` and its upload to the
@@ -832,9 +835,11 @@ int hr_rerank_score(hr_model* m, const hr_pool* pool, int32_t n_pairs, const int
     // must first win back.
     int32_t n_a = n_pairs;
     int64_t T_a = T;
-    // Measured, two streams against one, by the fill of those rounds: 0.5B shape 62 % -> -11 %, 78 % -> -5 %, 94 % ->
-    // +9 % and -3 %, 100 % -> -0.7 %, -2 %, +2 %; 8B shape 83 % -> -1.5 %, 87 % -> 0, 92 % -> +5.4 %, 94 % -> -1.2 %,
-    // +3.8 %, +1 %, 98 % -> +3 %, 100 % -> 0, +3.5 %.
+    // Measured, time on two streams against one, by the fill of those rounds (0.5B shape, 9728 .. 40960 query tokens, 32 a
+    // pair, whole calls): 58 % -> -6.2 %, 61 % -> -3.6 .. -6.1 %, 67 % -> -2.1 %, 73 % -> -1.6 .. -3.1 %, 79 % -> -1.3 %,
+    // 82 % -> +0.1 %, 85 % -> +0.6 %, 91 % -> +0.7 %, and without order above that: 87 % -> +5.0, -2.2 %, 95 % -> -2.4 %, 97 % ->
+    // -1.9, +1.2 %, 98 % -> +5.8 %, 100 % -> +0.3, -2.5, +2.4 %.  8B shape: every call of 8192 tokens or more fills its
+    // rounds (full rounds of large tiles, then the best shape for the rest), two streams +0.2 .. +10.5 %.
     if (mfma_attn && n_pairs >= 2 && split_wanted(m, T)) {
         int64_t t = 0;
         int32_t p = 0;

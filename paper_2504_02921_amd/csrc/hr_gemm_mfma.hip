@@ -874,8 +874,6 @@ int cu_count() {
 
 int device_cu_count() { return cu_count(); }
 
-double gemm_resid_fill(int64_t M, int N) { return gemm_tile_fill(M, N, cu_count()); }
-
 bool gemm_mfma_supported(const hr_model_cfg& c) {
     if (c.dtype != HR_BF16) return false;
     if (c.head_dim != 64 && c.head_dim != 128) return false;

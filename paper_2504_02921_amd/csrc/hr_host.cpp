@@ -515,28 +515,21 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) 
     return g;
 }
 
-TileChoice choose_gemm_tile(int64_t M, int N, int small_bn, bool tall_ok, int cus_) {
+double gemm_resid_fill(int64_t M, int N, int k_o, int k_down, int cus_) {
     const int64_t cus = cus_ > 0 ? cus_ : 1;
-    const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
-    const int64_t tall_tiles = ((M + 319) / 320) * ((N + 255) / 256);
-    const int64_t small_tiles = ((M + 127) / 128) * ((N + small_bn - 1) / small_bn);
-    const double big = (double)((big_tiles + cus - 1) / cus) * 256.0 * 256.0 * 1.0;
-    const double tall = (double)((tall_tiles + cus - 1) / cus) * 320.0 * 256.0 * 0.9;
-    const double small = (double)((small_tiles + 2 * cus - 1) / (2 * cus)) * 2.0 * 128.0 * small_bn * 1.14;
-    if (tall_ok && tall < big && tall <= small) return TILE_TALL;
-    return big <= small ? TILE_BIG : TILE_SMALL;
-}
-
-double gemm_tile_fill(int64_t M, int N, int cus_) {
-    const int64_t cus = cus_ > 0 ? cus_ : 1;
-    int64_t tiles = 0, slots = cus;
-    switch (choose_gemm_tile(M, N, 128, true, (int)cus)) {
-        case TILE_TALL: tiles = ((M + 319) / 320) * ((N + 255) / 256); break;
-        case TILE_BIG: tiles = ((M + 255) / 256) * ((N + 255) / 256); break;
-        case TILE_SMALL: tiles = ((M + 127) / 128) * ((N + 127) / 128); slots = 2 * cus; break;
+    double busy = 0.0, total = 0.0;
+    for (int K : {k_o, k_down}) {
+        const GemmLaunch g = choose_gemm_launch(GEMM_RESID, M, N, K, (int)cus);
+        for (int i = 0; i < g.n; ++i) {
+            const GemmShape* s = kResidShapes;
+            while (s->tile != g.part[i].tile) ++s;
+            const int64_t tiles = ((g.part[i].rows + s->bm - 1) / s->bm) * ((N + s->bn - 1) / s->bn), slots = cus * s->per_cu;
+            const double round = (double)s->c0 + (double)s->c1 * K;
+            busy += round * (double)tiles / (double)slots;
+            total += round * (double)((tiles + slots - 1) / slots);
+        }
     }
-    if (tiles <= 0) return 1.0;
-    return (double)tiles / (double)(((tiles + slots - 1) / slots) * slots);
+    return total > 0.0 ? busy / total : 1.0;
 }
 
 }  // namespace hr

@@ -170,14 +170,10 @@ struct GemmPart { GemmTile tile; int64_t rows; };
 struct GemmLaunch { int n = 0; GemmPart part[2]; };
 GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus);
 
-// ---- the measure by which a scoring call is cut in two halves: "big" = 256 x 256 tiles, "tall" = 320 x 256 (where the caller
-// allows it), "small" = 128 x small_bn, two workgroups per CU; cost = rounds x resident workgroups x tile area x relative
-// cost per output.
-enum TileChoice { TILE_SMALL, TILE_BIG, TILE_TALL };
-TileChoice choose_gemm_tile(int64_t M, int N, int small_bn, bool tall_ok, int cus);
-// Share of the workgroup slots that the tiles of an M x N residual GEMM fill in the rounds they take, in the shape
-// choose_gemm_tile picks for it (tall allowed): 1.0 = every round full.
-double gemm_tile_fill(int64_t M, int N, int cus);
+// The measure by which a scoring call is cut in two halves: the share of the workgroup slots that the O (K = k_o) and the down
+// projection's (K = k_down) tiles fill in the rounds they take, in the launches chosen above, weighted by the rounds' times.
+// 1.0 = every round full.
+double gemm_resid_fill(int64_t M, int N, int k_o, int k_down, int cus);
 // Writes the plan at dst (>= plan.ints() entries) in the order p0, blk_cu, sub_cu, blk_seq, blk_row0, sub_page, sub_seq,
 // sub_key0.
 void store_group_plan(const GroupPlan& plan, int32_t* dst);

@@ -192,35 +192,23 @@ int main() {
     CHECK(hr::score_check_args(mc, pool, 2, table, 3, dls, qt, qls, 1 << 20, &T) == HR_ERR_TABLE_SHORT);
     hr_kv_pool_destroy(pool);
 
-    // tile shape choice: the chosen shape is the cheapest of the model, the tall tile only where allowed and only where it
-    // saves rounds, the fill of the rounds lies in (0, 1]; the cases the design names come out as stated
+    // the measure by which a call is cut in two halves follows the launches: in (0, 1], 1 where they leave no slot empty
     {
-        auto rounds = [](int64_t tiles, int64_t slots) { return (tiles + slots - 1) / slots; };
         std::srand(7);
         for (int it = 0; it < 2000; ++it) {
             const int64_t M = 1 + std::rand() % 120000;
-            const int N = 64 * (1 + std::rand() % 480);
-            const int cus = 8 * (1 + std::rand() % 40);
-            const hr::TileChoice no_tall = hr::choose_gemm_tile(M, N, 128, false, cus);
-            const hr::TileChoice any = hr::choose_gemm_tile(M, N, 128, true, cus);
-            CHECK(no_tall != hr::TILE_TALL);
-            if (any == hr::TILE_TALL) {
-                const int64_t big = ((M + 255) / 256) * ((N + 255) / 256), tall = ((M + 319) / 320) * ((N + 255) / 256);
-                CHECK(rounds(tall, cus) < rounds(big, cus));
-            } else {
-                CHECK(any == no_tall);
-            }
-            const double fill = hr::gemm_tile_fill(M, N, cus);
+            const int N = 64 * (1 + std::rand() % 480), ko = 64 * (1 + std::rand() % 80), kd = 64 * (1 + std::rand() % 230);
+            const double fill = hr::gemm_resid_fill(M, N, ko, kd, 8 * (1 + std::rand() % 40));
             CHECK(fill > 0.0 && fill <= 1.0);
         }
-        CHECK(hr::choose_gemm_tile(20480, 896, 128, true, 256) == hr::TILE_TALL);      // 320 big tiles = 2 rounds, 256 tall = 1
-        CHECK(hr::choose_gemm_tile(20480, 896, 128, false, 256) == hr::TILE_SMALL);     // 1120 small tiles in 3 rounds beat 2 big rounds
-        CHECK(hr::gemm_tile_fill(20480, 896, 256) == 1.0);
-        CHECK(hr::choose_gemm_tile(10240, 896, 128, true, 256) == hr::TILE_BIG);       // one round either way: the cheaper tile
-        CHECK(hr::choose_gemm_tile(12800, 4096, 128, true, 256) == hr::TILE_TALL);     // 800 -> 640 tiles, 4 -> 3 rounds
-        const double f8b = hr::gemm_tile_fill(12800, 4096, 256);
-        CHECK(f8b > 0.83 && f8b < 0.84);                                               // 640 of 768 slots
-        CHECK(hr::gemm_tile_fill(25600, 4096, 256) == 1.0);                            // 1280 tall tiles = 5 full rounds
+        CHECK(hr::gemm_resid_fill(20480, 896, 896, 4864, 256) == 1.0);          // 320 x 256: 256 tiles, one round
+        // 8B shape, 12800 tokens: three rounds of 256 x 256 and one of 64 x 128 for the last 512 rows, no slot empty
+        const hr::GemmLaunch d8 = hr::choose_gemm_launch(hr::GEMM_RESID, 12800, 4096, 14336, 256);
+        CHECK(d8.n == 2 && d8.part[0].rows == 12288 && d8.part[1].rows == 512);
+        CHECK(hr::gemm_resid_fill(12800, 4096, 4096, 14336, 256) == 1.0);
+        // 0.5B shape, 10240 tokens: O as 560 tiles of 128 x 128 in two rounds of 512, down as 160 tiles of 256 x 256 in one
+        const double f = hr::gemm_resid_fill(10240, 896, 896, 4864, 256);
+        CHECK(f > 0.59 && f < 0.62);
     }
     {   // GEMM launches: the parts cover the rows, in order, with shapes the epilogue has; a cut leaves whole rounds in front
         std::srand(11);
