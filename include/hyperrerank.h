@@ -422,8 +422,12 @@ int hr_profile_read(hr_model* model, double* ms_out, int64_t* launches_out);
  * can be dropped).  HR_ERR_INVALID_ARG on null or misaligned pointers or bytes < 1024. */
 int hr_probe_read_bandwidth(const void* src_dev, size_t bytes, void* sink_dev, size_t sink_bytes, int to_lds, void* stream);
 
-/* Name of the kernel family a model / pool combination runs: "mfma" or "generic" ("none" for a null handle); never
- * NULL.  The MFMA attention is only chosen together with the MFMA projections.  hr_attention_path answers for short
+/* Name of the kernel family a model / pool combination runs; never NULL:
+ *   "mfma"     16-bit models on the half matrix instructions
+ *   "f32"      fp32 models with heads of 16, 32 or 64 channels: the fused pass on the fp32 matrix instruction
+ *   "generic"  everything else, step by step (projections on the fp32 matrix instruction, the rest on the vector units)
+ *   "none"     a null handle
+ * The MFMA attention is only chosen together with the MFMA projections.  hr_attention_path answers for short
  * queries.  One attention work item holds 512 rows (query tokens x query heads per kv head) at 64-wide heads and 256 at
  * 128-wide heads; a scoring call spreads a longer query's rows over up to eight work items (each streams the document),
  * and beyond that (or with HR_NO_DOC_GROUPS=1, which switches the plan off that does the spreading) runs its attention on

@@ -89,6 +89,9 @@ bool use_mfma_attn(const hr_model* m, int kv_dtype, int max_new_len, bool may_cu
     return attn_mfma_supported(m->cfg, kv_dtype, max_new_len);
 }
 
+// fp32 models: the pass of hr_f32.hip (five launches a layer) instead of the step-by-step kernels
+bool use_fused_f32(const hr_model* m) { return !m->force_generic && f32_fused_supported(m->cfg); }
+
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 char* g_scratch_ptr[kMaxDevices] = {};      // device address of g_static_scratch, per HIP device
@@ -297,7 +300,6 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
     }
     const bool mfma_attn = use_mfma_attn(m, pv.kv_dtype, max_new_len, groups && groups->n_groups > 0);
     if (self_prefix && !mfma_attn) return HR_ERR_UNSUPPORTED_SHAPE;
-    const bool fused_f32 = !m->force_generic && f32_fused_supported(c);
     if (!mfma_attn && max_keys > kGenericMaxKeys) return HR_ERR_UNSUPPORTED_SHAPE;     // the generic attention keeps a row's scores in LDS
     // the shortened last layer needs one output row per sequence, the MFMA kernels, something to save (T > P), and
     // room for P fp32 rows in the q buffer
@@ -319,7 +321,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
     HR_TIMED(PC_EMBED, launch_prologue(dt, m->embedding, mv, x, H, rope, d, c.rope_base, k, mfma_attn ? kv_region : 0, src.host,
                                        (int32_t*)(wsb + ws.off_meta), src.ints, st));
     if (src.read_ev) HR_HIP(hipEventRecord(src.read_ev, st));
-    if (fused_f32) return run_layers_f32(m, pv, mv, ws, wsb, max_new_len, scores, st);
+    if (use_fused_f32(m)) return run_layers_f32(m, pv, mv, ws, wsb, max_new_len, scores, st);
     auto gemm_plain = [&](F32Epilogue epi, const void* A, const void* W, float* C, int N, int K) {
         F32GemmArgs a{};
         a.A = A; a.W = W; a.M = T; a.N = N; a.K = K; a.C = C;
@@ -1315,12 +1317,12 @@ const char* hr_last_error(void) { return g_last_error; }
 
 const char* hr_attention_path(const hr_model* m, const hr_pool* pool) {
     if (!m || !pool) return "none";
-    return use_mfma_attn(m, pool->cfg.kv_dtype, 1) ? "mfma" : "generic";
+    return use_mfma_attn(m, pool->cfg.kv_dtype, 1) ? "mfma" : use_fused_f32(m) ? "f32" : "generic";
 }
 
 const char* hr_gemm_path(const hr_model* m) {
     if (!m) return "none";
-    return m->mfma_gemm ? "mfma" : "generic";
+    return m->mfma_gemm ? "mfma" : use_fused_f32(m) ? "f32" : "generic";
 }
 
 }  // extern "C"

@@ -70,6 +70,26 @@ def test_fp32_projection_tiles_give_a_pair_the_same_bits_alone_and_in_a_batch(n_
     case.close()
 
 
+@pytest.mark.parametrize("n_q,n_kv,d,force,path", [
+    (4, 2, 48, "0", "generic"), (2, 1, 128, "0", "generic"), (2, 2, 256, "0", "generic"),     # head sizes the fused pass does not take
+    (4, 2, 64, "1", "generic"), (6, 2, 16, "1", "generic"),                                     # ... and ones that it would
+    (4, 2, 64, "0", "f32"), (6, 2, 16, "0", "f32"), (4, 1, 32, "0", "f32"),
+])
+def test_fp32_step_by_step_and_fused_passes(n_q, n_kv, d, force, path, monkeypatch):
+    """fp32 models run the fused pass or the step-by-step kernels, by head size and HR_FORCE_GENERIC; the handle says which.
+    Both match the oracle, and a pair scores the same bits alone and in the batch."""
+    monkeypatch.setenv("HR_FORCE_GENERIC", force)
+    model = small_model(n_q=n_q, n_kv=n_kv, d=d, hidden=88, ffn=104)
+    cfg = wlmod.WorkloadCfg("f32_paths", model, 3, 4, (1, 70), (1, 19), "f32", pool_docs=7, zipf_a=0.5, seed=d)
+    w = wlmod.SeededWeights(model, seed=5, std=0.08, gain_jitter=0.1)
+    case, got, want = run_case(cfg, w, H.TOL["f32"])
+    assert (case.model.gemm_path(), case.model.attention_path(case.pool)) == (path, path)
+    assert np.abs(want).max() > 1e-2
+    for i in (0, len(got) - 1):
+        assert np.array_equal(case.gpu_scores(case.wl.subset([i])), got[i:i + 1])
+    case.close()
+
+
 def test_fp32_page_aligned_and_single_token_edges():
     model = small_model()
     w = wlmod.SeededWeights(model, seed=2, std=0.08, gain_jitter=0.1)
