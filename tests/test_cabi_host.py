@@ -212,6 +212,10 @@ def test_null_handles_are_rejected_everywhere():
     fake = C.c_void_p(FAKE_DEV)
     for n_q, max_c, k in [(-1, 4, 1), (1, 0, 1), (1, 4097, 1), (1, 4, 0), (1, 4, 5)]:      # sizes out of range: rejected before any launch
         assert hb.lib.hr_rerank_topk(fake, fake, n_q, max_c, k, fake, None, None) == hb.HR_ERR_INVALID_ARG
+    assert hb.lib.hr_rerank_topk_host(None, None, 1, 4, 1, None, None, None) == hb.HR_ERR_INVALID_ARG
+    seg = np.array([0, 4], np.int32)
+    for n_q, max_c, k in [(-1, 4, 1), (1, 0, 1), (1, 4097, 1), (1, 4, 0), (1, 4, 5)]:
+        assert hb.lib.hr_rerank_topk_host(fake, i32p(seg), n_q, max_c, k, fake, None, None) == hb.HR_ERR_INVALID_ARG
     assert hb.lib.hr_attention_path(None, None).decode() == "none"
     assert hb.lib.hr_gemm_path(None).decode() == "none"
     hb.lib.hr_model_destroy(None)

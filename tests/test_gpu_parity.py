@@ -670,6 +670,35 @@ def test_pairs_sharing_a_document_are_batched_bit_identically(d, n_q, n_kv, kv, 
     np.testing.assert_array_equal(scores[0], scores[1])
 
 
+@pytest.mark.parametrize("n_queries,with_scores", [(1, True), (255, False), (256, True), (257, True), (257, False), (600, True)])
+def test_topk_with_offsets_on_the_device_and_on_the_host(n_queries, with_scores):
+    """hr_rerank_topk (offsets in device memory) and hr_rerank_topk_host (offsets as kernel arguments, 256 segments per
+    launch) on both sides of that bound: the oracle's indices and the scores at them."""
+    import torch
+    from paper_2504_02921_amd import binding as hb
+    rng = np.random.default_rng(n_queries)
+    k, max_c = 4, 12
+    seg = np.concatenate([[0], np.cumsum(rng.integers(0, max_c + 1, n_queries))]).astype(np.int32)
+    s = (np.round(rng.normal(size=int(seg[-1]) + 1) * 4) / 4).astype(np.float32)       # many ties
+    want = orr.topk(s.astype(np.float64), seg, k)
+    at = np.where(want >= 0, seg[:-1, None] + want, 0)
+    want_sc = np.where(want >= 0, s[at], np.float32(0))
+    dev, seg_dev = torch.from_numpy(s).to("cuda:0"), torch.from_numpy(seg).to("cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    for where in ("device", "host"):
+        idx = torch.full((n_queries, k), -9, dtype=torch.int32, device="cuda:0")
+        sc = torch.full((n_queries, k), -9.0, device="cuda:0") if with_scores else None
+        sc_ptr = sc.data_ptr() if with_scores else None
+        if where == "device":
+            st = hb.lib.hr_rerank_topk(dev.data_ptr(), seg_dev.data_ptr(), n_queries, max_c, k, idx.data_ptr(), sc_ptr, stream)
+        else:
+            st = hb.lib.hr_rerank_topk_host(dev.data_ptr(), seg.ctypes.data, n_queries, max_c, k, idx.data_ptr(), sc_ptr, stream)
+        assert st == hb.HR_OK
+        np.testing.assert_array_equal(idx.cpu().numpy(), want)
+        if with_scores:
+            np.testing.assert_array_equal(sc.cpu().numpy(), want_sc)
+
+
 def test_two_stream_halves_are_bit_identical_and_ordered_on_the_callers_stream():
     """A call with more than 8192 query tokens runs as two halves on two streams.  Scores must equal the single-stream
     run bit for bit and the oracle within the bar, work enqueued behind the call on the caller's stream (here the
