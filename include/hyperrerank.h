@@ -274,8 +274,9 @@ int hr_rerank_score(hr_model* model, const hr_pool* pool, int32_t n_pairs,
 /* ---- fixed-shape plans: a scoring call whose launches can be recorded once and replayed (Section 4.2: the static
  * [document prefix | query suffix] layout exists so that the reranker's execution can be captured ahead of time) ----
  * A plan fixes the shape of a call: the number of pairs and every pair's document and query length.  Which pages and
- * which query tokens it scores can change between runs.  hr_rerank_plan_run enqueues one host-to-device copy from a
- * pinned block the plan owns, and the kernels; it never waits on the host, allocates nothing and uses `stream` only,
+ * which query tokens it scores can change between runs.  hr_rerank_plan_run enqueues the kernels, the
+ * first of which reads a pinned block that the plan owns over the bus (plans of more than 1024 query tokens or 64 KiB of
+ * metadata: behind a host-to-device copy of that block); it never waits on the host, allocates nothing and uses `stream` only,
  * so it may be recorded into a HIP graph (stream capture) and replayed.  The work of a plan depends on the lengths
  * alone: pairs are not regrouped by shared documents or shared query strings as hr_rerank_score does, which changes no
  * score bit.
@@ -283,8 +284,8 @@ int hr_rerank_score(hr_model* model, const hr_pool* pool, int32_t n_pairs,
  *                              sizes, private to the plan while it lives) and allocates the pinned metadata block (the one
  *                              allocation of a plan's life).  Uses the model's split-operand setting at this moment.
  *   hr_rerank_plan_set_inputs  host: validates page_table [n_pairs][pt_stride] and query_tokens (flat, pair after pair)
- *                              like hr_rerank_score and writes them into the pinned block.  The copy in a run or replay
- *                              reads that block when it executes: do not call this while a run or replay that has not
+ *                              like hr_rerank_score and writes them into the pinned block.  A run or replay reads
+ *                              that block when it executes: do not call this while a run or replay that has not
  *                              finished could still read the block.
  *   hr_rerank_plan_run         stream work only (see above); scores_dev fp32 [n_pairs].  HR_ERR_INVALID_ARG before the
  *                              first set_inputs.  Run it once outside capture first: the first launch of a kernel sets
@@ -438,13 +439,13 @@ const char* hr_gemm_path(const hr_model* model);
 
 /* Environment switches, read once per model handle at hr_weights_load.  They exist for A/B runs of the tests and
  * benchmarks (each pair of settings must give the same score bits) and change no result:
- *   HR_FORCE_GENERIC=1      every step on the generic fp32-arithmetic kernels
  *   HR_NO_LAST_SHORTCUT=1   the last layer runs on every token instead of each pair's last one
  *   HR_NO_DOC_GROUPS=1      pairs that share a document are not batched into one attention work item
  *   HR_NO_QUERY_SHARING=1   the first layer's projections are computed for every pair instead of once per distinct query
  *   HR_STREAMS=1            the initial value of hr_rerank_set_streams is 1
- * and one that does change results (within the tolerance): HR_PRECISE_LAYERS=n, the initial value of
- * hr_model_set_precise_layers. */
+ * and two that do change results (within the tolerance):
+ *   HR_FORCE_GENERIC=1      every step on the step-by-step kernels (fp32 arithmetic)
+ *   HR_PRECISE_LAYERS=n     the initial value of hr_model_set_precise_layers */
 
 #ifdef __cplusplus
 }

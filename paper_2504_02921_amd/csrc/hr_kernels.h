@@ -38,7 +38,7 @@ struct MetaView {
     int64_t T;
 };
 
-// ---- generic (any shape, VALU arithmetic in fp32) ----
+// ---- any shape, VALU arithmetic in fp32 (hr_kernels_generic.hip) ----
 // Everything in front of the first layer as one launch: the embedding rows -> x, the RoPE table, `zero_bytes` (a multiple of
 // 16) cleared at `zero`, and, with meta_host (pinned host memory as the device addresses it), the metadata block copied to
 // meta_dev, which the pointers of `mv` lie in.

@@ -1,7 +1,7 @@
-// Shape-agnostic kernels of the scoring pass: fp32 VALU arithmetic, storage type templated.
-// They are the whole path for fp32 models and the fallback for shapes the MFMA kernels do not
-// cover; the elementwise ones (embedding gather, RMSNorm, RoPE table, scoring head, pool scatter,
-// weight packing) serve every path.
+// Shape-agnostic kernels of the scoring pass: fp32 VALU arithmetic, storage type templated.  RoPE split, SwiGLU and
+// one-wave-per-row attention are the step-by-step path of fp32 head sizes that hr_f32.hip's fused pass does not take and of
+// 16-bit shapes the MFMA kernels do not cover (their projections are hr_f32.hip's too); the others (embedding gather
+// and RoPE table, RMSNorm, scoring head, pool moves, weight packing, top-k) serve every path.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -24,7 +24,7 @@ namespace hr {
 
 // esz: bytes per element of the pool dtype
 HR_HD int k_swizzle(int t, int d, int esz) {
-    if (esz > 2) return 0;                       // fp32 pools are only read by the generic kernels
+    if (esz > 2) return 0;                       // fp32 pages are read straight into registers, not through LDS
     const int row_bytes = d * esz;
     return row_bytes == 128 ? ((t >> 1) & 7) : row_bytes == 256 ? (t & 15) : 0;
 }
