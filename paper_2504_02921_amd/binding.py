@@ -209,6 +209,12 @@ def hr_weights_pack_bytes(cfg: hr_model_cfg) -> int:
 # ----------------------------------------------------------------------------------------------
 # convenience holders: own the torch tensors behind the handles
 # ----------------------------------------------------------------------------------------------
+# Up to this many queries the offsets travel as kernel arguments, 256 a launch; beyond, one upload and one launch are less.
+# Offsets as arguments / uploaded, whole calls: 1 query 11.9 / 25.2 us, 256 10.9 / 26.4, 512 13.7 / 27.5, 1024 20.9 / 27.4, 4096
+# 79.5 / 39.9, 16384 181 / 42.
+_TOPK_HOST_QUERIES = 1024
+
+
 def rerank_topk(scores, seg_offsets, k: int, with_scores: bool = False, stream=None):
     """Per-query top-k of device scores: seg_offsets (host ints, [n_queries + 1]) delimits each query's pairs.
     Returns an int32 device tensor [n_queries][k] of candidate indices inside each segment (-1 padded), and the
@@ -219,9 +225,13 @@ def rerank_topk(scores, seg_offsets, k: int, with_scores: bool = False, stream=N
     max_c = max(int((seg[1:] - seg[:-1]).max()) if n_q > 0 else 1, k, 1)      # an upper bound is all the library needs
     idx = torch.empty((max(n_q, 0), k), dtype=torch.int32, device=scores.device)
     sc = torch.empty((max(n_q, 0), k), dtype=torch.float32, device=scores.device) if with_scores else None
-    check(lib.hr_rerank_topk_host(scores.data_ptr(), _i32p(seg), n_q, max_c, k,
-                                  idx.data_ptr(), sc.data_ptr() if with_scores else None, _stream_ptr(stream)),
-          "hr_rerank_topk")
+    out = (idx.data_ptr(), sc.data_ptr() if with_scores else None, _stream_ptr(stream))
+    if n_q <= _TOPK_HOST_QUERIES or torch.cuda.is_current_stream_capturing():      # a blocking upload cannot be captured
+        check(lib.hr_rerank_topk_host(scores.data_ptr(), _i32p(seg), n_q, max_c, k, *out), "hr_rerank_topk")
+    else:
+        seg_dev = torch.from_numpy(seg).to(scores.device)
+        check(lib.hr_rerank_topk(scores.data_ptr(), seg_dev.data_ptr(), n_q, max_c, k, *out), "hr_rerank_topk")
+        idx._hr_seg = seg_dev      # keep the offsets alive until the result is dropped (the kernel may still be queued)
     return (idx, sc) if with_scores else idx
 
 

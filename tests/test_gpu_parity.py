@@ -699,6 +699,33 @@ def test_topk_with_offsets_on_the_device_and_on_the_host(n_queries, with_scores)
             np.testing.assert_array_equal(sc.cpu().numpy(), want_sc)
 
 
+@pytest.mark.parametrize("n_queries,on_device", [(1024, False), (1025, True), (3000, True)])
+def test_topk_of_many_queries_uploads_the_offsets_once(n_queries, on_device, monkeypatch):
+    """binding.rerank_topk on both sides of the number of queries from which one upload and one launch replace a launch per
+    256 queries; under capture the offsets always travel as kernel arguments."""
+    import torch
+    from paper_2504_02921_amd import binding as hb
+    rng = np.random.default_rng(n_queries)
+    seg = np.concatenate([[0], np.cumsum(rng.integers(0, 9, n_queries))]).astype(np.int32)
+    s = (np.round(rng.normal(size=int(seg[-1])) * 4) / 4).astype(np.float32)
+    want = orr.topk(s.astype(np.float64), seg, 3)
+    dev = torch.from_numpy(s).to("cuda:0")
+    ran = []
+    for name in ("hr_rerank_topk", "hr_rerank_topk_host"):
+        fn = getattr(hb.lib, name)
+        monkeypatch.setattr(hb.lib, name, lambda *a, fn=fn, name=name: (ran.append(name), fn(*a))[1])
+    np.testing.assert_array_equal(hb.rerank_topk(dev, seg, 3).cpu().numpy(), want)
+    assert ran == ["hr_rerank_topk" if on_device else "hr_rerank_topk_host"]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        idx = hb.rerank_topk(dev, seg, 3)
+    for _ in range(3):
+        idx.fill_(-9)
+        graph.replay()
+        np.testing.assert_array_equal(idx.cpu().numpy(), want)
+
+
 def test_two_stream_halves_are_bit_identical_and_ordered_on_the_callers_stream():
     """A call with more than 8192 query tokens runs as two halves on two streams.  Scores must equal the single-stream
     run bit for bit and the oracle within the bar, work enqueued behind the call on the caller's stream (here the
