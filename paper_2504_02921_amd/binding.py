@@ -226,12 +226,13 @@ def rerank_topk(scores, seg_offsets, k: int, with_scores: bool = False, stream=N
     idx = torch.empty((max(n_q, 0), k), dtype=torch.int32, device=scores.device)
     sc = torch.empty((max(n_q, 0), k), dtype=torch.float32, device=scores.device) if with_scores else None
     out = (idx.data_ptr(), sc.data_ptr() if with_scores else None, _stream_ptr(stream))
-    if n_q <= _TOPK_HOST_QUERIES or torch.cuda.is_current_stream_capturing():      # a blocking upload cannot be captured
-        check(lib.hr_rerank_topk_host(scores.data_ptr(), _i32p(seg), n_q, max_c, k, *out), "hr_rerank_topk")
-    else:
-        seg_dev = torch.from_numpy(seg).to(scores.device)
-        check(lib.hr_rerank_topk(scores.data_ptr(), seg_dev.data_ptr(), n_q, max_c, k, *out), "hr_rerank_topk")
-        idx._hr_seg = seg_dev      # keep the offsets alive until the result is dropped (the kernel may still be queued)
+    if n_q > _TOPK_HOST_QUERIES:
+        with torch.cuda.stream(stream):              # the offsets belong to the stream that reads them (None: the current one)
+            if not torch.cuda.is_current_stream_capturing():      # a blocking upload cannot be captured
+                seg_dev = torch.from_numpy(seg).to(scores.device)
+                check(lib.hr_rerank_topk(scores.data_ptr(), seg_dev.data_ptr(), n_q, max_c, k, *out), "hr_rerank_topk")
+                return (idx, sc) if with_scores else idx
+    check(lib.hr_rerank_topk_host(scores.data_ptr(), _i32p(seg), n_q, max_c, k, *out), "hr_rerank_topk")
     return (idx, sc) if with_scores else idx
 
 

@@ -726,6 +726,36 @@ def test_topk_of_many_queries_uploads_the_offsets_once(n_queries, on_device, mon
         np.testing.assert_array_equal(idx.cpu().numpy(), want)
 
 
+def test_topk_of_many_queries_on_a_given_stream():
+    """The offsets of a large selection are uploaded on the stream it runs on: a stream that is being captured takes them as
+    kernel arguments whatever the current one is, and an upload is not overwritten while its kernel is still queued."""
+    import torch
+    from paper_2504_02921_amd import binding as hb
+    n_queries = 1500
+    rng = np.random.default_rng(3)
+    seg = np.concatenate([[0], np.cumsum(rng.integers(0, 9, n_queries))]).astype(np.int32)
+    s = rng.normal(size=int(seg[-1])).astype(np.float32)
+    want = orr.topk(s.astype(np.float64), seg, 3)
+    dev, side = torch.from_numpy(s).to("cuda:0"), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        busy = torch.ones((4096, 4096), device="cuda:0")
+        for _ in range(20):
+            busy = busy @ busy * 1e-4
+    idx = hb.rerank_topk(dev, seg, 3, stream=side)
+    for _ in range(4):
+        torch.full((n_queries + 1,), 7, dtype=torch.int32, device="cuda:0")      # takes whatever the current stream may reuse
+    side.synchronize()
+    np.testing.assert_array_equal(idx.cpu().numpy(), want)
+
+    ran = []
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setattr(torch.cuda, "is_current_stream_capturing", lambda: torch.cuda.current_stream() == side)
+        mp.setattr(hb.lib, "hr_rerank_topk_host", lambda *a: ran.append(a[-1]) or hb.HR_OK)
+        hb.rerank_topk(dev, seg, 3, stream=side)
+    assert ran == [side.cuda_stream]
+
+
 def test_two_stream_halves_are_bit_identical_and_ordered_on_the_callers_stream():
     """A call with more than 8192 query tokens runs as two halves on two streams.  Scores must equal the single-stream
     run bit for bit and the oracle within the bar, work enqueued behind the call on the caller's stream (here the
