@@ -398,10 +398,11 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
 
 // BM x BN x 64 macro tile, WM x WN wavefronts, each wave (BM/WM) x (BN/WN) = MI x NI blocks of 16 x 16.
 //
-// What bounds it at large M is power: with operands of full mantissas the chip holds 1.65-1.85 GHz under this kernel (2.2
-// with zeros), and every variant of the schedule that spends the same energy per product ends at the same rate.  A
-// register-only loop reaches 1.94 PFLOP/s with v_mfma_f32_16x16x32_f16 and 1.71 with v_mfma_f32_32x32x16_f16 (twice the
-// accumulator traffic per product), 1.57 / 1.43 with the fragments read from LDS as here: hence the 16 x 16 x 32 form.
+// What bounds it at large M is power: with operands of full mantissas the chip holds 1.45 GHz (8B gate/up, K = 8192: matrix
+// pipe busy 81 %) to 1.9 GHz (K = 896: 64 %) under this kernel, and every variant of the schedule that spends the same
+// energy per product ends at the same rate.  A register-only loop reaches 1.97 PFLOP/s with v_mfma_f32_16x16x32_f16 and 1.73
+// with v_mfma_f32_32x32x16_f16 (twice the accumulator traffic per product; 2.44 and 2.48 with zeros), 1.57 / 1.43 with the
+// fragments read from LDS as here: hence the 16 x 16 x 32 form.
 //
 // Data path: buffer loads straight to LDS, 16 bytes a lane (TileSrc; nothing passes through VGPRs; lane l of a wave writes LDS bytes
 // [base + 16 l, base + 16 l + 16)); SA stages of A and two of W.  A k-tile is two k-steps of 32.  A fragment of A is
@@ -845,7 +846,8 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
 // The reading-ahead wavefront pays where several tiles share a column of W and the k loop is long: with two row tiles it
 // cannot keep up (65 rows, K = 4864: 17.1 us without, 22.2 with), at K = 4096 it is worth -3 to +5 %, from K = 4864 on -14 to -18 %.
 // The loop's own length counts, both halves of a split operand, although W is read ahead along the first only: O projection of
-// the 8B shape on split operands (K = 8192 over 4096 columns of W), without / with it: 320 rows 52.7 / 47.9 us, 512 rows 56.2 / 50.3, 640 rows 79.1 / 70.7, 800 rows 75.1 / 76.8, 1024 rows 85.6 / 84.4.
+// the 8B shape on split operands (K = 8192 over 4096 columns of W), without / with it: 320 rows 52.7 / 47.9 us, 512 rows
+// 56.2 / 50.3, 640 rows 79.1 / 70.7, 800 rows 75.1 / 76.8, 1024 rows 85.6 / 84.4.
 // The 32-row tiles are for fewer rows than that.
 inline bool use_ahead(const GemmArgs& a, int bm, int tiles_m) { return bm >= 64 && tiles_m >= 4 && a.K > 4096; }
 
