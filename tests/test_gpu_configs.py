@@ -88,6 +88,25 @@ def test_config2_qwen0p5b_full_size_all_pairs():
     run_full_size("c2_qwen0p5b")
 
 
+def test_first_queries_of_config2_run_as_two_halves_with_the_same_bits():
+    """10240 query tokens of the 0.5B shape leave the narrow projections' rounds partly empty, so the call runs as two
+    halves (no configuration does at its full size): same bits as on one stream, with plain and with split operands."""
+    wl = wlmod.make_workload(wlmod.CONFIGS["c2_qwen0p5b"]).subset(np.arange(320))
+    case = H.Case(wl, wlmod.SeededWeights(wl.cfg.model, seed=wl.cfg.seed))
+    try:
+        case.fill_synthetic(oracle_doc_ids=[])
+        for n_precise in (0, 2):
+            case.model.set_precise_layers(n_precise)
+            case.model.set_streams(2)
+            assert case.model.parts(wl.total_q_tokens) == 2
+            two = case.gpu_scores()
+            case.model.set_streams(1)
+            assert np.all(np.isfinite(two))
+            np.testing.assert_array_equal(two, case.gpu_scores())
+    finally:
+        case.close()
+
+
 @pytest.mark.timeout(900)
 def test_config3_llama8b_full_size_all_pairs():
     run_full_size("c3_llama8b")
