@@ -141,7 +141,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
         constexpr int CW = BN / PASSES;                 // slab width in columns
         constexpr int CPRW = CW / 4;                    // 16-byte chunks per slab row
         constexpr int ITER = BM * CPRW / NT;
-        constexpr int NG = ITER == 1 ? 1 : ITER % 4 == 0 ? 4 : 5;       // register groups of the x update (320-row tiles: 10 = 5 x 2)
+        constexpr int NG = ITER == 1 ? 1 : ITER % 4 == 0 ? 4 : ITER % 5 == 0 ? 5 : 2;      // register groups of the x update (320-row tiles: 10 = 5 x 2)
         constexpr int SWZ = CPRW < 16 ? CPRW - 1 : 15;
         static_assert(EPI != EPI_RESID_ADD || ((CW % TN == 0 || TN % CW == 0) && (CPRW == 8 || CPRW % 16 == 0) && (BM * CPRW) % (NG * NT) == 0 && BM * CW * 4 <= LDS_BYTES),
                       "slab shape");
@@ -619,17 +619,20 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 // one k-step ahead) took ~750 cycles per 64 x 64 k-tile whatever the number of workgroups: the down projection of 65 or
 // 640 rows (K = 4864) 27 / 28 us.
 //
-// A residual-add launch may bring one wavefront more (use_ahead below), which reads W kAhead k-tiles ahead of the ring and drops
-// it: the tiles of one column, neighbours on one XCD, take turns, so a k-tile's lines are in their L2 when the ring asks.
-// The ring alone has 128 KiB in flight, one 64 x 64 k-tile per ~590 cycles at the ~2.3 us that a first touch of HBM takes.
-// Down projection, 640 rows: 0.5B shape 23.1 -> 19.9 us, 8B shape 142 -> 117 us.
+// A launch of four wavefronts or fewer may bring one more (use_ahead below), which reads W kAhead k-tiles ahead of the ring and
+// drops it: the tiles of one column, neighbours on one XCD, take turns, so a k-tile's lines are in their L2 when the ring asks.
+// The ring alone has 128 KiB in flight: W of a 64 x 64 tile is 64 KiB of that, shared by all tiles of a column, and a first touch of
+// HBM takes ~2.3 us.  Down projection of the 8B shape (K = 14336, N = 4096), 640 rows, without / with it: 139.6 / 105.1 us
+// (operands in L2: 92); QKV of that shape (K = 4096), 512 rows 41.2 / 37.3.
 //
-// 32 x 32 tiles, 18 stages, take residual-add launches that fit one round with them: twice the k-tiles in flight, half the bytes
-// to deliver per k-tile and four times the workgroups.  Down projection, 0.5B shape (K = 4864, times with two event records
-// around the launch): 65 rows 20.0 -> 12.9 us, 288 rows 22.3 -> 15.5; 8B shape (K = 14336), 40 rows 59.7 -> 33.1.  More rows than a
-// round holds pay for A and W read twice as often: 350 rows 21.7 -> 22.5, 640 rows 21.9 -> 31.2 us.
+// Tiles of 32 rows (32 x 32 for residual adds, 18 stages; 32 x 64 and 32 x 128 for QKV) take launches that fit one round with
+// them: more k-tiles in flight, fewer bytes to deliver per k-tile and more workgroups.  65 rows, weights from HBM: down
+// projection of the 0.5B shape (K = 4864) 64 x 64 17.1 -> 32 x 32 10.3 us, QKV (K = 896) 64 x 64 7.1 -> 32 x 64 5.3 us.  More rows than
+// a round holds pay for A and W read twice as often: down projection, 640 rows 19.7 -> 30.5 us.
+// Tiles of 96 and 160 rows x 64 (residual adds) fill rounds that the powers of two leave a third empty: 8B down projection, 640
+// rows 128 x 128 (160 tiles) 105.1 -> 160 x 64 (256 tiles) 97.6 us.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
-__global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
+__global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 16, NI = TN / 16;
@@ -657,7 +660,7 @@ __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) ge
     TileSrc<PA, RPP> srcA;
     TileSrc<PB, RPP> srcB;
     srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
-    if constexpr (EPI == EPI_RESID_ADD) {
+    if constexpr (WM * WN <= 4) {
         if (wave == WM * WN) {
             // touches one 4-byte word of every 64 bytes: 32 rows of a k-tile per request.  Every row offset sits in the vector
             // offset, so rows past the end fail the range check
@@ -685,8 +688,9 @@ __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) ge
         }
     }
 
-    // x of a residual add: requested first, so that it has arrived long before the epilogue
-    constexpr bool XPRE = EPI == EPI_RESID_ADD;
+    // x of a residual add: requested first, so that it has arrived long before the epilogue.  Small tiles only: a 128 x 128 one
+    // would hold 64 registers for it through the k loop (and spilled them)
+    constexpr bool XPRE = EPI == EPI_RESID_ADD && BM * BN <= 64 * 64;
     float4 xv[XPRE ? BM * BN / 4 / NT : 1];
     if constexpr (XPRE) x_prefetch<BN, NT>(xv, a, m0, n0);
 
@@ -733,10 +737,12 @@ __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) ge
     };
 
     // One k-tile, its fragments in (or on their way to) set SET, stage `slot`.  YOUNGER: how many of the k-tiles requested so
-    // far come after the next one (their loads may still be outstanding), -1: there is no next one.
+    // far come after the next one (their loads may still be outstanding), -1: there is no next one.  request: k-tile
+    // kt + NS is requested into the stage that this k-tile leaves.
     int slot = 0;
-    auto step = [&](auto set_c, auto younger_c, bool request, int kt) {
+    auto step = [&](auto set_c, auto younger_c, auto request_c, int kt) {
         constexpr int SET = decltype(set_c)::value, YOUNGER = decltype(younger_c)::value;
+        constexpr bool REQUEST = decltype(request_c)::value;
         const int next = slot + 1 == NS ? 0 : slot + 1;
         if constexpr (YOUNGER >= 0) {
             // the wait is the compiler's to see (its own waits in front of the MFMAs then leave the reads below alone);
@@ -745,29 +751,41 @@ __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) ge
             __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0070);       // vmcnt(V) lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            fload(SET ^ 1, next);
-            if (request) dma(kt + NS, slot);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        // A wave issues in order, and a request or an LDS read that finds its queue full holds up the MFMAs behind it: reads and
+        // requests go between the MFMAs one by one.  The order is pinned by scheduling barriers: asked for as groups, the
+        // compiler kept it in one of the two copies of the loop body and put all requests in front of the MFMAs in the other.
+        // Requests behind the MFMAs / spread, operands in L2, one k-tile at 2.4 GHz: 64 x 64 415 / 290 cycles, 128 x 128 945 / 593.
+        constexpr int NM = KS * MI * NI, ND = KS * (MI + NI);
+        const half_t *nA = sA + next * BM * BK, *nB = sB + next * BN * BK;
+        half_t *dA = sA + slot * BM * BK + wave * 64 * 8, *dB = sB + slot * BN * BK + wave * 64 * 8;
+        const int ktn = kt + NS, ka = ktn * (BK * 2), kb = (ktn < nkw ? ktn : ktn - nkw) * (BK * 2);
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk)
+        for (int n = 0; n < NM; ++n) {
+            const int mk = n / (MI * NI), mi = n / NI % MI, mj = n % NI;
+            acc[mi][mj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bfr[SET][mk][mj], af[SET][mk][mi], acc[mi][mj], 0, 0, 0);
+            if constexpr (YOUNGER >= 0) {
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+                for (int r = 0; r < ND; ++r) {
+                    if (r * NM / ND != n) continue;
+                    const int rk = r / (MI + NI), f = r % (MI + NI);
+                    if (f < MI) af[SET ^ 1][rk][f] = *(const halfx8*)(nA + at_a[rk] + f * 16 * BK);
+                    else bfr[SET ^ 1][rk][f - MI] = *(const halfx8*)(nB + at_b[rk] + (f - MI) * 16 * BK);
+                }
+                if constexpr (REQUEST) {
 #pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bfr[SET][kk][j], af[SET][kk][i], acc[i][j], 0, 0, 0);
-        if constexpr (YOUNGER >= 0) {
-            // a wave issues in order, one LDS read or one MFMA per ~16 cycles: reads (early), then requests between the MFMAs
-            constexpr int NM = KS * MI * NI, ND = KS * (MI + NI), DPM = (ND + NM - 1) / NM;
-            constexpr int MD = (ND + DPM - 1) / DPM;                       // MFMAs with reads behind them
-            constexpr int VPM = (LPT + NM - 1) / NM, MV = (LPT + VPM - 1) / VPM;
-#pragma unroll
-            for (int n = 0; n < NM; ++n) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (n < MD) __builtin_amdgcn_sched_group_barrier(0x100, DPM, 0);
-                if (n >= NM - MV) __builtin_amdgcn_sched_group_barrier(0x010, VPM, 0);
+                    for (int p = 0; p < LPT; ++p) {
+                        if (p * NM / LPT != n) continue;
+                        if (p < PA) srcA.load(p, dA + p * NT * 8, va, ka);
+                        else srcB.load(p - PA, dB + (p - PA) * NT * 8, vb, kb);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            asm volatile("" ::: "memory");
         }
+        if constexpr (YOUNGER >= 0) asm volatile("" ::: "memory");
         slot = next;
     };
     using std::integral_constant;
@@ -788,15 +806,15 @@ __global__ void __launch_bounds__((WM * WN + (EPI == EPI_RESID_ADD)) * 64, 1) ge
     if ((nk - 1) & 1) fload(1, 0);
     else fload(0, 0);
     int kt = 0;
-    if (nk > NS && ((nk - NS) & 1)) step(set_q, steady, true, kt++);
+    if (nk > NS && ((nk - NS) & 1)) step(set_q, steady, std::true_type{}, kt++);
     for (; kt + NS < nk; kt += 2) {
-        step(set_p, steady, true, kt);
-        step(set_q, steady, true, kt + 1);
+        step(set_p, steady, std::true_type{}, kt);
+        step(set_q, steady, std::true_type{}, kt + 1);
     }
     // the last NS k-tiles (all requested): k-tile nk - 1 - R has R - 1 requested ones behind the next
     auto tail = [&](auto self, auto r_c) -> void {
         constexpr int R = decltype(r_c)::value;
-        if (R < nk) step(integral_constant<int, R & 1>{}, integral_constant<int, R - 1>{}, false, 0);
+        if (R < nk) step(integral_constant<int, R & 1>{}, integral_constant<int, R - 1>{}, std::false_type{}, 0);
         if constexpr (R > 0) self(self, integral_constant<int, R - 1>{});
     };
     tail(tail, integral_constant<int, NS - 1>{});
@@ -843,20 +861,18 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// The reading-ahead wavefront pays where several tiles share a column of W and the k loop is long: with two row tiles it
-// cannot keep up (65 rows, K = 4864: 17.1 us without, 22.2 with), at K = 4096 it is worth -3 to +5 %, from K = 4864 on -14 to -18 %.
-// The loop's own length counts, both halves of a split operand, although W is read ahead along the first only: O projection of
-// the 8B shape on split operands (K = 8192 over 4096 columns of W), without / with it: 320 rows 52.7 / 47.9 us, 512 rows
-// 56.2 / 50.3, 640 rows 79.1 / 70.7, 800 rows 75.1 / 76.8, 1024 rows 85.6 / 84.4.
-// The 32-row tiles are for fewer rows than that.
-inline bool use_ahead(const GemmArgs& a, int bm, int tiles_m) { return bm >= 64 && tiles_m >= 4 && a.K > 4096; }
+// The reading-ahead wavefront pays where several tiles share a column of W and the k loop is long.  Without / with it, weights
+// from HBM, N = 4096: two row tiles lose (K = 4096, 128 rows of 64: 21.0 / 23.1 us; K = 14336: 70.2 / 75.6), three gain (192 rows:
+// 21.0 / 20.4, 69.9 / 64.0), five more (320 rows of 64 x 128: 31.2 / 26.1, 105.6 / 84.2); K = 2048 gains (512 rows 19.0 / 17.5),
+// K = 896 loses (512 rows 9.1 / 9.2, 640 rows of 64 x 64 at N = 896 5.7 / 5.8).  The line lies between those two.
+inline bool use_ahead(const GemmArgs& a, int tiles_m) { return tiles_m >= 3 && a.K >= 2048; }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
-    const bool ahead = EPI == EPI_RESID_ADD && use_ahead(a, BM, tiles_m);
-    constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (EPI == EPI_RESID_ADD ? kAheadLds : 0);
+    const bool ahead = WM * WN <= 4 && use_ahead(a, tiles_m);
+    constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (WM * WN <= 4 ? kAheadLds : 0);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS>, lds_most, attr_done); e != hipSuccess) return e;
     gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS><<<dim3((unsigned)grid), (WM * WN + ahead) * 64, ahead ? lds_most : ring, st>>>(a);
@@ -904,6 +920,11 @@ static void advance_rows(GemmEpilogue epi, GemmArgs& r, int64_t rows) {
     }
 }
 
+// The narrowest tile of a QKV projection is 32 rows tall instead of 64 while that still is one tile per CU: half the rows to
+// deliver per k-tile.  Weights from HBM, 64 / 32 rows: 0.5B shape (N = 1152, K = 896) 65 rows 7.1 / 5.3 us, 400 rows (234 tiles)
+// 7.4 / 5.7, two rounds (640 rows) 7.7 / 9.7; 8B shape (N = 6144, K = 4096) 128 rows (192 tiles) 31.2 / 26.0, 256 rows 28.1 / 44.3.
+static bool half_tall(const GemmArgs& a, int bn) { return (a.M + 31) / 32 * ((a.N + bn - 1) / bn) <= cu_count(); }
+
 hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st) {
     if (a.M == 0) return hipSuccess;
     if (a.K % BK != 0) return hipErrorInvalidValue;
@@ -921,7 +942,10 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                     case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1, 3>(r, st); break;
                     case GT_SMALL: e = launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 2>(r, st); break;
                     case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(r, st); break;
-                    case GT_RING64: e = launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(r, st); break;
+                    case GT_RING64:
+                        if (half_tall(r, 64)) e = launch_ring<EPI_QKV_ROPE, 32, 64, 2, 1, 1, 8>(r, st);
+                        else e = launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(r, st);
+                        break;
                     default: break;
                 }
                 break;
@@ -929,7 +953,10 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                 switch (g.part[i].tile) {
                     case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 4, 2, 2, 3>(r, st); break;
                     case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 4, 1, 2, 4>(r, st); break;
-                    case GT_RING64_128: e = launch_ring<EPI_QKV_ROPE, 64, 128, 2, 1, 2, 5>(r, st); break;
+                    case GT_RING64_128:
+                        if (half_tall(r, 128)) e = launch_ring<EPI_QKV_ROPE, 32, 128, 2, 1, 2, 7>(r, st);
+                        else e = launch_ring<EPI_QKV_ROPE, 64, 128, 4, 1, 2, 6>(r, st);
+                        break;
                     default: break;
                 }
                 break;
@@ -940,6 +967,8 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                     case GT_SMALL: e = launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 2>(r, st); break;
                     case GT_RING128: e = launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(r, st); break;
                     case GT_RING64_128: e = launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(r, st); break;
+                    case GT_RING160_64: e = launch_ring<EPI_RESID_ADD, 160, 64, 2, 2, 1, 5>(r, st); break;
+                    case GT_RING96_64: e = launch_ring<EPI_RESID_ADD, 96, 64, 2, 2, 1, 7>(r, st); break;
                     case GT_RING64: e = launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(r, st); break;
                     case GT_RING32: e = launch_ring<EPI_RESID_ADD, 32, 32, 2, 2, 1, 18>(r, st); break;
                     default: break;
@@ -950,7 +979,7 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                     case GT_BIG: e = launch_tile<EPI_SWIGLU, 256, 256, 2, 4, 1, 3>(r, st); break;
                     case GT_TALL: e = launch_tile<EPI_SWIGLU, 320, 256, 2, 4, 1, 2>(r, st); break;
                     case GT_SMALL: e = launch_tile<EPI_SWIGLU, 128, 128, 2, 2, 1, 2>(r, st); break;
-                    case GT_RING128_256: e = launch_ring<EPI_SWIGLU, 128, 256, 2, 2, 1, 3>(r, st); break;
+                    case GT_RING128_256: e = launch_ring<EPI_SWIGLU, 128, 256, 2, 4, 1, 3>(r, st); break;
                     case GT_RING128: e = launch_ring<EPI_SWIGLU, 128, 128, 2, 2, 1, 4>(r, st); break;
                     case GT_RING64_128: e = launch_ring<EPI_SWIGLU, 64, 128, 2, 2, 1, 6>(r, st); break;
                     default: break;

@@ -450,21 +450,20 @@ struct GemmShape {
 // Measured (MI355X, full rounds, weights from HBM).  256 x 256 is the most efficient per output; 320 x 256 equals it per output
 // and takes other row counts in whole rounds (not for short k loops behind gate / up, whose 256-row form is
 // persistent); the two-per-CU tile costs 1.2-1.4 times as much per output but comes in quarter steps; the ring shapes
-// run one workgroup per CU and are what short launches take (32 x 32 where all tiles fit one round).
-const GemmShape kResidShapes[] = {{GT_BIG, 256, 256, 1, 21.3f, 0.0245f, 0},      {GT_TALL, 320, 256, 1, 19.0f, 0.0309f, 0},
-                                  {GT_SMALL, 128, 128, 2, 6.0f, 0.0175f, 0},     {GT_RING128, 128, 128, 1, 8.6f, 0.0098f, 0},
-                                  {GT_RING64_128, 64, 128, 1, 5.3f, 0.0064f, 0}, {GT_RING64, 64, 64, 1, 3.5f, 0.0042f, 0},
-                                  {GT_RING32, 32, 32, 1, 3.3f, 0.0024f, 0}};
+// run one workgroup per CU and are what short launches take (32 rows where all tiles fit one round; 96 and 160 rows between the
+// powers of two, from k loops of more k-tiles than they have stages on: shorter ones are not measured).
+const GemmShape kResidShapes[] = {{GT_BIG, 256, 256, 1, 19.5f, 0.0237f, 0},      {GT_TALL, 320, 256, 1, 19.0f, 0.0309f, 0},
+                                  {GT_SMALL, 128, 128, 2, 6.0f, 0.0165f, 0},     {GT_RING128, 128, 128, 1, 8.4f, 0.0075f, 0},
+                                  {GT_RING64_128, 64, 128, 1, 4.2f, 0.0055f, 0}, {GT_RING160_64, 160, 64, 1, 5.9f, 0.0064f, 512},
+                                  {GT_RING96_64, 96, 64, 1, 3.5f, 0.0049f, 512},   {GT_RING64, 64, 64, 1, 2.4f, 0.0041f, 0},
+                                  {GT_RING32, 32, 32, 1, 2.5f, 0.0022f, 0}};
 const GemmShape kSwigluShapes[] = {{GT_BIG, 256, 256, 1, 4.9f, 0.0239f, 0},          {GT_TALL, 320, 256, 1, 5.0f, 0.0295f, 2048},
-                                   {GT_SMALL, 128, 128, 2, 0.5f, 0.0177f, 0},         {GT_RING128_256, 128, 256, 1, 4.0f, 0.0170f, 0},
-                                   {GT_RING128, 128, 128, 1, 3.5f, 0.0092f, 0},       {GT_RING64_128, 64, 128, 1, 3.5f, 0.0064f, 0}};
-const GemmShape kQkv64Shapes[] = {{GT_BIG, 256, 256, 1, 12.0f, 0.0235f, 0},
-                                  {GT_SMALL, 128, 128, 2, 3.5f, 0.0175f, 0},
-                                  {GT_RING128, 128, 128, 1, 9.0f, 0.0098f, 0},
-                                  {GT_RING64, 64, 64, 1, 4.0f, 0.0046f, 0}};
-const GemmShape kQkv128Shapes[] = {{GT_BIG, 256, 256, 1, 12.0f, 0.0232f, 0},
-                                   {GT_RING128, 128, 128, 1, 5.0f, 0.0088f, 0},
-                                   {GT_RING64_128, 64, 128, 1, 4.5f, 0.0061f, 0}};
+                                   {GT_SMALL, 128, 128, 2, 2.8f, 0.0177f, 0},         {GT_RING128_256, 128, 256, 1, 5.2f, 0.0131f, 0},
+                                   {GT_RING128, 128, 128, 1, 5.6f, 0.0072f, 0},       {GT_RING64_128, 64, 128, 1, 5.3f, 0.0043f, 0}};
+const GemmShape kQkv64Shapes[] = {{GT_BIG, 256, 256, 1, 12.0f, 0.0235f, 0},  {GT_SMALL, 128, 128, 2, 4.9f, 0.0175f, 0},
+                                  {GT_RING128, 128, 128, 1, 6.3f, 0.0075f, 0}, {GT_RING64, 64, 64, 1, 3.9f, 0.0041f, 0}};
+const GemmShape kQkv128Shapes[] = {{GT_BIG, 256, 256, 1, 12.0f, 0.0232f, 0},      {GT_RING128, 128, 128, 1, 7.5f, 0.0078f, 0},
+                                   {GT_RING64_128, 64, 128, 1, 4.5f, 0.0055f, 0}};
 }  // namespace
 
 GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) {
@@ -474,12 +473,14 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) 
     if (kind == GEMM_SWIGLU) { shapes = kSwigluShapes; n_shapes = (int)(sizeof(kSwigluShapes) / sizeof(GemmShape)); }
     if (kind == GEMM_QKV64) { shapes = kQkv64Shapes; n_shapes = (int)(sizeof(kQkv64Shapes) / sizeof(GemmShape)); }
     if (kind == GEMM_QKV128) { shapes = kQkv128Shapes; n_shapes = (int)(sizeof(kQkv128Shapes) / sizeof(GemmShape)); }
-    // a round that fills little of the chip still takes three quarters of a full one: a tile's k loop has its length, and only
-    // the shared memory system and the clock give way
+    // a round that fills little of the chip still takes three quarters of a full one (a tile's k loop has its length, and only
+    // the shared memory system and the clock give way), or 70 % where two tiles share a CU: down projection of the 0.5B shape, 128 x 128
+    // tiles, 112 / 350 / 448 of 512 slots 55 / 66 / 72 us, 86 for all
     auto cost = [&](const GemmShape& s, int64_t rows) {
         const int64_t tiles = ((rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), slots = cus * s.per_cu;
         const double full = (double)(tiles / slots), part = (double)(tiles % slots) / (double)slots;
-        return (full + (part > 0.0 ? 0.75 + 0.25 * part : 0.0)) * ((double)s.c0 + (double)s.c1 * K);
+        const double least = s.per_cu > 1 ? 0.7 : 0.75;
+        return (full + (part > 0.0 ? least + (1.0 - least) * part : 0.0)) * ((double)s.c0 + (double)s.c1 * K);
     };
     auto best_single = [&](int64_t rows, double* t) {
         int best = -1;

@@ -291,6 +291,18 @@ def test_projections_cut_by_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden,
         case.close()
 
 
+@pytest.mark.parametrize("d,n_q,n_kv,hidden,ffn,n_queries,qlen", [
+    (64, 14, 2, 896, 2112, 7, (37, 37)),        # 1295 rows: O and down as 96 x 64 tiles, the last one with 47 rows; down reads W ahead
+    (64, 14, 2, 896, 576, 12, (41, 41)),        # 2460 rows: O and down as 160 x 64 tiles, the last one with 60 rows
+    (64, 4, 2, 256, 320, 1, (33, 33)),          # 165 rows: QKV of 64-wide heads as 32 x 64 tiles, the last one with 5 rows
+    (128, 8, 2, 2048, 320, 1, (33, 37)),        # QKV of 128-wide heads as 32 x 128 tiles, QKV and gate / up (K = 2048) read W ahead
+])
+def test_projection_tiles_for_few_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen):
+    """Row counts at which the projections take the 96 x 64, 160 x 64, 32 x 64 and 32 x 128 tiles, with a partial last tile:
+    the oracle within the bar, and the bits of a pair scored alone (other tiles)."""
+    test_projections_cut_by_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen)
+
+
 @pytest.mark.parametrize("hidden,ffn", [(256, 688), (200, 320)])
 def test_bf16_wide_heads_with_projection_shapes_outside_the_mfma_family(hidden, ffn):
     """head_dim 64 suits the MFMA attention, but hidden / ffn are not multiples of 64, so the projections run on the
