@@ -42,6 +42,7 @@ namespace {
 constexpr int BK = 64;
 constexpr int kXcds = 8, kGroupM = 8;
 constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
+constexpr int kAheadShares = 4;                  // ... and how many tiles of a column take turns at least
 
 struct TileCoord { int tm, tn, share, shares; bool valid; };     // tile; its number among the `shares` that follow each other in one tile column
 
@@ -662,6 +663,7 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
     srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
     if constexpr (WM * WN <= 4) {
         if (wave == WM * WN) {
+            if (tc.shares < kAheadShares) return;     // too few to take turns (barriers go on without the wave)
             // touches one 4-byte word of every 64 bytes: 32 rows of a k-tile per request.  Every row offset sits in the vector
             // offset, so rows past the end fail the range check
             int vt[BN / 32];
@@ -683,7 +685,7 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
                 __builtin_amdgcn_s_barrier();
                 touch(kt + NS + kAhead);
             }
-            __builtin_amdgcn_s_waitcnt(0x0F70);       // nothing is on its way into LDS when the wave ends; barriers go on without it
+            __builtin_amdgcn_s_waitcnt(0x0F70);       // nothing is on its way into LDS when the wave ends
             return;
         }
     }
@@ -751,7 +753,6 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
             __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0070);       // vmcnt(V) lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
         }
         // A wave issues in order, and a request or an LDS read that finds its queue full holds up the MFMAs behind it: reads and
         // requests go between the MFMAs one by one.  The order is pinned by scheduling barriers: asked for as groups, the
@@ -761,28 +762,49 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
         const half_t *nA = sA + next * BM * BK, *nB = sB + next * BN * BK;
         half_t *dA = sA + slot * BM * BK + wave * 64 * 8, *dB = sB + slot * BN * BK + wave * 64 * 8;
         const int ktn = kt + NS, ka = ktn * (BK * 2), kb = (ktn < nkw ? ktn : ktn - nkw) * (BK * 2);
+        auto read_op = [&](int r) {
+            const int rk = r / (MI + NI), f = r % (MI + NI);
+            if (f < MI) af[SET ^ 1][rk][f] = *(const halfx8*)(nA + at_a[rk] + f * 16 * BK);
+            else bfr[SET ^ 1][rk][f - MI] = *(const halfx8*)(nB + at_b[rk] + (f - MI) * 16 * BK);
+        };
+        auto request_op = [&](int p) {
+            if (p < PA) srcA.load(p, dA + p * NT * 8, va, ka);
+            else srcB.load(p - PA, dB + (p - PA) * NT * 8, vb, kb);
+        };
+        constexpr bool PIN = YOUNGER >= 0 && 2 * NM > ND;  // a 32 x 32 tile has two MFMAs: left to the groups (pinned 2.5 % slower)
+        if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (YOUNGER >= 0 && !PIN) {
+#pragma unroll
+            for (int r = 0; r < ND; ++r) read_op(r);
+            if constexpr (REQUEST) {
+#pragma unroll
+                for (int p = 0; p < LPT; ++p) request_op(p);
+            }
+        }
 #pragma unroll
         for (int n = 0; n < NM; ++n) {
             const int mk = n / (MI * NI), mi = n / NI % MI, mj = n % NI;
             acc[mi][mj] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bfr[SET][mk][mj], af[SET][mk][mi], acc[mi][mj], 0, 0, 0);
-            if constexpr (YOUNGER >= 0) {
+            if constexpr (PIN) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int r = 0; r < ND; ++r) {
-                    if (r * NM / ND != n) continue;
-                    const int rk = r / (MI + NI), f = r % (MI + NI);
-                    if (f < MI) af[SET ^ 1][rk][f] = *(const halfx8*)(nA + at_a[rk] + f * 16 * BK);
-                    else bfr[SET ^ 1][rk][f - MI] = *(const halfx8*)(nB + at_b[rk] + (f - MI) * 16 * BK);
-                }
+                for (int r = 0; r < ND; ++r)
+                    if (r * NM / ND == n) read_op(r);
                 if constexpr (REQUEST) {
 #pragma unroll
-                    for (int p = 0; p < LPT; ++p) {
-                        if (p * NM / LPT != n) continue;
-                        if (p < PA) srcA.load(p, dA + p * NT * 8, va, ka);
-                        else srcB.load(p - PA, dB + (p - PA) * NT * 8, vb, kb);
-                    }
+                    for (int p = 0; p < LPT; ++p)
+                        if (p * NM / LPT == n) request_op(p);
                 }
                 __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (YOUNGER >= 0 && !PIN) {
+            constexpr int DPM = (ND + NM - 1) / NM, MD = (ND + DPM - 1) / DPM, VPM = (LPT + NM - 1) / NM, MV = (LPT + VPM - 1) / VPM;
+#pragma unroll
+            for (int n = 0; n < NM; ++n) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (n < MD) __builtin_amdgcn_sched_group_barrier(0x100, DPM, 0);
+                if (n >= NM - MV) __builtin_amdgcn_sched_group_barrier(0x010, VPM, 0);
             }
         }
         if constexpr (YOUNGER >= 0) asm volatile("" ::: "memory");
@@ -862,16 +884,20 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
 }
 
 // The reading-ahead wavefront pays where several tiles share a column of W and the k loop is long.  Without / with it, weights
-// from HBM, N = 4096: two row tiles lose (K = 4096, 128 rows of 64: 21.0 / 23.1 us; K = 14336: 70.2 / 75.6), three gain (192 rows:
-// 21.0 / 20.4, 69.9 / 64.0), five more (320 rows of 64 x 128: 31.2 / 26.1, 105.6 / 84.2); K = 2048 gains (512 rows 19.0 / 17.5),
-// K = 896 loses (512 rows 9.1 / 9.2, 640 rows of 64 x 64 at N = 896 5.7 / 5.8).  The line lies between those two.
-inline bool use_ahead(const GemmArgs& a, int tiles_m) { return tiles_m >= 3 && a.K >= 2048; }
+// from HBM, N = 4096: two row tiles of 64 lose (128 rows, K = 4096 21.0 / 23.1 us, K = 14336 70.2 / 75.6), three gain when they are
+// full (192 rows 69.9 / 64.0) and lose when the last is not (145 rows 53.1 / 60.5: the short tile runs ahead of the others by
+// itself), five gain (320 rows of 64 x 128, K = 4096 31.2 / 26.1, K = 14336 105.6 / 84.2); K = 2048 gains (512 rows 19.0 / 17.5), K = 896
+// loses (512 rows 9.1 / 9.2, 640 rows of 64 x 64 at N = 896 5.7 / 5.8): the line lies between those two.  A rest of fewer tiles
+// behind groups of eight goes without (QKV, 1034 rows of 128 x 128, K = 4096: 77 us, with it 90).
+// A 32 x 32 tile asks for so little of W per k-tile that the ring is ahead enough: 65 rows, K = 4864, 10.3 / 12.3 us (32 x 128, K = 4096,
+// 128 rows: 27.7 / 26.0).
+inline bool use_ahead(const GemmArgs& a, int bm, int bn, int tiles_m) { return bm * bn >= 64 * 64 && tiles_m >= kAheadShares && a.K >= 2048; }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
-    const bool ahead = WM * WN <= 4 && use_ahead(a, tiles_m);
+    const bool ahead = WM * WN <= 4 && use_ahead(a, BM, BN, tiles_m);
     constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (WM * WN <= 4 ? kAheadLds : 0);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS>, lds_most, attr_done); e != hipSuccess) return e;
