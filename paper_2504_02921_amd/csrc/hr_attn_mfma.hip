@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "hr_device_types.h"
+#include "hr_gemm_tiles.h"
 #include "hr_kernels.h"
 #include "hr_layout.h"
 
@@ -45,6 +46,9 @@ constexpr int kStageBytesHalf = 32768;
 constexpr int stage_bytes(bool fp8) { return fp8 ? kStageBytesHalf / 2 : kStageBytesHalf; }
 constexpr int kMaxRowsPerWg = 512;
 constexpr float kLazyMax = 8.0f;
+// Workgroups that read weights ahead (warm_weights), where the work items leave room for them on the chip.  0.5B shape, one query x 20
+// candidates x 32 tokens, whole call: none 1805 us, 64 1746, 128 1634, 256 1636, 384 1700 (they then share CUs with work items).
+constexpr int kWarmWgs = 128;
 
 template <int HD, bool FP8, int kStageBytes>
 struct Geo {
@@ -120,7 +124,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
                                                            const int32_t* __restrict__ g_p0, const int32_t* __restrict__ g_blk_cu,
                                                            const int32_t* __restrict__ g_sub_cu, const int32_t* __restrict__ g_blk_seq,
                                                            const int32_t* __restrict__ g_blk_row0, const int32_t* __restrict__ g_sub_page,
-                                                           const int32_t* __restrict__ g_sub_seq, const int32_t* __restrict__ g_sub_key0) {
+                                                           const int32_t* __restrict__ g_sub_seq, const int32_t* __restrict__ g_sub_key0,
+                                                           int n_wg, WeightWalks warm) {
     // The metadata arrays come as separate read-only, non-aliased parameters so that the per-item lookups (uniform
     // over the workgroup) compile to scalar loads: a vector load that is used right away makes the wave wait for
     // everything it has in flight, including the stage it requested a moment earlier, because vector memory
@@ -133,6 +138,10 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
     constexpr int KC = HD / 16;                      // MFMA k-steps over head_dim
     constexpr int MB = HD / 32;                      // 32-channel blocks of the output
     extern __shared__ __attribute__((aligned(16))) char smem[];      // [2][kStageBytes] + scales + (fp8) expanded stage
+    if ((int)blockIdx.x >= n_wg) {
+        warm_weights<NW>(warm, n_wg, smem);
+        return;
+    }
     float* s_scale = (float*)(smem + 2 * kStageBytes);              // [2][PPS][2]  (fp8 only)
     char* hbuf = smem + 2 * kStageBytes + 2 * G::PPS * 2 * sizeof(float);   // fp8 only: the current stage as half pages
     char* lobuf = hbuf + (FP8 ? 2 * kStageBytes : 0);                       // PREC only: [2][kStageBytes] lo pages of the pair's own keys
@@ -264,7 +273,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
             ids_load(c, tile + 1);
             return;
         }
-        for (int it = c_item + (int)gridDim.x; it < n_items; it += (int)gridDim.x) {
+        for (int it = c_item + n_wg; it < n_items; it += n_wg) {
             const ItemCtx n = load_ctx(it);
             if (n.n_tiles > 0) {
                 ids_load(n, 0);
@@ -540,8 +549,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
     dma_first(cur, 0);
     ids_after(cur, 0, (int)blockIdx.x);
     setup_rows(cur);
-    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int next_item = item + gridDim.x;
+    for (int item = blockIdx.x; item < n_items; item += n_wg) {
+        const int next_item = item + n_wg;
         const bool has_next = next_item < n_items;
         const ItemCtx nxt = has_next ? load_ctx(next_item) : cur;
 #pragma unroll
@@ -703,7 +712,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
 
 template <int HD, int NW, int R, bool FP8, bool PREC>
 hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo, half_t* o, const MetaView& mv, const PoolView& pv,
-                      int layer, int n_q, int last_only, const GroupView& gv, hipStream_t st) {
+                      int layer, int n_q, int last_only, const GroupView& gv, const WeightWalks* warm, hipStream_t st) {
     constexpr int SB = stage_bytes(FP8);
     const size_t lds = 2 * SB + 2 * Geo<HD, FP8, SB>::PPS * 2 * sizeof(float) + (FP8 ? 2 * SB : 0) + (PREC ? 2 * SB : 0);
     // once per kernel instantiation and device (a host thread may drive any device): the LDS attribute, and the size of
@@ -726,11 +735,12 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
         max_wgs_dev[dev].store(max_wgs, std::memory_order_release);
     }
     const int n_items = (gv.n_groups > 0 ? gv.n_groups : mv.n_seq) * pv.n_kv;
-    const int grid = std::min(n_items, max_wgs);
-    attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)grid), NW * 64, lds, st>>>(q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, mv.cu, mv.prefix_len,
+    const int n_wg = std::min(n_items, max_wgs);
+    const int extra = warm && warm->n > 0 ? std::min(kWarmWgs, max_wgs - n_wg) / kXcds * kXcds : 0;
+    attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)(n_wg + extra)), NW * 64, lds, st>>>(q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, mv.cu, mv.prefix_len,
                                                                                    mv.page_table, mv.new_cu, pv.scales, last_only, gv.n_groups, gv.p0,
                                                                                    gv.blk_cu, gv.sub_cu, gv.blk_seq, gv.blk_row0, gv.sub_page,
-                                                                                   gv.sub_seq, gv.sub_key0);
+                                                                                   gv.sub_seq, gv.sub_key0, n_wg, warm ? *warm : WeightWalks{});
     return hipGetLastError();
 }
 
@@ -758,7 +768,8 @@ bool attn_mfma_supported_cut(const hr_model_cfg& c, int kv_dtype, int max_q_len)
 }
 
 hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, const MetaView& mv, const PoolView& pv, int layer,
-                            int n_q, int max_q_len, hipStream_t st, bool last_only, const GroupView* groups, const void* kv_new_lo_pages) {
+                            int n_q, int max_q_len, hipStream_t st, bool last_only, const GroupView* groups, const void* kv_new_lo_pages,
+                            const WeightWalks* warm) {
     if (mv.n_seq == 0) return hipSuccess;
     const GroupView gv = groups && !last_only ? *groups : GroupView{};
     const int rows = gv.n_groups > 0 ? gv.max_blocks * 32 : n_q / pv.n_kv * (last_only ? 1 : max_q_len);
@@ -772,8 +783,8 @@ hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, co
         // the 22-bit form: split q / o and lo pages of the new keys (see the kernel); one wave per SIMD, 8 waves
         if (last_only) return hipErrorInvalidValue;
 #define HR_ATTN_PREC(HD, R)                                                                                 \
-    return fp8 ? launch_one<HD, 8, R, true, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, st)             \
-               : launch_one<HD, 8, R, false, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, st)
+    return fp8 ? launch_one<HD, 8, R, true, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, warm, st)             \
+               : launch_one<HD, 8, R, false, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, warm, st)
         if (pv.d == 64) {
             if (rows <= 256) { HR_ATTN_PREC(64, 1); }
             HR_ATTN_PREC(64, 2);
@@ -784,8 +795,8 @@ hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, co
 #undef HR_ATTN_PREC
     }
 #define HR_ATTN_CASE(HD, NW, R)                                                                                   \
-    return fp8 ? launch_one<HD, NW, R, true, false>(qh, kvn, nullptr, oh, mv, pv, layer, n_q, last_only ? 1 : 0, gv, st)   \
-               : launch_one<HD, NW, R, false, false>(qh, kvn, nullptr, oh, mv, pv, layer, n_q, last_only ? 1 : 0, gv, st)
+    return fp8 ? launch_one<HD, NW, R, true, false>(qh, kvn, nullptr, oh, mv, pv, layer, n_q, last_only ? 1 : 0, gv, warm, st)   \
+               : launch_one<HD, NW, R, false, false>(qh, kvn, nullptr, oh, mv, pv, layer, n_q, last_only ? 1 : 0, gv, warm, st)
     if (pv.d == 64) {
         if (rows <= 128) { HR_ATTN_CASE(64, 4, 1); }
         if (rows <= 256) { HR_ATTN_CASE(64, 4, 2); }

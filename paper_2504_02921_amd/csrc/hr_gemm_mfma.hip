@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "hr_device_types.h"
+#include "hr_gemm_tiles.h"
 #include "hr_internal.h"
 #include "hr_kernels.h"
 #include "hr_layout.h"
@@ -40,29 +41,8 @@ typedef __attribute__((ext_vector_type(4))) unsigned uint4v;
 namespace {
 
 constexpr int BK = 64;
-constexpr int kXcds = 8, kGroupM = 8;
 constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
 constexpr int kAheadShares = 4;                  // ... and how many tiles of a column take turns at least
-
-struct TileCoord { int tm, tn, share, shares; bool valid; };     // tile; its number among the `shares` that follow each other in one tile column
-
-__device__ __forceinline__ TileCoord map_tile(int pid, int tiles_m, int tiles_n) {
-    int n_tiles = tiles_m * tiles_n;
-    int per_xcd = (n_tiles + kXcds - 1) / kXcds;
-    int tile = (pid % kXcds) * per_xcd + pid / kXcds;
-    TileCoord c;
-    c.valid = tile < n_tiles && pid / kXcds < per_xcd;
-    int width = kGroupM * tiles_n;
-    int group = tile / width;
-    int first_m = group * kGroupM;
-    int gsz = min(tiles_m - first_m, kGroupM);
-    int in = tile - group * width;
-    c.share = in % gsz;
-    c.shares = gsz;
-    c.tm = first_m + c.share;
-    c.tn = in / gsz;
-    return c;
-}
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
@@ -891,6 +871,9 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
 // behind groups of eight goes without (QKV, 1034 rows of 128 x 128, K = 4096: 77 us, with it 90).
 // A 32 x 32 tile asks for so little of W per k-tile that the ring is ahead enough: 65 rows, K = 4864, 10.3 / 12.3 us (32 x 128, K = 4096,
 // 128 rows: 27.7 / 26.0).
+// It also stays where the attention has read W ahead (WeightWalks): of the down projection's little is left in the L2s once the
+// activations of 2000 rows have passed through them (whole calls without / with it: 640 tokens 1633 / 1634 us, 2000 2864 / 2766, 4000
+// 4279 / 4002).
 inline bool use_ahead(const GemmArgs& a, int bm, int bn, int tiles_m) { return bm * bn >= 64 * 64 && tiles_m >= kAheadShares && a.K >= 2048; }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
@@ -951,12 +934,50 @@ static void advance_rows(GemmEpilogue epi, GemmArgs& r, int64_t rows) {
 // 7.4 / 5.7, two rounds (640 rows) 7.7 / 9.7; 8B shape (N = 6144, K = 4096) 128 rows (192 tiles) 31.2 / 26.0, 256 rows 28.1 / 44.3.
 static bool half_tall(const GemmArgs& a, int bn) { return (a.M + 31) / 32 * ((a.N + bn - 1) / bn) <= cu_count(); }
 
+static GemmKind kind_of(GemmEpilogue epi, const GemmArgs& a) {
+    const bool wide_head = epi == EPI_QKV_ROPE && a.d == 128;       // a wave must span a whole 128-wide head
+    return epi == EPI_RESID_ADD ? GEMM_RESID : epi == EPI_SWIGLU ? GEMM_SWIGLU : wide_head ? GEMM_QKV128 : GEMM_QKV64;
+}
+
+// The XCDs' L2s hold 4 MiB each; the activations pass through them as well.  A layer of the 0.5B shape is 28.4 MiB.  O alone of the
+// 8B shape (32 MiB): 100 rows 6083 -> 5946 us a call, 640 rows 10630 -> 10680.
+constexpr int64_t kWarmBytes = (int64_t)30 << 20;
+
+bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out) {
+    const GemmKind kind = kind_of(epi, a);
+    const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count());
+    const int Kw = a.Kw > 0 ? a.Kw : a.K;
+    const int64_t bytes = (int64_t)a.N * Kw * (int64_t)sizeof(half_t);
+    if (g.n != 1 || out->n >= kWarmMost || out->bytes + bytes > kWarmBytes) return false;
+    int bm = 0, bn = 0;
+    switch (g.part[0].tile) {
+        case GT_BIG: bm = 256; bn = 256; break;
+        case GT_TALL: bm = 320; bn = 256; break;
+        case GT_SMALL: case GT_RING128: bm = 128; bn = 128; break;
+        case GT_RING128_256: bm = 128; bn = 256; break;
+        case GT_RING64_128: bm = 64; bn = 128; break;
+        case GT_RING160_64: bm = 160; bn = 64; break;
+        case GT_RING96_64: bm = 96; bn = 64; break;
+        case GT_RING64: bm = 64; bn = 64; break;
+        case GT_RING32: bm = 32; bn = 32; break;
+    }
+    if ((kind == GEMM_QKV64 || kind == GEMM_QKV128) && bm == 64 && half_tall(a, bn)) bm = 32;
+    WeightWalk& w = out->w[out->n++];
+    w.W = (const char*)a.W;
+    w.row_bytes = Kw * (int)sizeof(half_t);
+    w.rows = a.N;
+    w.tiles_m = (int)((a.M + bm - 1) / bm);
+    w.tiles_n = (a.N + bn - 1) / bn;
+    w.bn = bn;
+    out->bytes += bytes;
+    return true;
+}
+
 hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st) {
     if (a.M == 0) return hipSuccess;
     if (a.K % BK != 0) return hipErrorInvalidValue;
     if (a.Kw > 0 && (a.Kw % BK != 0 || (a.K != a.Kw && a.K != 2 * a.Kw))) return hipErrorInvalidValue;
-    const bool wide_head = epi == EPI_QKV_ROPE && a.d == 128;       // a wave must span a whole 128-wide head
-    const GemmKind kind = epi == EPI_RESID_ADD ? GEMM_RESID : epi == EPI_SWIGLU ? GEMM_SWIGLU : wide_head ? GEMM_QKV128 : GEMM_QKV64;
+    const GemmKind kind = kind_of(epi, a);
     const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count());
     GemmArgs r = a;
     for (int i = 0; i < g.n; ++i) {

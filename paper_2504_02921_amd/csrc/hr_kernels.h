@@ -38,6 +38,21 @@ struct MetaView {
     int64_t T;
 };
 
+// Weights that the next launches read, for a launch whose idle CUs bring them into the L2 of the XCD that will want them
+// (warm_weights).
+// A walk describes one projection's tiles (the order in which its workgroups take them is known), at most kWarmMost of them.
+constexpr int kWarmMost = 4;
+struct WeightWalk {
+    const char* W;
+    int row_bytes, rows;          // W is [rows][row_bytes]
+    int tiles_m, tiles_n, bn;
+};
+struct WeightWalks {
+    int n = 0;
+    int64_t bytes = 0;
+    WeightWalk w[kWarmMost];
+};
+
 // ---- any shape, VALU arithmetic in fp32 (hr_kernels_generic.hip) ----
 // Everything in front of the first layer as one launch: the embedding rows -> x, the RoPE table, `zero_bytes` (a multiple of
 // 16) cleared at `zero`, and, with meta_host (pinned host memory as the device addresses it), the metadata block copied to
@@ -119,6 +134,10 @@ struct GemmArgs {
 };
 hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st);
 
+// adds the projection `a` (its M, N, K and W) as it would be launched.  Nothing is added (and false returned) when it runs as
+// several launches, or when its weights and those added so far would not stay in the L2s together.
+bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out);
+
 bool attn_mfma_supported(const hr_model_cfg& c, int kv_dtype, int max_q_len);          // one work item per (sequence, kv head)
 bool attn_mfma_supported_cut(const hr_model_cfg& c, int kv_dtype, int max_q_len);      // ... or several, by a group plan
 // Device-side view of a group plan (GroupPlan): sequences that share a cached document are one work item per kv head.
@@ -128,11 +147,12 @@ struct GroupView {
                   *sub_seq = nullptr, *sub_key0 = nullptr;
 };
 // kv_new_pages: the new tokens' K/V as pages (see GemmArgs::kv_pages).  groups: nullptr = every sequence on its own.
+// warm: what workgroups of the launch that find no work item may read ahead.
 // kv_new_lo_pages: if set, the 22-bit form: q and o are [T][hi | lo] halves, and this buffer (same arrangement as
 // kv_new_pages) holds what the rounding of the new tokens' K/V to half left out.
 hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, const MetaView& mv,
                             const PoolView& pv, int layer, int n_q, int max_q_len, hipStream_t st, bool last_only = false,
-                            const GroupView* groups = nullptr, const void* kv_new_lo_pages = nullptr);
+                            const GroupView* groups = nullptr, const void* kv_new_lo_pages = nullptr, const WeightWalks* warm = nullptr);
 // fp8 pools: quantising copy of whole pages (amax -> scale -> E4M3 codes per page and kv head) from the half new-KV buffer
 hipError_t launch_pages_to_pool_fp8(const char* kv_new, char* pool_layer_base, float* scales_layer_base, const int32_t* src_page,
                                     const int32_t* dst_page, int n_pages, int n_kv, int d, hipStream_t st);
