@@ -712,7 +712,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
 
 template <int HD, int NW, int R, bool FP8, bool PREC>
 hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo, half_t* o, const MetaView& mv, const PoolView& pv,
-                      int layer, int n_q, int last_only, const GroupView& gv, const WeightWalks* warm, hipStream_t st) {
+                      int layer, int n_q, int last_only, const GroupView& gv, WeightWalks* warm, hipStream_t st) {
     constexpr int SB = stage_bytes(FP8);
     const size_t lds = 2 * SB + 2 * Geo<HD, FP8, SB>::PPS * 2 * sizeof(float) + (FP8 ? 2 * SB : 0) + (PREC ? 2 * SB : 0);
     // once per kernel instantiation and device (a host thread may drive any device): the LDS attribute, and the size of
@@ -737,6 +737,7 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
     const int n_items = (gv.n_groups > 0 ? gv.n_groups : mv.n_seq) * pv.n_kv;
     const int n_wg = std::min(n_items, max_wgs);
     const int extra = warm && warm->n > 0 ? std::min(kWarmWgs, max_wgs - n_wg) / kXcds * kXcds : 0;
+    if (warm) warm->done = extra > 0;
     attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)(n_wg + extra)), NW * 64, lds, st>>>(q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, mv.cu, mv.prefix_len,
                                                                                    mv.page_table, mv.new_cu, pv.scales, last_only, gv.n_groups, gv.p0,
                                                                                    gv.blk_cu, gv.sub_cu, gv.blk_seq, gv.blk_row0, gv.sub_page,
@@ -769,7 +770,7 @@ bool attn_mfma_supported_cut(const hr_model_cfg& c, int kv_dtype, int max_q_len)
 
 hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, const MetaView& mv, const PoolView& pv, int layer,
                             int n_q, int max_q_len, hipStream_t st, bool last_only, const GroupView* groups, const void* kv_new_lo_pages,
-                            const WeightWalks* warm) {
+                            WeightWalks* warm) {
     if (mv.n_seq == 0) return hipSuccess;
     const GroupView gv = groups && !last_only ? *groups : GroupView{};
     const int rows = gv.n_groups > 0 ? gv.max_blocks * 32 : n_q / pv.n_kv * (last_only ? 1 : max_q_len);

@@ -871,10 +871,9 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
 // behind groups of eight goes without (QKV, 1034 rows of 128 x 128, K = 4096: 77 us, with it 90).
 // A 32 x 32 tile asks for so little of W per k-tile that the ring is ahead enough: 65 rows, K = 4864, 10.3 / 12.3 us (32 x 128, K = 4096,
 // 128 rows: 27.7 / 26.0).
-// It also stays where the attention has read W ahead (WeightWalks): of the down projection's little is left in the L2s once the
-// activations of 2000 rows have passed through them (whole calls without / with it: 640 tokens 1633 / 1634 us, 2000 2864 / 2766, 4000
-// 4279 / 4002).
-inline bool use_ahead(const GemmArgs& a, int bm, int bn, int tiles_m) { return bm * bn >= 64 * 64 && tiles_m >= kAheadShares && a.K >= 2048; }
+// Where the attention has read W ahead (WeightWalks) the wavefront only takes LDS and issue slots: 0.5B shape, whole calls with /
+// without it: 640 tokens 1652 / 1630 us, 1000 1963 / 1949, 2000 2879 / 2842, 4000 4283 / 4274.
+inline bool use_ahead(const GemmArgs& a, int bm, int bn, int tiles_m) { return !a.w_near && bm * bn >= 64 * 64 && tiles_m >= kAheadShares && a.K >= 2048; }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
 hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {

@@ -50,6 +50,7 @@ struct WeightWalk {
 struct WeightWalks {
     int n = 0;
     int64_t bytes = 0;
+    bool done = false;            // set by the launch that was handed them: it has workgroups for them
     WeightWalk w[kWarmMost];
 };
 
@@ -118,6 +119,7 @@ struct GemmArgs {
     // Split A operand: 0 (or K) = plain; K / 2 = A is [M][K] holding [hi | lo] halves of a K/2-wide activation (the value
     // is hi + lo, 22 significant bits) and W has K / 2 columns, met by both halves: C = hi W^T + lo W^T
     int Kw;
+    bool w_near;        // W has just been brought into the L2s (WeightWalks)
     // EPI_SWIGLU: m is written as [M][2 * N/2] = [hi | lo]
     int split_out;
     // epilogue operands
@@ -152,7 +154,7 @@ struct GroupView {
 // kv_new_pages) holds what the rounding of the new tokens' K/V to half left out.
 hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, const MetaView& mv,
                             const PoolView& pv, int layer, int n_q, int max_q_len, hipStream_t st, bool last_only = false,
-                            const GroupView* groups = nullptr, const void* kv_new_lo_pages = nullptr, const WeightWalks* warm = nullptr);
+                            const GroupView* groups = nullptr, const void* kv_new_lo_pages = nullptr, WeightWalks* warm = nullptr);
 // fp8 pools: quantising copy of whole pages (amax -> scale -> E4M3 codes per page and kv head) from the half new-KV buffer
 hipError_t launch_pages_to_pool_fp8(const char* kv_new, char* pool_layer_base, float* scales_layer_base, const int32_t* src_page,
                                     const int32_t* dst_page, int n_pages, int n_kv, int d, hipStream_t st);
