@@ -56,9 +56,18 @@ __device__ __forceinline__ float e4m3_to_float(uint8_t c) {
 __device__ __forceinline__ float rope_lo(float x1, float x2, float c, float s) { return __fmaf_rn(x1, c, -__fmul_rn(x2, s)); }
 __device__ __forceinline__ float rope_hi(float x1, float x2, float c, float s) { return __fmaf_rn(x2, c, __fmul_rn(x1, s)); }
 
+// Sum over the wavefront, in every lane: a butterfly over lane ^ 32, ^ 16, .. ^ 1 in the VALU's lane swaps and row permutations
+// (through LDS, as __shfl_xor goes, each step is a round trip).  A rotation by 8 or 4 within a row of 16 lanes brings the partner's
+// value: what the steps before left depends on the lane modulo 16 and 8 only.
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x128, 0xF, 0xF, true));      // row_ror:8
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x124, 0xF, 0xF, true));      // row_ror:4
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x4E, 0xF, 0xF, true));       // quad_perm:[2,3,0,1]
+    v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0xB1, 0xF, 0xF, true));       // quad_perm:[1,0,3,2]
     return v;
 }
 __device__ __forceinline__ float wave_max(float v) {
