@@ -571,16 +571,17 @@ int hr_weights_load(const hr_model_cfg* cfg, const hr_weight_ptrs* w, void* pack
             return HR_ERR_DEVICE;
         }
     }
+    auto half_n = [&](int N) { return m->mfma_gemm ? N : 0; };
     for (int l = 0; l < cfg->n_layers; ++l) {
         char* slab = (char*)pack_dev + (size_t)l * pl.layer_elems * esz;
         char* wqkv = slab + pl.wqkv * esz;
-        hipError_t e = hr::launch_pack_rows(dt, w->wq[l], wqkv, nq, H, nq, 1, 0, rc, st);
-        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wk[l], wqkv + (size_t)nq * H * esz, nkv, H, nkv, 1, 0, rc, st);
-        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wv[l], wqkv + (size_t)(nq + nkv) * H * esz, nkv, H, nkv, 1, 0, rc, st);
-        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wo[l], slab + pl.wo * esz, H, nq, H, 1, 0, rc, st);
-        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wg[l], slab + pl.wgu * esz, F, H, pl.gu_interleave, 2, 0, rc, st);
-        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wu[l], slab + pl.wgu * esz, F, H, pl.gu_interleave, 2, 1, rc, st);
-        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wd[l], slab + pl.wd * esz, H, F, H, 1, 0, rc, st);
+        hipError_t e = hr::launch_pack_rows(dt, w->wq[l], wqkv, nq, H, nq, 1, 0, 0, half_n(nq + 2 * nkv), rc, st);
+        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wk[l], wqkv, nkv, H, nkv, 1, 0, nq, half_n(nq + 2 * nkv), rc, st);
+        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wv[l], wqkv, nkv, H, nkv, 1, 0, nq + nkv, half_n(nq + 2 * nkv), rc, st);
+        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wo[l], slab + pl.wo * esz, H, nq, H, 1, 0, 0, half_n(H), rc, st);
+        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wg[l], slab + pl.wgu * esz, F, H, pl.gu_interleave, 2, 0, 0, half_n(2 * F), rc, st);
+        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wu[l], slab + pl.wgu * esz, F, H, pl.gu_interleave, 2, 1, 0, half_n(2 * F), rc, st);
+        if (e == hipSuccess) e = hr::launch_pack_rows(dt, w->wd[l], slab + pl.wd * esz, H, F, H, 1, 0, 0, half_n(H), rc, st);
         if (e != hipSuccess) {
             note_hip_error(e, "weight packing kernels");
             hr_model_destroy(m);

@@ -41,6 +41,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned uint4v;
 namespace {
 
 constexpr int BK = 64;
+static_assert(kWBlock == BK, "a k-tile of W is whole lines");
 constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
 constexpr int kAheadShares = 4;                  // ... and how many tiles of a column take turns at least
 
@@ -69,10 +70,41 @@ struct TileSrc {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 16, voff, pass[p] + koff, 0, 0);
 #endif
     }
-    // four bytes a lane into 256 bytes nobody reads: what counts is that their lines are in the L2 afterwards
-    __device__ __forceinline__ void touch(half_t* lds, int voff, int koff) const {
+};
+
+// The same for W, from row n0 on; BLK: blocked (w_elem).  Constants and not a run-time stride: the ring kernel's k loop with a
+// multiplication per request took 0.4 % of a 640-token call of the 0.5B shape.  N is a multiple of 64: a pass is inside the
+// matrix or behind it as a whole, and lies in one block.
+template <int BN, int RPP, bool BLK>
+struct WTileSrc {
+    static constexpr int PASSES = BN / RPP;
+    static constexpr int kTile = (BLK ? kWBlock * BK : BK) * (int)sizeof(half_t);       // bytes from one k-tile to the next
+    static __device__ __forceinline__ int row(int K) { return BLK ? kWBlock : K; }
+    int pass[PASSES];
 #ifdef __HIP_DEVICE_COMPILE__
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 4, voff, koff, 0, 0);
+    __amdgpu_buffer_rsrc_t rsrc;
+#endif
+    __device__ __forceinline__ void set(const half_t* W, int n0, int rows, int K) {
+        constexpr bool HALF = BLK && BN < kWBlock;         // a 32-row tile may start in the middle of a block
+        const int in_block = HALF ? n0 % kWBlock * kWBlock * 2 : 0;
+#ifdef __HIP_DEVICE_COMPILE__
+        rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)(HALF ? n0 / kWBlock * kWBlock : n0) * K), 0, (HALF ? kWBlock : rows) * K * 2, 0x00020000);
+#endif
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            const int first = BLK ? p * RPP / kWBlock * kWBlock * K + p * RPP % kWBlock * kWBlock : p * RPP * K;
+            pass[p] = (p * RPP < rows ? first * 2 : 0) + in_block;
+        }
+    }
+    __device__ __forceinline__ void load(int p, half_t* lds, int voff, int koff) const {
+#ifdef __HIP_DEVICE_COMPILE__
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 16, voff, pass[p] + koff, 0, 0);
+#endif
+    }
+    // four bytes a lane into 256 bytes nobody reads: what counts is that their lines are in the L2 afterwards
+    __device__ __forceinline__ void touch(int p, half_t* lds, int voff, int koff) const {
+#ifdef __HIP_DEVICE_COMPILE__
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)lds, 4, voff, pass[p] + koff, 0, 0);
 #endif
     }
 };
@@ -394,7 +426,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
 // MFMAs (a wave issues in order, and the CU takes 60 bytes per cycle).
 // Accumulation is transposed (D = W_frag * A_frag^T): a lane owns ONE output row (lane & 15) and 4 consecutive columns
 // per block, so the epilogues address one row pointer per block and store 8 / 16 bytes at a time.
-template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA, bool BLK>
 __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 1) gemm_mfma_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;      // wave tile
@@ -429,14 +461,14 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
     // chunk that the row-pair swizzle maps there
     const int lrow = tid >> 3;
     const int lchunk = (tid & 7) ^ ((lrow >> 1) & 7);
-    const int va = (lrow * K + lchunk * 8) * 2, vb = (lrow * Kw + lchunk * 8) * 2;
+    const int va = (lrow * K + lchunk * 8) * 2, vb = (lrow * WTileSrc<BN, RPP, BLK>::row(Kw) + lchunk * 8) * 2;
     TileSrc<PA, RPP> srcA;
-    TileSrc<PB, RPP> srcB;
+    WTileSrc<BN, RPP, BLK> srcB;
     auto set_tile = [&](const TileCoord& t) {
         m0 = (int64_t)t.tm * BM;
         n0 = t.tn * BN;
         srcA.set((const half_t*)a.A + m0 * K, (int)min((int64_t)BM, a.M - m0), K);
-        srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
+        srcB.set((const half_t*)a.W, n0, min(BN, a.N - n0), Kw);
     };
     set_tile(tc);
     // load p of the PA of A's k-tile kt / of the PB of W's (the LDS address is wave-uniform: the hardware adds 16 bytes per
@@ -446,7 +478,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
     };
     auto dma_b = [&](int p, int kt, int slot) {
         const int ktw = kt < nkw ? kt : kt - nkw;             // the lo half of a split A meets the same W columns again
-        srcB.load(p, sB + slot * BN * BK + wave * 64 * 8 + p * NT * 8, kt < nk ? vb : kNoLoad, kt < nk ? ktw * (BK * 2) : 0);
+        srcB.load(p, sB + slot * BN * BK + wave * 64 * 8 + p * NT * 8, kt < nk ? vb : kNoLoad, kt < nk ? ktw * srcB.kTile : 0);
     };
     auto dma_first = [&]() {                                  // k-tile 0 of a tile, into stages 0
 #pragma unroll
@@ -612,7 +644,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 // a round holds pay for A and W read twice as often: down projection, 640 rows 19.7 -> 30.5 us.
 // Tiles of 96 and 160 rows x 64 (residual adds) fill rounds that the powers of two leave a third empty: 8B down projection, 640
 // rows 128 x 128 (160 tiles) 105.1 -> 160 x 64 (256 tiles) 97.6 us.
-template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS, bool BLK>
 __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
@@ -639,21 +671,20 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
     const int Kw = a.Kw > 0 ? a.Kw : K;
     const int nkw = Kw / BK, nk = K / BK;
     TileSrc<PA, RPP> srcA;
-    TileSrc<PB, RPP> srcB;
-    srcB.set((const half_t*)a.W + (size_t)n0 * Kw, min(BN, a.N - n0), Kw);
+    WTileSrc<BN, RPP, BLK> srcB;
+    srcB.set((const half_t*)a.W, n0, min(BN, a.N - n0), Kw);
     if constexpr (WM * WN <= 4) {
         if (wave == WM * WN) {
             if (tc.shares < kAheadShares) return;     // too few to take turns (barriers go on without the wave)
-            // touches one 4-byte word of every 64 bytes: 32 rows of a k-tile per request.  Every row offset sits in the vector
-            // offset, so rows past the end fail the range check
-            int vt[BN / 32];
-#pragma unroll
-            for (int p = 0; p < BN / 32; ++p) vt[p] = (p * 32 + (lane >> 1)) * Kw * 2 + (lane & 1) * 64;
+            // touches one 4-byte word of every 64 bytes: 32 rows of a k-tile per request
+            WTileSrc<BN, 32, BLK> src;
+            const int vt = (lane >> 1) * src.row(Kw) * 2 + (lane & 1) * 64;
+            src.set((const half_t*)a.W, n0, min(BN, a.N - n0), Kw);
             int turn = NS % tc.shares;                // k-tile mod shares: whose turn it is
             auto touch = [&](int kt) {
                 if (turn == tc.share && kt < nkw) {
 #pragma unroll
-                    for (int p = 0; p < BN / 32; ++p) srcB.touch((half_t*)(smem + (size_t)NS * (BM + BN) * BK * sizeof(half_t)), vt[p], kt * (BK * 2));
+                    for (int p = 0; p < BN / 32; ++p) src.touch(p, (half_t*)(smem + (size_t)NS * (BM + BN) * BK * sizeof(half_t)), vt, kt * src.kTile);
                 }
                 turn = turn + 1 == tc.shares ? 0 : turn + 1;
             };
@@ -679,7 +710,7 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
     const int lrow = tid >> 3;
     const int lchunk = (tid & 7) ^ ((lrow >> 1) & 7);
     srcA.set((const half_t*)a.A + m0 * K, (int)min((int64_t)BM, a.M - m0), K);
-    const int va = (lrow * K + lchunk * 8) * 2, vb = (lrow * Kw + lchunk * 8) * 2;
+    const int va = (lrow * K + lchunk * 8) * 2, vb = (lrow * srcB.row(Kw) + lchunk * 8) * 2;
     auto dma = [&](int kt, int buf) {
         half_t* da = sA + buf * BM * BK + wave * 64 * 8;
         half_t* db = sB + buf * BN * BK + wave * 64 * 8;
@@ -687,7 +718,7 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
 #pragma unroll
         for (int p = 0; p < PA; ++p) srcA.load(p, da + p * NT * 8, va, kt * (BK * 2));
 #pragma unroll
-        for (int p = 0; p < PB; ++p) srcB.load(p, db + p * NT * 8, vb, ktw * (BK * 2));
+        for (int p = 0; p < PB; ++p) srcB.load(p, db + p * NT * 8, vb, ktw * srcB.kTile);
     };
     floatx4 acc[MI][NI];
 #pragma unroll
@@ -741,7 +772,7 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
         constexpr int NM = KS * MI * NI, ND = KS * (MI + NI);
         const half_t *nA = sA + next * BM * BK, *nB = sB + next * BN * BK;
         half_t *dA = sA + slot * BM * BK + wave * 64 * 8, *dB = sB + slot * BN * BK + wave * 64 * 8;
-        const int ktn = kt + NS, ka = ktn * (BK * 2), kb = (ktn < nkw ? ktn : ktn - nkw) * (BK * 2);
+        const int ktn = kt + NS, ka = ktn * (BK * 2), kb = (ktn < nkw ? ktn : ktn - nkw) * srcB.kTile;
         auto read_op = [&](int r) {
             const int rk = r / (MI + NI), f = r % (MI + NI);
             if (f < MI) af[SET ^ 1][rk][f] = *(const halfx8*)(nA + at_a[rk] + f * 16 * BK);
@@ -844,8 +875,8 @@ hipError_t allow_dynamic_lds(K kernel, size_t lds, std::atomic<uint64_t>& done) 
     return e;
 }
 
-template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
-hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA, bool BLK>
+hipError_t launch_tile_of(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int n_tiles = tiles_m * tiles_n;
     const int per_xcd = (n_tiles + kXcds - 1) / kXcds;
@@ -858,9 +889,15 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
     }
     const size_t lds = (size_t)(SA * BM + 2 * BN) * BK * sizeof(half_t);
     static std::atomic<uint64_t> attr_done{0};
-    if (hipError_t e = allow_dynamic_lds(gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA>, lds, attr_done); e != hipSuccess) return e;
-    gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(a);
+    if (hipError_t e = allow_dynamic_lds(gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA, BLK>, lds, attr_done); e != hipSuccess) return e;
+    gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA, BLK><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(a);
     return hipGetLastError();
+}
+
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
+hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
+    return w_blocked(a.N, a.Kw > 0 ? a.Kw : a.K) ? launch_tile_of<EPI, BM, BN, WM, WN, HB, SA, true>(a, st)
+                                                 : launch_tile_of<EPI, BM, BN, WM, WN, HB, SA, false>(a, st);
 }
 
 // The reading-ahead wavefront pays where several tiles share a column of W and the k loop is long.  Without / with it, weights
@@ -875,16 +912,22 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
 // without it: 640 tokens 1652 / 1630 us, 1000 1963 / 1949, 2000 2879 / 2842, 4000 4283 / 4274.
 inline bool use_ahead(const GemmArgs& a, int bm, int bn, int tiles_m) { return !a.w_near && bm * bn >= 64 * 64 && tiles_m >= kAheadShares && a.K >= 2048; }
 
-template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
-hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS, bool BLK>
+hipError_t launch_ring_of(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
     const bool ahead = WM * WN <= 4 && use_ahead(a, BM, BN, tiles_m);
     constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (WM * WN <= 4 ? kAheadLds : 0);
     static std::atomic<uint64_t> attr_done{0};
-    if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS>, lds_most, attr_done); e != hipSuccess) return e;
-    gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS><<<dim3((unsigned)grid), (WM * WN + ahead) * 64, ahead ? lds_most : ring, st>>>(a);
+    if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS, BLK>, lds_most, attr_done); e != hipSuccess) return e;
+    gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS, BLK><<<dim3((unsigned)grid), (WM * WN + ahead) * 64, ahead ? lds_most : ring, st>>>(a);
     return hipGetLastError();
+}
+
+template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
+hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
+    return w_blocked(a.N, a.Kw > 0 ? a.Kw : a.K) ? launch_ring_of<EPI, BM, BN, WM, WN, HB, NS, true>(a, st)
+                                                 : launch_ring_of<EPI, BM, BN, WM, WN, HB, NS, false>(a, st);
 }
 
 int cu_count() {
@@ -961,6 +1004,7 @@ bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out) {
         case GT_RING32: bm = 32; bn = 32; break;
     }
     if ((kind == GEMM_QKV64 || kind == GEMM_QKV128) && bm == 64 && half_tall(a, bn)) bm = 32;
+    if (w_blocked(a.N, Kw)) bn = std::max(bn, kWBlock);       // what is walked is one run of memory: whole blocks
     WeightWalk& w = out->w[out->n++];
     w.W = (const char*)a.W;
     w.row_bytes = Kw * (int)sizeof(half_t);

@@ -103,17 +103,18 @@ hipError_t launch_score_head(int dtype, const float* x, const float* gain, const
 // counters: 8 int64 in device memory (RangeCounter indices), or nullptr
 hipError_t launch_kv_scatter(const PoolLayout& lay, char* pool_base, const int32_t* page_ids_host, int doc_len,
                              const void* k, const void* v, const float* ks, const float* vs, long long* counters, hipStream_t st);
-// dst row ((r / ib) * mul + sel) * ib + r % ib  <-  src row r   (rows of `cols` elements)
-hipError_t launch_pack_rows(int dtype, const void* src, void* dst, int rows, int cols, int ib, int mul, int sel,
-                            long long* counters, hipStream_t st);
+// dst row row0 + ((r / ib) * mul + sel) * ib + r % ib  <-  src row r   (rows of `cols` elements); N > 0: into the
+// matrix of N rows that the half MFMA kernels read (w_elem), else row-major
+hipError_t launch_pack_rows(int dtype, const void* src, void* dst, int rows, int cols, int ib, int mul, int sel, int row0,
+                            int N, long long* counters, hipStream_t st);
 
 // ---- MFMA paths (bf16) ----
 bool gemm_mfma_supported(const hr_model_cfg& c);
 int device_cu_count();      // compute units of the current device (256 if it cannot be asked)
 enum GemmEpilogue { EPI_QKV_ROPE = 0, EPI_RESID_ADD = 1, EPI_SWIGLU = 2 };
 struct GemmArgs {
-    const void* A;      // [M][K] bf16
-    const void* W;      // [N][K] bf16 (packed)
+    const void* A;      // [M][K] half
+    const void* W;      // [N][K] half, arranged as w_elem says, whole: N is the matrix's own
     int64_t M;
     int N, K;
     // Split A operand: 0 (or K) = plain; K / 2 = A is [M][K] holding [hi | lo] halves of a K/2-wide activation (the value

@@ -505,15 +505,15 @@ __global__ void __launch_bounds__(256) kv_scatter_kernel(KVT* __restrict__ pool,
 
 template <typename S, typename D>
 __global__ void pack_rows_kernel(const S* __restrict__ src, D* __restrict__ dst, int rows, int cols, int ib, int mul, int sel,
-                                 long long* __restrict__ counters) {
+                                 int row0, int N, long long* __restrict__ counters) {
     int r = blockIdx.x;
     if (r >= rows) return;
-    size_t drow = ((size_t)(r / ib) * mul + sel) * ib + r % ib;
+    size_t drow = row0 + ((size_t)(r / ib) * mul + sel) * ib + r % ib;
     int over = 0, under = 0, nonfinite = 0;
     for (int c = threadIdx.x; c < cols; c += blockDim.x) {
         const float v = to_float<S>(src[(size_t)r * cols + c]);
         if constexpr (sizeof(D) == 2) count_half_range(v, over, under, nonfinite);
-        dst[drow * cols + c] = from_float<D>(v);
+        dst[N > 0 ? (size_t)w_elem((int64_t)drow, c, N, cols) : drow * cols + c] = from_float<D>(v);
     }
     flush_range_counts(counters, over, under, nonfinite, 0, 0);
 }
@@ -852,13 +852,13 @@ hipError_t launch_kv_scatter(const PoolLayout& lay, char* pool_base, const int32
     return hipSuccess;
 }
 
-hipError_t launch_pack_rows(int dtype, const void* src, void* dst, int rows, int cols, int ib, int mul, int sel,
-                            long long* counters, hipStream_t st) {
+hipError_t launch_pack_rows(int dtype, const void* src, void* dst, int rows, int cols, int ib, int mul, int sel, int row0,
+                            int N, long long* counters, hipStream_t st) {
     if (dtype == HR_F32)
-        pack_rows_kernel<float, float><<<dim3((unsigned)rows), 256, 0, st>>>((const float*)src, (float*)dst, rows, cols, ib, mul, sel, counters);
+        pack_rows_kernel<float, float><<<dim3((unsigned)rows), 256, 0, st>>>((const float*)src, (float*)dst, rows, cols, ib, mul, sel, row0, N, counters);
     else   // the caller's bf16 weights become half operands (same rule as the pool write)
         pack_rows_kernel<bf16_t, half_t><<<dim3((unsigned)rows), 256, 0, st>>>((const bf16_t*)src, (half_t*)dst, rows, cols, ib,
-                                                                              mul, sel, counters);
+                                                                              mul, sel, row0, N, counters);
     return hipGetLastError();
 }
 

@@ -303,6 +303,35 @@ def test_projection_tiles_for_few_rows_give_a_pair_the_same_bits(d, n_q, n_kv, h
     test_projections_cut_by_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen)
 
 
+@pytest.mark.parametrize("n_q,n_queries,qlen", [
+    (16, 1, (33, 37)),         # all four matrices in blocks of 64 rows (w_elem); residual adds in 32 x 32 tiles, which read half blocks
+    (16, 7, (37, 37)),         # ... in 64-row and wider tiles
+    (8, 1, (33, 37)),          # QKV (N = 1536) and O (K = 1024) row-major beside blocked gate / up and down
+])
+def test_projections_on_blocked_weights_give_a_pair_the_same_bits(n_q, n_queries, qlen):
+    """Matrices of 2048 rows and columns and more are packed in blocks: the oracle within the bar, and the bits of a pair alone."""
+    test_projections_cut_by_rows_give_a_pair_the_same_bits(128, n_q, 2, 2048, 2112, n_queries, qlen)
+
+
+@pytest.mark.parametrize("hidden", [256, 960])     # one whole float4 per lane; four, of which the last reaches past the row
+def test_norms_of_many_rows_give_a_pair_the_same_bits(hidden):
+    """A wavefront per row (RMSNorm of 32768 rows and more, in both halves of a batch cut over two streams) against a
+    workgroup per row: the bits of a pair scored alone."""
+    model = small_model(dtype="bf16", n_layers=2, hidden=hidden, n_q=4, n_kv=2, d=64, ffn=320, vocab=500)
+    cfg = wlmod.WorkloadCfg("many_rows", model, 200, 4, (20, 60), (83, 83), "bf16", seed=hidden)
+    w = wlmod.SeededWeights(model, seed=18, std=0.05, gain_jitter=0.1)
+    wl = wlmod.make_workload(cfg, spare_pages=2)
+    case = H.Case(wl, w)
+    try:
+        case.fill_from_prefill()
+        got = case.gpu_scores()
+        assert np.isfinite(got).all()
+        for i in (0, wl.n_pairs // 2, wl.n_pairs - 1):
+            np.testing.assert_array_equal(case.gpu_scores(wl.subset(np.array([i]))), got[i:i + 1])
+    finally:
+        case.close()
+
+
 @pytest.mark.parametrize("hidden,ffn", [(256, 688), (200, 320)])
 def test_bf16_wide_heads_with_projection_shapes_outside_the_mfma_family(hidden, ffn):
     """head_dim 64 suits the MFMA attention, but hidden / ffn are not multiples of 64, so the projections run on the
