@@ -72,9 +72,8 @@ struct TileSrc {
     }
 };
 
-// The same for W, from row n0 on; BLK: blocked (w_elem).  Constants and not a run-time stride: the ring kernel's k loop with a
-// multiplication per request took 0.4 % of a 640-token call of the 0.5B shape.  N is a multiple of 64: a pass is inside the
-// matrix or behind it as a whole, and lies in one block.
+// The same for W, from row n0 on; BLK: blocked (w_elem), a template argument so that the k loops step by constants.  N is a
+// multiple of 64: a pass is inside the matrix or behind it as a whole, and lies in one block.
 template <int BN, int RPP, bool BLK>
 struct WTileSrc {
     static constexpr int PASSES = BN / RPP;
