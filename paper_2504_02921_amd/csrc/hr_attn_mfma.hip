@@ -25,6 +25,7 @@
 
 #include "hr_device_types.h"
 #include "hr_gemm_tiles.h"
+#include "hr_internal.h"
 #include "hr_kernels.h"
 #include "hr_layout.h"
 
@@ -736,12 +737,20 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
     }
     const int n_items = (gv.n_groups > 0 ? gv.n_groups : mv.n_seq) * pv.n_kv;
     const int n_wg = std::min(n_items, max_wgs);
-    const int extra = warm && warm->n > 0 ? std::min(kWarmWgs, max_wgs - n_wg) / kXcds * kXcds : 0;
-    if (warm) warm->done = extra > 0;
+    WeightWalks walks;                                              // those of `warm` that the launch has room for
+    int extra = std::min(kWarmWgs, max_wgs - n_wg) / kXcds * kXcds;
+    if (warm) {
+        int64_t bytes[kWarmMost];
+        for (int i = 0; i < warm->n; ++i) bytes[i] = (int64_t)warm->w[i].rows * warm->w[i].row_bytes;
+        warm->done = pick_weight_walks(bytes, warm->n, extra);
+        for (int i = 0; i < warm->n; ++i)
+            if (warm->done >> i & 1) walks.w[walks.n++] = warm->w[i];
+    }
+    if (walks.n == 0) extra = 0;
     attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)(n_wg + extra)), NW * 64, lds, st>>>(q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, mv.cu, mv.prefix_len,
                                                                                    mv.page_table, mv.new_cu, pv.scales, last_only, gv.n_groups, gv.p0,
                                                                                    gv.blk_cu, gv.sub_cu, gv.blk_seq, gv.blk_row0, gv.sub_page,
-                                                                                   gv.sub_seq, gv.sub_key0, n_wg, warm ? *warm : WeightWalks{});
+                                                                                   gv.sub_seq, gv.sub_key0, n_wg, walks);
     return hipGetLastError();
 }
 

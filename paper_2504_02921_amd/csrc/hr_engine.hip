@@ -332,16 +332,17 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
     // few tokens: the attention leaves most of the chip idle, and the projections behind it, up to the next layer's first, spend a
     // third of their time waiting for weights
     WeightWalks walks;
-    bool walk_o = false, walk_gu = false, walk_down = false, walk_qkv = false;
+    int walk_o = -1, walk_gu = -1, walk_down = -1;            // their numbers among the walks
+    bool walk_qkv = false;
     if (mfma_attn && T <= kWarmMaxTokens) {
         GemmArgs a{};
         a.M = T; a.d = d;
         a.W = layer_w(m, 0, m->pack.wo); a.N = H; a.K = nq;
-        walk_o = gemm_weight_walk(EPI_RESID_ADD, a, &walks);
+        if (gemm_weight_walk(EPI_RESID_ADD, a, &walks)) walk_o = walks.n - 1;
         a.W = layer_w(m, 0, m->pack.wgu); a.N = 2 * F; a.K = H;
-        walk_gu = gemm_weight_walk(EPI_SWIGLU, a, &walks);
+        if (gemm_weight_walk(EPI_SWIGLU, a, &walks)) walk_gu = walks.n - 1;
         a.W = layer_w(m, 0, m->pack.wd); a.N = H; a.K = F;
-        walk_down = gemm_weight_walk(EPI_RESID_ADD, a, &walks);
+        if (gemm_weight_walk(EPI_RESID_ADD, a, &walks)) walk_down = walks.n - 1;
         a.W = layer_w(m, 1, m->pack.wqkv); a.N = nqkv; a.K = H;
         walk_qkv = gemm_weight_walk(EPI_QKV_ROPE, a, &walks);
     }
@@ -438,19 +439,20 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
                                                       c.no_id, st));
             return HR_OK;
         }
-        bool near = false;                                    // the weights walked are in the L2s
+        unsigned walked = 0;                                  // whose weights are in the L2s
+        auto near = [&](int walk) { return walk >= 0 && (walked >> walk & 1); };
         if (mfma_attn) {
             WeightWalks ahead = walks;                       // of layer 0 and layer 1's QKV: the layers' packs are equally far apart
             if (walk_qkv && l + 1 == c.n_layers) --ahead.n;
             for (int i = 0; i < ahead.n; ++i) ahead.w[i].W += (size_t)l * m->pack.layer_elems * dtype_size(dt);
             HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, self_prefix ? 0 : l, c.n_q_heads, max_new_len, st, false, groups, nullptr, &ahead));
-            near = ahead.done;
+            walked = ahead.done;
         } else {
             HR_TIMED(PC_ATTENTION, launch_attn_generic(dt, q, k, v, o, mv, pv, l, c.n_q_heads, max_keys, st));
         }
         if (m->mfma_gemm) {
             GemmArgs a{};
-            a.A = o; a.W = layer_w(m, l, m->pack.wo); a.M = T; a.N = H; a.K = nq; a.x = x; a.w_near = near && walk_o;
+            a.A = o; a.W = layer_w(m, l, m->pack.wo); a.M = T; a.N = H; a.K = nq; a.x = x; a.w_near = near(walk_o);
             HR_TIMED(PC_GEMM_O, launch_gemm_mfma(EPI_RESID_ADD, a, st));
         } else {
             HR_TIMED(PC_GEMM_O, gemm_plain(F32_ADD, o, layer_w(m, l, m->pack.wo), x, H, nq));
@@ -458,10 +460,10 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
         HR_TIMED(PC_RMSNORM, launch_rmsnorm(dt, x, m->norm2[l], y, T, H, c.rms_eps, st));
         if (m->mfma_gemm) {
             GemmArgs a{};
-            a.A = y; a.W = layer_w(m, l, m->pack.wgu); a.M = T; a.N = 2 * F; a.K = H; a.out0 = mm; a.w_near = near && walk_gu;
+            a.A = y; a.W = layer_w(m, l, m->pack.wgu); a.M = T; a.N = 2 * F; a.K = H; a.out0 = mm; a.w_near = near(walk_gu);
             HR_TIMED(PC_GEMM_GATE_UP, launch_gemm_mfma(EPI_SWIGLU, a, st));
             GemmArgs b{};
-            b.A = mm; b.W = layer_w(m, l, m->pack.wd); b.M = T; b.N = H; b.K = F; b.x = x; b.w_near = near && walk_down;
+            b.A = mm; b.W = layer_w(m, l, m->pack.wd); b.M = T; b.N = H; b.K = F; b.x = x; b.w_near = near(walk_down);
             HR_TIMED(PC_GEMM_DOWN, launch_gemm_mfma(EPI_RESID_ADD, b, st));
         } else {
             HR_TIMED(PC_GEMM_GATE_UP, gemm_plain(F32_STORE, y, layer_w(m, l, m->pack.wgu), f32, 2 * F, H));

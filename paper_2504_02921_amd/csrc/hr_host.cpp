@@ -516,6 +516,17 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) 
     return g;
 }
 
+unsigned pick_weight_walks(const int64_t* bytes, int n, int wgs) {
+    unsigned picked = 0;
+    int64_t room = (int64_t)std::max(wgs, 0) * kWarmBytesPerWg;
+    for (int i = 0; i < n; ++i) {
+        if (bytes[i] > room) continue;
+        room -= bytes[i];
+        picked |= 1u << i;
+    }
+    return picked;
+}
+
 double gemm_resid_fill(int64_t M, int N, int k_o, int k_down, int cus_) {
     const int64_t cus = cus_ > 0 ? cus_ : 1;
     double busy = 0.0, total = 0.0;

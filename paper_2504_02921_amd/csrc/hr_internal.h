@@ -170,6 +170,13 @@ struct GemmPart { GemmTile tile; int64_t rows; };
 struct GemmLaunch { int n = 0; GemmPart part[2]; };
 GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus);
 
+// Which of n matrices `wgs` idle workgroups of a launch read ahead (bit i): each takes at most kWarmBytesPerWg, or the launch ends
+// later for their sake, and a matrix that does not fit beside those before it is left out.  496 work items leave 16 workgroups.  Whole
+// calls, nothing read ahead / everything / what fits: 0.5B shape (28.4 MiB a layer), 248 pairs x 4 tokens 2090 / 2741 / 2038 us; 16 layers of
+// hidden 2048 (O and QKV, 20 MiB), 62 pairs x 38 tokens 5096 / 5809 / 5100.
+constexpr int64_t kWarmBytesPerWg = 240 << 10;
+unsigned pick_weight_walks(const int64_t* bytes, int n, int wgs);
+
 // The measure by which a scoring call is cut in two halves: the share of the workgroup slots that the O (K = k_o) and the down
 // projection's (K = k_down) tiles fill in the rounds they take, in the launches chosen above, weighted by the rounds' times.
 // 1.0 = every round full.

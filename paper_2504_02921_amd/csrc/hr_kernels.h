@@ -50,7 +50,7 @@ struct WeightWalk {
 struct WeightWalks {
     int n = 0;
     int64_t bytes = 0;
-    bool done = false;            // set by the launch that was handed them: it has workgroups for them
+    unsigned done = 0;            // set by the launch that was handed them: bit i, it has workgroups for w[i]
     WeightWalk w[kWarmMost];
 };
 

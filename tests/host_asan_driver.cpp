@@ -249,6 +249,26 @@ int main() {
         CHECK(hr::choose_gemm_launch(hr::GEMM_QKV64, 6600, 2560, 512, 256).n == 2);
         CHECK(hr::choose_gemm_launch(hr::GEMM_QKV128, 12000, 1536, 256, 256).n == 2);
     }
+    {   // weights read ahead by a launch's idle workgroups: never more than they can take, in order, what does not fit left out
+        const int64_t q05[] = {896 * 896 * 2, 9728 * 896 * 2, 896 * 4864 * 2, 1152 * 896 * 2};      // O, gate / up, down, QKV of the 0.5B shape
+        CHECK(hr::pick_weight_walks(q05, 4, 128) == 15);
+        CHECK(hr::pick_weight_walks(q05, 4, 64) == 13);      // 248 pairs x 2 kv heads leave 16 of 512 workgroups, 224 pairs 64
+        CHECK(hr::pick_weight_walks(q05, 4, 16) == 9);
+        CHECK(hr::pick_weight_walks(q05, 4, 0) == 0 && hr::pick_weight_walks(q05, 4, -8) == 0 && hr::pick_weight_walks(q05, 0, 128) == 0);
+        std::srand(17);
+        for (int it = 0; it < 2000; ++it) {
+            int64_t b[4], sum = 0;
+            for (int64_t& x : b) x = (int64_t)128 * 64 * (1 + std::rand() % 4000);
+            const int n = 1 + std::rand() % 4, wgs = 8 * (std::rand() % 17);
+            const unsigned p = hr::pick_weight_walks(b, n, wgs);
+            CHECK(p < 1u << n);
+            for (int i = 0; i < n; ++i) {
+                const bool fits = sum + b[i] <= (int64_t)wgs * hr::kWarmBytesPerWg;
+                CHECK(fits == (bool)(p >> i & 1));
+                if (fits) sum += b[i];
+            }
+        }
+    }
     {   // sequences with the same token string share first-layer rows: tables written into a layout of exactly the computed size
         // strings: A = {5, 6, 7}, B = {5, 6}, C = {9}; sequences A B A C B A C
         const std::vector<int32_t> lens = {3, 2, 3, 1, 2, 3, 1};

@@ -313,6 +313,24 @@ def test_projections_on_blocked_weights_give_a_pair_the_same_bits(n_q, n_queries
     test_projections_cut_by_rows_give_a_pair_the_same_bits(128, n_q, 2, 2048, 2112, n_queries, qlen)
 
 
+def test_weights_read_ahead_in_part_give_a_pair_the_same_bits():
+    """62 pairs with documents of their own and 8 kv heads leave the attention launch room for few workgroups that read weights
+    ahead: they take some of the layer's matrices (here O, down and the next layer's QKV, not gate / up) and not the others."""
+    model = small_model(dtype="bf16", n_layers=3, hidden=512, n_q=8, n_kv=8, d=64, ffn=2112, vocab=500)
+    cfg = wlmod.WorkloadCfg("part_ahead", model, 2, 31, (20, 60), (5, 9), "bf16", seed=62)
+    w = wlmod.SeededWeights(model, seed=18, std=0.05, gain_jitter=0.1)
+    wl = wlmod.make_workload(cfg, spare_pages=2)
+    case = H.Case(wl, w)
+    try:
+        case.fill_from_prefill()
+        got = case.gpu_scores()
+        H.assert_scores_close(got, case.oracle_scores(), H.TOL["bf16"], "part of the weights read ahead")
+        for i in (0, 30, wl.n_pairs - 1):
+            np.testing.assert_array_equal(case.gpu_scores(wl.subset(np.array([i]))), got[i:i + 1])
+    finally:
+        case.close()
+
+
 @pytest.mark.parametrize("hidden", [256, 960])     # one whole float4 per lane; four, of which the last reaches past the row
 def test_norms_of_many_rows_give_a_pair_the_same_bits(hidden):
     """A wavefront per row (RMSNorm of 32768 rows and more, in both halves of a batch cut over two streams) against a
