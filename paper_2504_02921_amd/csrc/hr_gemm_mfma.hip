@@ -894,7 +894,8 @@ hipError_t launch_tile_of(const GemmArgs& a, hipStream_t st) {
 }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
-hipError_t launch_tile(const GemmArgs& a, hipStream_t st) {
+hipError_t launch_tile(const GemmArgs& a, const GemmPart& p, hipStream_t st) {
+    if (p.bm != BM || p.bn != BN) return hipErrorInvalidValue;      // the choice and the weight walk go by the part's sizes
     return w_blocked(a.N, a.Kw > 0 ? a.Kw : a.K) ? launch_tile_of<EPI, BM, BN, WM, WN, HB, SA, true>(a, st)
                                                  : launch_tile_of<EPI, BM, BN, WM, WN, HB, SA, false>(a, st);
 }
@@ -924,7 +925,8 @@ hipError_t launch_ring_of(const GemmArgs& a, hipStream_t st) {
 }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS>
-hipError_t launch_ring(const GemmArgs& a, hipStream_t st) {
+hipError_t launch_ring(const GemmArgs& a, const GemmPart& p, hipStream_t st) {
+    if (p.bm != BM || p.bn != BN) return hipErrorInvalidValue;      // the choice and the weight walk go by the part's sizes
     return w_blocked(a.N, a.Kw > 0 ? a.Kw : a.K) ? launch_ring_of<EPI, BM, BN, WM, WN, HB, NS, true>(a, st)
                                                  : launch_ring_of<EPI, BM, BN, WM, WN, HB, NS, false>(a, st);
 }
@@ -970,11 +972,6 @@ static void advance_rows(GemmEpilogue epi, GemmArgs& r, int64_t rows) {
     }
 }
 
-// The narrowest tile of a QKV projection is 32 rows tall instead of 64 while that still is one tile per CU: half the rows to
-// deliver per k-tile.  Weights from HBM, 64 / 32 rows: 0.5B shape (N = 1152, K = 896) 65 rows 7.1 / 5.3 us, 400 rows (234 tiles)
-// 7.4 / 5.7, two rounds (640 rows) 7.7 / 9.7; 8B shape (N = 6144, K = 4096) 128 rows (192 tiles) 31.2 / 26.0, 256 rows 28.1 / 44.3.
-static bool half_tall(const GemmArgs& a, int bn) { return (a.M + 31) / 32 * ((a.N + bn - 1) / bn) <= cu_count(); }
-
 static GemmKind kind_of(GemmEpilogue epi, const GemmArgs& a) {
     const bool wide_head = epi == EPI_QKV_ROPE && a.d == 128;       // a wave must span a whole 128-wide head
     return epi == EPI_RESID_ADD ? GEMM_RESID : epi == EPI_SWIGLU ? GEMM_SWIGLU : wide_head ? GEMM_QKV128 : GEMM_QKV64;
@@ -990,19 +987,8 @@ bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out) {
     const int Kw = a.Kw > 0 ? a.Kw : a.K;
     const int64_t bytes = (int64_t)a.N * Kw * (int64_t)sizeof(half_t);
     if (g.n != 1 || out->n >= kWarmMost || out->bytes + bytes > kWarmBytes) return false;
-    int bm = 0, bn = 0;
-    switch (g.part[0].tile) {
-        case GT_BIG: bm = 256; bn = 256; break;
-        case GT_TALL: bm = 320; bn = 256; break;
-        case GT_SMALL: case GT_RING128: bm = 128; bn = 128; break;
-        case GT_RING128_256: bm = 128; bn = 256; break;
-        case GT_RING64_128: bm = 64; bn = 128; break;
-        case GT_RING160_64: bm = 160; bn = 64; break;
-        case GT_RING96_64: bm = 96; bn = 64; break;
-        case GT_RING64: bm = 64; bn = 64; break;
-        case GT_RING32: bm = 32; bn = 32; break;
-    }
-    if ((kind == GEMM_QKV64 || kind == GEMM_QKV128) && bm == 64 && half_tall(a, bn)) bm = 32;
+    const int bm = g.part[0].bm;
+    int bn = g.part[0].bn;
     if (w_blocked(a.N, Kw)) bn = std::max(bn, kWBlock);       // what is walked is one run of memory: whole blocks
     WeightWalk& w = out->w[out->n++];
     w.W = (const char*)a.W;
@@ -1023,60 +1009,57 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
     const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count());
     GemmArgs r = a;
     for (int i = 0; i < g.n; ++i) {
-        r.M = g.part[i].rows;
+        const GemmPart& p = g.part[i];
+        r.M = p.rows;
         hipError_t e = hipErrorInvalidValue;
         switch (kind) {
             case GEMM_QKV64:
-                switch (g.part[i].tile) {
-                    case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1, 3>(r, st); break;
-                    case GT_SMALL: e = launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 2>(r, st); break;
-                    case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(r, st); break;
-                    case GT_RING64:
-                        if (half_tall(r, 64)) e = launch_ring<EPI_QKV_ROPE, 32, 64, 2, 1, 1, 8>(r, st);
-                        else e = launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(r, st);
-                        break;
+                switch (p.tile) {
+                    case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1, 3>(r, p, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 2>(r, p, st); break;
+                    case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(r, p, st); break;
+                    case GT_RING64: e = launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(r, p, st); break;
+                    case GT_RING32_64: e = launch_ring<EPI_QKV_ROPE, 32, 64, 2, 1, 1, 8>(r, p, st); break;
                     default: break;
                 }
                 break;
             case GEMM_QKV128:
-                switch (g.part[i].tile) {
-                    case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 4, 2, 2, 3>(r, st); break;
-                    case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 4, 1, 2, 4>(r, st); break;
-                    case GT_RING64_128:
-                        if (half_tall(r, 128)) e = launch_ring<EPI_QKV_ROPE, 32, 128, 2, 1, 2, 7>(r, st);
-                        else e = launch_ring<EPI_QKV_ROPE, 64, 128, 4, 1, 2, 6>(r, st);
-                        break;
+                switch (p.tile) {
+                    case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 4, 2, 2, 3>(r, p, st); break;
+                    case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 4, 1, 2, 4>(r, p, st); break;
+                    case GT_RING64_128: e = launch_ring<EPI_QKV_ROPE, 64, 128, 4, 1, 2, 6>(r, p, st); break;
+                    case GT_RING32_128: e = launch_ring<EPI_QKV_ROPE, 32, 128, 2, 1, 2, 7>(r, p, st); break;
                     default: break;
                 }
                 break;
             case GEMM_RESID:
-                switch (g.part[i].tile) {
-                    case GT_BIG: e = launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(r, st); break;
-                    case GT_TALL: e = launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1, 2>(r, st); break;
-                    case GT_SMALL: e = launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 2>(r, st); break;
-                    case GT_RING128: e = launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(r, st); break;
-                    case GT_RING64_128: e = launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(r, st); break;
-                    case GT_RING160_64: e = launch_ring<EPI_RESID_ADD, 160, 64, 2, 2, 1, 5>(r, st); break;
-                    case GT_RING96_64: e = launch_ring<EPI_RESID_ADD, 96, 64, 2, 2, 1, 7>(r, st); break;
-                    case GT_RING64: e = launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(r, st); break;
-                    case GT_RING32: e = launch_ring<EPI_RESID_ADD, 32, 32, 2, 2, 1, 18>(r, st); break;
+                switch (p.tile) {
+                    case GT_BIG: e = launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(r, p, st); break;
+                    case GT_TALL: e = launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1, 2>(r, p, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 2>(r, p, st); break;
+                    case GT_RING128: e = launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(r, p, st); break;
+                    case GT_RING64_128: e = launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(r, p, st); break;
+                    case GT_RING160_64: e = launch_ring<EPI_RESID_ADD, 160, 64, 2, 2, 1, 5>(r, p, st); break;
+                    case GT_RING96_64: e = launch_ring<EPI_RESID_ADD, 96, 64, 2, 2, 1, 7>(r, p, st); break;
+                    case GT_RING64: e = launch_ring<EPI_RESID_ADD, 64, 64, 2, 2, 1, 9>(r, p, st); break;
+                    case GT_RING32: e = launch_ring<EPI_RESID_ADD, 32, 32, 2, 2, 1, 18>(r, p, st); break;
                     default: break;
                 }
                 break;
             case GEMM_SWIGLU:
-                switch (g.part[i].tile) {
-                    case GT_BIG: e = launch_tile<EPI_SWIGLU, 256, 256, 2, 4, 1, 3>(r, st); break;
-                    case GT_TALL: e = launch_tile<EPI_SWIGLU, 320, 256, 2, 4, 1, 2>(r, st); break;
-                    case GT_SMALL: e = launch_tile<EPI_SWIGLU, 128, 128, 2, 2, 1, 2>(r, st); break;
-                    case GT_RING128_256: e = launch_ring<EPI_SWIGLU, 128, 256, 2, 4, 1, 3>(r, st); break;
-                    case GT_RING128: e = launch_ring<EPI_SWIGLU, 128, 128, 2, 2, 1, 4>(r, st); break;
-                    case GT_RING64_128: e = launch_ring<EPI_SWIGLU, 64, 128, 2, 2, 1, 6>(r, st); break;
+                switch (p.tile) {
+                    case GT_BIG: e = launch_tile<EPI_SWIGLU, 256, 256, 2, 4, 1, 3>(r, p, st); break;
+                    case GT_TALL: e = launch_tile<EPI_SWIGLU, 320, 256, 2, 4, 1, 2>(r, p, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_SWIGLU, 128, 128, 2, 2, 1, 2>(r, p, st); break;
+                    case GT_RING128_256: e = launch_ring<EPI_SWIGLU, 128, 256, 2, 4, 1, 3>(r, p, st); break;
+                    case GT_RING128: e = launch_ring<EPI_SWIGLU, 128, 128, 2, 2, 1, 4>(r, p, st); break;
+                    case GT_RING64_128: e = launch_ring<EPI_SWIGLU, 64, 128, 2, 2, 1, 6>(r, p, st); break;
                     default: break;
                 }
                 break;
         }
         if (e != hipSuccess) return e;
-        if (i + 1 < g.n) advance_rows(epi, r, g.part[i].rows);
+        if (i + 1 < g.n) advance_rows(epi, r, p.rows);
     }
     return hipSuccess;
 }

@@ -482,19 +482,27 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) 
         const double least = s.per_cu > 1 ? 0.7 : 0.75;
         return (full + (part > 0.0 ? least + (1.0 - least) * part : 0.0)) * ((double)s.c0 + (double)s.c1 * K);
     };
-    auto best_single = [&](int64_t rows, double* t) {
+    auto best_single = [&](int64_t rows, double* t) -> const GemmShape& {
         int best = -1;
         for (int i = 0; i < n_shapes; ++i) {
             if (K < shapes[i].k_min) continue;
             const double c = cost(shapes[i], rows);
             if (best < 0 || c < *t) { best = i; *t = c; }
         }
-        return shapes[best].tile;
+        return shapes[best];
+    };
+    // The narrowest tile of a QKV projection is 32 rows tall instead of 64 while that still is one tile per CU: half the rows to
+    // deliver per k-tile.  Weights from HBM, 64 / 32 rows: 0.5B shape (N = 1152, K = 896) 65 rows 7.1 / 5.3 us, 400 rows (234 tiles)
+    // 7.4 / 5.7, two rounds (640 rows) 7.7 / 9.7; 8B shape (N = 6144, K = 4096) 128 rows (192 tiles) 31.2 / 26.0, 256 rows 28.1 / 44.3.
+    auto part = [&](const GemmShape& s, int64_t rows) {
+        const bool qkv = kind == GEMM_QKV64 || kind == GEMM_QKV128;
+        if (!qkv || s.bm != 64 || (rows + 31) / 32 * ((N + s.bn - 1) / s.bn) > cus) return GemmPart{s.tile, rows, s.bm, s.bn};
+        return GemmPart{s.bn == 64 ? GT_RING32_64 : GT_RING32_128, rows, 32, s.bn};
     };
     GemmLaunch g;
     double t1 = 0.0;
     g.n = 1;
-    g.part[0] = GemmPart{best_single(M, &t1), M};
+    g.part[0] = part(best_single(M, &t1), M);
     for (int i = 0; i < n_shapes; ++i) {
         const GemmShape& s = shapes[i];
         if (s.bm < 256 || K < s.k_min) continue;
@@ -504,13 +512,13 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) 
         const int64_t rows = rounds * cus / tn * s.bm;
         if (rows <= 0 || rows >= M) continue;
         double t2 = 0.0;
-        const GemmTile rest = best_single(M - rows, &t2);
+        const GemmShape& rest = best_single(M - rows, &t2);
         const double t = cost(s, rows) + t2 + 2.0;                         // one launch more
         if (t < t1) {
             t1 = t;
             g.n = 2;
-            g.part[0] = GemmPart{s.tile, rows};
-            g.part[1] = GemmPart{rest, M - rows};
+            g.part[0] = part(s, rows);
+            g.part[1] = part(rest, M - rows);
         }
     }
     return g;

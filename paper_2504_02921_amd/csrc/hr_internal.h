@@ -165,8 +165,8 @@ size_t group_plan_ints_bound(int64_t n_seq, int64_t T, int g);
 // a shape is rounds x measured time of a round (c0 + c1 K), and full rounds of a large tile may be followed by the best
 // shape for the rows that are left.
 enum GemmKind { GEMM_QKV64, GEMM_QKV128, GEMM_RESID, GEMM_SWIGLU };
-enum GemmTile { GT_BIG, GT_TALL, GT_SMALL, GT_RING128, GT_RING128_256, GT_RING64_128, GT_RING160_64, GT_RING96_64, GT_RING64, GT_RING32 };
-struct GemmPart { GemmTile tile; int64_t rows; };
+enum GemmTile { GT_BIG, GT_TALL, GT_SMALL, GT_RING128, GT_RING128_256, GT_RING64_128, GT_RING160_64, GT_RING96_64, GT_RING64, GT_RING32, GT_RING32_64, GT_RING32_128 };
+struct GemmPart { GemmTile tile; int64_t rows; int bm, bn; };       // bm x bn: the tile's outputs
 struct GemmLaunch { int n = 0; GemmPart part[2]; };
 GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus);
 

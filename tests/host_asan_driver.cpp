@@ -222,14 +222,25 @@ int main() {
             CHECK(g.n == 1 || g.n == 2);
             int64_t rows = 0;
             for (int i = 0; i < g.n; ++i) {
-                const hr::GemmTile t = g.part[i].tile;
-                CHECK(g.part[i].rows > 0);
+                const hr::GemmPart& p = g.part[i];
+                const hr::GemmTile t = p.tile;
+                CHECK(p.rows > 0 && p.bm >= 32 && p.bm % 32 == 0 && p.bn >= 32 && p.bn % 32 == 0);
+                if (t == hr::GT_RING32_64 || t == hr::GT_RING32_128) {      // one tile per CU
+                    CHECK(p.bm == 32 && p.bn == (t == hr::GT_RING32_64 ? 64 : 128));
+                    CHECK((p.rows + 31) / 32 * ((N + p.bn - 1) / p.bn) <= cus);
+                }
                 rows += g.part[i].rows;
                 switch (kind) {
-                    case hr::GEMM_QKV64: CHECK(t == hr::GT_BIG || t == hr::GT_SMALL || t == hr::GT_RING128 || t == hr::GT_RING64); break;
-                    case hr::GEMM_QKV128: CHECK(t == hr::GT_BIG || t == hr::GT_RING128 || t == hr::GT_RING64_128); break;
-                    case hr::GEMM_RESID: CHECK(t != hr::GT_RING128_256); break;
-                    case hr::GEMM_SWIGLU: CHECK(t != hr::GT_RING64 && (t != hr::GT_TALL || K >= 2048)); break;
+                    case hr::GEMM_QKV64: CHECK(t == hr::GT_BIG || t == hr::GT_SMALL || t == hr::GT_RING128 || t == hr::GT_RING64 || t == hr::GT_RING32_64); break;
+                    case hr::GEMM_QKV128: CHECK(t == hr::GT_BIG || t == hr::GT_RING128 || t == hr::GT_RING64_128 || t == hr::GT_RING32_128); break;
+                    case hr::GEMM_RESID:
+                        CHECK(t == hr::GT_BIG || t == hr::GT_TALL || t == hr::GT_SMALL || t == hr::GT_RING128 || t == hr::GT_RING64_128 ||
+                              ((t == hr::GT_RING160_64 || t == hr::GT_RING96_64) && K >= 512) || t == hr::GT_RING64 || t == hr::GT_RING32);
+                        break;
+                    case hr::GEMM_SWIGLU:
+                        CHECK(t == hr::GT_BIG || (t == hr::GT_TALL && K >= 2048) || t == hr::GT_SMALL || t == hr::GT_RING128_256 ||
+                              t == hr::GT_RING128 || t == hr::GT_RING64_128);
+                        break;
                 }
             }
             CHECK(rows == M);
