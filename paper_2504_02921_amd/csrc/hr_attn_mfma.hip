@@ -139,9 +139,11 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
     constexpr int KC = HD / 16;                      // MFMA k-steps over head_dim
     constexpr int MB = HD / 32;                      // 32-channel blocks of the output
     extern __shared__ __attribute__((aligned(16))) char smem[];      // [2][kStageBytes] + scales + (fp8) expanded stage
-    if ((int)blockIdx.x >= n_wg) {
-        warm_weights<NW>(warm, n_wg, smem);
-        return;
+    if constexpr (!PREC) {
+        if ((int)blockIdx.x >= n_wg) {
+            warm_weights<NW>(warm, n_wg, smem);
+            return;
+        }
     }
     float* s_scale = (float*)(smem + 2 * kStageBytes);              // [2][PPS][2]  (fp8 only)
     char* hbuf = smem + 2 * kStageBytes + 2 * G::PPS * 2 * sizeof(float);   // fp8 only: the current stage as half pages
@@ -793,8 +795,8 @@ hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, co
         // the 22-bit form: split q / o and lo pages of the new keys (see the kernel); one wave per SIMD, 8 waves
         if (last_only) return hipErrorInvalidValue;
 #define HR_ATTN_PREC(HD, R)                                                                                 \
-    return fp8 ? launch_one<HD, 8, R, true, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, warm, st)             \
-               : launch_one<HD, 8, R, false, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, warm, st)
+    return fp8 ? launch_one<HD, 8, R, true, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, nullptr, st)          \
+               : launch_one<HD, 8, R, false, true>(qh, kvn, kvl, oh, mv, pv, layer, n_q, 0, gv, nullptr, st)
         if (pv.d == 64) {
             if (rows <= 256) { HR_ATTN_PREC(64, 1); }
             HR_ATTN_PREC(64, 2);

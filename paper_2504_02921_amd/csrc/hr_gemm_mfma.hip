@@ -44,6 +44,9 @@ constexpr int BK = 64;
 static_assert(kWBlock == BK, "a k-tile of W is whole lines");
 constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
 constexpr int kAheadShares = 4;                  // ... and how many tiles of a column take turns at least
+// ... and the tiles that may bring it: a smaller one asks for so little of W per k-tile that the ring is ahead enough.  Without / with
+// it: 32 x 32, 65 rows, K = 4864, 10.3 / 12.3 us, but 32 x 128, 128 rows, K = 4096, 27.7 / 26.0
+constexpr bool may_read_ahead(int BM, int BN, int waves) { return waves <= 4 && BM * BN >= 64 * 64; }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
@@ -631,7 +634,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 // one k-step ahead) took ~750 cycles per 64 x 64 k-tile whatever the number of workgroups: the down projection of 65 or
 // 640 rows (K = 4864) 27 / 28 us.
 //
-// A launch of four wavefronts or fewer may bring one more (use_ahead below), which reads W kAhead k-tiles ahead of the ring and
+// A launch of four wavefronts or fewer may bring one more (may_read_ahead, use_ahead below), which reads W kAhead k-tiles ahead of the ring and
 // drops it: the tiles of one column, neighbours on one XCD, take turns, so a k-tile's lines are in their L2 when the ring asks.
 // The ring alone has 128 KiB in flight: W of a 64 x 64 tile is 64 KiB of that, shared by all tiles of a column, and a first touch of
 // HBM takes ~2.3 us.  Down projection of the 8B shape (K = 14336, N = 4096), 640 rows, without / with it: 139.6 / 105.1 us
@@ -644,7 +647,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 // Tiles of 96 and 160 rows x 64 (residual adds) fill rounds that the powers of two leave a third empty: 8B down projection, 640
 // rows 128 x 128 (160 tiles) 105.1 -> 160 x 64 (256 tiles) 97.6 us.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS, bool BLK>
-__global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
+__global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 16, NI = TN / 16;
@@ -672,7 +675,7 @@ __global__ void __launch_bounds__((WM * WN + (WM * WN <= 4)) * 64, 1) gemm_ring_
     TileSrc<PA, RPP> srcA;
     WTileSrc<BN, RPP, BLK> srcB;
     srcB.set((const half_t*)a.W, n0, min(BN, a.N - n0), Kw);
-    if constexpr (WM * WN <= 4) {
+    if constexpr (may_read_ahead(BM, BN, WM * WN)) {
         if (wave == WM * WN) {
             if (tc.shares < kAheadShares) return;     // too few to take turns (barriers go on without the wave)
             // touches one 4-byte word of every 64 bytes: 32 rows of a k-tile per request
@@ -906,18 +909,17 @@ hipError_t launch_tile(const GemmArgs& a, const GemmPart& p, hipStream_t st) {
 // itself), five gain (320 rows of 64 x 128, K = 4096 31.2 / 26.1, K = 14336 105.6 / 84.2); K = 2048 gains (512 rows 19.0 / 17.5), K = 896
 // loses (512 rows 9.1 / 9.2, 640 rows of 64 x 64 at N = 896 5.7 / 5.8): the line lies between those two.  A rest of fewer tiles
 // behind groups of eight goes without (QKV, 1034 rows of 128 x 128, K = 4096: 77 us, with it 90).
-// A 32 x 32 tile asks for so little of W per k-tile that the ring is ahead enough: 65 rows, K = 4864, 10.3 / 12.3 us (32 x 128, K = 4096,
-// 128 rows: 27.7 / 26.0).
 // Where the attention has read W ahead (WeightWalks) the wavefront only takes LDS and issue slots: 0.5B shape, whole calls with /
 // without it: 640 tokens 1652 / 1630 us, 1000 1963 / 1949, 2000 2879 / 2842, 4000 4283 / 4274.
-inline bool use_ahead(const GemmArgs& a, int bm, int bn, int tiles_m) { return !a.w_near && bm * bn >= 64 * 64 && tiles_m >= kAheadShares && a.K >= 2048; }
+inline bool use_ahead(const GemmArgs& a, int tiles_m) { return !a.w_near && tiles_m >= kAheadShares && a.K >= 2048; }
 
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS, bool BLK>
 hipError_t launch_ring_of(const GemmArgs& a, hipStream_t st) {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (a.N + BN - 1) / BN;
     const int grid = (tiles_m * tiles_n + kXcds - 1) / kXcds * kXcds;
-    const bool ahead = WM * WN <= 4 && use_ahead(a, BM, BN, tiles_m);
-    constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (WM * WN <= 4 ? kAheadLds : 0);
+    constexpr bool may = may_read_ahead(BM, BN, WM * WN);
+    const bool ahead = may && use_ahead(a, tiles_m);
+    constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (may ? kAheadLds : 0);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS, BLK>, lds_most, attr_done); e != hipSuccess) return e;
     gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS, BLK><<<dim3((unsigned)grid), (WM * WN + ahead) * 64, ahead ? lds_most : ring, st>>>(a);

@@ -150,7 +150,7 @@ struct GroupView {
                   *sub_seq = nullptr, *sub_key0 = nullptr;
 };
 // kv_new_pages: the new tokens' K/V as pages (see GemmArgs::kv_pages).  groups: nullptr = every sequence on its own.
-// warm: what workgroups of the launch that find no work item may read ahead.
+// warm: what workgroups of the launch that find no work item may read ahead (not in the 22-bit form).
 // kv_new_lo_pages: if set, the 22-bit form: q and o are [T][hi | lo] halves, and this buffer (same arrangement as
 // kv_new_pages) holds what the rounding of the new tokens' K/V to half left out.
 hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, const MetaView& mv,
