@@ -259,6 +259,29 @@ int main() {
         CHECK(hr::choose_gemm_launch(hr::GEMM_SWIGLU, 1980, 2 * 4864, 896, 256).n == 2);
         CHECK(hr::choose_gemm_launch(hr::GEMM_QKV64, 6600, 2560, 512, 256).n == 2);
         CHECK(hr::choose_gemm_launch(hr::GEMM_QKV128, 12000, 1536, 256, 256).n == 2);
+        // ... and those of single tile shapes
+        struct Pin { hr::GemmKind kind; int64_t M; int N, K; hr::GemmTile tile; };
+        const Pin pins[] = {
+            {hr::GEMM_RESID, 1980, 896, 4864, hr::GT_RING64_128},  {hr::GEMM_RESID, 205, 256, 4864, hr::GT_RING32},
+            {hr::GEMM_RESID, 350, 320, 4160, hr::GT_RING32},
+            // tiles for few rows
+            {hr::GEMM_RESID, 1295, 896, 896, hr::GT_RING96_64},    {hr::GEMM_RESID, 1295, 896, 2112, hr::GT_RING96_64},
+            {hr::GEMM_RESID, 2460, 896, 896, hr::GT_RING160_64},   {hr::GEMM_RESID, 2460, 896, 576, hr::GT_RING160_64},
+            {hr::GEMM_QKV64, 165, 512, 256, hr::GT_RING32_64},     {hr::GEMM_QKV128, 175, 1536, 2048, hr::GT_RING32_128},
+            // blocked weights
+            {hr::GEMM_RESID, 175, 2048, 2048, hr::GT_RING64},      {hr::GEMM_RESID, 37, 2048, 2112, hr::GT_RING32},
+            {hr::GEMM_RESID, 1295, 2048, 2112, hr::GT_RING128},
+            // W read ahead of the ring
+            {hr::GEMM_RESID, 1295, 896, 17600, hr::GT_RING96_64},  {hr::GEMM_RESID, 2460, 896, 17600, hr::GT_RING160_64},
+            {hr::GEMM_RESID, 4290, 896, 4864, hr::GT_RING128},     {hr::GEMM_RESID, 330, 2048, 8192, hr::GT_RING64},
+            {hr::GEMM_RESID, 700, 2048, 8192, hr::GT_RING96_64},   {hr::GEMM_RESID, 1260, 2048, 8192, hr::GT_RING160_64},
+            {hr::GEMM_RESID, 1295, 2048, 8192, hr::GT_RING128},    {hr::GEMM_QKV128, 330, 2560, 2048, hr::GT_RING32_128},
+            {hr::GEMM_QKV128, 700, 2560, 2048, hr::GT_RING64_128}, {hr::GEMM_QKV128, 1260, 2560, 2048, hr::GT_RING128},
+            {hr::GEMM_SWIGLU, 4290, 640, 2048, hr::GT_RING128},    {hr::GEMM_QKV128, 4290, 1536, 2048, hr::GT_RING128}};
+        for (const Pin& p : pins) {
+            const hr::GemmLaunch g = hr::choose_gemm_launch(p.kind, p.M, p.N, p.K, 256);
+            CHECK(g.n == 1 && g.part[0].tile == p.tile);
+        }
     }
     {   // weights read ahead by a launch's idle workgroups: never more than they can take, in order, what does not fit left out
         const int64_t q05[] = {896 * 896 * 2, 9728 * 896 * 2, 896 * 4864 * 2, 1152 * 896 * 2};      // O, gate / up, down, QKV of the 0.5B shape

@@ -263,15 +263,15 @@ def test_more_query_rows_than_a_work_item_holds(d, n_q, n_kv, kv, q_len, monkeyp
 
 
 @pytest.mark.parametrize("d,n_q,n_kv,hidden,ffn,n_queries,qlen", [
-    (64, 14, 2, 896, 4864, 12, (33, 33)),       # gate / up: full rounds of large tiles and a rest; down: W read ahead of the ring
-    (64, 8, 2, 256, 4864, 1, (41, 41)),         # down, K = 4864: four row tiles, the last one with 13 rows
-    (128, 8, 2, 320, 4160, 2, (33, 37)),        # down, K = 4160: 65 k-tiles, a column tile of 64
+    (64, 14, 2, 896, 4864, 12, (33, 33)),       # gate / up: full rounds of large tiles and a rest; O and down as 64 x 128 tiles, the last one with 60 rows
+    (64, 8, 2, 256, 4864, 1, (41, 41)),         # down, K = 4864: 32 x 32 tiles, the last one with 13 rows
+    (128, 8, 2, 320, 4160, 2, (33, 37)),        # down, K = 4160: 65 k-tiles, 32 x 32 tiles
     (64, 32, 4, 512, 320, 40, (33, 33)),        # QKV of 64-wide heads in two launches
     (128, 8, 2, 256, 320, 60, (40, 40)),        # QKV of 128-wide heads in two launches
 ])
 def test_projections_cut_by_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen):
-    """A projection may be launched as two row ranges with tile shapes of their own, and the ring kernel may bring a
-    wavefront that reads W ahead: neither changes the order in which an output element is summed."""
+    """A projection may be launched as two row ranges with tile shapes of their own, and the attention launch reads weights ahead
+    where they fit: neither changes the order in which an output element is summed."""
     model = small_model(dtype="bf16", n_layers=2, hidden=hidden, n_q=n_q, n_kv=n_kv, d=d, ffn=ffn, vocab=500)
     cfg = wlmod.WorkloadCfg("row_ranges", model, n_queries, 5, (5, 60), qlen, "bf16", pool_docs=9, zipf_a=0.3, seed=ffn + d)
     w = wlmod.SeededWeights(model, seed=18, std=0.05, gain_jitter=0.1)
@@ -292,10 +292,10 @@ def test_projections_cut_by_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden,
 
 
 @pytest.mark.parametrize("d,n_q,n_kv,hidden,ffn,n_queries,qlen", [
-    (64, 14, 2, 896, 2112, 7, (37, 37)),        # 1295 rows: O and down as 96 x 64 tiles, the last one with 47 rows; down reads W ahead
+    (64, 14, 2, 896, 2112, 7, (37, 37)),        # 1295 rows: O and down as 96 x 64 tiles, the last one with 47 rows
     (64, 14, 2, 896, 576, 12, (41, 41)),        # 2460 rows: O and down as 160 x 64 tiles, the last one with 60 rows
     (64, 4, 2, 256, 320, 1, (33, 33)),          # 165 rows: QKV of 64-wide heads as 32 x 64 tiles, the last one with 5 rows
-    (128, 8, 2, 2048, 320, 1, (33, 37)),        # QKV of 128-wide heads as 32 x 128 tiles, QKV and gate / up (K = 2048) read W ahead
+    (128, 8, 2, 2048, 320, 1, (33, 37)),        # QKV of 128-wide heads as 32 x 128 tiles, six of them in a column: it reads W ahead of its ring
 ])
 def test_projection_tiles_for_few_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen):
     """Row counts at which the projections take the 96 x 64, 160 x 64, 32 x 64 and 32 x 128 tiles, with a partial last tile:
@@ -304,13 +304,45 @@ def test_projection_tiles_for_few_rows_give_a_pair_the_same_bits(d, n_q, n_kv, h
 
 
 @pytest.mark.parametrize("n_q,n_queries,qlen", [
-    (16, 1, (33, 37)),         # all four matrices in blocks of 64 rows (w_elem); residual adds in 32 x 32 tiles, which read half blocks
-    (16, 7, (37, 37)),         # ... in 64-row and wider tiles
+    (16, 1, (33, 37)),         # all four matrices in blocks of 64 rows (w_elem); residual adds in 64 x 64 tiles, a pair alone in 32 x 32, which read half blocks
+    (16, 7, (37, 37)),         # ... in 128 x 128 tiles
     (8, 1, (33, 37)),          # QKV (N = 1536) and O (K = 1024) row-major beside blocked gate / up and down
 ])
 def test_projections_on_blocked_weights_give_a_pair_the_same_bits(n_q, n_queries, qlen):
     """Matrices of 2048 rows and columns and more are packed in blocks: the oracle within the bar, and the bits of a pair alone."""
     test_projections_cut_by_rows_give_a_pair_the_same_bits(128, n_q, 2, 2048, 2112, n_queries, qlen)
+
+
+@pytest.mark.parametrize("d,n_q,n_kv,hidden,ffn,n_queries,qlen", [
+    (64, 14, 2, 896, 17600, 7, 37),             # row-major W, 1295 rows: down as 96 x 64 tiles, the last one with 47 rows
+    (64, 14, 2, 896, 17600, 12, 41),            # 2460 rows: down as 160 x 64 tiles, the last one with 60 rows
+    (64, 14, 2, 896, 4864, 26, 33),             # 4290 rows: down as 128 x 128 tiles, the last one with 66 rows
+    (128, 16, 2, 2048, 8192, 2, 33),            # blocked W, 330 rows: down as 64 x 64 tiles (last: 10 rows), QKV as 32 x 128
+    (128, 16, 2, 2048, 8192, 4, 35),            # 700 rows: down as 96 x 64 tiles (last: 28 rows), QKV as 64 x 128
+    (128, 16, 2, 2048, 8192, 7, 36),            # 1260 rows: down as 160 x 64 tiles (last: 140 rows), QKV as 128 x 128
+    (128, 16, 2, 2048, 8192, 7, 37),            # 1295 rows: down and QKV as 128 x 128 tiles (last: 15 rows)
+    (128, 8, 2, 2048, 320, 26, 33),             # 4290 rows, row-major: gate / up and QKV (K = 2048) as 128 x 128 tiles (last: 66 rows)
+])
+def test_wavefront_that_reads_w_ahead_leaves_the_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen):
+    """Ring launches that bring the wavefront that reads W ahead: four row tiles and more, K of 2048 and more, and weights that the
+    attention launch has not read ahead (more than 30 MiB, or calls of more than 4096 tokens).  The oracle within the bar, and
+    the bits of a pair scored alone, whose few rows go without."""
+    model = small_model(dtype="bf16", n_layers=2, hidden=hidden, n_q=n_q, n_kv=n_kv, d=d, ffn=ffn, vocab=500)
+    cfg = wlmod.WorkloadCfg("w_ahead", model, n_queries, 5, (5, 40), qlen, "bf16", pool_docs=5, zipf_a=0.3, seed=ffn + d)
+    w = wlmod.SeededWeights(model, seed=18, std=0.02, gain_jitter=0.1)
+    wl = wlmod.make_workload(cfg, spare_pages=2)
+    case = H.Case(wl, w)
+    try:
+        case.fill_from_prefill()
+        case.model.set_streams(1)
+        got = case.gpu_scores()
+        assert np.isfinite(got).all()
+        idx = np.unique(np.linspace(0, wl.n_pairs - 1, 5).astype(int))
+        H.assert_scores_close(got[idx], case.oracle_scores(wl.subset(idx)), H.TOL["bf16"], "W read ahead")
+        for i in idx:
+            np.testing.assert_array_equal(case.gpu_scores(wl.subset(np.array([i]))), got[i:i + 1])
+    finally:
+        case.close()
 
 
 def test_weights_read_ahead_in_part_give_a_pair_the_same_bits():
