@@ -63,6 +63,8 @@ constexpr int64_t kSplitMinTokens = 8192;      // query tokens from which a scor
 constexpr double kSplitMaxFill = 0.8;          // ... when the N = hidden GEMMs' tiles fill less than this share of their rounds
 // Up to this many new tokens the attention's idle workgroups read the layer's weights ahead.  Whole calls of 20-token queries, 0.5B
 // shape, without / with: 2000 tokens 2849 / 2765 us, 4000 4110 / 4002, 8000 7505 / 7504 (the work items fill the chip).
+// Long documents, whose pages pass through the same L2s, do not undo it: 100 documents of 2048 tokens (105 MB a layer), 800 tokens 2668 /
+// 2574, 3200 4659 / 4490.
 constexpr int64_t kWarmMaxTokens = 4096;
 constexpr size_t kSplitSlackBytes = (size_t)1 << 20;   // what two carvings of a workspace may need beyond one (alignment gaps,
                                                        // the larger group-plan room of calls with few pairs)
@@ -343,6 +345,8 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
         if (gemm_weight_walk(EPI_SWIGLU, a, &walks)) walk_gu = walks.n - 1;
         a.W = layer_w(m, 0, m->pack.wd); a.N = H; a.K = F;
         if (gemm_weight_walk(EPI_RESID_ADD, a, &walks)) walk_down = walks.n - 1;
+        // QKV's launch is not told (w_near): its own reading-ahead wavefront made no difference behind a walk (16 layers of hidden
+        // 2048, 65 to 4000 rows, within 0.3 %)
         a.W = layer_w(m, 1, m->pack.wqkv); a.N = nqkv; a.K = H;
         walk_qkv = gemm_weight_walk(EPI_QKV_ROPE, a, &walks);
     }

@@ -629,10 +629,12 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 //   * the fragments of k-tile kt + 1 are read from LDS into a second register set before the MFMAs of k-tile kt issue, so
 //     a k-tile costs one barrier, and neither LDS latency nor the loads sit in front of the matrix pipe.  The barrier that
 //     says k-tile kt + 1 has landed also says that every wave holds k-tile kt in registers: its stage is free for kt + NS.
-// What is left is the delivery to the CU: about 60 bytes per cycle from L2 (measured with a bare direct-to-LDS loop: 272
-// cycles for the 16 KiB of a 64 x 64 k-tile, 544 for 128 x 128).  The previous loop (fragments read behind the barrier,
-// one k-step ahead) took ~750 cycles per 64 x 64 k-tile whatever the number of workgroups: the down projection of 65 or
-// 640 rows (K = 4864) 27 / 28 us.
+// What a k-tile takes in a full round (256 CUs, N = 4096, residual add), 64 x 64 / 160 x 64 / 128 x 128 tiles: operands in the L2s 159-177 /
+// 323 / 410-450 ns; W from HBM 266 / 407 / 514, with the wavefront below 229 / 384 / 496 (16-19 TB/s into the CUs).  The same loop on
+// zeros that its CU's L2 holds takes 137 / - / 284 ns, and requests alone 113 ns per 16 KiB: neither a CU's 60 bytes per cycle (16 KiB
+// = 272 cycles) nor the L2s' rate to 256 CUs (35-37 TB/s) bounds a full round.  Small tiles wait for first touches of W, large ones run
+// at 0.9-1.0 PFLOP/s with hot operands.  The previous loop (fragments read behind the barrier, one k-step ahead) took ~750 cycles per
+// 64 x 64 k-tile whatever the number of workgroups: the down projection of 65 or 640 rows (K = 4864) 27 / 28 us.
 //
 // A launch of four wavefronts or fewer may bring one more (may_read_ahead, use_ahead below), which reads W kAhead k-tiles ahead of the ring and
 // drops it: the tiles of one column, neighbours on one XCD, take turns, so a k-tile's lines are in their L2 when the ring asks.
@@ -981,6 +983,9 @@ static GemmKind kind_of(GemmEpilogue epi, const GemmArgs& a) {
 
 // The XCDs' L2s hold 4 MiB each; the activations pass through them as well.  A layer of the 0.5B shape is 28.4 MiB.  O alone of the
 // 8B shape (32 MiB): 100 rows 6083 -> 5946 us a call, 640 rows 10630 -> 10680.
+// Matrices that are left out do not count, although their bytes pass through the L2s in between: 16 layers of hidden 2048 and ffn 8192 (gate / up
+// and down, 96 MiB, left out), nothing / O / O and QKV read ahead, 640 rows 2140 / 2124 / 2103 us a call, 1300 rows 3484 / 3480 / 3400;
+// 28 layers of 1536 and 8960, 160 rows 2602 / 2580 / 2504.
 constexpr int64_t kWarmBytes = (int64_t)30 << 20;
 
 bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out) {

@@ -138,7 +138,7 @@ struct GemmArgs {
 hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st);
 
 // adds the projection `a` (its M, N, K and W) as it would be launched.  Nothing is added (and false returned) when it runs as
-// several launches, or when its weights and those added so far would not stay in the L2s together.
+// several launches, or when its weights and those added so far would not stay in the L2s together; later ones may still be added.
 bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out);
 
 bool attn_mfma_supported(const hr_model_cfg& c, int kv_dtype, int max_q_len);          // one work item per (sequence, kv head)
