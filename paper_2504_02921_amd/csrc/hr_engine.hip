@@ -274,9 +274,11 @@ int run_layers_f32(hr_model* m, const PoolView& pv, const MetaView& mv, const Wo
 //   groups       if set, the attention work items are these groups of sequences with one shared document
 //   after_qkv0   if set, recorded on `st` behind the first layer's QKV projection
 //   src          where the metadata still has to come from, if it has not been uploaded
+//   beside       the other half of the call runs at the same time, on another stream
 int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaView& mv, const Workspace& ws, char* wsb,
                int max_keys, int max_new_len, float* scores, hipStream_t st, const PrefillTarget* fill = nullptr,
-               const GroupView* groups = nullptr, hipEvent_t after_qkv0 = nullptr, int n_precise = 0, const MetaSource& src = {}) {
+               const GroupView* groups = nullptr, hipEvent_t after_qkv0 = nullptr, int n_precise = 0, const MetaSource& src = {},
+               bool beside = false) {
     const hr_model_cfg& c = m->cfg;
     const int dt = c.dtype;
     const int H = c.hidden, d = c.head_dim, F = c.ffn;
@@ -338,7 +340,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
     bool walk_qkv = false;
     if (mfma_attn && T <= kWarmMaxTokens) {
         GemmArgs a{};
-        a.M = T; a.d = d;
+        a.M = T; a.d = d; a.beside = beside;
         a.W = layer_w(m, 0, m->pack.wo); a.N = H; a.K = nq;
         if (gemm_weight_walk(EPI_RESID_ADD, a, &walks)) walk_o = walks.n - 1;
         a.W = layer_w(m, 0, m->pack.wgu); a.N = 2 * F; a.K = H;
@@ -350,6 +352,10 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
         a.W = layer_w(m, 1, m->pack.wqkv); a.N = nqkv; a.K = H;
         walk_qkv = gemm_weight_walk(EPI_QKV_ROPE, a, &walks);
     }
+    auto gemm = [&](GemmEpilogue epi, GemmArgs a) {
+        a.beside = beside;
+        return launch_gemm_mfma(epi, a, st);
+    };
     auto gemm_plain = [&](F32Epilogue epi, const void* A, const void* W, float* C, int N, int K) {
         F32GemmArgs a{};
         a.A = A; a.W = W; a.M = T; a.N = N; a.K = K; a.C = C;
@@ -370,20 +376,20 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             HR_TIMED(PC_ELEMENTWISE, launch_fill_zero(f32, (size_t)Tq * nqkv * sizeof(float), st));
             GemmArgs a{};
             a.A = y; a.W = layer_w(m, l, m->pack.wqkv); a.M = Tq; a.N = nqkv; a.K = 2 * H; a.Kw = H; a.x = f32;
-            HR_TIMED(PC_GEMM_QKV, launch_gemm_mfma(EPI_RESID_ADD, a, st));
+            HR_TIMED(PC_GEMM_QKV, gemm(EPI_RESID_ADD, a));
             HR_TIMED(PC_ELEMENTWISE, launch_rope_pages(f32, rope, q, k, kvlo, mv.new_slot, src0, T, c.n_q_heads, c.n_kv_heads, d, st));
             if (l == 0 && after_qkv0) HR_HIP(hipEventRecord(after_qkv0, st));
             HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, l, c.n_q_heads, max_new_len, st, false, groups, kvlo));
             GemmArgs b{};
             b.A = o; b.W = layer_w(m, l, m->pack.wo); b.M = T; b.N = H; b.K = 2 * nq; b.Kw = nq; b.x = x;
-            HR_TIMED(PC_GEMM_O, launch_gemm_mfma(EPI_RESID_ADD, b, st));
+            HR_TIMED(PC_GEMM_O, gemm(EPI_RESID_ADD, b));
             HR_TIMED(PC_RMSNORM, launch_rmsnorm_split(x, m->norm2[l], y, T, H, c.rms_eps, st));
             GemmArgs gu{};
             gu.A = y; gu.W = layer_w(m, l, m->pack.wgu); gu.M = T; gu.N = 2 * F; gu.K = 2 * H; gu.Kw = H; gu.out0 = mm; gu.split_out = 1;
-            HR_TIMED(PC_GEMM_GATE_UP, launch_gemm_mfma(EPI_SWIGLU, gu, st));
+            HR_TIMED(PC_GEMM_GATE_UP, gemm(EPI_SWIGLU, gu));
             GemmArgs dn{};
             dn.A = mm; dn.W = layer_w(m, l, m->pack.wd); dn.M = T; dn.N = H; dn.K = 2 * F; dn.Kw = F; dn.x = x;
-            HR_TIMED(PC_GEMM_DOWN, launch_gemm_mfma(EPI_RESID_ADD, dn, st));
+            HR_TIMED(PC_GEMM_DOWN, gemm(EPI_RESID_ADD, dn));
             continue;
         }
         HR_TIMED(PC_RMSNORM, launch_rmsnorm(dt, x, m->norm1[l], y, Tq, H, c.rms_eps, st, rows0));
@@ -391,14 +397,14 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             HR_TIMED(PC_ELEMENTWISE, launch_fill_zero(f32, (size_t)Tq * nqkv * sizeof(float), st));
             GemmArgs a{};
             a.A = y; a.W = layer_w(m, l, m->pack.wqkv); a.M = Tq; a.N = nqkv; a.K = H; a.x = f32;
-            HR_TIMED(PC_GEMM_QKV, launch_gemm_mfma(EPI_RESID_ADD, a, st));
+            HR_TIMED(PC_GEMM_QKV, gemm(EPI_RESID_ADD, a));
             HR_TIMED(PC_ELEMENTWISE, launch_rope_pages(f32, rope, q, k, nullptr, mv.new_slot, src0, T, c.n_q_heads, c.n_kv_heads, d, st));
         } else if (m->mfma_gemm) {
             GemmArgs a{};
             a.A = y; a.W = layer_w(m, l, m->pack.wqkv); a.M = T; a.N = nqkv; a.K = H;
             a.out0 = q; a.out1 = k; a.out2 = v; a.rope = rope; a.n_q = c.n_q_heads; a.n_kv = c.n_kv_heads; a.d = d;
             if (mfma_attn) { a.kv_pages = k; a.new_slot = mv.new_slot; }
-            HR_TIMED(PC_GEMM_QKV, launch_gemm_mfma(EPI_QKV_ROPE, a, st));
+            HR_TIMED(PC_GEMM_QKV, gemm(EPI_QKV_ROPE, a));
         } else {
             HR_TIMED(PC_GEMM_QKV, gemm_plain(F32_STORE, y, layer_w(m, l, m->pack.wqkv), f32, nqkv, H));
             HR_TIMED(PC_ELEMENTWISE, launch_rope_split(dt, f32, rope, q, k, v, T, c.n_q_heads, c.n_kv_heads, d, st));
@@ -429,14 +435,14 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             HR_TIMED(PC_ELEMENTWISE, launch_gather_rows_f32(x, mv.out_row, x_last, (int)P, H, st));
             GemmArgs a{};
             a.A = o; a.W = layer_w(m, l, m->pack.wo); a.M = P; a.N = H; a.K = nq; a.x = x_last;
-            HR_TIMED(PC_GEMM_O, launch_gemm_mfma(EPI_RESID_ADD, a, st));
+            HR_TIMED(PC_GEMM_O, gemm(EPI_RESID_ADD, a));
             HR_TIMED(PC_RMSNORM, launch_rmsnorm(dt, x_last, m->norm2[l], y, P, H, c.rms_eps, st));
             GemmArgs gu{};
             gu.A = y; gu.W = layer_w(m, l, m->pack.wgu); gu.M = P; gu.N = 2 * F; gu.K = H; gu.out0 = mm;
-            HR_TIMED(PC_GEMM_GATE_UP, launch_gemm_mfma(EPI_SWIGLU, gu, st));
+            HR_TIMED(PC_GEMM_GATE_UP, gemm(EPI_SWIGLU, gu));
             GemmArgs b{};
             b.A = mm; b.W = layer_w(m, l, m->pack.wd); b.M = P; b.N = H; b.K = F; b.x = x_last;
-            HR_TIMED(PC_GEMM_DOWN, launch_gemm_mfma(EPI_RESID_ADD, b, st));
+            HR_TIMED(PC_GEMM_DOWN, gemm(EPI_RESID_ADD, b));
             MetaView compact = mv;
             compact.out_row = nullptr;                      // row p of x_last belongs to pair p
             HR_TIMED(PC_SCORE_HEAD, launch_score_head(dt, x_last, m->final_norm, m->embedding, compact, scores, H, c.rms_eps, c.yes_id,
@@ -457,7 +463,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
         if (m->mfma_gemm) {
             GemmArgs a{};
             a.A = o; a.W = layer_w(m, l, m->pack.wo); a.M = T; a.N = H; a.K = nq; a.x = x; a.w_near = near(walk_o);
-            HR_TIMED(PC_GEMM_O, launch_gemm_mfma(EPI_RESID_ADD, a, st));
+            HR_TIMED(PC_GEMM_O, gemm(EPI_RESID_ADD, a));
         } else {
             HR_TIMED(PC_GEMM_O, gemm_plain(F32_ADD, o, layer_w(m, l, m->pack.wo), x, H, nq));
         }
@@ -465,10 +471,10 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
         if (m->mfma_gemm) {
             GemmArgs a{};
             a.A = y; a.W = layer_w(m, l, m->pack.wgu); a.M = T; a.N = 2 * F; a.K = H; a.out0 = mm; a.w_near = near(walk_gu);
-            HR_TIMED(PC_GEMM_GATE_UP, launch_gemm_mfma(EPI_SWIGLU, a, st));
+            HR_TIMED(PC_GEMM_GATE_UP, gemm(EPI_SWIGLU, a));
             GemmArgs b{};
             b.A = mm; b.W = layer_w(m, l, m->pack.wd); b.M = T; b.N = H; b.K = F; b.x = x; b.w_near = near(walk_down);
-            HR_TIMED(PC_GEMM_DOWN, launch_gemm_mfma(EPI_RESID_ADD, b, st));
+            HR_TIMED(PC_GEMM_DOWN, gemm(EPI_RESID_ADD, b));
         } else {
             HR_TIMED(PC_GEMM_GATE_UP, gemm_plain(F32_STORE, y, layer_w(m, l, m->pack.wgu), f32, 2 * F, H));
             HR_TIMED(PC_ELEMENTWISE, launch_swiglu(dt, f32, mm, T, F, m->pack.gu_interleave, st));
@@ -816,9 +822,9 @@ static int prepare_score_part(hr_model* m, int32_t n_pairs, const int32_t* page_
 }
 
 static int run_score_part(hr_model* m, const hr_pool* pool, const ScorePart& part, const hr::Workspace& ws, char* wsb, int max_q,
-                          float* scores_dev, hipStream_t st, hipEvent_t after_qkv0 = nullptr, const MetaSource& src = {}) {
+                          float* scores_dev, hipStream_t st, hipEvent_t after_qkv0 = nullptr, const MetaSource& src = {}, bool beside = false) {
     return run_layers(m, pool, false, part.mv, ws, wsb, part.max_keys, max_q, scores_dev, st, nullptr,
-                      part.gv.n_groups > 0 ? &part.gv : nullptr, after_qkv0, m->n_precise, src);
+                      part.gv.n_groups > 0 ? &part.gv : nullptr, after_qkv0, m->n_precise, src, beside);
 }
 
 // A scoring call (already validated) in one piece on `st`, with the workspace at `wsb`.
@@ -917,10 +923,10 @@ int hr_rerank_score(hr_model* m, const hr_pool* pool, int32_t n_pairs, const int
             HR_HIP(hipEventRecord(m->stage_ev, st));
             m->stage_pending = true;
             if (rc != HR_OK) return rc;
-            const int rc_a = run_score_part(m, pool, pa, ws_a, wsb, max_q, scores_dev, st, m->fork_ev);
+            const int rc_a = run_score_part(m, pool, pa, ws_a, wsb, max_q, scores_dev, st, m->fork_ev, {}, true);
             if (rc_a != HR_OK) return rc_a;
             HR_HIP(hipStreamWaitEvent(m->aux_stream, m->fork_ev, 0));
-            const int rc_b = run_score_part(m, pool, pb, ws_b, wsb_b, max_q, scores_dev + n_a, m->aux_stream);
+            const int rc_b = run_score_part(m, pool, pb, ws_b, wsb_b, max_q, scores_dev + n_a, m->aux_stream, nullptr, {}, true);
             HR_HIP(hipEventRecord(m->join_ev, m->aux_stream));
             HR_HIP(hipStreamWaitEvent(st, m->join_ev, 0));
             return rc_a != HR_OK ? rc_a : rc_b;

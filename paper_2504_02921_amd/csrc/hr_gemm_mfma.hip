@@ -990,7 +990,7 @@ constexpr int64_t kWarmBytes = (int64_t)30 << 20;
 
 bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out) {
     const GemmKind kind = kind_of(epi, a);
-    const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count());
+    const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count(), a.beside);
     const int Kw = a.Kw > 0 ? a.Kw : a.K;
     const int64_t bytes = (int64_t)a.N * Kw * (int64_t)sizeof(half_t);
     if (g.n != 1 || out->n >= kWarmMost || out->bytes + bytes > kWarmBytes) return false;
@@ -1013,7 +1013,7 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
     if (a.K % BK != 0) return hipErrorInvalidValue;
     if (a.Kw > 0 && (a.Kw % BK != 0 || (a.K != a.Kw && a.K != 2 * a.Kw))) return hipErrorInvalidValue;
     const GemmKind kind = kind_of(epi, a);
-    const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count());
+    const GemmLaunch g = choose_gemm_launch(kind, a.M, a.N, a.K, cu_count(), a.beside);
     GemmArgs r = a;
     for (int i = 0; i < g.n; ++i) {
         const GemmPart& p = g.part[i];

@@ -466,7 +466,7 @@ const GemmShape kQkv128Shapes[] = {{GT_BIG, 256, 256, 1, 12.0f, 0.0232f, 0},    
                                    {GT_RING64_128, 64, 128, 1, 4.5f, 0.0055f, 0}};
 }  // namespace
 
-GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) {
+GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_, bool beside) {
     const int64_t cus = cus_ > 0 ? cus_ : 1;
     const GemmShape* shapes = kResidShapes;
     int n_shapes = (int)(sizeof(kResidShapes) / sizeof(GemmShape));
@@ -480,7 +480,8 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_) 
         const int64_t tiles = ((rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), slots = cus * s.per_cu;
         const double full = (double)(tiles / slots), part = (double)(tiles % slots) / (double)slots;
         const double least = s.per_cu > 1 ? 0.7 : 0.75;
-        return (full + (part > 0.0 ? least + (1.0 - least) * part : 0.0)) * ((double)s.c0 + (double)s.c1 * K);
+        const double t = (full + (part > 0.0 ? least + (1.0 - least) * part : 0.0)) * ((double)s.c0 + (double)s.c1 * K);
+        return beside && s.tile >= GT_RING128 ? kRingBeside * t : t;
     };
     auto best_single = [&](int64_t rows, double* t) -> const GemmShape& {
         int best = -1;

@@ -168,7 +168,12 @@ enum GemmKind { GEMM_QKV64, GEMM_QKV128, GEMM_RESID, GEMM_SWIGLU };
 enum GemmTile { GT_BIG, GT_TALL, GT_SMALL, GT_RING128, GT_RING128_256, GT_RING64_128, GT_RING160_64, GT_RING96_64, GT_RING64, GT_RING32, GT_RING32_64, GT_RING32_128 };
 struct GemmPart { GemmTile tile; int64_t rows; int bm, bn; };       // bm x bn: the tile's outputs
 struct GemmLaunch { int n = 0; GemmPart part[2]; };
-GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus);
+// beside: launches of another stream run at the same time (the other half of a scoring call).  A ring tile, measured with the chip to itself,
+// needs a whole CU and waits for both places of one, while two-per-CU tiles start in the gaps: it counts kRingBeside times its time.
+// 0.5B shape, two halves of 4700 to 5800 tokens: down as 160 x 64 instead of 128 x 128 tiles, or gate / up's rest as 128 x 256, 9400 tokens
+// 9370 against 8740 us a call, 11400 tokens 11020 against 10080.
+constexpr double kRingBeside = 1.2;
+GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus, bool beside = false);
 
 // Which of n matrices `wgs` idle workgroups of a launch read ahead (bit i): each takes at most kWarmBytesPerWg, or the launch ends
 // later for their sake, and a matrix that does not fit beside those before it is left out.  496 work items leave 16 workgroups.  Whole

@@ -121,6 +121,7 @@ struct GemmArgs {
     // is hi + lo, 22 significant bits) and W has K / 2 columns, met by both halves: C = hi W^T + lo W^T
     int Kw;
     bool w_near;        // W has just been brought into the L2s (WeightWalks)
+    bool beside;        // another stream's launches run at the same time (choose_gemm_launch)
     // EPI_SWIGLU: m is written as [M][2 * N/2] = [hi | lo]
     int split_out;
     // epilogue operands

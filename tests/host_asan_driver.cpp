@@ -218,7 +218,7 @@ int main() {
             const hr::GemmKind kind = kinds[it % 4];
             const int64_t M = it % 8 < 4 ? 1 + std::rand() % 3000 : 1 + std::rand() % 120000;
             const int N = 64 * (1 + std::rand() % 480), K = 64 * (1 + std::rand() % 230), cus = 8 * (1 + std::rand() % 40);
-            const hr::GemmLaunch g = hr::choose_gemm_launch(kind, M, N, K, cus);
+            const hr::GemmLaunch g = hr::choose_gemm_launch(kind, M, N, K, cus, it % 16 >= 12);
             CHECK(g.n == 1 || g.n == 2);
             int64_t rows = 0;
             for (int i = 0; i < g.n; ++i) {
@@ -259,6 +259,13 @@ int main() {
         CHECK(hr::choose_gemm_launch(hr::GEMM_SWIGLU, 1980, 2 * 4864, 896, 256).n == 2);
         CHECK(hr::choose_gemm_launch(hr::GEMM_QKV64, 6600, 2560, 512, 256).n == 2);
         CHECK(hr::choose_gemm_launch(hr::GEMM_QKV128, 12000, 1536, 256, 256).n == 2);
+        // halves of a call, 0.5B shape: tiles that share a CU, whatever a launch with the chip to itself would take
+        for (int64_t M = 4704; M <= 5760; M += 4) {
+            const hr::GemmLaunch alone = hr::choose_gemm_launch(hr::GEMM_RESID, M, 896, 4864, 256), half = hr::choose_gemm_launch(hr::GEMM_RESID, M, 896, 4864, 256, true);
+            CHECK(alone.n == 1 && alone.part[0].tile == hr::GT_RING160_64 && half.n == 1 && half.part[0].tile == hr::GT_SMALL);
+        }
+        const hr::GemmLaunch gu = hr::choose_gemm_launch(hr::GEMM_SWIGLU, 5720, 2 * 4864, 896, 256, true);
+        CHECK(gu.n == 2 && gu.part[0].tile == hr::GT_BIG && gu.part[1].tile == hr::GT_SMALL);
         // ... and those of single tile shapes
         struct Pin { hr::GemmKind kind; int64_t M; int N, K; hr::GemmTile tile; };
         const Pin pins[] = {
