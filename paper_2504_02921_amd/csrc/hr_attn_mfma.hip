@@ -744,6 +744,7 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
     if (warm) {
         int64_t bytes[kWarmMost];
         for (int i = 0; i < warm->n; ++i) bytes[i] = (int64_t)warm->w[i].rows * warm->w[i].row_bytes;
+        walks.pace = warm->pace;
         warm->done = pick_weight_walks(bytes, warm->n, extra);
         for (int i = 0; i < warm->n; ++i)
             if (warm->done >> i & 1) walks.w[walks.n++] = warm->w[i];

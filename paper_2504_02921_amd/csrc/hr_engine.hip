@@ -66,6 +66,11 @@ constexpr double kSplitMaxFill = 0.8;          // ... when the N = hidden GEMMs'
 // Long documents, whose pages pass through the same L2s, do not undo it: 100 documents of 2048 tokens (105 MB a layer), 800 tokens 2668 /
 // 2574, 3200 4659 / 4490.
 constexpr int64_t kWarmMaxTokens = 4096;
+// Wavefronts that read ahead pause behind every 4 KiB: in a burst the weights hold up the pages of long documents, too slow a walk outlasts
+// the attention of short ones.  One pause of 64 cycles per 32 keys of the longest sequence, 20 at most.  Whole calls, 0.5B shape, none /
+// 16 / 30 / by this rule: 640 tokens, documents of 64 tokens 1461 / 1539 / 1731 / 1451 us, of 512 tokens 1640 / 1630 / 1740 / 1614; 1200
+// tokens, documents of 512 tokens 2242 / 2148 / 2312 / 2116.
+constexpr int kWarmPaceMost = 20, kWarmPaceKeys = 32;
 constexpr size_t kSplitSlackBytes = (size_t)1 << 20;   // what two carvings of a workspace may need beyond one (alignment gaps,
                                                        // the larger group-plan room of calls with few pairs)
 
@@ -350,6 +355,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
         // QKV's launch is not told (w_near): its own reading-ahead wavefront made no difference behind a walk (16 layers of hidden
         // 2048, 65 to 4000 rows, within 0.3 %)
         a.W = layer_w(m, 1, m->pack.wqkv); a.N = nqkv; a.K = H;
+        walks.pace = std::min(kWarmPaceMost, max_keys / kWarmPaceKeys);
         walk_qkv = gemm_weight_walk(EPI_QKV_ROPE, a, &walks);
     }
     auto gemm = [&](GemmEpilogue epi, GemmArgs a) {

@@ -42,8 +42,7 @@ namespace {
 
 constexpr int BK = 64;
 static_assert(kWBlock == BK, "a k-tile of W is whole lines");
-constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
-constexpr int kAheadShares = 4;                  // ... and how many tiles of a column take turns at least
+constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS (kAheadShares: tiles)
 // ... and the tiles that may bring it: a smaller one asks for so little of W per k-tile that the ring is ahead enough.  Without / with
 // it: 32 x 32, 65 rows, K = 4864, 10.3 / 12.3 us, but 32 x 128, 128 rows, K = 4096, 27.7 / 26.0
 constexpr bool may_read_ahead(int BM, int BN, int waves) { return waves <= 4 && BM * BN >= 64 * 64; }

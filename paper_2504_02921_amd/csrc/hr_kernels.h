@@ -50,6 +50,7 @@ struct WeightWalk {
 struct WeightWalks {
     int n = 0;
     int64_t bytes = 0;
+    int pace = 0;                 // pauses of 64 cycles behind every 4 KiB that a wavefront reads
     unsigned done = 0;            // set by the launch that was handed them: bit i, it has workgroups for w[i]
     WeightWalk w[kWarmMost];
 };

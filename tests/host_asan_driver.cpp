@@ -1,11 +1,13 @@
 // Host-only logic of the library (layouts, chunk plan, metadata builder, validation) run on exact-size buffers
 // under AddressSanitizer / UBSan.  Built and run by tests/test_host_asan.py; no GPU involved.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <cstdint>
 #include <cstdlib>
 #include <vector>
 
+#include "hr_gemm_tiles.h"
 #include "hr_internal.h"
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__); return 1; } } while (0)
@@ -309,6 +311,35 @@ int main() {
                 if (fits) sum += b[i];
             }
         }
+    }
+    {   // the columns that an XCD's idle workgroups read ahead: those of its tiles, once per group of tile rows, and none of a short last
+        // group, whose one or two XCDs would read the whole matrix
+        for (int tiles_m = 1; tiles_m <= 70; ++tiles_m)
+            for (int tiles_n : {1, 2, 3, 14, 18, 28, 76, 152}) {
+                const int n_tiles = tiles_m * tiles_n, per = (n_tiles + hr::kXcds - 1) / hr::kXcds;
+                for (int xcd = 0; xcd < hr::kXcds; ++xcd) {
+                    const int t1 = std::min((xcd + 1) * per, n_tiles);
+                    std::vector<int> want(tiles_n, 0), got(tiles_n, 0);
+                    int last_group = -1, last_tn = -1;
+                    for (int t = xcd * per; t < t1; ++t) {
+                        const hr::TileCoord c = hr::map_tile((t - xcd * per) * hr::kXcds + xcd, tiles_m, tiles_n);
+                        CHECK(c.valid && c.tm < tiles_m && c.tn < tiles_n);
+                        const int group = c.tm / hr::kGroupM;
+                        if (group > 0 && c.shares < hr::kAheadShares) continue;
+                        if (group != last_group || c.tn != last_tn) ++want[c.tn];
+                        last_group = group;
+                        last_tn = c.tn;
+                    }
+                    int runs = 0;
+                    for (int t = xcd * per; t < t1; ++runs) {
+                        const hr::ColumnRun r = hr::column_run(t, t1, tiles_m, tiles_n);
+                        CHECK(r.end > t && r.end <= t1 && r.c0 >= 0 && r.c0 < r.c1 && r.c1 <= tiles_n);
+                        for (int c = r.c0; r.near && c < r.c1; ++c) ++got[c];
+                        t = r.end;
+                    }
+                    CHECK(got == want && runs <= per / (hr::kGroupM * tiles_n) + 2);
+                }
+            }
     }
     {   // sequences with the same token string share first-layer rows: tables written into a layout of exactly the computed size
         // strings: A = {5, 6, 7}, B = {5, 6}, C = {9}; sequences A B A C B A C
