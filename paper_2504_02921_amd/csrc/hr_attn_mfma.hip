@@ -48,7 +48,7 @@ constexpr int stage_bytes(bool fp8) { return fp8 ? kStageBytesHalf / 2 : kStageB
 constexpr int kMaxRowsPerWg = 512;
 constexpr float kLazyMax = 8.0f;
 // Workgroups that read weights ahead (warm_weights), where the work items leave room for them on the chip.  0.5B shape, one query x 20
-// candidates x 32 tokens, whole call: none 1805 us, 64 1746, 128 1634, 256 1636, 384 1700 (they then share CUs with work items).
+// candidates x 32 tokens, whole call: none 1800 us, 64 (twice the bytes each) 1815, 128 1625, 256 1671 (they then share CUs with work items).
 constexpr int kWarmWgs = 128;
 
 template <int HD, bool FP8, int kStageBytes>

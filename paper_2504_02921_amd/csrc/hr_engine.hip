@@ -62,9 +62,9 @@ constexpr int64_t kChunkedMaxKeys = 1 << 15;   // longest sequence of the chunke
 constexpr int64_t kSplitMinTokens = 8192;      // query tokens from which a scoring call is cut in two halves
 constexpr double kSplitMaxFill = 0.8;          // ... when the N = hidden GEMMs' tiles fill less than this share of their rounds
 // Up to this many new tokens the attention's idle workgroups read the layer's weights ahead.  Whole calls of 20-token queries, 0.5B
-// shape, without / with: 2000 tokens 2849 / 2765 us, 4000 4110 / 4002, 8000 7505 / 7504 (the work items fill the chip).
-// Long documents, whose pages pass through the same L2s, do not undo it: 100 documents of 2048 tokens (105 MB a layer), 800 tokens 2668 /
-// 2574, 3200 4659 / 4490.
+// shape, without / with: 2000 tokens 2960 / 2870 us, 4000 4365 / 4255, 8000 7940 / 7920 (the work items fill the chip).
+// Long documents, whose pages pass through the same L2s, do not undo it: 100 documents of 2048 tokens (105 MB a layer), 800 tokens 2673 /
+// 2540, 3200 4948 / 4806.
 constexpr int64_t kWarmMaxTokens = 4096;
 // Wavefronts that read ahead pause behind every 4 KiB: in a burst the weights hold up the pages of long documents, too slow a walk outlasts
 // the attention of short ones.  One pause of 64 cycles per 32 keys of the longest sequence, 20 at most.  Whole calls, 0.5B shape, none /

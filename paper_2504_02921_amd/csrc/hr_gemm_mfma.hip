@@ -42,7 +42,7 @@ namespace {
 
 constexpr int BK = 64;
 static_assert(kWBlock == BK, "a k-tile of W is whole lines");
-constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS (kAheadShares: tiles)
+constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
 // ... and the tiles that may bring it: a smaller one asks for so little of W per k-tile that the ring is ahead enough.  Without / with
 // it: 32 x 32, 65 rows, K = 4864, 10.3 / 12.3 us, but 32 x 128, 128 rows, K = 4096, 27.7 / 26.0
 constexpr bool may_read_ahead(int BM, int BN, int waves) { return waves <= 4 && BM * BN >= 64 * 64; }
@@ -983,8 +983,8 @@ static GemmKind kind_of(GemmEpilogue epi, const GemmArgs& a) {
 // The XCDs' L2s hold 4 MiB each; the activations pass through them as well.  A layer of the 0.5B shape is 28.4 MiB.  O alone of the
 // 8B shape (32 MiB): 100 rows 6083 -> 5946 us a call, 640 rows 10630 -> 10680.
 // Matrices that are left out do not count, although their bytes pass through the L2s in between: 16 layers of hidden 2048 and ffn 8192 (gate / up
-// and down, 96 MiB, left out), nothing / O / O and QKV read ahead, 640 rows 2140 / 2124 / 2103 us a call, 1300 rows 3484 / 3480 / 3400;
-// 28 layers of 1536 and 8960, 160 rows 2602 / 2580 / 2504.
+// and down, 96 MiB, left out), nothing / O / O and QKV read ahead, 1300 rows 3635 / 3630 / 3600 us a call (640 rows 2173 each); 28 layers of
+// 1536 and 8960, 160 rows 2585 / 2563 / 2490.
 constexpr int64_t kWarmBytes = (int64_t)30 << 20;
 
 bool gemm_weight_walk(GemmEpilogue epi, const GemmArgs& a, WeightWalks* out) {
