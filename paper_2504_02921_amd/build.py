@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhyperrerank.so")
 
-SOURCES = ["hr_host.cpp", "hr_engine.hip", "hr_kernels_generic.hip", "hr_f32.hip", "hr_gemm_mfma.hip", "hr_attn_mfma.hip"]
+SOURCES = ["hr_host.cpp", "hr_engine.hip", "hr_kernels_generic.hip", "hr_f32.hip", "hr_gemm_mfma.hip", "hr_attn_mfma.hip", "hr_attn_rows.hip"]
 
 # packed-fp32 instruction selection is switched off for all device code
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

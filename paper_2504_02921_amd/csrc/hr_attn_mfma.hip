@@ -23,6 +23,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "hr_attn_common.h"
 #include "hr_device_types.h"
 #include "hr_gemm_tiles.h"
 #include "hr_internal.h"
@@ -31,14 +32,6 @@
 
 namespace hr {
 
-typedef __attribute__((ext_vector_type(8))) _Float16 halfx8;
-typedef __attribute__((ext_vector_type(4))) _Float16 halfx4;
-typedef __attribute__((ext_vector_type(2))) _Float16 halfx2;
-typedef __attribute__((ext_vector_type(16))) float floatx16;
-typedef __attribute__((ext_vector_type(2))) float floatx2;
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
-
 namespace {
 
 // LDS stage: 32 KiB of half pages; an fp8 pool streams the same number of keys per stage in 16 KiB and spends the
@@ -46,10 +39,6 @@ namespace {
 constexpr int kStageBytesHalf = 32768;
 constexpr int stage_bytes(bool fp8) { return fp8 ? kStageBytesHalf / 2 : kStageBytesHalf; }
 constexpr int kMaxRowsPerWg = 512;
-constexpr float kLazyMax = 8.0f;
-// Workgroups that read weights ahead (warm_weights), where the work items leave room for them on the chip.  0.5B shape, one query x 20
-// candidates x 32 tokens, whole call: none 1800 us, 64 (twice the bytes each) 1815, 128 1625, 256 1671 (they then share CUs with work items).
-constexpr int kWarmWgs = 128;
 
 template <int HD, bool FP8, int kStageBytes>
 struct Geo {
@@ -59,47 +48,6 @@ struct Geo {
     static constexpr int PPS = kStageBytes / PAGE_BYTES;         // pages per stage
     static constexpr int TK = kPageTokens * PPS;                 // keys per stage
 };
-
-// 8 consecutive fp8 codes (one 64-bit LDS word) -> 8 halves, times a power of two.
-// An E4M3 code s.eeee.mmm placed at bits 15, 13..7 of a half (sign kept, exponent and mantissa fields shifted down
-// by one) reads as (-1)^s 2^(e-15) (1 + m/8), or (-1)^s 2^-14 (m/8) when e = 0: in both cases the E4M3 value
-// (bias 7, subnormals m/8 * 2^-6) divided by 2^8.  So the conversion is a byte shuffle, two masks, a shift and one
-// packed half multiplication by 2^8 * 2^k, exact while the product is a half.  (The hardware's scaled conversion
-// instruction gives the same values but measured ~88 cycles per wavefront instruction, against 4 for these.)
-// The two NaN codes (0x7f, 0xff) read as +-480; a pool never holds them.
-__device__ __forceinline__ halfx8 fp8x8_to_half(uint2 w, halfx2 pow2) {
-    auto pair = [&](unsigned x, unsigned sel) {
-        const unsigned t = __builtin_amdgcn_perm(x, 0u, sel);                    // code bytes to the high byte of each 16-bit half
-        const unsigned h = (t & 0x80008000u) | ((t & 0x7F007F00u) >> 1);
-        halfx2 v;
-        __builtin_memcpy(&v, &h, 4);
-        return v * pow2;
-    };
-    const halfx2 a = pair(w.x, 0x050c040cu), b = pair(w.x, 0x070c060cu), c = pair(w.y, 0x050c040cu), d = pair(w.y, 0x070c060cu);
-    halfx8 r;
-    r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1]; r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
-    return r;
-}
-
-// Reductions over lanes l and l ^ 32 (the two lanes that share a query row) through the VALU lane-swap instruction instead of an
-// LDS round trip: v_permlane32_swap exchanges the upper half of its first operand with the lower half of its second, so
-// with the same value in both the first result holds lanes 0..31 twice and the second lanes 32..63 twice.
-__device__ __forceinline__ float row_max2(float x) {       // max over the two lanes of a row, in both
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float row_sum2(float x) {       // sum over the two lanes of a row, in both (same bits in both)
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// 2^8 times the power of two of a positive scale, as a pair of halves (clamped to the normal range of half)
-__device__ __forceinline__ halfx2 fp8_expand_factor(float scale) {
-    int e = (int)((__float_as_uint(scale) >> 23) & 0xFFu) - 127 + 8;
-    e = e < -14 ? -14 : (e > 15 ? 15 : e);
-    const _Float16 f = (_Float16)__uint_as_float((unsigned)(e + 127) << 23);
-    return halfx2{f, f};
-}
 
 // What a workgroup needs to know about one work item = (pair or group of pairs with one document, kv head)
 struct ItemCtx {
@@ -141,7 +89,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
     extern __shared__ __attribute__((aligned(16))) char smem[];      // [2][kStageBytes] + scales + (fp8) expanded stage
     if constexpr (!PREC) {
         if ((int)blockIdx.x >= n_wg) {
-            warm_weights<NW>(warm, n_wg, smem);
+            warm_weights<NW>(warm, (int)blockIdx.x, n_wg, (int)gridDim.x, smem);
             return;
         }
     }
@@ -386,8 +334,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
         if constexpr (KV8) {
             cs0 *= sc[(st * 2) * 2];
             cs1 *= sc[(st * 2 + 1) * 2];
-            vs0 = __uint_as_float((__float_as_uint(sc[(st * 2) * 2 + 1]) & 0x007FFFFFu) | 0x3F800000u);
-            vs1 = __uint_as_float((__float_as_uint(sc[(st * 2 + 1) * 2 + 1]) & 0x007FFFFFu) | 0x3F800000u);
+            vs0 = fp8_scale_mantissa(sc[(st * 2) * 2 + 1]);
+            vs1 = fp8_scale_mantissa(sc[(st * 2 + 1) * 2 + 1]);
         }
         // V^T fragments (A operand): lane = channel mb*32 + ln, 8 keys of key group hh of page s2
         halfx8 vf[MB][2];
@@ -439,7 +387,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PR
                 lsum += pr;
                 sr[r] = pr;
             }
-            l_run[rb] = l_run[rb] * alpha + lsum;
+            l_run[rb] = fmaf(l_run[rb], alpha, lsum);
             m_run[rb] = m_new;
             if (__any(alpha != 1.0f)) {
 #pragma unroll
@@ -740,16 +688,7 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
     const int n_items = (gv.n_groups > 0 ? gv.n_groups : mv.n_seq) * pv.n_kv;
     const int n_wg = std::min(n_items, max_wgs);
     WeightWalks walks;                                              // those of `warm` that the launch has room for
-    int extra = std::min(kWarmWgs, max_wgs - n_wg) / kXcds * kXcds;
-    if (warm) {
-        int64_t bytes[kWarmMost];
-        for (int i = 0; i < warm->n; ++i) bytes[i] = (int64_t)warm->w[i].rows * warm->w[i].row_bytes;
-        walks.pace = warm->pace;
-        warm->done = pick_weight_walks(bytes, warm->n, extra);
-        for (int i = 0; i < warm->n; ++i)
-            if (warm->done >> i & 1) walks.w[walks.n++] = warm->w[i];
-    }
-    if (walks.n == 0) extra = 0;
+    const int extra = warm ? pick_walks(warm, max_wgs - n_wg, &walks) : 0;
     attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)(n_wg + extra)), NW * 64, lds, st>>>(q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, mv.cu, mv.prefix_len,
                                                                                    mv.page_table, mv.new_cu, pv.scales, last_only, gv.n_groups, gv.p0,
                                                                                    gv.blk_cu, gv.sub_cu, gv.blk_seq, gv.blk_row0, gv.sub_page,
@@ -757,7 +696,22 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
     return hipGetLastError();
 }
 
+// Workgroups that read weights ahead (warm_weights), where the work items leave room for them on the chip.  0.5B shape, one query x 20
+// candidates x 32 tokens, whole call: none 1800 us, 64 (twice the bytes each) 1815, 128 1625, 256 1671 (they then share CUs with work items).
+constexpr int kWarmWgs = 128;
+
 }  // namespace
+
+int pick_walks(WeightWalks* warm, int free_wgs, WeightWalks* walks) {
+    const int extra = std::min(kWarmWgs, std::max(free_wgs, 0)) / kXcds * kXcds;
+    int64_t bytes[kWarmMost];
+    for (int i = 0; i < warm->n; ++i) bytes[i] = (int64_t)warm->w[i].rows * warm->w[i].row_bytes;
+    walks->pace = warm->pace;
+    warm->done = pick_weight_walks(bytes, warm->n, extra);
+    for (int i = 0; i < warm->n; ++i)
+        if (warm->done >> i & 1) walks->w[walks->n++] = warm->w[i];
+    return walks->n > 0 ? extra : 0;
+}
 
 // rows per workgroup = (n_q / n_kv) * max_q_len must fit NW * R blocks of 32 (the pair's own keys may take any number of
 // stages: they are streamed like document pages)
@@ -781,10 +735,14 @@ bool attn_mfma_supported_cut(const hr_model_cfg& c, int kv_dtype, int max_q_len)
 }
 
 hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, const MetaView& mv, const PoolView& pv, int layer,
-                            int n_q, int max_q_len, hipStream_t st, bool last_only, const GroupView* groups, const void* kv_new_lo_pages,
+                            int n_q, int max_q_len, int max_keys, hipStream_t st, bool last_only, const GroupView* groups, const void* kv_new_lo_pages,
                             WeightWalks* warm) {
     if (mv.n_seq == 0) return hipSuccess;
     const GroupView gv = groups && !last_only ? *groups : GroupView{};
+    const int seq_blocks = (n_q / pv.n_kv * (last_only ? 1 : max_q_len) + 31) / 32;
+    if (!kv_new_lo_pages && attn_takes_rows((int64_t)mv.n_seq * pv.n_kv * seq_blocks, gv.n_groups > 0 ? gv.max_blocks : seq_blocks, pv.d, max_keys,
+                                            device_cu_count()))
+        return launch_attn_rows(q, kv_new_pages, o, mv, pv, layer, n_q, seq_blocks, st, last_only, warm);
     const int rows = gv.n_groups > 0 ? gv.max_blocks * 32 : n_q / pv.n_kv * (last_only ? 1 : max_q_len);
     if (rows > kMaxRowsPerWg) return hipErrorInvalidValue;
     const half_t* qh = (const half_t*)q;

@@ -385,7 +385,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             HR_TIMED(PC_GEMM_QKV, gemm(EPI_RESID_ADD, a));
             HR_TIMED(PC_ELEMENTWISE, launch_rope_pages(f32, rope, q, k, kvlo, mv.new_slot, src0, T, c.n_q_heads, c.n_kv_heads, d, st));
             if (l == 0 && after_qkv0) HR_HIP(hipEventRecord(after_qkv0, st));
-            HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, l, c.n_q_heads, max_new_len, st, false, groups, kvlo));
+            HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, l, c.n_q_heads, max_new_len, max_keys, st, false, groups, kvlo));
             GemmArgs b{};
             b.A = o; b.W = layer_w(m, l, m->pack.wo); b.M = T; b.N = H; b.K = 2 * nq; b.Kw = nq; b.x = x;
             HR_TIMED(PC_GEMM_O, gemm(EPI_RESID_ADD, b));
@@ -437,7 +437,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             // of T (exact: the other rows' outputs of this layer are never read).
             const int64_t P = mv.n_seq;
             float* x_last = (float*)q;                      // q is dead once attention has run
-            HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, l, c.n_q_heads, max_new_len, st, true));
+            HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, l, c.n_q_heads, max_new_len, max_keys, st, true));
             HR_TIMED(PC_ELEMENTWISE, launch_gather_rows_f32(x, mv.out_row, x_last, (int)P, H, st));
             GemmArgs a{};
             a.A = o; a.W = layer_w(m, l, m->pack.wo); a.M = P; a.N = H; a.K = nq; a.x = x_last;
@@ -461,7 +461,7 @@ int run_layers(hr_model* m, const hr_pool* pool, bool self_prefix, const MetaVie
             WeightWalks ahead = walks;                       // of layer 0 and layer 1's QKV: the layers' packs are equally far apart
             if (walk_qkv && l + 1 == c.n_layers) --ahead.n;
             for (int i = 0; i < ahead.n; ++i) ahead.w[i].W += (size_t)l * m->pack.layer_elems * dtype_size(dt);
-            HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, self_prefix ? 0 : l, c.n_q_heads, max_new_len, st, false, groups, nullptr, &ahead));
+            HR_TIMED(PC_ATTENTION, launch_attn_mfma(q, k, o, mv, pv, self_prefix ? 0 : l, c.n_q_heads, max_new_len, max_keys, st, false, groups, nullptr, &ahead));
             walked = ahead.done;
         } else {
             HR_TIMED(PC_ATTENTION, launch_attn_generic(dt, q, k, v, o, mv, pv, l, c.n_q_heads, max_keys, st));

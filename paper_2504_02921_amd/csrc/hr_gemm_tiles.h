@@ -56,7 +56,7 @@ HR_HD ColumnRun column_run(int t0, int t1, int tiles_m, int tiles_n) {
 
 namespace hr {
 
-// The workgroups behind the `first`-th of a launch with idle CUs do not take part in it: they touch the weights that the next
+// The workgroups first .. end - 1 of a launch with idle CUs (wg: this one) do not take part in it: they touch the weights that the next
 // launches read, XCD by XCD in the order above, 64 bytes per lane, so that those find them in their XCD's L2 (what a kernel read
 // stays there for the next: 256 workgroups reading 8 MB take 1.5 us from HBM, 0.65 from their own L2 and 1.5 from
 // another XCD's reading).  NW: wavefronts of a workgroup; lds: room for 256 bytes for each of them, read by nobody.
@@ -64,12 +64,12 @@ namespace hr {
 // ~0.2 us each, the weights of a layer took up to 24 us, longer than the attention of short documents: 0.5B shape, 16 pairs x 18 tokens,
 // documents of 64 tokens 1433 -> 1113 us a call, 20 x 32 tokens 1608 -> 1451, documents of 512 tokens 1620 -> 1614.
 template <int NW>
-__device__ __forceinline__ void warm_weights(const WeightWalks& ws, int first, char* lds) {
+__device__ __forceinline__ void warm_weights(const WeightWalks& ws, int wg, int first, int end, char* lds) {
     typedef __attribute__((address_space(3))) void* lds_p;
     typedef const __attribute__((address_space(1))) void* gbl_p;
-    const int xcd = (int)blockIdx.x % kXcds;
+    const int xcd = wg % kXcds;
     const int skip = ((xcd - first) % kXcds + kXcds) % kXcds;            // first + skip: the first such workgroup on this XCD
-    const int me = ((int)blockIdx.x - first - skip) / kXcds, all = ((int)gridDim.x - first - skip + kXcds - 1) / kXcds;
+    const int me = (wg - first - skip) / kXcds, all = (end - first - skip + kXcds - 1) / kXcds;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     for (int i = 0; i < ws.n; ++i) {
         const WeightWalk& w = ws.w[i];

@@ -525,6 +525,11 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_, 
     return g;
 }
 
+bool attn_takes_rows(int64_t blocks, int item_blocks, int head_dim, int max_keys, int cus) {
+    const int64_t most = std::min(max_keys, head_dim == 64 ? cus * 11 / 8 : cus);
+    return blocks <= most * (item_blocks > 4 ? 2 : 1);
+}
+
 unsigned pick_weight_walks(const int64_t* bytes, int n, int wgs) {
     unsigned picked = 0;
     int64_t room = (int64_t)std::max(wgs, 0) * kWarmBytesPerWg;

@@ -159,6 +159,17 @@ GroupPlan make_group_plan(int64_t n_seq, const int32_t* prefix_lens, const int32
                           int64_t pt_stride, int g, int cap_blocks, bool cut_long = false);
 size_t group_plan_ints_bound(int64_t n_seq, int64_t T, int g);
 
+// Whether an attention launch of `blocks` 32-row blocks (all sequences and kv heads together) goes to the kernel that spreads a block's keys over
+// a workgroup's wavefronts (hr_attn_rows.hip) instead of walking them in one chain.  item_blocks: blocks of the largest work item
+// of the other kernel.
+// It saves the length of the chain, which grows with the keys and is twice as long where a wavefront has two blocks (more than four in an item);
+// it costs a workgroup per block, and more blocks than are resident wait for the first.  Whole calls, one chain / spread: 0.5B
+// shape, 30 blocks, 100-300 keys 1100 / 1003 us; 200 blocks, 304 keys 1503 / 1453; 280 blocks, 544 keys 1605 / 1565, 2080 keys 2277 /
+// 2061; 350 blocks, 544 keys 1875 / 1814; but 140 blocks, 96 keys 1262 / 1275; 280 blocks, 160 keys 1460 / 1511; 400 blocks, 520 keys 1888 /
+// 1905; 560 blocks, 544 keys 2110 / 2344.  Prefill (items of 14 blocks): 224 blocks, 512 keys 1862 / 1529, 448 blocks 2238 / 1970, 896
+// blocks 2941 / 2998.  8B shape (one workgroup per CU): 256 blocks, 288 keys 6694 / 6538; 288 blocks 8196 / 8284; 640 blocks 10267 / 10530.
+bool attn_takes_rows(int64_t blocks, int item_blocks, int head_dim, int max_keys, int cus);
+
 // ---- how an M x N x K MFMA GEMM is launched on a device of `cus` compute units: as one or two launches over consecutive row
 // ranges, each with a tile shape of the epilogue's list.  With M x N outputs spread over the CUs the last round of tiles is what
 // decides (8B down projection of 12800 rows: 3.1 rounds of 256 x 256 tiles, a fourth round for 512 rows), so the cost of

@@ -151,13 +151,20 @@ struct GroupView {
     const int32_t *p0 = nullptr, *blk_cu = nullptr, *sub_cu = nullptr, *blk_seq = nullptr, *blk_row0 = nullptr, *sub_page = nullptr,
                   *sub_seq = nullptr, *sub_key0 = nullptr;
 };
+// max_keys: keys of the longest sequence, its new tokens among them.
 // kv_new_pages: the new tokens' K/V as pages (see GemmArgs::kv_pages).  groups: nullptr = every sequence on its own.
 // warm: what workgroups of the launch that find no work item may read ahead (not in the 22-bit form).
 // kv_new_lo_pages: if set, the 22-bit form: q and o are [T][hi | lo] halves, and this buffer (same arrangement as
 // kv_new_pages) holds what the rounding of the new tokens' K/V to half left out.
 hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, const MetaView& mv,
-                            const PoolView& pv, int layer, int n_q, int max_q_len, hipStream_t st, bool last_only = false,
+                            const PoolView& pv, int layer, int n_q, int max_q_len, int max_keys, hipStream_t st, bool last_only = false,
                             const GroupView* groups = nullptr, const void* kv_new_lo_pages = nullptr, WeightWalks* warm = nullptr);
+// The form for launches of few 32-row blocks (hr_attn_rows.hip; launch_attn_mfma hands them on, see attn_takes_rows): the same bits.
+// blocks: of the sequence that has the most
+hipError_t launch_attn_rows(const void* q, const void* kv_new_pages, void* o, const MetaView& mv, const PoolView& pv, int layer, int n_q,
+                            int blocks, hipStream_t st, bool last_only, WeightWalks* warm);
+// The walks of `warm` that a launch with room for `free_wgs` more workgroups takes, marked in warm->done; how many workgroups read them
+int pick_walks(WeightWalks* warm, int free_wgs, WeightWalks* walks);
 // fp8 pools: quantising copy of whole pages (amax -> scale -> E4M3 codes per page and kv head) from the half new-KV buffer
 hipError_t launch_pages_to_pool_fp8(const char* kv_new, char* pool_layer_base, float* scales_layer_base, const int32_t* src_page,
                                     const int32_t* dst_page, int n_pages, int n_kv, int d, hipStream_t st);

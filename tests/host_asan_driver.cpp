@@ -292,6 +292,18 @@ int main() {
             CHECK(g.n == 1 && g.part[0].tile == p.tile);
         }
     }
+    {   // attention: whether a block's keys are spread over wavefronts or walked in one chain
+        // five pairs of the GPU test that compares the two (most blocks per pair x kv heads x 5, keys, head size), and its whole batch
+        struct Spread { int n_kv, blocks, d, keys; };
+        for (const Spread& c : {Spread{2, 16, 64, 2150}, Spread{4, 2, 64, 2120}, Spread{2, 5, 128, 2120}, Spread{4, 3, 128, 2150}, Spread{1, 1, 64, 2081}}) {
+            CHECK(hr::attn_takes_rows(5 * c.n_kv * c.blocks, std::min(c.blocks, 16), c.d, c.keys, 256));
+            CHECK(!hr::attn_takes_rows(880 * c.n_kv * c.blocks, std::min(c.blocks, 16), c.d, c.keys, 256));
+        }
+        CHECK(hr::attn_takes_rows(352, 4, 64, 352, 256) && !hr::attn_takes_rows(353, 4, 64, 4096, 256));
+        CHECK(hr::attn_takes_rows(256, 4, 128, 256, 256) && !hr::attn_takes_rows(257, 4, 128, 4096, 256));
+        CHECK(hr::attn_takes_rows(96, 1, 64, 96, 256) && !hr::attn_takes_rows(97, 1, 64, 96, 256));        // short documents
+        CHECK(hr::attn_takes_rows(704, 14, 64, 512, 256) && !hr::attn_takes_rows(705, 14, 64, 512, 256));  // two blocks per wavefront in the other
+    }
     {   // weights read ahead by a launch's idle workgroups: never more than they can take, in order, what does not fit left out
         const int64_t q05[] = {896 * 896 * 2, 9728 * 896 * 2, 896 * 4864 * 2, 1152 * 896 * 2};      // O, gate / up, down, QKV of the 0.5B shape
         CHECK(hr::pick_weight_walks(q05, 4, 128) == 15);

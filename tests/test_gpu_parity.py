@@ -1151,6 +1151,38 @@ def test_four_bit_host_tier_matches_the_oracle_quantiser(d, n_q, n_kv):
         case.close()
 
 
+# Document lengths around what the kernel for few row blocks works in: pages of 16 keys, sub-tiles of 32, rounds of 12 of them (384
+# keys), page addresses for two rounds (768)
+ROW_SPREAD_LENS = (0, 1, 15, 16, 17, 31, 32, 33, 352, 383, 384, 385, 416, 767, 768, 769, 1151, 1152, 1153, 1536, 1537, 2080)
+
+
+@pytest.mark.parametrize("d,n_q,n_kv,kv,qlen", [
+    (64, 14, 2, "bf16", (1, 70)),        # 1 to 16 row blocks, three sub-tiles of own keys
+    (64, 4, 4, "fp8", (1, 40)),
+    (128, 8, 2, "bf16", (1, 40)),
+    (128, 4, 4, "fp8", (20, 70)),
+    (64, 3, 1, "bf16", (1, 1)),          # one row block of three rows
+])
+def test_keys_spread_over_wavefronts_give_the_bits_of_one_chain(d, n_q, n_kv, kv, qlen):
+    """A call of few row blocks spreads a block's keys over a workgroup's wavefronts, a batch walks them in one chain (which call
+    goes where is pinned in host_asan_driver.cpp): the same bits, at every document length around the edges."""
+    import dataclasses
+    model = small_model(dtype="bf16", n_layers=2, hidden=256, n_q=n_q, n_kv=n_kv, d=d, ffn=320, vocab=500)
+    cfg = wlmod.WorkloadCfg("row_spread", model, 44, 20, (2080, 2080), qlen, kv, pool_docs=24, zipf_a=0.1, seed=91)
+    wl = wlmod.make_workload(cfg)
+    wl = dataclasses.replace(wl, doc_lens=np.array([ROW_SPREAD_LENS[i % len(ROW_SPREAD_LENS)] for i in range(wl.n_pairs)], np.int32))
+    case = H.Case(wl, wlmod.SeededWeights(model, seed=92, std=0.05, gain_jitter=0.1))
+    try:
+        case.fill_synthetic(oracle_doc_ids=[], all_docs=True)
+        whole = case.gpu_scores()
+        assert np.all(np.isfinite(whole))
+        for first in list(range(0, 110, 5)) + [wl.n_pairs - 3]:
+            idx = np.arange(first, min(first + 5, wl.n_pairs))
+            np.testing.assert_array_equal(case.gpu_scores(wl.subset(idx)), whole[idx], err_msg=f"pairs from {first} on")
+    finally:
+        case.close()
+
+
 @pytest.mark.parametrize("d,n_q,n_kv,kv", [(64, 14, 2, "bf16"), (128, 8, 8, "fp8")])
 def test_prefixes_of_a_batch_score_the_same_bits_across_scheduling_thresholds(d, n_q, n_kv, kv):
     """The library picks tile shapes, ring or two-stage GEMMs, attention work-item plans and one or two streams from the
