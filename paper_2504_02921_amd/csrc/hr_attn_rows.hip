@@ -266,6 +266,7 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
             lds_barrier();                                                        // P is there
             if (FP8 && (r & 1)) cur = ahead;
         }
+        __builtin_amdgcn_s_waitcnt(0x0F70);          // nothing is on its way into LDS when the wave ends
         return;
     }
     const int ch0 = (wave - kSWaves) * G::MBW * 32;                               // this wave's first channel
