@@ -113,14 +113,14 @@ constexpr int kNoLoad = 0x7FF00000;      // a vector offset past every range: no
 
 // A thread's 16-byte chunks of the tile's part of x, for tiles whose fp32 form fits the two stages (one slab below).
 template <int BN, int NT, int CHUNKS>
-__device__ __forceinline__ void x_prefetch(float4 (&xv)[CHUNKS], const GemmArgs& a, int64_t tile_m0, int tile_n0) {
+__device__ __forceinline__ void x_prefetch(floatx4 (&xv)[CHUNKS], const GemmArgs& a, int64_t tile_m0, int tile_n0) {
     constexpr int CPRW = BN / 4;
 #pragma unroll
     for (int it = 0; it < CHUNKS; ++it) {
         const int L = it * NT + threadIdx.x, row = L / CPRW, pch = L % CPRW;
         const int64_t grow = min(tile_m0 + row, a.M - 1);
         const int col = min(tile_n0 + ((pch ^ (row & (min(CPRW, 16) - 1))) << 2), a.N - 4);
-        xv[it] = *(const float4*)(a.x + grow * a.N + col);
+        xv[it] = *(const floatx4*)(a.x + grow * a.N + col);
     }
 }
 
@@ -130,7 +130,7 @@ __device__ __forceinline__ void x_prefetch(float4 (&xv)[CHUNKS], const GemmArgs&
 // x_prefetch read (nullptr: x is read here).
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
 __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / WN / 16], const GemmArgs& a, char* smem,
-                                              int64_t tile_m0, int tile_n0, const float4* x_pre = nullptr) {
+                                              int64_t tile_m0, int tile_n0, const floatx4* x_pre = nullptr) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 16, NI = TN / 16;
@@ -166,7 +166,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
             // its latency hides behind the write and the barrier.  Every address is clamped into the matrix, only
             // valid chunks are written back.
             constexpr int G = ITER / NG;
-            float4 xv[G];
+            floatx4 xv[G];
             auto load_x = [&](int first) {
 #pragma unroll
                 for (int it = 0; it < G; ++it) {
@@ -176,7 +176,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
                     int64_t grow = tile_m0 + row;
                     grow = grow < a.M ? grow : a.M - 1;
                     col = col < a.N ? col : a.N - 4;
-                    xv[it] = *(const float4*)(a.x + grow * a.N + col);
+                    xv[it] = *(const floatx4*)(a.x + grow * a.N + col);
                 }
             };
             auto update_x = [&](int first) {
@@ -187,13 +187,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
                     const int col = tile_n0 + p * CW + ((pch ^ (row & SWZ)) << 2);
                     const int64_t grow = tile_m0 + row;
                     if (grow >= a.M || col >= a.N) continue;        // N is a multiple of 8: whole chunks
-                    const float4 c = *(const float4*)(stage + row * CW + (pch << 2));
-                    float4 v = xv[it];
-                    v.x += c.x;
-                    v.y += c.y;
-                    v.z += c.z;
-                    v.w += c.w;
-                    *(float4*)(a.x + grow * a.N + col) = v;
+                    *(floatx4*)(a.x + grow * a.N + col) = xv[it] + *(const floatx4*)(stage + row * CW + (pch << 2));
                 }
             };
             if (PASSES == 1 && x_pre) {
@@ -488,6 +482,12 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
         for (int p = 0; p < PB; ++p) dma_b(p, 0, 0);
     };
 
+    // x of a residual add, for the tiles whose registers hold all of it: requested behind the last k-tile, one round trip instead of four in
+    // the epilogue, which took half of such a tile's time.  O of the 0.5B shape (K = 896), 230 k rows 597 -> 548 us, with a third stage of
+    // A 524; 65536 rows 178 -> 165 -> 158.
+    constexpr bool XPRE = EPI == EPI_RESID_ADD && BM * BN <= 128 * 128;
+    constexpr int XCH = BM * BN / 4 / NT;
+    floatx4 xv[XPRE ? XCH : 1];
     floatx4 acc[MI][NI];
     const int frow = lane & 15, fq = lane >> 4;
     const int sw = (frow >> 1) & 7;           // row pair index: rows are 128 bytes, the bank window 256
@@ -543,11 +543,12 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
         for (int i = 0; i < XR; ++i) mfma_row(i, 1);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto tail = [&](auto last_c, int kt) {
+    auto tail = [&](auto last_c, auto younger_c, int kt) {
         constexpr bool LAST = decltype(last_c)::value;
         if constexpr (!LAST) {
-            // the next k-tile has landed (own loads; A of the one after may be outstanding) and every wave has read this one
-            constexpr int V = SA == 3 ? PA : 0;
+            // the next k-tile has landed (own loads; A of the one after, or what else was requested since, may be outstanding) and
+            // every wave has read this one
+            constexpr int V = (SA == 3 ? PA : 0) + decltype(younger_c)::value;
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0070);       // vmcnt(V) lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
@@ -594,11 +595,19 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 #pragma unroll
     for (int j = 0; j < NI; ++j) read_b(j, sB, 0);
     head(0);
-    for (int kt = 0; kt + 1 < nk; ++kt) {
-        tail(std::false_type{}, kt);
+    int kt = 0;
+    for (; kt + 1 + XPRE < nk; ++kt) {
+        tail(std::false_type{}, c0, kt);
         head(kt + 1);
     }
-    tail(std::true_type{}, nk - 1);
+    if constexpr (XPRE) {                     // x behind the last k-tile's loads, which do not wait for it
+        x_prefetch<BN, NT>(xv, a, m0, n0);
+        if (kt + 1 < nk) {
+            tail(std::false_type{}, integral_constant<int, XCH>{}, kt);
+            head(kt + 1);
+        }
+    }
+    tail(std::true_type{}, c0, nk - 1);
     // nobody reads the stages any more, and nothing is on its way into them
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
@@ -616,7 +625,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
             dma_first();                      // stages 0: nobody reads LDS behind the loop's last barrier
         }
     }
-    gemm_epilogue<EPI, BM, BN, WM, WN, HB, SA>(acc, a, smem, tile_m0, tile_n0);
+    gemm_epilogue<EPI, BM, BN, WM, WN, HB, SA>(acc, a, smem, tile_m0, tile_n0, XPRE ? xv : nullptr);
     if (!has_next) break;
     }
 }
@@ -704,10 +713,10 @@ __global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 
         }
     }
 
-    // x of a residual add: requested first, so that it has arrived long before the epilogue.  Small tiles only: a 128 x 128 one
-    // would hold 64 registers for it through the k loop (and spilled them)
-    constexpr bool XPRE = EPI == EPI_RESID_ADD && BM * BN <= 64 * 64;
-    float4 xv[XPRE ? BM * BN / 4 / NT : 1];
+    // x of a residual add: requested first, so that it has arrived long before the epilogue (8B shape, 640 rows, 160 x 64 tiles: O and down
+    // 69.2 -> 68.5 us on average).  A 128 x 128 tile would hold 64 registers for it through the k loop (and spilled them)
+    constexpr bool XPRE = EPI == EPI_RESID_ADD && BM * BN <= 160 * 64;
+    floatx4 xv[XPRE ? BM * BN / 4 / NT : 1];
     if constexpr (XPRE) x_prefetch<BN, NT>(xv, a, m0, n0);
 
     const int lrow = tid >> 3;
@@ -1022,7 +1031,7 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
             case GEMM_QKV64:
                 switch (p.tile) {
                     case GT_BIG: e = launch_tile<EPI_QKV_ROPE, 256, 256, 2, 4, 1, 3>(r, p, st); break;
-                    case GT_SMALL: e = launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 2>(r, p, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 3>(r, p, st); break;
                     case GT_RING128: e = launch_ring<EPI_QKV_ROPE, 128, 128, 2, 2, 1, 4>(r, p, st); break;
                     case GT_RING64: e = launch_ring<EPI_QKV_ROPE, 64, 64, 2, 1, 1, 8>(r, p, st); break;
                     case GT_RING32_64: e = launch_ring<EPI_QKV_ROPE, 32, 64, 2, 1, 1, 8>(r, p, st); break;
@@ -1042,7 +1051,7 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                 switch (p.tile) {
                     case GT_BIG: e = launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(r, p, st); break;
                     case GT_TALL: e = launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1, 2>(r, p, st); break;
-                    case GT_SMALL: e = launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 2>(r, p, st); break;
+                    case GT_SMALL: e = launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 3>(r, p, st); break;
                     case GT_RING128: e = launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(r, p, st); break;
                     case GT_RING64_128: e = launch_ring<EPI_RESID_ADD, 64, 128, 2, 2, 1, 6>(r, p, st); break;
                     case GT_RING160_64: e = launch_ring<EPI_RESID_ADD, 160, 64, 2, 2, 1, 5>(r, p, st); break;
