@@ -78,7 +78,7 @@ struct TileSrc {
 // multiple of 64: a pass is inside the matrix or behind it as a whole, and lies in one block.
 template <int BN, int RPP, bool BLK>
 struct WTileSrc {
-    static constexpr int PASSES = BN / RPP;
+    static constexpr int PASSES = (BN + RPP - 1) / RPP;             // the last pass of a 224-row tile is half empty: out of the range
     static constexpr int kTile = (BLK ? kWBlock * BK : BK) * (int)sizeof(half_t);       // bytes from one k-tile to the next
     static __device__ __forceinline__ int row(int K) { return BLK ? kWBlock : K; }
     int pass[PASSES];
@@ -149,23 +149,25 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
         // bank conflicts of the column-wise writes) the update reads and writes whole 512-byte row segments.  The
         // stages hold BM x CW floats, so the tile goes in PASSES column slabs; a wave tile lies in one slab or is cut into
         // whole slabs.
-        constexpr int LDS_BYTES = 2 * (BM + BN) * BK * (int)sizeof(half_t);
+        constexpr int LDS_BYTES = 2 * (BM + (BN + 63) / 64 * 64) * BK * (int)sizeof(half_t);
         constexpr int PASSES_MIN = (BM * BN * 4 + LDS_BYTES - 1) / LDS_BYTES;
         constexpr int PASSES = PASSES_MIN <= 2 ? PASSES_MIN : (PASSES_MIN <= 4 ? 4 : 8);     // a divisor of BN
         constexpr int CW = BN / PASSES;                 // slab width in columns
         constexpr int CPRW = CW / 4;                    // 16-byte chunks per slab row
-        constexpr int ITER = BM * CPRW / NT;
-        constexpr int NG = ITER == 1 ? 1 : ITER % 4 == 0 ? 4 : ITER % 5 == 0 ? 5 : 2;      // register groups of the x update (320-row tiles: 10 = 5 x 2)
-        constexpr int SWZ = CPRW < 16 ? CPRW - 1 : 15;
-        static_assert(EPI != EPI_RESID_ADD || ((CW % TN == 0 || TN % CW == 0) && (CPRW == 8 || CPRW % 16 == 0) && (BM * CPRW) % (NG * NT) == 0 && BM * CW * 4 <= LDS_BYTES),
-                      "slab shape");
+        constexpr bool POW2 = CPRW == 8 || CPRW % 16 == 0;              // else (112-wide slabs) rows are padded instead of swizzled
+        constexpr int LD = POW2 ? CW : CW + 4;
+        constexpr int ITER = (BM * CPRW + NT - 1) / NT;
+        // register groups of the x update (320-row tiles: 10 = 5 x 2)
+        constexpr int NG = !POW2 ? (ITER + 3) / 4 : ITER == 1 ? 1 : ITER % 4 == 0 ? 4 : ITER % 5 == 0 ? 5 : 2;
+        constexpr int SWZ = !POW2 ? 0 : CPRW < 16 ? CPRW - 1 : 15;
+        static_assert(EPI != EPI_RESID_ADD || ((CW % TN == 0 || TN % CW == 0) && (!POW2 || (BM * CPRW) % (NG * NT) == 0) && BM * LD * 4 <= LDS_BYTES), "slab shape");
         float* stage = (float*)smem;
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) {
             // x in NG groups of G chunks per lane (registers): the first is requested before the stage is written, so
             // its latency hides behind the write and the barrier.  Every address is clamped into the matrix, only
             // valid chunks are written back.
-            constexpr int G = ITER / NG;
+            constexpr int G = POW2 ? ITER / NG : 4;
             floatx4 xv[G];
             auto load_x = [&](int first) {
 #pragma unroll
@@ -186,8 +188,8 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
                     const int row = L / CPRW, pch = L % CPRW;
                     const int col = tile_n0 + p * CW + ((pch ^ (row & SWZ)) << 2);
                     const int64_t grow = tile_m0 + row;
-                    if (grow >= a.M || col >= a.N) continue;        // N is a multiple of 8: whole chunks
-                    *(floatx4*)(a.x + grow * a.N + col) = xv[it] + *(const floatx4*)(stage + row * CW + (pch << 2));
+                    if (grow >= a.M || col >= a.N || (!POW2 && row >= BM)) continue;        // N is a multiple of 8: whole chunks
+                    *(floatx4*)(a.x + grow * a.N + col) = xv[it] + *(const floatx4*)(stage + row * LD + (pch << 2));
                 }
             };
             if (PASSES == 1 && x_pre) {
@@ -207,7 +209,7 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) {
                         const int ch = (c_off + j * 16) >> 2;
-                        *(floatx4*)(stage + lr * CW + ((ch ^ (lr & SWZ)) << 2)) = acc[i][j0 + j];
+                        *(floatx4*)(stage + lr * LD + ((ch ^ (lr & SWZ)) << 2)) = acc[i][j0 + j];
                     }
                 }
             }
@@ -427,12 +429,12 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
     constexpr int TM = BM / WM, TN = BN / WN;      // wave tile
     constexpr int MI = TM / 16, NI = TN / 16;
     constexpr int RPP = NT / 8;                     // rows per loader pass (8 lanes cover one 128-byte k row)
-    constexpr int PA = BM / RPP, PB = BN / RPP;
-    static_assert(RPP % 16 == 0 && BM % RPP == 0 && BN % RPP == 0, "loader shape");
+    constexpr int PA = BM / RPP, PB = (BN + RPP - 1) / RPP, BNP = PB * RPP;
+    static_assert(RPP % 16 == 0 && BM % RPP == 0 && (BN % RPP == 0 || (EPI == EPI_RESID_ADD && !BLK)), "loader shape");
     static_assert(BK == 64 && (SA == 2 || SA == 3), "two k-steps per k-tile");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     half_t* sA = (half_t*)smem;                         // [SA][BM][BK]
-    half_t* sB = sA + SA * BM * BK;                     // [2][BN][BK]
+    half_t* sB = sA + SA * BM * BK;                     // [2][BNP][BK]
 
     // The gate/up launch is persistent: a workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ... (the same
     // XCD-chunked order) and requests the first k-tile of its next tile before it starts the epilogue of the current
@@ -473,7 +475,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
     };
     auto dma_b = [&](int p, int kt, int slot) {
         const int ktw = kt < nkw ? kt : kt - nkw;             // the lo half of a split A meets the same W columns again
-        srcB.load(p, sB + slot * BN * BK + wave * 64 * 8 + p * NT * 8, kt < nk ? vb : kNoLoad, kt < nk ? ktw * srcB.kTile : 0);
+        srcB.load(p, sB + slot * BNP * BK + wave * 64 * 8 + p * NT * 8, kt < nk ? vb : kNoLoad, kt < nk ? ktw * srcB.kTile : 0);
     };
     auto dma_first = [&]() {                                  // k-tile 0 of a tile, into stages 0
 #pragma unroll
@@ -528,7 +530,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
     // scheduling barriers keep a fragment's replacement behind the MFMAs that use it (the same registers) and the
     // memory operations spread.
     auto head = [&](int kt) {
-        const half_t *cA = sA + slot_a * BM * BK, *cB = sB + (kt & 1) * BN * BK;
+        const half_t *cA = sA + slot_a * BM * BK, *cB = sB + (kt & 1) * BNP * BK;
         const int sa2 = slot_a == 0 ? SA - 1 : slot_a - 1;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
@@ -556,7 +558,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
         }
         const int cur = kt & 1, sa_old = slot_a;
         slot_a = slot_a + 1 == SA ? 0 : slot_a + 1;
-        const half_t *nA = sA + slot_a * BM * BK, *nB = sB + (cur ^ 1) * BN * BK;
+        const half_t *nA = sA + slot_a * BM * BK, *nB = sB + (cur ^ 1) * BNP * BK;
         if constexpr (!LAST) {
 #pragma unroll
             for (int r = 0; r < XR; ++r) read_a(r, nA, 0);
@@ -899,7 +901,7 @@ hipError_t launch_tile_of(const GemmArgs& a, hipStream_t st) {
         const int resident = cu_count() * (BM >= 256 ? 1 : 2) / kXcds * kXcds;
         if (resident >= kXcds && grid > resident) grid = resident;
     }
-    const size_t lds = (size_t)(SA * BM + 2 * BN) * BK * sizeof(half_t);
+    constexpr size_t lds = (size_t)(SA * BM + 2 * ((BN + 63) / 64 * 64)) * BK * sizeof(half_t);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA, BLK>, lds, attr_done); e != hipSuccess) return e;
     gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA, BLK><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(a);
@@ -909,6 +911,10 @@ hipError_t launch_tile_of(const GemmArgs& a, hipStream_t st) {
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA>
 hipError_t launch_tile(const GemmArgs& a, const GemmPart& p, hipStream_t st) {
     if (p.bm != BM || p.bn != BN) return hipErrorInvalidValue;      // the choice and the weight walk go by the part's sizes
+    if constexpr (BN == 224) {
+        if (w_blocked(a.N, a.Kw > 0 ? a.Kw : a.K)) return hipErrorInvalidValue;
+        return launch_tile_of<EPI, BM, BN, WM, WN, HB, SA, false>(a, st);
+    } else
     return w_blocked(a.N, a.Kw > 0 ? a.Kw : a.K) ? launch_tile_of<EPI, BM, BN, WM, WN, HB, SA, true>(a, st)
                                                  : launch_tile_of<EPI, BM, BN, WM, WN, HB, SA, false>(a, st);
 }
@@ -1049,7 +1055,9 @@ hipError_t launch_gemm_mfma(GemmEpilogue epi, const GemmArgs& a, hipStream_t st)
                 break;
             case GEMM_RESID:
                 switch (p.tile) {
-                    case GT_BIG: e = launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(r, p, st); break;
+                    case GT_BIG:
+                        e = p.bn == 224 ? launch_tile<EPI_RESID_ADD, 256, 224, 4, 2, 1, 3>(r, p, st) : launch_tile<EPI_RESID_ADD, 256, 256, 2, 4, 1, 3>(r, p, st);
+                        break;
                     case GT_TALL: e = launch_tile<EPI_RESID_ADD, 320, 256, 2, 4, 1, 2>(r, p, st); break;
                     case GT_SMALL: e = launch_tile<EPI_RESID_ADD, 128, 128, 2, 2, 1, 3>(r, p, st); break;
                     case GT_RING128: e = launch_ring<EPI_RESID_ADD, 128, 128, 2, 2, 1, 4>(r, p, st); break;

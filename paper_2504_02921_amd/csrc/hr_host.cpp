@@ -473,6 +473,10 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_, 
     if (kind == GEMM_SWIGLU) { shapes = kSwigluShapes; n_shapes = (int)(sizeof(kSwigluShapes) / sizeof(GemmShape)); }
     if (kind == GEMM_QKV64) { shapes = kQkv64Shapes; n_shapes = (int)(sizeof(kQkv64Shapes) / sizeof(GemmShape)); }
     if (kind == GEMM_QKV128) { shapes = kQkv128Shapes; n_shapes = (int)(sizeof(kQkv128Shapes) / sizeof(GemmShape)); }
+    // 256-row tiles of a residual add are 224 columns wide where as many of them cover N: an eighth fewer products.  They save less,
+    // the 256-wide ones multiply zeros there, which cost no power: 0.5B shape (N = 896), K = 4864, 65536 rows 519 / 499 us, 230 k rows
+    // 1790 / 1771.  320 x 224 tiles spill and are slower (20480 rows, K = 896 58.8 / 65.3 us).  Matrices in blocks of 64 rows do not fit them.
+    const bool narrow = kind == GEMM_RESID && N < kWBlockMin && (N + 223) / 224 == (N + 255) / 256;
     // a round that fills little of the chip still takes three quarters of a full one (a tile's k loop has its length, and only
     // the shared memory system and the clock give way), or 70 % where two tiles share a CU: down projection of the 0.5B shape, 128 x 128
     // tiles, 112 / 350 / 448 of 512 slots 55 / 66 / 72 us, 86 for all
@@ -497,6 +501,7 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_, 
     // 7.4 / 5.7, two rounds (640 rows) 7.7 / 9.7; 8B shape (N = 6144, K = 4096) 128 rows (192 tiles) 31.2 / 26.0, 256 rows 28.1 / 44.3.
     auto part = [&](const GemmShape& s, int64_t rows) {
         const bool qkv = kind == GEMM_QKV64 || kind == GEMM_QKV128;
+        if (s.tile == GT_BIG && narrow) return GemmPart{s.tile, rows, s.bm, 224};
         if (!qkv || s.bm != 64 || (rows + 31) / 32 * ((N + s.bn - 1) / s.bn) > cus) return GemmPart{s.tile, rows, s.bm, s.bn};
         return GemmPart{s.bn == 64 ? GT_RING32_64 : GT_RING32_128, rows, 32, s.bn};
     };

@@ -292,6 +292,13 @@ int main() {
             CHECK(g.n == 1 && g.part[0].tile == p.tile);
         }
     }
+    {   // 256-row residual tiles of 224 columns: the calls of the GPU test, and where 256-wide ones stay (fewer columns, blocked weights)
+        struct Narrow { int64_t M; int N, K, bn; };
+        for (const Narrow& c : {Narrow{6600, 1344, 1792, 224}, Narrow{9900, 832, 2432, 224}, Narrow{16384, 1024, 4864, 256}, Narrow{12288, 4096, 14336, 256}}) {
+            const hr::GemmLaunch g = hr::choose_gemm_launch(hr::GEMM_RESID, c.M, c.N, c.K, 256);
+            CHECK(g.n == 1 && g.part[0].tile == hr::GT_BIG && g.part[0].bm == 256 && g.part[0].bn == c.bn);
+        }
+    }
     {   // attention: whether a block's keys are spread over wavefronts or walked in one chain
         // five pairs of the GPU test that compares the two (most blocks per pair x kv heads x 5, keys, head size), and its whole batch
         struct Spread { int n_kv, blocks, d, keys; };

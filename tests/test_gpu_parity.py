@@ -303,6 +303,15 @@ def test_projection_tiles_for_few_rows_give_a_pair_the_same_bits(d, n_q, n_kv, h
     test_projections_cut_by_rows_give_a_pair_the_same_bits(d, n_q, n_kv, hidden, ffn, n_queries, qlen)
 
 
+@pytest.mark.parametrize("n_q,n_kv,hidden,ffn,n_queries,qlen", [
+    (14, 2, 1344, 1792, 40, (33, 33)),          # down as six columns of 224, the last tile with 200 rows
+    (13, 1, 832, 2432, 60, (33, 33)),           # 9900 rows: down as four columns, the last one with 160; the last tile with 172 rows
+])
+def test_residual_tiles_224_columns_wide_give_a_pair_the_same_bits(n_q, n_kv, hidden, ffn, n_queries, qlen):
+    """256 x 224 tiles (host_asan_driver.cpp pins that these calls take them): the oracle within the bar, and the bits of a pair alone."""
+    test_projections_cut_by_rows_give_a_pair_the_same_bits(64, n_q, n_kv, hidden, ffn, n_queries, qlen)
+
+
 @pytest.mark.parametrize("n_q,n_queries,qlen", [
     (16, 1, (33, 37)),         # all four matrices in blocks of 64 rows (w_elem); residual adds in 64 x 64 tiles, a pair alone in 32 x 32, which read half blocks
     (16, 7, (37, 37)),         # ... in 128 x 128 tiles
