@@ -637,7 +637,7 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 // itself, one wavefront per SIMD, and what counts is the serial length of a k-tile:
 //   * NS k-tiles are requested ahead; vector memory operations complete in order, so "k-tile kt has landed" is a counted wait;
 //   * the fragments of k-tile kt + 1 are read from LDS into a second register set before the MFMAs of k-tile kt issue, so
-//     a k-tile costs one barrier, and neither LDS latency nor the loads sit in front of the matrix pipe.  The barrier that
+//     a k-tile costs one barrier (two k-tiles in deep rings), and neither LDS latency nor the loads sit in front of the matrix pipe.  The barrier that
 //     says k-tile kt + 1 has landed also says that every wave holds k-tile kt in registers: its stage is free for kt + NS.
 // What a k-tile takes in a full round (256 CUs, N = 4096, residual add), 64 x 64 / 160 x 64 / 128 x 128 tiles: operands in the L2s 159-177 /
 // 323 / 410-450 ns; W from HBM 266 / 407 / 514, with the wavefront below 229 / 384 / 496 (16-19 TB/s into the CUs).  The same loop on
@@ -667,6 +667,12 @@ __global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 
     constexpr int PA = BM / RPP, PB = BN / RPP;
     constexpr int KS = BK / 32;
     constexpr int LPT = PA + PB;                    // loads per thread and k-tile
+    // Rings of many stages have one barrier for two k-tiles: behind it both next ones have landed, and the stages of this k-tile and the one
+    // before are free, which are requested into a step later (LAG).  Whole calls, 0.5B shape, without / with: 5 candidates 973 / 965 us (32 x 32
+    // tiles, 7.3 -> 7.1 us a launch), 20 candidates 1517 / 1511, 100 pairs x 4 tokens 1413 / 1404.  With six and seven stages (64 x 128 and
+    // 32 x 128 tiles, W from HBM) it lost: 8B shape, 5 candidates 6090 / 6108.
+    constexpr bool PAIR = NS >= 8;
+    constexpr int LAG = PAIR ? 1 : 0;
     static_assert(RPP % 16 == 0 && BM % RPP == 0 && BN % RPP == 0, "loader shape");
     static_assert(NS >= 2 && (NS - 1) * LPT < 64, "the load counter has six bits");
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -706,8 +712,8 @@ __global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 
             for (int kt = NS; kt < NS + kAhead; ++kt) touch(kt);
             __builtin_amdgcn_s_barrier();
 #pragma unroll 1
-            for (int kt = 0; kt + 1 < nk; ++kt) {     // one barrier per k-tile but the last, as below
-                __builtin_amdgcn_s_barrier();
+            for (int kt = 0; kt + 1 < nk; ++kt) {     // barriers as below
+                if (!PAIR || ((nk - kt) & 1) == 0) __builtin_amdgcn_s_barrier();
                 touch(kt + NS + kAhead);
             }
             __builtin_amdgcn_s_waitcnt(0x0F70);       // nothing is on its way into LDS when the wave ends
@@ -765,16 +771,16 @@ __global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 
 
     // One k-tile, its fragments in (or on their way to) set SET, stage `slot`.  YOUNGER: how many of the k-tiles requested so
     // far come after the next one (their loads may still be outstanding), -1: there is no next one.  request: k-tile
-    // kt + NS is requested into the stage that this k-tile leaves.
+    // kt + NS - LAG is requested into the stage that the k-tile LAG steps before leaves.
     int slot = 0;
     auto step = [&](auto set_c, auto younger_c, auto request_c, int kt) {
         constexpr int SET = decltype(set_c)::value, YOUNGER = decltype(younger_c)::value;
         constexpr bool REQUEST = decltype(request_c)::value;
-        const int next = slot + 1 == NS ? 0 : slot + 1;
-        if constexpr (YOUNGER >= 0) {
+        const int next = slot + 1 == NS ? 0 : slot + 1, free_slot = !PAIR ? slot : slot == 0 ? NS - 1 : slot - 1;
+        if constexpr (YOUNGER >= 0 && (!PAIR || SET == 1)) {
             // the wait is the compiler's to see (its own waits in front of the MFMAs then leave the reads below alone);
             // a __syncthreads() would wait for the loads in flight as well
-            constexpr int V = YOUNGER * LPT;
+            constexpr int V = (YOUNGER > LAG ? YOUNGER - LAG : 0) * LPT;
             __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0070);       // vmcnt(V) lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
@@ -785,8 +791,8 @@ __global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 
         // Requests behind the MFMAs / spread, operands in L2, one k-tile at 2.4 GHz: 64 x 64 415 / 290 cycles, 128 x 128 945 / 593.
         constexpr int NM = KS * MI * NI, ND = KS * (MI + NI);
         const half_t *nA = sA + next * BM * BK, *nB = sB + next * BN * BK;
-        half_t *dA = sA + slot * BM * BK + wave * 64 * 8, *dB = sB + slot * BN * BK + wave * 64 * 8;
-        const int ktn = kt + NS, ka = ktn * (BK * 2), kb = (ktn < nkw ? ktn : ktn - nkw) * srcB.kTile;
+        half_t *dA = sA + free_slot * BM * BK + wave * 64 * 8, *dB = sB + free_slot * BN * BK + wave * 64 * 8;
+        const int ktn = kt + NS - LAG, ka = ktn * (BK * 2), kb = (ktn < nkw ? ktn : ktn - nkw) * srcB.kTile;
         auto read_op = [&](int r) {
             const int rk = r / (MI + NI), f = r % (MI + NI);
             if (f < MI) af[SET ^ 1][rk][f] = *(const halfx8*)(nA + at_a[rk] + f * 16 * BK);
@@ -836,35 +842,36 @@ __global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 
         slot = next;
     };
     using std::integral_constant;
-    constexpr integral_constant<int, (NS - 1) & 1> set_p{};         // sets alternate, counted from the last k-tile (set 0)
-    constexpr integral_constant<int, NS & 1> set_q{};
-    constexpr integral_constant<int, NS - 2> steady{};
+    constexpr int AHEAD = NS - LAG;                                 // k-tiles requested in front of the loop
+    constexpr integral_constant<int, (AHEAD - 1) & 1> set_p{};      // sets alternate, counted from the last k-tile (set 0)
+    constexpr integral_constant<int, AHEAD & 1> set_q{};
+    constexpr integral_constant<int, AHEAD - 2> steady{};
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
+    for (int s = 0; s < AHEAD; ++s)
         if (s < nk) dma(s, s);
-    auto first_landed = [&](auto self, auto r_c) -> void {          // R k-tiles requested behind the first
-        constexpr int R = decltype(r_c)::value;
-        if (R == 0 || nk > R) __builtin_amdgcn_s_waitcnt(((R * LPT) & 15) | (((R * LPT) >> 4) << 14) | 0x0F70);
+    auto first_landed = [&](auto self, auto r_c) -> void {          // R k-tiles requested behind the first, of which LAG are waited for as well
+        constexpr int R = decltype(r_c)::value, V = (R > LAG ? R - LAG : 0) * LPT;
+        if (R == 0 || nk > R) __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0F70);
         else if constexpr (R > 0) self(self, integral_constant<int, R - 1>{});
     };
-    first_landed(first_landed, integral_constant<int, NS - 1>{});
+    first_landed(first_landed, integral_constant<int, AHEAD - 1>{});
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if ((nk - 1) & 1) fload(1, 0);
     else fload(0, 0);
     int kt = 0;
-    if (nk > NS && ((nk - NS) & 1)) step(set_q, steady, std::true_type{}, kt++);
-    for (; kt + NS < nk; kt += 2) {
+    if (nk > AHEAD && ((nk - AHEAD) & 1)) step(set_q, steady, std::true_type{}, kt++);
+    for (; kt + AHEAD < nk; kt += 2) {
         step(set_p, steady, std::true_type{}, kt);
         step(set_q, steady, std::true_type{}, kt + 1);
     }
-    // the last NS k-tiles (all requested): k-tile nk - 1 - R has R - 1 requested ones behind the next
+    // the last AHEAD k-tiles (all requested): k-tile nk - 1 - R has R - 1 requested ones behind the next
     auto tail = [&](auto self, auto r_c) -> void {
         constexpr int R = decltype(r_c)::value;
         if (R < nk) step(integral_constant<int, R & 1>{}, integral_constant<int, R - 1>{}, std::false_type{}, 0);
         if constexpr (R > 0) self(self, integral_constant<int, R - 1>{});
     };
-    tail(tail, integral_constant<int, NS - 1>{});
+    tail(tail, integral_constant<int, AHEAD - 1>{});
     __syncthreads();                               // every wave is done reading the stages before the epilogue reuses them
     gemm_epilogue<EPI, BM, BN, WM, WN, HB, NS>(acc, a, smem, m0, n0, XPRE ? xv : nullptr);
 }
