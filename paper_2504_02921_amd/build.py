@@ -14,9 +14,10 @@ LIB = os.path.join(HERE, "libhyperrerank.so")
 
 SOURCES = ["hr_host.cpp", "hr_engine.hip", "hr_kernels_generic.hip", "hr_f32.hip", "hr_gemm_mfma.hip", "hr_attn_mfma.hip", "hr_attn_rows.hip"]
 
-# packed-fp32 instruction selection is switched off for all device code
+# packed-fp32 instruction selection is switched off for all device code.  Kernarg preload: a kernel's first parameters are in scalar registers when
+# a wavefront starts, where a fetch of them is a trip to memory in every launch
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
-               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16",
                "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
                "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 

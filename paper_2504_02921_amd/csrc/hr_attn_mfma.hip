@@ -64,21 +64,18 @@ struct ItemCtx {
 //   S = K q_hi + K q_lo (+ K_lo q_hi for the pair's own keys),  O = V p_hi + V p_lo (+ V_lo p_hi likewise).
 // Document K/V from the pool are exact as stored.  One wave per SIMD (the extra fragments need the registers).
 template <int HD, int NW, int R, bool FP8, bool PREC>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PREC ? 1 : ((HD == 64 && R == 1 && NW == 8) ? 4 : (HD * R <= 128 ? 2 : 1)), 8))) attn_mfma_kernel(const half_t* __restrict__ q, const char* __restrict__ kv_new,
-                                                           const char* __restrict__ kv_new_lo,
-                                                           half_t* __restrict__ o, MetaView mv, PoolView pv, int layer, int n_q,
-                                                           const int32_t* __restrict__ m_cu, const int32_t* __restrict__ m_prefix,
-                                                           const int32_t* __restrict__ m_pt, const int32_t* __restrict__ m_new_cu,
-                                                           const float* __restrict__ p_scales, int last_only, int n_groups,
-                                                           const int32_t* __restrict__ g_p0, const int32_t* __restrict__ g_blk_cu,
-                                                           const int32_t* __restrict__ g_sub_cu, const int32_t* __restrict__ g_blk_seq,
-                                                           const int32_t* __restrict__ g_blk_row0, const int32_t* __restrict__ g_sub_page,
-                                                           const int32_t* __restrict__ g_sub_seq, const int32_t* __restrict__ g_sub_key0,
-                                                           int n_wg, WeightWalks warm) {
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(PREC ? 1 : ((HD == 64 && R == 1 && NW == 8) ? 4 : (HD * R <= 128 ? 2 : 1)), 8))) attn_mfma_kernel(
+    const int32_t* __restrict__ g_p0, const int32_t* __restrict__ g_blk_cu, const int32_t* __restrict__ g_sub_cu, const int32_t* __restrict__ m_cu,
+    const int32_t* __restrict__ m_prefix, const int32_t* __restrict__ m_pt, int n_groups, int n_wg, const int32_t* __restrict__ m_new_cu,
+    const int32_t* __restrict__ g_blk_seq, const int32_t* __restrict__ g_blk_row0, const int32_t* __restrict__ g_sub_page,
+    const int32_t* __restrict__ g_sub_seq, const int32_t* __restrict__ g_sub_key0, const half_t* __restrict__ q, const char* __restrict__ kv_new,
+    const char* __restrict__ kv_new_lo, half_t* __restrict__ o, MetaView mv, PoolView pv, int layer, int n_q, const float* __restrict__ p_scales,
+    int last_only, WeightWalks warm) {
     // The metadata arrays come as separate read-only, non-aliased parameters so that the per-item lookups (uniform
     // over the workgroup) compile to scalar loads: a vector load that is used right away makes the wave wait for
     // everything it has in flight, including the stage it requested a moment earlier, because vector memory
-    // operations complete in order.
+    // operations complete in order.  The first 14 words of the parameters are in scalar registers when a wavefront starts (kernarg
+    // preload): where its first item is found.
     constexpr int kStageBytes = stage_bytes(FP8);
     using G = Geo<HD, FP8, kStageBytes>;
     using GN = Geo<HD, false, kStageBytes>;          // the pair's own keys are always half
@@ -689,10 +686,9 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
     const int n_wg = std::min(n_items, max_wgs);
     WeightWalks walks;                                              // those of `warm` that the launch has room for
     const int extra = warm ? pick_walks(warm, max_wgs - n_wg, &walks) : 0;
-    attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)(n_wg + extra)), NW * 64, lds, st>>>(q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, mv.cu, mv.prefix_len,
-                                                                                   mv.page_table, mv.new_cu, pv.scales, last_only, gv.n_groups, gv.p0,
-                                                                                   gv.blk_cu, gv.sub_cu, gv.blk_seq, gv.blk_row0, gv.sub_page,
-                                                                                   gv.sub_seq, gv.sub_key0, n_wg, walks);
+    attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)(n_wg + extra)), NW * 64, lds, st>>>(
+        gv.p0, gv.blk_cu, gv.sub_cu, mv.cu, mv.prefix_len, mv.page_table, gv.n_groups, n_wg, mv.new_cu, gv.blk_seq, gv.blk_row0, gv.sub_page,
+        gv.sub_seq, gv.sub_key0, q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, pv.scales, last_only, walks);
     return hipGetLastError();
 }
 

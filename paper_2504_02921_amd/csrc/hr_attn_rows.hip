@@ -61,29 +61,31 @@ struct RowsGeo {
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }      // loads stay in flight
 
 // What a workgroup divides by comes with a multiplier (exact for dividend x divisor below 2^32): a division is 40 instructions
-struct Divisor { int n; unsigned mul; };
-inline Divisor make_divisor(int n) { return {n, n > 1 ? (unsigned)((((uint64_t)1 << 32) + n - 1) / n) : 0u}; }
-__device__ __forceinline__ int divided(int a, Divisor d) { return d.n > 1 ? (int)__umulhi((unsigned)a, d.mul) : a; }
+inline unsigned make_divisor(int n) { return n > 1 ? (unsigned)((((uint64_t)1 << 32) + n - 1) / n) : 0u; }
+__device__ __forceinline__ int divided(int a, unsigned mul) { return mul ? (int)__umulhi((unsigned)a, mul) : a; }
 
+// The first 14 words of the parameters are in scalar registers when a wavefront starts (kernarg preload): what it needs to find its
+// pages.  shape: sequences << 9 | blocks << 1 | last token only.
 template <int HD, bool FP8>
 __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(HD == 64 ? 4 : 2, 8))) attn_rows_kernel(
-    const half_t* __restrict__ q, const char* __restrict__ kv_new, half_t* __restrict__ o, const char* __restrict__ layer_data,
-    const float* __restrict__ layer_scales, int n_seq, int pt_stride, Divisor by_kv, Divisor by_g, const int32_t* __restrict__ m_cu,
-    const int32_t* __restrict__ m_prefix, const int32_t* __restrict__ m_pt, const int32_t* __restrict__ m_new_cu, int last_only, int blocks,
-    int warm_wgs, WeightWalks warm) {
+    const int32_t* __restrict__ m_cu, const int32_t* __restrict__ m_prefix, const int32_t* __restrict__ m_pt, const int32_t* __restrict__ m_new_cu,
+    int pt_stride, int n_kv, unsigned mul_kv, int g, unsigned mul_g, unsigned shape, const half_t* __restrict__ q, const char* __restrict__ kv_new,
+    half_t* __restrict__ o, const char* __restrict__ layer_data, const float* __restrict__ layer_scales, int warm_wgs, WeightWalks warm) {
     using G = RowsGeo<HD>;
     constexpr int KC = HD / 16, KB = G::KB, PAGE = 2 * KB;                        // half pages
     constexpr int KBP = FP8 ? KB / 2 : KB, PAGE_P = 2 * KBP;                      // the pool's
     constexpr int KL = 2 * KB / 1024;                                             // 16-byte loads per lane and sub-tile
     constexpr int NSUB = G::NSUB;
     extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int blocks = shape >> 1 & 0xFF, n_seq = shape >> 9;
+    const bool last_only = shape & 1;
     if ((int)blockIdx.y >= blocks) {                                              // behind the rows' workgroups
         const int first = blocks * (int)gridDim.x, me = (int)(blockIdx.y * gridDim.x + blockIdx.x);
         if (me < first + warm_wgs) warm_weights<kWaves>(warm, me, first, first + warm_wgs, smem);
         return;
     }
-    const int n_kv = by_kv.n, g = by_g.n, row0 = (int)blockIdx.y * 32;
-    const int p = divided((int)blockIdx.x, by_kv), h = (int)blockIdx.x - p * n_kv;
+    const int row0 = (int)blockIdx.y * 32;
+    const int p = divided((int)blockIdx.x, mul_kv), h = (int)blockIdx.x - p * n_kv;
     if (p >= n_seq) return;
     const int t0 = m_cu[p], qn = m_cu[p + 1] - t0, D = m_prefix[p], own_page = m_new_cu[p] >> 4;
     const int M = last_only ? g : qn * g;
@@ -91,11 +93,11 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
     const int lane = threadIdx.x & 63, ln = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_doc = (D + 31) / 32;                                              // sub-tiles of the document
-    const int n_sub = n_doc + (last_only ? qn - 1 : divided(min(row0 + 31, M - 1), by_g)) / 32 + 1;   // ... and of the own keys that some row sees
+    const int n_sub = n_doc + (last_only ? qn - 1 : divided(min(row0 + 31, M - 1), mul_g)) / 32 + 1;   // ... and of the own keys that some row sees
     const int last_page = (D + kPageTokens - 1) / kPageTokens - 1;
     const int32_t* pt = last_page >= 0 ? m_pt + (size_t)p * pt_stride : m_cu;     // no document: read and not used
     const int row = row0 + ln, rc = min(row, M - 1);
-    const int row_i = last_only ? qn - 1 : divided(rc, by_g), head = last_only ? rc : rc - row_i * g;
+    const int row_i = last_only ? qn - 1 : divided(rc, mul_g), head = last_only ? rc : rc - row_i * g;
     const float c_log2 = 1.4426950408889634f / sqrtf((float)HD);
     float* s_max = (float*)(smem + G::MX_AT);                                     // [2][NSUB][32]
     float* s_sum = (float*)(smem + G::SUM_AT);                                    // [NSUB][64]
@@ -363,6 +365,7 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
 template <int HD, bool FP8>
 hipError_t launch_rows(const half_t* q, const char* kv_new, half_t* o, const MetaView& mv, const PoolView& pv, int layer, int n_q,
                        int last_only, int blocks, WeightWalks* warm, hipStream_t st) {
+    if (blocks > 0xFF || mv.n_seq >= 1 << 23) return hipErrorInvalidValue;      // attn_takes_rows is far below
     constexpr int kMaxDevices = 64;
     constexpr int lds = RowsGeo<HD>::LDS;
     static std::atomic<int> max_wgs_dev[kMaxDevices];
@@ -385,9 +388,9 @@ hipError_t launch_rows(const half_t* q, const char* kv_new, half_t* o, const Met
     const int extra = warm ? pick_walks(warm, max_wgs - items * blocks, &walks) : 0;
     const size_t layer_page0 = (size_t)layer * pv.num_pages * pv.n_kv;
     attn_rows_kernel<HD, FP8><<<dim3((unsigned)items, (unsigned)(blocks + (extra + items - 1) / items)), kWaves * 64, lds, st>>>(
-        q, kv_new, o, pv.data + layer_page0 * (2 * kPageTokens * HD * (FP8 ? 1 : 2)), FP8 ? pv.scales + layer_page0 * 2 : nullptr, mv.n_seq,
-        mv.pt_stride, make_divisor(pv.n_kv), make_divisor(n_q / pv.n_kv), mv.cu, mv.prefix_len, mv.page_table, mv.new_cu, last_only, blocks, extra,
-        walks);
+        mv.cu, mv.prefix_len, mv.page_table, mv.new_cu, mv.pt_stride, pv.n_kv, make_divisor(pv.n_kv), n_q / pv.n_kv, make_divisor(n_q / pv.n_kv),
+        (unsigned)mv.n_seq << 9 | (unsigned)blocks << 1 | (unsigned)last_only, q, kv_new, o,
+        pv.data + layer_page0 * (2 * kPageTokens * HD * (FP8 ? 1 : 2)), FP8 ? pv.scales + layer_page0 * 2 : nullptr, extra, walks);
     return hipGetLastError();
 }
 

@@ -42,8 +42,12 @@ __device__ __forceinline__ floatx4 load4(const T* row, int k, int K) {
 // operand, so a lane holds four consecutive columns of one output row and the partial tiles go to LDS as 16-byte words.
 // The k order inside a 16-wide unit is permuted alike on both sides: lane group g holds k = 4 g + j for MFMA j, i.e. one
 // 16-byte load per row and unit.
+// What the loads need comes in front, as parameters of its own: 14 words are in scalar registers when a wavefront starts (kernarg preload).
 template <typename T, F32Epilogue EPI, bool NORM, int MI, int NI>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(F32GemmArgs a) {
+__global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const void* W_, int M_, int N_, int K_, float eps_, const float* gain_,
+                                                       F32GemmArgs rest) {
+    F32GemmArgs a = rest;
+    a.A = A_; a.W = W_; a.M = M_; a.N = N_; a.K = K_; a.eps = eps_; a.gain = gain_;
     constexpr int BM = 16 * MI, BN = 16 * NI, LD = BN + 4;
     constexpr int UN = MI + NI <= 5 ? 4 : 2;       // k-units in flight per wavefront
     __shared__ __attribute__((aligned(16))) float part[2][BM * LD];
@@ -182,7 +186,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(F32GemmArgs a) {
 template <typename T, F32Epilogue EPI, bool NORM, int MI, int NI>
 hipError_t launch_f32_tile(const F32GemmArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)((a.M + 16 * MI - 1) / (16 * MI)), (unsigned)((a.N + 16 * NI - 1) / (16 * NI)));
-    gemm_f32_kernel<T, EPI, NORM, MI, NI><<<grid, 256, 0, st>>>(a);
+    gemm_f32_kernel<T, EPI, NORM, MI, NI><<<grid, 256, 0, st>>>(a.A, a.W, (int)a.M, a.N, a.K, a.eps, a.gain, a);
     return hipGetLastError();
 }
 
@@ -203,16 +207,18 @@ hipError_t launch_f32_shape(const F32GemmArgs& a, hipStream_t st) {
 // words straight from the pages.  8 sequences x 128 + 16 keys, 4 heads: one lane per key with scalar loads took 35 us.
 // Rows are token-major with g heads per token; last_only: the g rows of the last token, written compactly.
 template <int D, int NW>
-__global__ void __launch_bounds__(NW * 64) attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_new,
-                                                           const float* __restrict__ v_new, float* __restrict__ o, MetaView mv,
-                                                           PoolView pv, int layer, int n_q, int last_only, int block0) {
+__global__ void __launch_bounds__(NW * 64) attn_f32_kernel(const int32_t* __restrict__ m_cu, const int32_t* __restrict__ m_prefix,
+                                                           const int32_t* __restrict__ m_pt, int pt_stride, int n_q, int n_kv, int last_only,
+                                                           const float* __restrict__ q, const float* __restrict__ layer_data,
+                                                           const float* __restrict__ k_new, const float* __restrict__ v_new,
+                                                           float* __restrict__ o, int block0) {
     constexpr int CB = D / 16, LD = D + 4;
     __shared__ __attribute__((aligned(16))) float so[NW][16 * LD];
     __shared__ float sml[2][NW][16];
     const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int p = blockIdx.x, h = blockIdx.y, n_kv = pv.n_kv, g = n_q / n_kv;
-    const int t0 = mv.cu[p], q_len = mv.cu[p + 1] - t0, Dl = mv.prefix_len[p];
+    const int p = blockIdx.x, h = blockIdx.y, g = n_q / n_kv;
+    const int t0 = m_cu[p], q_len = m_cu[p + 1] - t0, Dl = m_prefix[p];
     const int row_first = last_only ? (q_len - 1) * g : 0, rows = last_only ? g : q_len * g;
     const int row0 = (block0 + (int)blockIdx.z) * 16;
     if (row0 >= rows) return;
@@ -223,7 +229,7 @@ __global__ void __launch_bounds__(NW * 64) attn_f32_kernel(const float* __restri
 #pragma unroll
     for (int c = 0; c < CB; ++c) qv[c] = *(const floatx4*)(qr + c * 16 + 4 * kg);
     const float scale = 1.0f / sqrtf((float)D);
-    const int32_t* pt = mv.page_table + (size_t)p * mv.pt_stride;
+    const int32_t* pt = m_pt + (size_t)p * pt_stride;
     const int n_pages = (Dl + kPageTokens - 1) / kPageTokens;
     const int tok_last = (row_first + min(row0 + 15, rows - 1)) / g;
     const int n_tiles = n_pages + tok_last / 16 + 1;
@@ -235,7 +241,7 @@ __global__ void __launch_bounds__(NW * 64) attn_f32_kernel(const float* __restri
         floatx4 kv[CB], vv[CB];
         int lim;                                               // key j of the tile is visible where j <= lim
         if (tile < n_pages) {
-            const float* kb = (const float*)pv.data + (((size_t)layer * pv.num_pages + pt[tile]) * n_kv + h) * (2 * kPageTokens * D);
+            const float* kb = layer_data + ((size_t)pt[tile] * n_kv + h) * (2 * kPageTokens * D);
             const float* vb = kb + kPageTokens * D;
             lim = Dl - 1 - tile * 16;
 #pragma unroll
@@ -351,16 +357,21 @@ hipError_t launch_attn_f32(const float* q, const float* k_new, const float* v_ne
     const int64_t rows = last_only ? g : (int64_t)g * max_q_len;
     // one launch as a rule: a grid holds 65535 row blocks in its third dimension
     const int64_t blocks = (rows + 15) / 16;
+    const float* layer_data = (const float*)pv.data + (size_t)layer * pv.num_pages * pv.n_kv * (2 * kPageTokens * pv.d);
+#define HR_ATTN_F32(D)                                                                                                                  \
+    attn_f32_kernel<D, 8><<<grid, 512, 0, st>>>(mv.cu, mv.prefix_len, mv.page_table, mv.pt_stride, n_q, pv.n_kv, last_only, q, layer_data, \
+                                                k_new, v_new, o, (int)b0)
     for (int64_t b0 = 0; b0 < blocks; b0 += 65535) {
         const dim3 grid((unsigned)mv.n_seq, (unsigned)pv.n_kv, (unsigned)std::min<int64_t>(blocks - b0, 65535));
         switch (pv.d) {
-            case 16: attn_f32_kernel<16, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only, (int)b0); break;
-            case 32: attn_f32_kernel<32, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only, (int)b0); break;
-            case 64: attn_f32_kernel<64, 8><<<grid, 512, 0, st>>>(q, k_new, v_new, o, mv, pv, layer, n_q, last_only, (int)b0); break;
+            case 16: HR_ATTN_F32(16); break;
+            case 32: HR_ATTN_F32(32); break;
+            case 64: HR_ATTN_F32(64); break;
             default: return hipErrorInvalidValue;
         }
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
+#undef HR_ATTN_F32
     return hipSuccess;
 }
 

@@ -40,6 +40,20 @@ typedef __attribute__((ext_vector_type(4))) unsigned uint4v;
 
 namespace {
 
+// What a workgroup needs first comes as parameters of its own: up to 14 words in front are in scalar registers when a wavefront starts
+// (kernarg preload), where a struct's are fetched from memory.
+#define HR_GEMM_PARAMS const void *A_, const void *W_, int M_, int N_, int K_, int Kw_, void *out_, const float2 *rope_, const int32_t *slot_, GemmArgs rest_
+#define HR_GEMM_PASS(a) (a).A, (a).W, (int)(a).M, (a).N, (a).K, (a).Kw, EPI == EPI_RESID_ADD ? (void*)(a).x : (a).out0, (a).rope, (a).new_slot, (a)
+#define HR_GEMM_WHOLE gemm_whole<EPI>(A_, W_, M_, N_, K_, Kw_, out_, rope_, slot_, rest_)
+template <int EPI>
+__device__ __forceinline__ GemmArgs gemm_whole(const void* A, const void* W, int M, int N, int K, int Kw, void* out, const float2* rope,
+                                               const int32_t* slot, const GemmArgs& rest) {
+    GemmArgs a = rest;
+    a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.Kw = Kw; a.rope = rope; a.new_slot = slot;
+    if (EPI == EPI_RESID_ADD) a.x = (float*)out;
+    else a.out0 = out;
+    return a;
+}
 constexpr int BK = 64;
 static_assert(kWBlock == BK, "a k-tile of W is whole lines");
 constexpr int kAhead = 8, kAheadLds = 256;       // reading-ahead wavefront of the ring kernel: k-tiles, bytes of LDS
@@ -424,7 +438,8 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
 // Accumulation is transposed (D = W_frag * A_frag^T): a lane owns ONE output row (lane & 15) and 4 consecutive columns
 // per block, so the epilogues address one row pointer per block and store 8 / 16 bytes at a time.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int SA, bool BLK>
-__global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 1) gemm_mfma_kernel(GemmArgs a) {
+__global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 1) gemm_mfma_kernel(HR_GEMM_PARAMS) {
+    GemmArgs a = HR_GEMM_WHOLE;
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;      // wave tile
     constexpr int MI = TM / 16, NI = TN / 16;
@@ -659,7 +674,8 @@ __global__ void __launch_bounds__(WM * WN * 64, WM * WN == 4 && BM <= 128 ? 2 : 
 // Tiles of 96 and 160 rows x 64 (residual adds) fill rounds that the powers of two leave a third empty: 8B down projection, 640
 // rows 128 x 128 (160 tiles) 105.1 -> 160 x 64 (256 tiles) 97.6 us.
 template <int EPI, int BM, int BN, int WM, int WN, int HB, int NS, bool BLK>
-__global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 64, 1) gemm_ring_kernel(GemmArgs a) {
+__global__ void __launch_bounds__((WM * WN + may_read_ahead(BM, BN, WM * WN)) * 64, 1) gemm_ring_kernel(HR_GEMM_PARAMS) {
+    GemmArgs a = HR_GEMM_WHOLE;
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int MI = TM / 16, NI = TN / 16;
@@ -911,7 +927,7 @@ hipError_t launch_tile_of(const GemmArgs& a, hipStream_t st) {
     constexpr size_t lds = (size_t)(SA * BM + 2 * ((BN + 63) / 64 * 64)) * BK * sizeof(half_t);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA, BLK>, lds, attr_done); e != hipSuccess) return e;
-    gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA, BLK><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(a);
+    gemm_mfma_kernel<EPI, BM, BN, WM, WN, HB, SA, BLK><<<dim3((unsigned)grid), WM * WN * 64, lds, st>>>(HR_GEMM_PASS(a));
     return hipGetLastError();
 }
 
@@ -945,7 +961,7 @@ hipError_t launch_ring_of(const GemmArgs& a, hipStream_t st) {
     constexpr size_t ring = (size_t)NS * (BM + BN) * BK * sizeof(half_t), lds_most = ring + (may ? kAheadLds : 0);
     static std::atomic<uint64_t> attr_done{0};
     if (hipError_t e = allow_dynamic_lds(gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS, BLK>, lds_most, attr_done); e != hipSuccess) return e;
-    gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS, BLK><<<dim3((unsigned)grid), (WM * WN + ahead) * 64, ahead ? lds_most : ring, st>>>(a);
+    gemm_ring_kernel<EPI, BM, BN, WM, WN, HB, NS, BLK><<<dim3((unsigned)grid), (WM * WN + ahead) * 64, ahead ? lds_most : ring, st>>>(HR_GEMM_PASS(a));
     return hipGetLastError();
 }
 
