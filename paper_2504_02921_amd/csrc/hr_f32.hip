@@ -42,25 +42,26 @@ __device__ __forceinline__ floatx4 load4(const T* row, int k, int K) {
 // operand, so a lane holds four consecutive columns of one output row and the partial tiles go to LDS as 16-byte words.
 // The k order inside a 16-wide unit is permuted alike on both sides: lane group g holds k = 4 g + j for MFMA j, i.e. one
 // 16-byte load per row and unit.
+// UN: k-units in flight per wavefront.  NG: groups of four wavefronts beside each other, each with NI blocks of the tile's columns: a wavefront's
+// MFMAs (16 x 16 x 4: 32 cycles each) are as long as its loads.
 // What the loads need comes in front, as parameters of its own: 14 words are in scalar registers when a wavefront starts (kernarg preload).
-template <typename T, F32Epilogue EPI, bool NORM, int MI, int NI>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const void* W_, int M_, int N_, int K_, float eps_, const float* gain_,
+template <typename T, F32Epilogue EPI, bool NORM, int MI, int NI, int UN, int NG>
+__global__ void __launch_bounds__(256 * NG) gemm_f32_kernel(const void* A_, const void* W_, int M_, int N_, int K_, float eps_, const float* gain_,
                                                        F32GemmArgs rest) {
     F32GemmArgs a = rest;
     a.A = A_; a.W = W_; a.M = M_; a.N = N_; a.K = K_; a.eps = eps_; a.gain = gain_;
-    constexpr int BM = 16 * MI, BN = 16 * NI, LD = BN + 4;
-    constexpr int UN = MI + NI <= 5 ? 4 : 2;       // k-units in flight per wavefront
+    constexpr int BM = 16 * MI, BN = 16 * NI * NG, LD = BN + 4, NT = 256 * NG;
     __shared__ __attribute__((aligned(16))) float part[2][BM * LD];
     __shared__ float row_ss[4][BM];
     const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3, grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
     const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int n0 = blockIdx.y * BN, K = a.K;
+    const int n0 = blockIdx.y * BN, col0 = 16 * NI * grp, K = a.K;
     const T *pa[MI], *pw[NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i) pa[i] = (const T*)a.A + min(m0 + 16 * i + r, a.M - 1) * K;
 #pragma unroll
-    for (int j = 0; j < NI; ++j) pw[j] = (const T*)a.W + (size_t)min(n0 + 16 * j + r, a.N - 1) * K;
+    for (int j = 0; j < NI; ++j) pw[j] = (const T*)a.W + (size_t)min(n0 + col0 + 16 * j + r, a.N - 1) * K;
     floatx4 acc[MI][NI];
     float ss[MI];
 #pragma unroll
@@ -83,6 +84,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const voi
         }
 #pragma unroll
         for (int s = 0; s < UN; ++s) {
+            if (UN > 4 && u0 + 4 * s >= units) break;
             const int k = (u0 + 4 * s) * 16 + 4 * kg;
 #pragma unroll
             for (int i = 0; i < MI; ++i)
@@ -111,11 +113,11 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const voi
         for (int i = 0; i < MI; ++i) {
             ss[i] += __shfl_xor(ss[i], 16, 64);
             ss[i] += __shfl_xor(ss[i], 32, 64);
-            if (kg == 0) row_ss[wave][16 * i + r] = ss[i];
+            if (kg == 0 && grp == 0) row_ss[wave][16 * i + r] = ss[i];
         }
     }
     float* mine = part[wave & 1];
-    auto at = [&](int i, int j) { return (floatx4*)(mine + (16 * i + r) * LD + 16 * j + 4 * kg); };
+    auto at = [&](int i, int j) { return (floatx4*)(mine + (16 * i + r) * LD + col0 + 16 * j + 4 * kg); };
     if (wave >= 2) {
 #pragma unroll
         for (int i = 0; i < MI; ++i)
@@ -137,7 +139,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const voi
     auto value = [&](int m, int n) { return part[0][m * LD + n] + part[1][m * LD + n]; };
     if constexpr (EPI == F32_STORE || EPI == F32_ADD) {
 #pragma unroll
-        for (int e0 = 0; e0 < BM * BN; e0 += 256) {
+        for (int e0 = 0; e0 < BM * BN; e0 += NT) {
             const int e = e0 + threadIdx.x, m = e / BN, n = e % BN;
             const int64_t row = m0 + m;
             if (row >= a.M || n0 + n >= a.N) continue;
@@ -149,7 +151,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const voi
     } else if constexpr (EPI == F32_ROPE) {        // BN is a multiple of the head size: whole heads per tile
         const int d = a.d, half = d / 2, rot = a.n_q + a.n_kv;
 #pragma unroll
-        for (int e0 = 0; e0 < BM * BN / 2; e0 += 256) {
+        for (int e0 = 0; e0 < BM * BN / 2; e0 += NT) {
             const int e = e0 + threadIdx.x, m = e / (BN / 2), p = e % (BN / 2);
             const int lh = p / half, j = p - lh * half;
             const int64_t row = m0 + m;
@@ -171,7 +173,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const voi
     } else {                                       // F32_SWIGLU: BN is a multiple of a gate block and its up block
         const int F = a.N / 2, ib = a.ib;
 #pragma unroll
-        for (int e0 = 0; e0 < BM * BN / 2; e0 += 256) {
+        for (int e0 = 0; e0 < BM * BN / 2; e0 += NT) {
             const int e = e0 + threadIdx.x, m = e / (BN / 2), fl = e % (BN / 2);
             const int64_t row = m0 + m;
             const int f = n0 / 2 + fl, base = (fl / ib) * 2 * ib + fl % ib;
@@ -183,10 +185,10 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const void* A_, const voi
     }
 }
 
-template <typename T, F32Epilogue EPI, bool NORM, int MI, int NI>
+template <typename T, F32Epilogue EPI, bool NORM, int MI, int NI, int UN, int NG = 1>
 hipError_t launch_f32_tile(const F32GemmArgs& a, hipStream_t st) {
-    const dim3 grid((unsigned)((a.M + 16 * MI - 1) / (16 * MI)), (unsigned)((a.N + 16 * NI - 1) / (16 * NI)));
-    gemm_f32_kernel<T, EPI, NORM, MI, NI><<<grid, 256, 0, st>>>(a.A, a.W, (int)a.M, a.N, a.K, a.eps, a.gain, a);
+    const dim3 grid((unsigned)((a.M + 16 * MI - 1) / (16 * MI)), (unsigned)((a.N + 16 * NI * NG - 1) / (16 * NI * NG)));
+    gemm_f32_kernel<T, EPI, NORM, MI, NI, UN, NG><<<grid, 256 * NG, 0, st>>>(a.A, a.W, (int)a.M, a.N, a.K, a.eps, a.gain, a);
     return hipGetLastError();
 }
 
@@ -195,9 +197,17 @@ hipError_t launch_f32_tile(const F32GemmArgs& a, hipStream_t st) {
 template <typename T, F32Epilogue EPI, bool NORM>
 hipError_t launch_f32_shape(const F32GemmArgs& a, hipStream_t st) {
     const int64_t big = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-    if (big >= 192) return launch_f32_tile<T, EPI, NORM, 4, 4>(a, st);
-    if constexpr (EPI == F32_STORE || EPI == F32_ADD) return launch_f32_tile<T, EPI, NORM, 1, 1>(a, st);
-    else return launch_f32_tile<T, EPI, NORM, 1, 4>(a, st);
+    if (big >= 192) return launch_f32_tile<T, EPI, NORM, 4, 4, 2>(a, st);
+    if constexpr (EPI == F32_STORE || EPI == F32_ADD) {
+        // longer rows than four units a wavefront: twelve in flight (rows to 768 in one go; a pass over K is a trip to memory)
+        if (a.K > 256) return launch_f32_tile<T, EPI, NORM, 1, 1, 12>(a, st);
+        return launch_f32_tile<T, EPI, NORM, 1, 1, 4>(a, st);
+    } else {
+        // two groups of wavefronts where a CU has one workgroup at most: 128 tokens, hidden 256, ffn 688 (96 and 176 workgroups) 7.1 -> 6.5 us a
+        // launch, the call 80 -> 77; 480 tokens (360 and 660) 104 -> 106 us a call
+        if (((a.M + 15) / 16) * ((a.N + 63) / 64) <= device_cu_count()) return launch_f32_tile<T, EPI, NORM, 1, 2, 4, 2>(a, st);
+        return launch_f32_tile<T, EPI, NORM, 1, 4, 4>(a, st);
+    }
 }
 
 // ---- prefix + causal attention of fp32 models.  One workgroup per (sequence, kv head, 16 query rows); its wavefronts take

@@ -40,13 +40,17 @@ __global__ void __launch_bounds__(256) prologue_kernel(const T* __restrict__ E, 
         }
         return;
     }
-    const T* src = E + (size_t)tok_id[b] * H;
-    float* dst = x + (size_t)b * H;
-    for (int c = threadIdx.x; c < H / 4; c += 256) {               // H is a multiple of 8
-        const VecN<T, 4> e = ((const Loose<T, 4>*)src)[c].w;
-        ((float4*)dst)[c] = make_float4(to_float<T>(e[0]), to_float<T>(e[1]), to_float<T>(e[2]), to_float<T>(e[3]));
+    // the last wavefront rotates, the others fetch the embedding: either waits for a word of the token's on its own
+    if (threadIdx.x < 192) {
+        const T* src = E + (size_t)tok_id[b] * H;
+        float* dst = x + (size_t)b * H;
+        for (int c = threadIdx.x; c < H / 4; c += 192) {           // H is a multiple of 8
+            const VecN<T, 4> e = ((const Loose<T, 4>*)src)[c].w;
+            ((float4*)dst)[c] = make_float4(to_float<T>(e[0]), to_float<T>(e[1]), to_float<T>(e[2]), to_float<T>(e[3]));
+        }
+        return;
     }
-    for (int j = threadIdx.x; j < half; j += 256) {
+    for (int j = threadIdx.x - 192; j < half; j += 64) {
         const double inv_freq = pow(base, -(double)j / (double)half);
         const double ang = (double)tok_pos[b] * inv_freq;
         double s, c;
