@@ -442,10 +442,10 @@ __device__ __forceinline__ void flush_range_counts(long long* counters, int over
 
 template <typename KVT, typename KVS>
 __global__ void __launch_bounds__(256) kv_scatter_kernel(KVT* __restrict__ pool, float* __restrict__ scales,
-                                                         PageIdChunk page_ids, int pg0, int doc_len, int n_pages,
+                                                         int pg0, int doc_len, int n_pages,
                                                          const KVS* __restrict__ k, const KVS* __restrict__ v,
                                                          const float* __restrict__ ks, const float* __restrict__ vs,
-                                                         int num_pages, int n_kv, int d, int slabs, long long* __restrict__ counters) {
+                                                         int num_pages, int n_kv, int d, int slabs, long long* __restrict__ counters, PageIdChunk page_ids) {
     __shared__ Word8<KVT> turn[kPageTokens * kSlabLd / 8];
     const int pg = pg0 + blockIdx.x, page = page_ids.ids[blockIdx.x];
     const int layer = blockIdx.y / slabs, slab = blockIdx.y - layer * slabs;
@@ -582,10 +582,9 @@ __global__ void __launch_bounds__(256) pages_to_pool_fp8_kernel(const half_t* __
 }
 
 template <typename KVT>
-__global__ void __launch_bounds__(256) kv_gather_kernel(const KVT* __restrict__ pool, const float* __restrict__ scales, PageIdChunk page_ids,
-                                                        int pg0, int doc_len, int n_pages, KVT* __restrict__ k, KVT* __restrict__ v,
+__global__ void __launch_bounds__(256) kv_gather_kernel(const KVT* __restrict__ pool, const float* __restrict__ scales, int pg0, int doc_len, int n_pages, KVT* __restrict__ k, KVT* __restrict__ v,
                                                         float* __restrict__ ks, float* __restrict__ vs, int num_pages, int n_kv, int d,
-                                                        int slabs) {
+                                                        int slabs, PageIdChunk page_ids) {
     __shared__ Word8<KVT> turn[kPageTokens * kSlabLd / 8];
     const int pg = pg0 + blockIdx.x, page = page_ids.ids[blockIdx.x];
     const int layer = blockIdx.y / slabs, slab = blockIdx.y - layer * slabs;
@@ -644,14 +643,14 @@ hipError_t launch_kv_gather(const PoolLayout& lay, const char* pool_base, const 
         const int slabs = (lay.n_kv * lay.d + kSlab - 1) / kSlab;
         const dim3 grid((unsigned)n, (unsigned)(lay.n_layers * slabs));
         if (lay.kv_dtype == HR_F32)
-            kv_gather_kernel<float><<<grid, 256, 0, st>>>((const float*)pool_base, nullptr, ids, pg0, doc_len, n_pages, (float*)k, (float*)v,
-                                                          nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d, slabs);
+            kv_gather_kernel<float><<<grid, 256, 0, st>>>((const float*)pool_base, nullptr, pg0, doc_len, n_pages, (float*)k, (float*)v,
+                                                          nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d, slabs, ids);
         else if (lay.kv_dtype == HR_BF16)
-            kv_gather_kernel<half_t><<<grid, 256, 0, st>>>((const half_t*)pool_base, nullptr, ids, pg0, doc_len, n_pages, (half_t*)k,
-                                                           (half_t*)v, nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d, slabs);
+            kv_gather_kernel<half_t><<<grid, 256, 0, st>>>((const half_t*)pool_base, nullptr, pg0, doc_len, n_pages, (half_t*)k,
+                                                           (half_t*)v, nullptr, nullptr, lay.num_pages, lay.n_kv, lay.d, slabs, ids);
         else
-            kv_gather_kernel<uint8_t><<<grid, 256, 0, st>>>((const uint8_t*)pool_base, scales, ids, pg0, doc_len, n_pages, (uint8_t*)k,
-                                                            (uint8_t*)v, ks, vs, lay.num_pages, lay.n_kv, lay.d, slabs);
+            kv_gather_kernel<uint8_t><<<grid, 256, 0, st>>>((const uint8_t*)pool_base, scales, pg0, doc_len, n_pages, (uint8_t*)k,
+                                                            (uint8_t*)v, ks, vs, lay.num_pages, lay.n_kv, lay.d, slabs, ids);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -839,17 +838,17 @@ hipError_t launch_kv_scatter(const PoolLayout& lay, char* pool_base, const int32
         const int slabs = (lay.n_kv * lay.d + kSlab - 1) / kSlab;
         const dim3 grid((unsigned)n, (unsigned)(lay.n_layers * slabs));
         if (lay.kv_dtype == HR_F32)
-            kv_scatter_kernel<float, float><<<grid, 256, 0, st>>>((float*)pool_base, nullptr, ids, pg0, doc_len, n_pages,
+            kv_scatter_kernel<float, float><<<grid, 256, 0, st>>>((float*)pool_base, nullptr, pg0, doc_len, n_pages,
                                                            (const float*)k, (const float*)v, nullptr, nullptr, lay.num_pages,
-                                                           lay.n_kv, lay.d, slabs, counters);
+                                                           lay.n_kv, lay.d, slabs, counters, ids);
         else if (lay.kv_dtype == HR_BF16)
-            kv_scatter_kernel<half_t, bf16_t><<<grid, 256, 0, st>>>((half_t*)pool_base, nullptr, ids, pg0, doc_len, n_pages,
+            kv_scatter_kernel<half_t, bf16_t><<<grid, 256, 0, st>>>((half_t*)pool_base, nullptr, pg0, doc_len, n_pages,
                                                               (const bf16_t*)k, (const bf16_t*)v, nullptr, nullptr,
-                                                              lay.num_pages, lay.n_kv, lay.d, slabs, counters);
+                                                              lay.num_pages, lay.n_kv, lay.d, slabs, counters, ids);
         else
-            kv_scatter_kernel<uint8_t, uint8_t><<<grid, 256, 0, st>>>((uint8_t*)pool_base, scales, ids, pg0, doc_len, n_pages,
+            kv_scatter_kernel<uint8_t, uint8_t><<<grid, 256, 0, st>>>((uint8_t*)pool_base, scales, pg0, doc_len, n_pages,
                                                              (const uint8_t*)k, (const uint8_t*)v, ks, vs, lay.num_pages,
-                                                             lay.n_kv, lay.d, slabs, counters);
+                                                             lay.n_kv, lay.d, slabs, counters, ids);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
