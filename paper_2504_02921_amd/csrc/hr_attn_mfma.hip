@@ -38,6 +38,9 @@ namespace {
 // other 32 KiB on the expanded copy of the current stage, so both kinds fit two workgroups per CU.
 constexpr int kStageBytesHalf = 32768;
 constexpr int stage_bytes(bool fp8) { return fp8 ? kStageBytesHalf / 2 : kStageBytesHalf; }
+// Workgroups that read weights ahead (warm_weights), where the work items leave room for them on the chip.  0.5B shape, one query x 20
+// candidates x 32 tokens, whole call: none 1800 us, 64 (twice the bytes each) 1815, 128 1625, 256 1671 (they then share CUs with work items).
+constexpr int kWarmWgs = 128;
 constexpr int kMaxRowsPerWg = 512;
 
 template <int HD, bool FP8, int kStageBytes>
@@ -685,21 +688,17 @@ hipError_t launch_one(const half_t* q, const char* kv_new, const char* kv_new_lo
     const int n_items = (gv.n_groups > 0 ? gv.n_groups : mv.n_seq) * pv.n_kv;
     const int n_wg = std::min(n_items, max_wgs);
     WeightWalks walks;                                              // those of `warm` that the launch has room for
-    const int extra = warm ? pick_walks(warm, max_wgs - n_wg, &walks) : 0;
+    const int extra = warm ? pick_walks(warm, kWarmWgs, max_wgs - n_wg, &walks) : 0;
     attn_mfma_kernel<HD, NW, R, FP8, PREC><<<dim3((unsigned)(n_wg + extra)), NW * 64, lds, st>>>(
         gv.p0, gv.blk_cu, gv.sub_cu, mv.cu, mv.prefix_len, mv.page_table, gv.n_groups, n_wg, mv.new_cu, gv.blk_seq, gv.blk_row0, gv.sub_page,
         gv.sub_seq, gv.sub_key0, q, kv_new, kv_new_lo, o, mv, pv, layer, n_q, pv.scales, last_only, walks);
     return hipGetLastError();
 }
 
-// Workgroups that read weights ahead (warm_weights), where the work items leave room for them on the chip.  0.5B shape, one query x 20
-// candidates x 32 tokens, whole call: none 1800 us, 64 (twice the bytes each) 1815, 128 1625, 256 1671 (they then share CUs with work items).
-constexpr int kWarmWgs = 128;
-
 }  // namespace
 
-int pick_walks(WeightWalks* warm, int free_wgs, WeightWalks* walks) {
-    const int extra = std::min(kWarmWgs, std::max(free_wgs, 0)) / kXcds * kXcds;
+int pick_walks(WeightWalks* warm, int most, int free_wgs, WeightWalks* walks) {
+    const int extra = std::min(most, std::max(free_wgs, 0)) / kXcds * kXcds;
     int64_t bytes[kWarmMost];
     for (int i = 0; i < warm->n; ++i) bytes[i] = (int64_t)warm->w[i].rows * warm->w[i].row_bytes;
     walks->pace = warm->pace;

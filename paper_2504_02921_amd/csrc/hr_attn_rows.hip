@@ -385,7 +385,11 @@ hipError_t launch_rows(const half_t* q, const char* kv_new, half_t* o, const Met
     // a row of workgroups per block: the blocks of a (sequence, kv head) lie on one XCD.  Then those that read weights ahead.
     const int items = (mv.n_seq * pv.n_kv + kXcds - 1) / kXcds * kXcds;
     WeightWalks walks;
-    const int extra = warm ? pick_walks(warm, max_wgs - items * blocks, &walks) : 0;
+    // Workgroups that read weights ahead: this launch is short, and 160 have read them sooner.  Whole calls, 0.5B shape, 128 / 160 / 192: 5 candidates
+    // 960 / 946 / 951 us, 20 candidates 1508 / 1486 / 1491, 23 candidates 1587 / 1549 / 1527; where the keys are many or the codes are to be
+    // expanded they only take from the rows: 20 documents of 2048 tokens 1998 / 2005 / 2012, of 512 in an fp8 pool 1587 / 1591 / 1593.
+    const int most = FP8 || (warm && warm->pace == kWarmPaceMost) ? 128 : 160;
+    const int extra = warm ? pick_walks(warm, most, max_wgs - items * blocks, &walks) : 0;
     const size_t layer_page0 = (size_t)layer * pv.num_pages * pv.n_kv;
     attn_rows_kernel<HD, FP8><<<dim3((unsigned)items, (unsigned)(blocks + (extra + items - 1) / items)), kWaves * 64, lds, st>>>(
         mv.cu, mv.prefix_len, mv.page_table, mv.new_cu, mv.pt_stride, pv.n_kv, make_divisor(pv.n_kv), n_q / pv.n_kv, make_divisor(n_q / pv.n_kv),

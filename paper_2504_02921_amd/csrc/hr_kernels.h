@@ -42,6 +42,7 @@ struct MetaView {
 // (warm_weights).
 // A walk describes one projection's tiles (the order in which its workgroups take them is known), at most kWarmMost of them.
 constexpr int kWarmMost = 4;
+constexpr int kWarmPaceMost = 20;      // WeightWalks::pace: where the sequences have 640 keys and more
 struct WeightWalk {
     const char* W;
     int row_bytes, rows;          // W is [rows][row_bytes]
@@ -163,8 +164,9 @@ hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, co
 // blocks: of the sequence that has the most
 hipError_t launch_attn_rows(const void* q, const void* kv_new_pages, void* o, const MetaView& mv, const PoolView& pv, int layer, int n_q,
                             int blocks, hipStream_t st, bool last_only, WeightWalks* warm);
-// The walks of `warm` that a launch with room for `free_wgs` more workgroups takes, marked in warm->done; how many workgroups read them
-int pick_walks(WeightWalks* warm, int free_wgs, WeightWalks* walks);
+// The walks of `warm` that a launch with room for `free_wgs` more workgroups takes, marked in warm->done; how many workgroups read them, at
+// most `most`
+int pick_walks(WeightWalks* warm, int most, int free_wgs, WeightWalks* walks);
 // fp8 pools: quantising copy of whole pages (amax -> scale -> E4M3 codes per page and kv head) from the half new-KV buffer
 hipError_t launch_pages_to_pool_fp8(const char* kv_new, char* pool_layer_base, float* scales_layer_base, const int32_t* src_page,
                                     const int32_t* dst_page, int n_pages, int n_kv, int d, hipStream_t st);
