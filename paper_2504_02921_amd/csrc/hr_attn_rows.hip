@@ -26,6 +26,7 @@
 #include <atomic>
 
 #include "hr_attn_common.h"
+#include "hr_attn_rows.h"
 #include "hr_device_types.h"
 #include "hr_gemm_tiles.h"
 #include "hr_internal.h"
@@ -42,20 +43,17 @@ typedef const __attribute__((address_space(1))) uint4v* gbl_word_t;
 struct __attribute__((packed, aligned(8))) Word8 { uint4v w; };
 typedef const __attribute__((address_space(1))) Word8* gbl_word8_t;
 
-constexpr int kSWaves = 6, kOWaves = 2, kWaves = kSWaves + kOWaves;
-constexpr int kSPW = 2;              // sub-tiles per S wavefront and round: their S and K stay in registers
+constexpr int kWaves = kRowsWaves;
 
 template <int HD>
 struct RowsGeo {
-    static constexpr int NSUB = kSWaves * kSPW;              // sub-tiles per round
-    static constexpr int V_AHEAD = NSUB / 2;                 // sub-tiles whose V is on its way
+    static constexpr int NSUB = kRoundSubs, V_AHEAD = kVAhead;
     static constexpr int MBW = HD / 32 / kOWaves;            // 32-channel blocks per O wavefront
     static constexpr int KB = kPageTokens * HD * 2;          // bytes of a half page's K (or V) block
     // LDS: P, each S wavefront's K in page order, row maxima (two rounds), row sums, rescaling factors, 256 bytes that nobody reads
     static constexpr int P_AT = 0, K_AT = P_AT + NSUB * 2048, MX_AT = K_AT + kSWaves * 2 * KB, SUM_AT = MX_AT + 2 * NSUB * 128,
                          ALPHA_AT = SUM_AT + NSUB * 256, TOUCH_AT = ALPHA_AT + NSUB * 128,
                          LDS = TOUCH_AT + kSWaves * 256;
-    static_assert(4 * NSUB <= 64, "the pages of two rounds fit one lane each");
 };
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }      // loads stay in flight
@@ -107,7 +105,7 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
     // (finite data, masked), then the own keys'; behind the last sub-tile that one's again
     struct Pages { uint64_t at; float sk, sv; };
     auto load_pages = [&](int round) {                                            // an even one
-        const int pg = 2 * round * NSUB + lane, jj = min(pg >> 1, n_sub - 1), side = pg & 1;
+        const int jj = rows_lane_sub(round, lane, n_sub), side = lane & 1;
         const unsigned id = pt[max(min(2 * jj + side, last_page), 0)];
         const uint64_t doc = (uint64_t)id * (unsigned)(n_kv * PAGE_P) + (uint64_t)(layer_data + h * PAGE_P);
         const uint64_t own = (uint64_t)(unsigned)(own_page + (jj - n_doc) * 2 + side) * (unsigned)(n_kv * PAGE) + (uint64_t)(kv_new + h * PAGE);
@@ -144,8 +142,7 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
         uint4v kr[kSPW][KL];
         auto load_k = [&](const Pages& pg, int round, int i) {                    // the wave's i-th sub-tile of the round
             const int j = wave + kSWaves * i;
-            const int l = 2 * ((round & 1) * NSUB + j);
-            const gbl_char_t a = page_at(pg, l), b = page_at(pg, l + 1);
+            const gbl_char_t a = page_at(pg, rows_page_lane(round, j, 0)), b = page_at(pg, rows_page_lane(round, j, 1));
             const bool doc8 = FP8 && round * NSUB + j < n_doc;                    // half as many bytes: read twice
 #pragma unroll
             for (int e = 0; e < KL; ++e) {
@@ -216,8 +213,8 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
             }
             if (r & 1) follow(ahead, nxt);
 #pragma unroll
-            for (int i = 0; i < kSPW; ++i) load_k(ahead, r + 1, i);
-            if (!(r & 1) && r + 2 < rounds) nxt = load_pages(r + 2);
+            for (int i = 0; i < kSPW; ++i) load_k(ahead, rows_asked(r + 1, rounds), i);
+            if (rows_fetches_pages(r, rounds)) nxt = load_pages(r + 2);
             asm volatile("" ::: "memory");
             lds_barrier();                                                        // the maxima are there; P has been read
             // The running maximum in front of and behind the wave's sub-tiles; it only follows scores that exceed it by more than kLazyMax
@@ -278,14 +275,14 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[mb][e] = 0.f;
     float l_run = 0.f;
-    uint4v vr[G::V_AHEAD][G::MBW][2];                                             // fp8: the first half of each counts
+    uint4v vr[G::V_AHEAD][G::MBW][2];                // fp8: the first half of each counts; the last channel's ends 8 bytes behind its page
     auto load_v = [&](const Pages& pg, int round, int j) {
         const bool doc8 = FP8 && round * NSUB + j < n_doc;
         const int e = (hh * HD + ch0 + ln) * (doc8 ? 8 : 16) + (doc8 ? KBP : KB); // a channel's 8 keys follow each other
         const int step = doc8 ? 32 * 8 : 32 * 16;
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
-            const gbl_char_t at = page_at(pg, 2 * ((round & 1) * NSUB + j) + s2);
+            const gbl_char_t at = page_at(pg, rows_page_lane(round, j, s2));
 #pragma unroll
             for (int mb = 0; mb < G::MBW; ++mb) vr[j % G::V_AHEAD][mb][s2] = ((gbl_word8_t)(at + e + mb * step))->w;
         }
@@ -339,11 +336,11 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
                 }
             }
             if (j < G::V_AHEAD) load_v(cur, r, j + G::V_AHEAD);
-            else load_v(ahead, r + 1, j - G::V_AHEAD);
+            else load_v(ahead, rows_asked(r + 1, rounds), j - G::V_AHEAD);
             asm volatile("" ::: "memory");                                        // the requests stay here, in front of the way out
         }
         if (r & 1) cur = ahead;
-        else if (r + 2 < rounds) nxt = load_pages(r + 2);
+        if (rows_fetches_pages(r, rounds)) nxt = load_pages(r + 2);
         if (n <= NSUB) break;
     }
     const float inv = 1.0f / row_sum2(l_run);

@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <vector>
 
+#include "hr_attn_rows.h"
 #include "hr_gemm_tiles.h"
 #include "hr_internal.h"
 
@@ -310,6 +311,47 @@ int main() {
         CHECK(hr::attn_takes_rows(256, 4, 128, 256, 256) && !hr::attn_takes_rows(257, 4, 128, 4096, 256));
         CHECK(hr::attn_takes_rows(96, 1, 64, 96, 256) && !hr::attn_takes_rows(97, 1, 64, 96, 256));        // short documents
         CHECK(hr::attn_takes_rows(704, 14, 64, 512, 256) && !hr::attn_takes_rows(705, 14, 64, 512, 256));  // two blocks per wavefront in the other
+    }
+    {   // few-rows attention: every request finds the address of the sub-tile whose size it reads (a document's fp8 page is half as long
+        // as an own one), those past the last round too, at every length
+        for (int n_sub = 1; n_sub <= 200; ++n_sub)
+            for (int n_doc = 0; n_doc < n_sub; n_doc += n_doc < n_sub - 4 ? 3 : 1) {      // the last sub-tile holds own keys
+                const int rounds = (n_sub + hr::kRoundSubs - 1) / hr::kRoundSubs;
+                int at = 0;                                                               // the even round whose addresses a wavefront has
+                auto right = [&](int pages, int round, int j) {                           // the kernel's request goes by the round asked for
+                    const int asked = hr::rows_asked(round, rounds), there = std::min(asked * hr::kRoundSubs + j, n_sub - 1);
+                    bool ok = round >= rounds || asked == round;
+                    for (int side = 0; side < 2; ++side) {
+                        const int lane = hr::rows_page_lane(asked, j, side), sub = hr::rows_lane_sub(pages, lane, n_sub);
+                        ok = ok && lane < 64 && (lane & 1) == side && sub == there && (asked * hr::kRoundSubs + j < n_doc) == (sub < n_doc);
+                    }
+                    return ok;
+                };
+                // S wavefronts: K of the next round, requested in every round
+                for (int j = 0; j < hr::kRoundSubs; ++j) CHECK(right(0, 0, j));
+                for (int r = 0, nxt = 0; r < rounds; ++r) {
+                    if (r & 1) at = nxt;
+                    for (int j = 0; j < hr::kRoundSubs; ++j) CHECK(right(at, r + 1, j));
+                    if (hr::rows_fetches_pages(r, rounds)) nxt = r + 2;
+                }
+                // O wavefronts: V, half a round ahead; the last round ends at its half where nothing comes behind it
+                at = 0;
+                for (int j = 0; j < hr::kVAhead; ++j) CHECK(right(0, 0, j));
+                for (int r = 0, nxt = 0, cur = 0; r < rounds; ++r) {
+                    if (r & 1) at = nxt;
+                    for (int j = 0; j < hr::kRoundSubs; ++j) {
+                        if (j == hr::kRoundSubs / 2 && n_sub - r * hr::kRoundSubs <= j) break;
+                        CHECK(j < hr::kVAhead ? right(cur, r, j + hr::kVAhead) : right(at, r + 1, j - hr::kVAhead));
+                    }
+                    if (r & 1) cur = at;
+                    if (hr::rows_fetches_pages(r, rounds)) nxt = r + 2;
+                }
+            }
+        // V of an fp8 page comes in 16-byte requests of which 8 count: behind the pool's last page lie its scales
+        for (int d : {64, 128}) {
+            const hr::PoolLayout lay = hr::make_layout(hr_pool_cfg{1, 1, d, 16, 1, HR_FP8_E4M3});
+            CHECK(lay.total_bytes >= (size_t)2 * 16 * d + 8);
+        }
     }
     {   // weights read ahead by a launch's idle workgroups: never more than they can take, in order, what does not fit left out
         const int64_t q05[] = {896 * 896 * 2, 9728 * 896 * 2, 896 * 4864 * 2, 1152 * 896 * 2};      // O, gate / up, down, QKV of the 0.5B shape
