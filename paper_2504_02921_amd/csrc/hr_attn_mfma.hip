@@ -735,8 +735,8 @@ hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, co
     if (mv.n_seq == 0) return hipSuccess;
     const GroupView gv = groups && !last_only ? *groups : GroupView{};
     const int seq_blocks = (n_q / pv.n_kv * (last_only ? 1 : max_q_len) + 31) / 32;
-    if (!kv_new_lo_pages && attn_takes_rows((int64_t)mv.n_seq * pv.n_kv * seq_blocks, gv.n_groups > 0 ? gv.max_blocks : seq_blocks, pv.d, max_keys,
-                                            device_cu_count()))
+    if (!kv_new_lo_pages &&
+        attn_call_takes_rows(mv.n_seq, pv.n_kv, seq_blocks, gv.n_groups > 0 ? gv.max_blocks : seq_blocks, pv.d, max_keys, device_cu_count()))
         return launch_attn_rows(q, kv_new_pages, o, mv, pv, layer, n_q, seq_blocks, st, last_only, warm);
     const int rows = gv.n_groups > 0 ? gv.max_blocks * 32 : n_q / pv.n_kv * (last_only ? 1 : max_q_len);
     if (rows > kMaxRowsPerWg) return hipErrorInvalidValue;

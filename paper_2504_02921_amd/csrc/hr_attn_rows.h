@@ -28,4 +28,7 @@ HR_HD bool rows_fetches_pages(int r, int rounds) { return !(r & 1) && r + 2 < ro
 // (fetching the next pair's for it, 20 candidates of 512 + 32 keys, 0.5B shape: 1494 -> 1511 us a call)
 HR_HD int rows_asked(int round, int rounds) { return round == rounds && !(rounds & 1) ? round - 2 : round; }
 
+// sequences << 9 | blocks << 1 | last token only: one parameter word of the kernel.  A call that it does not hold stays with the chain kernel.
+HR_HD bool rows_holds(int64_t n_seq, int64_t blocks) { return n_seq < (1 << 23) && blocks <= 0xFF; }
+
 }  // namespace hr

@@ -63,7 +63,7 @@ inline unsigned make_divisor(int n) { return n > 1 ? (unsigned)((((uint64_t)1 <<
 __device__ __forceinline__ int divided(int a, unsigned mul) { return mul ? (int)__umulhi((unsigned)a, mul) : a; }
 
 // The first 14 words of the parameters are in scalar registers when a wavefront starts (kernarg preload): what it needs to find its
-// pages.  shape: sequences << 9 | blocks << 1 | last token only.
+// pages.  shape: see rows_holds.
 template <int HD, bool FP8>
 __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(HD == 64 ? 4 : 2, 8))) attn_rows_kernel(
     const int32_t* __restrict__ m_cu, const int32_t* __restrict__ m_prefix, const int32_t* __restrict__ m_pt, const int32_t* __restrict__ m_new_cu,
@@ -362,7 +362,7 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
 template <int HD, bool FP8>
 hipError_t launch_rows(const half_t* q, const char* kv_new, half_t* o, const MetaView& mv, const PoolView& pv, int layer, int n_q,
                        int last_only, int blocks, WeightWalks* warm, hipStream_t st) {
-    if (blocks > 0xFF || mv.n_seq >= 1 << 23) return hipErrorInvalidValue;      // attn_takes_rows is far below
+    if (!rows_holds(mv.n_seq, blocks)) return hipErrorInvalidValue;
     constexpr int kMaxDevices = 64;
     constexpr int lds = RowsGeo<HD>::LDS;
     static std::atomic<int> max_wgs_dev[kMaxDevices];

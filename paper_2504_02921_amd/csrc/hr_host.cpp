@@ -6,6 +6,7 @@
 #include <initializer_list>
 #include <new>
 
+#include "hr_attn_rows.h"
 #include "hr_internal.h"
 
 namespace hr {
@@ -533,6 +534,10 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_, 
 bool attn_takes_rows(int64_t blocks, int item_blocks, int head_dim, int max_keys, int cus) {
     const int64_t most = std::min(max_keys, head_dim == 64 ? cus * 11 / 8 : cus);
     return blocks <= most * (item_blocks > 4 ? 2 : 1);
+}
+
+bool attn_call_takes_rows(int64_t n_seq, int n_kv, int seq_blocks, int item_blocks, int head_dim, int max_keys, int cus) {
+    return rows_holds(n_seq, seq_blocks) && attn_takes_rows(n_seq * n_kv * seq_blocks, item_blocks, head_dim, max_keys, cus);
 }
 
 unsigned pick_weight_walks(const int64_t* bytes, int n, int wgs) {

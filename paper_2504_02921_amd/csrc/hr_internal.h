@@ -172,6 +172,8 @@ size_t group_plan_ints_bound(int64_t n_seq, int64_t T, int g);
 // 1905; 560 blocks, 544 keys 2110 / 2344.  Prefill (items of 14 blocks): 224 blocks, 512 keys 1862 / 1529, 448 blocks 2238 / 1970, 896
 // blocks 2941 / 2998.  8B shape (one workgroup per CU): 256 blocks, 288 keys 6694 / 6538; 288 blocks 8196 / 8284; 640 blocks 10267 / 10530.
 bool attn_takes_rows(int64_t blocks, int item_blocks, int head_dim, int max_keys, int cus);
+// ... and whether a call of n_seq sequences of up to seq_blocks blocks per kv head does: if its shape fits that kernel's parameters
+bool attn_call_takes_rows(int64_t n_seq, int n_kv, int seq_blocks, int item_blocks, int head_dim, int max_keys, int cus);
 
 // ---- how an M x N x K MFMA GEMM is launched on a device of `cus` compute units: as one or two launches over consecutive row
 // ranges, each with a tile shape of the epilogue's list.  With M x N outputs spread over the CUs the last round of tiles is what

@@ -19,7 +19,7 @@
 #include "hr_internal.h"
 
 #if defined(__HIPCC__)
-#define HR_HD __host__ __device__ __forceinline__
+#define HR_HD __host__ __device__ inline __attribute__((always_inline))
 #else
 #define HR_HD inline
 #endif

@@ -312,6 +312,11 @@ int main() {
         CHECK(hr::attn_takes_rows(96, 1, 64, 96, 256) && !hr::attn_takes_rows(97, 1, 64, 96, 256));        // short documents
         CHECK(hr::attn_takes_rows(704, 14, 64, 512, 256) && !hr::attn_takes_rows(705, 14, 64, 512, 256));  // two blocks per wavefront in the other
     }
+    {   // ... and a call whose shape the spread kernel's parameters cannot hold keeps to the chain, whatever a query may be cut into
+        CHECK(hr::attn_call_takes_rows(1, 1, 255, 16, 64, 4096, 256) && !hr::attn_call_takes_rows(1, 1, 256, 16, 64, 4096, 256));
+        CHECK(hr::attn_call_takes_rows(5, 2, 16, 16, 64, 2150, 256) && !hr::attn_call_takes_rows(880, 2, 16, 16, 64, 2150, 256));
+        CHECK(hr::rows_holds((1 << 23) - 1, 255) && !hr::rows_holds(1 << 23, 1) && !hr::rows_holds(1, 256));
+    }
     {   // few-rows attention: every request finds the address of the sub-tile whose size it reads (a document's fp8 page is half as long
         // as an own one), those past the last round too, at every length
         for (int n_sub = 1; n_sub <= 200; ++n_sub)
