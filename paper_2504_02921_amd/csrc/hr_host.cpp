@@ -532,8 +532,9 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_, 
 }
 
 bool attn_takes_rows(int64_t blocks, int item_blocks, int head_dim, int max_keys, int cus) {
-    const int64_t most = std::min(max_keys, head_dim == 64 ? cus * 11 / 8 : cus);
-    return blocks <= most * (item_blocks > 4 ? 2 : 1);
+    if (head_dim == 64) return blocks <= (int64_t)std::min(max_keys, cus * 11 / 8) * (item_blocks > 4 ? 2 : 1);
+    if (item_blocks <= 4 || blocks <= cus) return blocks <= std::min((int64_t)max_keys * (item_blocks > 4 ? 2 : 1), (int64_t)cus);
+    return blocks <= std::min((int64_t)max_keys * 3 / 2, (int64_t)cus * 7 / 4);
 }
 
 bool attn_call_takes_rows(int64_t n_seq, int n_kv, int seq_blocks, int item_blocks, int head_dim, int max_keys, int cus) {

@@ -165,12 +165,16 @@ size_t group_plan_ints_bound(int64_t n_seq, int64_t T, int g);
 // Whether an attention launch of `blocks` 32-row blocks (all sequences and kv heads together) goes to the kernel that spreads a block's keys over
 // a workgroup's wavefronts (hr_attn_rows.hip) instead of walking them in one chain.  item_blocks: blocks of the largest work item
 // of the other kernel.
-// It saves the length of the chain, which grows with the keys and is twice as long where a wavefront has two blocks (more than four in an item);
-// it costs a workgroup per block, and more blocks than are resident wait for the first.  Whole calls, one chain / spread: 0.5B
+// It saves the length of the chain, which grows with the keys and is twice as long where a wavefront has two blocks (64-wide heads, more than
+// four in an item); it costs a workgroup per block, and more blocks than are resident wait for the first.  Whole calls, one chain / spread: 0.5B
 // shape, 30 blocks, 100-300 keys 1100 / 1003 us; 200 blocks, 304 keys 1503 / 1453; 280 blocks, 544 keys 1605 / 1565, 2080 keys 2277 /
 // 2061; 350 blocks, 544 keys 1875 / 1814; but 140 blocks, 96 keys 1262 / 1275; 280 blocks, 160 keys 1460 / 1511; 400 blocks, 520 keys 1888 /
 // 1905; 560 blocks, 544 keys 2110 / 2344.  Prefill (items of 14 blocks): 224 blocks, 512 keys 1862 / 1529, 448 blocks 2238 / 1970, 896
 // blocks 2941 / 2998.  8B shape (one workgroup per CU): 256 blocks, 288 keys 6694 / 6538; 288 blocks 8196 / 8284; 640 blocks 10267 / 10530.
+// Items of 5 to 8 blocks are eight wavefronts of one block there, two on a SIMD: up to a round of workgroups as with two blocks each, behind it
+// only where the keys are as many.  Prefill of one 8B document of 65 tokens 4954 / 4840 us, 250 6620 / 6403, of 304 7505 / 7430, 376 8188 /
+// 8063, 448 8547 / 8513, but 470 (512 blocks) 8644 / 8707, 512 8795 / 8853; two of 128 (256 blocks) 6505 / 6388, of 192 (384) 8098 / 8154, of 256 (512)
+// 8566 / 8623.
 bool attn_takes_rows(int64_t blocks, int item_blocks, int head_dim, int max_keys, int cus);
 // ... and whether a call of n_seq sequences of up to seq_blocks blocks per kv head does: if its shape fits that kernel's parameters
 bool attn_call_takes_rows(int64_t n_seq, int n_kv, int seq_blocks, int item_blocks, int head_dim, int max_keys, int cus);

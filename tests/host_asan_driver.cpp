@@ -312,6 +312,17 @@ int main() {
         CHECK(hr::attn_takes_rows(96, 1, 64, 96, 256) && !hr::attn_takes_rows(97, 1, 64, 96, 256));        // short documents
         CHECK(hr::attn_takes_rows(704, 14, 64, 512, 256) && !hr::attn_takes_rows(705, 14, 64, 512, 256));  // two blocks per wavefront in the other
     }
+    {   // ... 128-wide heads, items of 5 to 8 blocks (documents in chunks of 64 tokens).  A round of workgroups: one document of 65 or of 250 tokens,
+        // two of 128, not three of 64
+        CHECK(hr::attn_call_takes_rows(2, 8, 8, 8, 128, 65, 256) && hr::attn_call_takes_rows(4, 8, 8, 8, 128, 250, 256));
+        CHECK(hr::attn_call_takes_rows(4, 8, 8, 8, 128, 128, 256) && !hr::attn_call_takes_rows(3, 8, 8, 8, 128, 64, 256));
+        // more: one document of 264 to 448 tokens, not of 449 (eight chunks), nor two of 192 or of 256
+        CHECK(hr::attn_call_takes_rows(5, 8, 8, 8, 128, 264, 256) && hr::attn_call_takes_rows(6, 8, 8, 8, 128, 376, 256));
+        CHECK(hr::attn_call_takes_rows(7, 8, 8, 8, 128, 448, 256) && !hr::attn_call_takes_rows(8, 8, 8, 8, 128, 449, 256));
+        CHECK(!hr::attn_call_takes_rows(6, 8, 8, 8, 128, 192, 256) && !hr::attn_call_takes_rows(8, 8, 8, 8, 128, 256, 256));
+        CHECK(hr::attn_takes_rows(256, 8, 128, 128, 256) && !hr::attn_takes_rows(257, 8, 128, 171, 256) && hr::attn_takes_rows(257, 8, 128, 172, 256));
+        CHECK(hr::attn_takes_rows(448, 8, 128, 4096, 256) && !hr::attn_takes_rows(449, 8, 128, 4096, 256));
+    }
     {   // ... and a call whose shape the spread kernel's parameters cannot hold keeps to the chain, whatever a query may be cut into
         CHECK(hr::attn_call_takes_rows(1, 1, 255, 16, 64, 4096, 256) && !hr::attn_call_takes_rows(1, 1, 256, 16, 64, 4096, 256));
         CHECK(hr::attn_call_takes_rows(5, 2, 16, 16, 64, 2150, 256) && !hr::attn_call_takes_rows(880, 2, 16, 16, 64, 2150, 256));
