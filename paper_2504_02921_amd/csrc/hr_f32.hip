@@ -42,8 +42,10 @@ __device__ __forceinline__ floatx4 load4(const T* row, int k, int K) {
 // operand, so a lane holds four consecutive columns of one output row and the partial tiles go to LDS as 16-byte words.
 // The k order inside a 16-wide unit is permuted alike on both sides: lane group g holds k = 4 g + j for MFMA j, i.e. one
 // 16-byte load per row and unit.
-// UN: k-units in flight per wavefront.  NG: groups of four wavefronts beside each other, each with NI blocks of the tile's columns: a wavefront's
-// MFMAs (16 x 16 x 4: 32 cycles each) are as long as its loads.
+// UN: k-units of one pass of a wavefront's k loop.  The compiler puts a unit's loads in front of its MFMAs whatever their place here: one unit is
+// in flight, and a unit is a trip to memory.
+// NG: groups of four wavefronts beside each other, each with NI blocks of the tile's columns: a wavefront's MFMAs (16 x 16 x 4: 32 cycles
+// each) are as long as its loads.
 // What the loads need comes in front, as parameters of its own: 14 words are in scalar registers when a wavefront starts (kernarg preload).
 template <typename T, F32Epilogue EPI, bool NORM, int MI, int NI, int UN, int NG>
 __global__ void __launch_bounds__(256 * NG) gemm_f32_kernel(const void* A_, const void* W_, int M_, int N_, int K_, float eps_, const float* gain_,
@@ -84,7 +86,6 @@ __global__ void __launch_bounds__(256 * NG) gemm_f32_kernel(const void* A_, cons
         }
 #pragma unroll
         for (int s = 0; s < UN; ++s) {
-            if (UN > 4 && u0 + 4 * s >= units) break;
             const int k = (u0 + 4 * s) * 16 + 4 * kg;
 #pragma unroll
             for (int i = 0; i < MI; ++i)
@@ -199,12 +200,10 @@ hipError_t launch_f32_shape(const F32GemmArgs& a, hipStream_t st) {
     const int64_t big = ((a.M + 63) / 64) * ((a.N + 63) / 64);
     if (big >= 192) return launch_f32_tile<T, EPI, NORM, 4, 4, 2>(a, st);
     if constexpr (EPI == F32_STORE || EPI == F32_ADD) {
-        // longer rows than four units a wavefront: twelve in flight (rows to 768 in one go; a pass over K is a trip to memory)
-        if (a.K > 256) return launch_f32_tile<T, EPI, NORM, 1, 1, 12>(a, st);
         return launch_f32_tile<T, EPI, NORM, 1, 1, 4>(a, st);
     } else {
         // two groups of wavefronts where a CU has one workgroup at most: 128 tokens, hidden 256, ffn 688 (96 and 176 workgroups) 7.1 -> 6.5 us a
-        // launch, the call 80 -> 77; 480 tokens (360 and 660) 104 -> 106 us a call
+        // launch, the call 71.4 -> 69.1; 480 tokens (360 and 660) 104 -> 106 us a call
         if (((a.M + 15) / 16) * ((a.N + 63) / 64) <= device_cu_count()) return launch_f32_tile<T, EPI, NORM, 1, 2, 4, 2>(a, st);
         return launch_f32_tile<T, EPI, NORM, 1, 4, 4>(a, st);
     }

@@ -71,12 +71,12 @@ def test_fp32_projection_tiles_give_a_pair_the_same_bits_alone_and_in_a_batch(n_
 
 
 @pytest.mark.parametrize("n_q,n_kv,d,hidden,ffn,n_queries", [
-    (4, 4, 64, 256, 264, 3),         # down: a row of 264, one unit behind the first four of a wavefront
-    (4, 2, 32, 136, 776, 2),         # 776: a second pass behind twelve units; gate / up with a last tile of 16 columns
-    (2, 2, 64, 264, 768, 9),         # O and down with twelve units in flight; more tiles than CUs in the batch, fewer for a pair alone
+    (4, 4, 64, 256, 264, 3),         # down: a row of 264, a second pass of one unit for one wavefront
+    (4, 2, 32, 136, 776, 2),         # 776: a fourth pass of one unit; gate / up with a last tile of 16 columns
+    (2, 2, 64, 264, 768, 9),         # three whole passes; more tiles than CUs in the batch, fewer for a pair alone
 ])
 def test_fp32_long_rows_and_column_groups(n_q, n_kv, d, hidden, ffn, n_queries):
-    """Rows longer than 256 (twelve k-units in flight) and the two column groups of small launches."""
+    """Rows longer than one pass of the k loop (four units of 16 for each of four wavefronts) and the two column groups of small launches."""
     test_fp32_projection_tiles_give_a_pair_the_same_bits_alone_and_in_a_batch(n_q, n_kv, d, hidden, ffn, n_queries)
 
 
