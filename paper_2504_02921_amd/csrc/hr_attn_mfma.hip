@@ -737,7 +737,7 @@ hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, co
     const int seq_blocks = (n_q / pv.n_kv * (last_only ? 1 : max_q_len) + 31) / 32;
     if (!kv_new_lo_pages &&
         attn_call_takes_rows(mv.n_seq, pv.n_kv, seq_blocks, gv.n_groups > 0 ? gv.max_blocks : seq_blocks, pv.d, max_keys, device_cu_count()))
-        return launch_attn_rows(q, kv_new_pages, o, mv, pv, layer, n_q, seq_blocks, st, last_only, warm);
+        return launch_attn_rows(q, kv_new_pages, o, mv, pv, layer, n_q, seq_blocks, max_keys, st, last_only, warm);
     const int rows = gv.n_groups > 0 ? gv.max_blocks * 32 : n_q / pv.n_kv * (last_only ? 1 : max_q_len);
     if (rows > kMaxRowsPerWg) return hipErrorInvalidValue;
     const half_t* qh = (const half_t*)q;

@@ -31,4 +31,10 @@ HR_HD int rows_asked(int round, int rounds) { return round == rounds && !(rounds
 // sequences << 9 | blocks << 1 | last token only: one parameter word of the kernel.  A call that it does not hold stays with the chain kernel.
 HR_HD bool rows_holds(int64_t n_seq, int64_t blocks) { return n_seq < (1 << 23) && blocks <= 0xFF; }
 
+// Workgroups that read weights ahead: the launch is short, and 160 have read them sooner.  Whole calls, 0.5B shape, 128 / 160 / 192: 5 candidates
+// 960 / 946 / 951 us, 20 candidates 1508 / 1486 / 1491, 23 candidates 1587 / 1549 / 1527; where the keys of the longest sequence are many or the
+// codes are to be expanded they only take from the rows: 20 documents of 2048 tokens 1998 / 2005 / 2012, of 512 in an fp8 pool 1587 / 1591 / 1593.
+constexpr int kRowsManyKeys = 640;
+HR_HD int rows_warm_wgs(int max_keys, bool fp8) { return fp8 || max_keys >= kRowsManyKeys ? 128 : 160; }
+
 }  // namespace hr

@@ -361,7 +361,7 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
 
 template <int HD, bool FP8>
 hipError_t launch_rows(const half_t* q, const char* kv_new, half_t* o, const MetaView& mv, const PoolView& pv, int layer, int n_q,
-                       int last_only, int blocks, WeightWalks* warm, hipStream_t st) {
+                       int last_only, int blocks, int max_keys, WeightWalks* warm, hipStream_t st) {
     if (!rows_holds(mv.n_seq, blocks)) return hipErrorInvalidValue;
     constexpr int kMaxDevices = 64;
     constexpr int lds = RowsGeo<HD>::LDS;
@@ -382,11 +382,7 @@ hipError_t launch_rows(const half_t* q, const char* kv_new, half_t* o, const Met
     // a row of workgroups per block: the blocks of a (sequence, kv head) lie on one XCD.  Then those that read weights ahead.
     const int items = (mv.n_seq * pv.n_kv + kXcds - 1) / kXcds * kXcds;
     WeightWalks walks;
-    // Workgroups that read weights ahead: this launch is short, and 160 have read them sooner.  Whole calls, 0.5B shape, 128 / 160 / 192: 5 candidates
-    // 960 / 946 / 951 us, 20 candidates 1508 / 1486 / 1491, 23 candidates 1587 / 1549 / 1527; where the keys are many or the codes are to be
-    // expanded they only take from the rows: 20 documents of 2048 tokens 1998 / 2005 / 2012, of 512 in an fp8 pool 1587 / 1591 / 1593.
-    const int most = FP8 || (warm && warm->pace == kWarmPaceMost) ? 128 : 160;
-    const int extra = warm ? pick_walks(warm, most, max_wgs - items * blocks, &walks) : 0;
+    const int extra = warm ? pick_walks(warm, rows_warm_wgs(max_keys, FP8), max_wgs - items * blocks, &walks) : 0;
     const size_t layer_page0 = (size_t)layer * pv.num_pages * pv.n_kv;
     attn_rows_kernel<HD, FP8><<<dim3((unsigned)items, (unsigned)(blocks + (extra + items - 1) / items)), kWaves * 64, lds, st>>>(
         mv.cu, mv.prefix_len, mv.page_table, mv.new_cu, mv.pt_stride, pv.n_kv, make_divisor(pv.n_kv), n_q / pv.n_kv, make_divisor(n_q / pv.n_kv),
@@ -398,17 +394,17 @@ hipError_t launch_rows(const half_t* q, const char* kv_new, half_t* o, const Met
 }  // namespace
 
 hipError_t launch_attn_rows(const void* q, const void* kv_new_pages, void* o, const MetaView& mv, const PoolView& pv, int layer, int n_q,
-                            int blocks, hipStream_t st, bool last_only, WeightWalks* warm) {
+                            int blocks, int max_keys, hipStream_t st, bool last_only, WeightWalks* warm) {
     const half_t* qh = (const half_t*)q;
     const char* kvn = (const char*)kv_new_pages;
     half_t* oh = (half_t*)o;
     const bool fp8 = pv.kv_dtype == HR_FP8_E4M3;
     const int lo = last_only ? 1 : 0;
     if (pv.d == 64)
-        return fp8 ? launch_rows<64, true>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, warm, st)
-                   : launch_rows<64, false>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, warm, st);
-    return fp8 ? launch_rows<128, true>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, warm, st)
-               : launch_rows<128, false>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, warm, st);
+        return fp8 ? launch_rows<64, true>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, max_keys, warm, st)
+                   : launch_rows<64, false>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, max_keys, warm, st);
+    return fp8 ? launch_rows<128, true>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, max_keys, warm, st)
+               : launch_rows<128, false>(qh, kvn, oh, mv, pv, layer, n_q, lo, blocks, max_keys, warm, st);
 }
 
 }  // namespace hr

@@ -70,7 +70,7 @@ constexpr int64_t kWarmMaxTokens = 4096;
 // the attention of short ones.  One pause of 64 cycles per 32 keys of the longest sequence, 20 at most.  Whole calls, 0.5B shape, none /
 // 16 / 30 / by this rule: 640 tokens, documents of 64 tokens 1461 / 1539 / 1731 / 1451 us, of 512 tokens 1640 / 1630 / 1740 / 1614; 1200
 // tokens, documents of 512 tokens 2242 / 2148 / 2312 / 2116.
-constexpr int kWarmPaceKeys = 32;
+constexpr int kWarmPaceMost = 20, kWarmPaceKeys = 32;
 constexpr size_t kSplitSlackBytes = (size_t)1 << 20;   // what two carvings of a workspace may need beyond one (alignment gaps,
                                                        // the larger group-plan room of calls with few pairs)
 

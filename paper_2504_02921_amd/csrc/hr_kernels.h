@@ -42,7 +42,6 @@ struct MetaView {
 // (warm_weights).
 // A walk describes one projection's tiles (the order in which its workgroups take them is known), at most kWarmMost of them.
 constexpr int kWarmMost = 4;
-constexpr int kWarmPaceMost = 20;      // WeightWalks::pace: where the sequences have 640 keys and more
 struct WeightWalk {
     const char* W;
     int row_bytes, rows;          // W is [rows][row_bytes]
@@ -163,7 +162,7 @@ hipError_t launch_attn_mfma(const void* q, const void* kv_new_pages, void* o, co
 // The form for launches of few 32-row blocks (hr_attn_rows.hip; launch_attn_mfma hands them on, see attn_takes_rows): the same bits.
 // blocks: of the sequence that has the most
 hipError_t launch_attn_rows(const void* q, const void* kv_new_pages, void* o, const MetaView& mv, const PoolView& pv, int layer, int n_q,
-                            int blocks, hipStream_t st, bool last_only, WeightWalks* warm);
+                            int blocks, int max_keys, hipStream_t st, bool last_only, WeightWalks* warm);
 // The walks of `warm` that a launch with room for `free_wgs` more workgroups takes, marked in warm->done; how many workgroups read them, at
 // most `most`
 int pick_walks(WeightWalks* warm, int most, int free_wgs, WeightWalks* walks);

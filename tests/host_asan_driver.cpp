@@ -328,6 +328,9 @@ int main() {
         CHECK(hr::attn_call_takes_rows(5, 2, 16, 16, 64, 2150, 256) && !hr::attn_call_takes_rows(880, 2, 16, 16, 64, 2150, 256));
         CHECK(hr::rows_holds((1 << 23) - 1, 255) && !hr::rows_holds(1 << 23, 1) && !hr::rows_holds(1, 256));
     }
+    {   // ... and how many of its workgroups read weights ahead
+        CHECK(hr::rows_warm_wgs(544, false) == 160 && hr::rows_warm_wgs(639, false) == 160 && hr::rows_warm_wgs(640, false) == 128 && hr::rows_warm_wgs(544, true) == 128);
+    }
     {   // few-rows attention: every request finds the address of the sub-tile whose size it reads (a document's fp8 page is half as long
         // as an own one), those past the last round too, at every length
         for (int n_sub = 1; n_sub <= 200; ++n_sub)
