@@ -8,6 +8,7 @@
 
 #include "hr_attn_rows.h"
 #include "hr_internal.h"
+#include "hr_layout.h"
 
 namespace hr {
 

@@ -9,9 +9,6 @@
 
 namespace hr {
 
-constexpr int kWBlock = 64, kWBlockMin = 2048;       // blocks of W: rows, and the least N and K of a matrix kept in them (w_elem)
-
-
 constexpr int kPageTokens = HR_PAGE_TOKENS;
 constexpr size_t kAlign = 256;
 constexpr size_t kRangeCounterBytes = 256;     // room for 8 int64 counters of what the one-time conversions of caller data met

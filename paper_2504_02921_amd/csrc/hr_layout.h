@@ -16,8 +16,6 @@
 
 #include <cstdint>
 
-#include "hr_internal.h"
-
 #if defined(__HIPCC__)
 #define HR_HD __host__ __device__ inline __attribute__((always_inline))
 #else
@@ -43,6 +41,7 @@ HR_HD int v_elem(int t, int c, int d) { return ((t >> 2) & 1) * (d * 8) + c * 8 
 // 5147 / 4856 us, 100 tokens 6070 / 5638, 250 tokens 6850 / 6542, 400 tokens 8855 / 8580, 10k tokens 146.7 / 145.3 ms.
 // Matrices that are narrow or short stay row-major: with those of the 0.5B shape (N or K of 896) blocked, whose 32-row tiles read
 // half blocks, a call of 150 tokens took 1112 us against 1104.
+constexpr int kWBlock = 64, kWBlockMin = 2048;       // rows of a block; the least N and K of a matrix kept in blocks
 HR_HD bool w_blocked(int N, int K) { return N >= kWBlockMin && K >= kWBlockMin; }
 HR_HD int64_t w_elem(int64_t n, int k, int N, int K) {
     if (!w_blocked(N, K)) return n * K + k;
