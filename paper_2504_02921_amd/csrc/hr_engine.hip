@@ -750,7 +750,8 @@ static void build_score_part(hr_model* m, int32_t n_pairs, const int32_t* page_t
                              size_t* upload_ints) {
     hr::fill_meta(stage, ml, n_pairs, doc_lens, query_lens, query_tokens, page_table, pt_stride);
     // Pairs that share a document become one attention work item per kv head (up to 16 row blocks at 64-wide heads,
-    // 8 at 128-wide heads, where two blocks per wave do not fit the register file at two waves per SIMD).
+    // 8 at 128-wide heads, where two blocks per wave do not fit the register file at two waves per SIMD).  The plan is for the chain kernel; of a
+    // call of few row blocks (attn_call_takes_rows) only split-operand layers read it, the others go by the size of its largest item.
     const int g = m->cfg.n_q_heads / m->cfg.n_kv_heads;
     hr::GroupView& gv = out->gv;
     size_t plan_ints = 0;                                    // of the room reserved for a plan, what this call uses

@@ -89,7 +89,9 @@ struct TileSrc {
 };
 
 // The same for W, from row n0 on; BLK: blocked (w_elem), a template argument so that the k loops step by constants.  N is a
-// multiple of 64: a pass is inside the matrix or behind it as a whole, and lies in one block.
+// multiple of 64.  Blocked: n0 is one of 32, a pass is inside the matrix or behind it as a whole and lies in one block.  Row-major 224-column tiles start
+// at multiples of 224, so that a pass may end inside the matrix and the last one of a whole tile is half beyond it: the range of `rows` rows
+// in the descriptor drops those rows lane by lane, as at the end of A.
 template <int BN, int RPP, bool BLK>
 struct WTileSrc {
     static constexpr int PASSES = (BN + RPP - 1) / RPP;             // the last pass of a 224-row tile is half empty: out of the range

@@ -478,6 +478,7 @@ GemmLaunch choose_gemm_launch(GemmKind kind, int64_t M, int N, int K, int cus_, 
     // 256-row tiles of a residual add are 224 columns wide where as many of them cover N: an eighth fewer products.  They save less,
     // the 256-wide ones multiply zeros there, which cost no power: 0.5B shape (N = 896), K = 4864, 65536 rows 519 / 499 us, 230 k rows
     // 1790 / 1771.  320 x 224 tiles spill and are slower (20480 rows, K = 896 58.8 / 65.3 us).  Matrices in blocks of 64 rows do not fit them.
+    // Which tile is chosen still goes by the constants of the 256-wide one above: a few percent too many for this.
     const bool narrow = kind == GEMM_RESID && N < kWBlockMin && (N + 223) / 224 == (N + 255) / 256;
     // a round that fills little of the chip still takes three quarters of a full one (a tile's k loop has its length, and only
     // the shared memory system and the clock give way), or 70 % where two tiles share a CU: down projection of the 0.5B shape, 128 x 128
