@@ -72,7 +72,8 @@ class CachedWeights:
 
 def kernel_sources_sha():
     h = hashlib.sha256()
-    for f in ("hr_gemm_mfma.hip", "hr_attn_mfma.hip", "hr_kernels_generic.hip"):
+    for f in ("hr_gemm_mfma.hip", "hr_attn_mfma.hip", "hr_kernels_generic.hip",          # and the headers with device code of theirs
+              "hr_attn_common.h", "hr_gemm_tiles.h", "hr_layout.h", "hr_device_types.h"):
         with open(os.path.join(ROOT, "paper_2504_02921_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
