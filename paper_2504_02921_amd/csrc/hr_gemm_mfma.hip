@@ -424,9 +424,10 @@ __device__ __forceinline__ void gemm_epilogue(floatx4 (&acc)[BM / WM / 16][BN / 
 
 // BM x BN x 64 macro tile, WM x WN wavefronts, each wave (BM/WM) x (BN/WN) = MI x NI blocks of 16 x 16.
 //
-// What bounds it at large M is power: with operands of full mantissas the chip holds 1.45 GHz (8B gate/up, K = 8192: matrix
-// pipe busy 81 %) to 1.9 GHz (K = 896: 64 %) under this kernel, and every variant of the schedule that spends the same
-// energy per product ends at the same rate.  A register-only loop reaches 1.97 PFLOP/s with v_mfma_f32_16x16x32_f16 and 1.73
+// What bounds it at large M is power in gate/up and at the 8B shape: with operands of full mantissas the chip holds 1.45 GHz (8B gate/up,
+// K = 8192: matrix pipe busy 81 %) to 1.8 GHz (K = 896: 64 %) under this kernel, and every variant of the schedule that spends the same
+// energy per product ends at the same rate.  QKV, O and down of the 0.5B shape (N = 896 and 1152; pipe busy 36-56 % at 1.84-1.90 GHz) are not at
+// that limit: a tile's start, its epilogue and what the last round leaves idle.  A register-only loop reaches 1.97 PFLOP/s with v_mfma_f32_16x16x32_f16 and 1.73
 // with v_mfma_f32_32x32x16_f16 (twice the accumulator traffic per product; 2.44 and 2.48 with zeros), 1.57 / 1.43 with the
 // fragments read from LDS as here: hence the 16 x 16 x 32 form.
 //
